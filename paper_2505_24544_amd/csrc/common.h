@@ -22,6 +22,30 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 }
 __device__ __forceinline__ bf16_t f32_to_bf16(float f) { return (bf16_t)(pack_bf16x2(f, 0.f) & 0xffffu); }
 
+// ---- LDS reads with the address split into a register and a compile-time byte offset (at most 65 535): one address
+// register serves every stage, plane and step that a fragment kind is read from.  As inline assembly they are invisible
+// to the compiler's wait insertion: for LDS reads it can see it waits until no HBM -> LDS request that may alias is in
+// flight, i.e. a prefetch deeper than one stage never overlaps anything.  The caller waits (lgkmcnt) itself and ties
+// the results behind the wait. ----
+typedef unsigned int lds_u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int lds_u32x2_t __attribute__((ext_vector_type(2)));
+template <int OFF> __device__ __forceinline__ void lds_read_b128(lds_u32x4_t& d, uint32_t addr) {
+  static_assert(OFF >= 0 && OFF < 65536, "16-bit offset field");
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF));
+}
+template <int OFF> __device__ __forceinline__ void lds_read_tr16_b64(lds_u32x2_t& d, uint32_t addr) {
+  static_assert(OFF >= 0 && OFF < 65536, "16-bit offset field");
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF));
+}
+// after the wait: nothing that uses the value may be scheduled above this
+__device__ __forceinline__ void lds_tie(lds_u32x4_t& v) { asm volatile("" : "+v"(v)); }
+// lambdas that hold register arrays by reference have to be inlined, whatever their size
+#define BEAGLE_INLINE_LAMBDA __attribute__((always_inline))
+template <int V> struct int_c { static constexpr int value = V; };
+template <int I, int N, class F> __device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) { f(int_c<I>{}); static_for<I + 1, N>(f); }
+}
+
 // ---- launch profiler (see beagle_xattn_profile_* in the public header) ----
 void prof_before(const char* name, hipStream_t s);
 void prof_after(hipStream_t s);

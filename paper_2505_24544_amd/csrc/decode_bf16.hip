@@ -662,21 +662,7 @@ __global__ __launch_bounds__(256) void rope_table_kernel(const int32_t* pos, int
   tab[i] = make_float2((float)cs, (float)sn);
 }
 
-// LDS reads with the address split into a register and a compile-time byte offset (at most 65 535): one address
-// register serves every stage, plane and 16-row step that a fragment kind is read from.
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-template <int OFF> __device__ __forceinline__ void lds_read_b128(xload_t& d, uint32_t addr) {
-  static_assert(OFF >= 0 && OFF < 65536, "16-bit offset field");
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF));
-}
-template <int OFF> __device__ __forceinline__ void lds_read_tr16_b64(u32x2_t& d, uint32_t addr) {
-  static_assert(OFF >= 0 && OFF < 65536, "16-bit offset field");
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF));
-}
-template <int V> struct int_c { static constexpr int value = V; };
-template <int I, int N, class F> __device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) { f(int_c<I>{}); static_for<I + 1, N>(f); }
-}
+typedef lds_u32x2_t u32x2_t;
 
 // One workgroup per (head, key range, block of 32 NQB queries): grid (H, R, ceil(M / (32 NQB))).
 // NQB = 1 (up to 32 queries): the four waves split each 128-key step by rows, 32 keys each.  A wave requests, reads

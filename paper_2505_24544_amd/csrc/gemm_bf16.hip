@@ -37,6 +37,7 @@
 //     that XCD's L2.
 //   * Several independent GEMMs can share one launch (Q, K, V projections;
 //     the three weight gradients) so that small ones do not leave CUs idle.
+#include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include "common.h"
@@ -55,6 +56,11 @@ constexpr int NUM_XCD = 8;
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, 0x00020000);
+}
+
+// 16 bytes per lane, HBM/L2 -> LDS at dst + 16 * lane
+__device__ __forceinline__ void request16(__amdgpu_buffer_rsrc_t rsrc, bf16_t* dst, int off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)dst, 16, off, 0, 0, 0);
 }
 
 // One BK slice of one operand, HBM -> LDS.  Chunk q = tid + 256 i of the tile
@@ -150,32 +156,38 @@ __device__ __forceinline__ void map_tile(int pid, const int* tiles, int count, i
   }
 }
 
+// Which tile of which problem a workgroup owns: map_tile, then tile rows in groups (of 1024 rows) so that the
+// workgroups that run together share operand tiles in their XCD's L2.
+template <int BM, int BN>
+__device__ __forceinline__ void locate_tile(const GemmGroup& grp, int wg, int& prob, int& m0, int& n0) {
+  constexpr int GROUP = GROUP_M * 256 / BM;
+  int ntile[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    ntile[i] = i < grp.count ? ((grp.p[i].M + BM - 1) / BM) * ((grp.p[i].N + BN - 1) / BN) : 0;
+  int pid;
+  map_tile(wg, ntile, grp.count, prob, pid);
+  const GemmArgs& g = grp.p[prob];
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+  const int per_group = GROUP * tiles_n;
+  const int first_m = (pid / per_group) * GROUP;
+  const int gsz = min(tiles_m - first_m, GROUP);
+  m0 = (first_m + (pid % per_group) % gsz) * BM;
+  n0 = ((pid % per_group) / gsz) * BN;
+}
+
 // RES: some problem of the group has a residual operand R (a separate instantiation, so that the kernels
 // without one keep their register allocation).
 template <int TM, int TN, bool XK, bool WK, bool F32OUT, bool RES>
-__global__ __launch_bounds__(256, TM * TN >= 16 ? 1 : 2) void gemm_bf16_kernel(GemmGroup grp, int total_tiles) {
+__global__ __launch_bounds__(256, TM * TN >= 16 ? 1 : 2) void gemm_bf16_kernel(GemmGroup grp) {
   constexpr int BM = 64 * TM, BN = 64 * TN;
   constexpr int XE = BM * BK, WE = BN * BK;      // elements per operand tile
   __shared__ __attribute__((aligned(1024))) bf16_t stage0[XE + WE];
   __shared__ __attribute__((aligned(1024))) bf16_t stage1[XE + WE];
 
-  // ---- which tile of which problem
-  int ntile[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    ntile[i] = i < grp.count ? ((grp.p[i].M + BM - 1) / BM) * ((grp.p[i].N + BN - 1) / BN) : 0;
-  int pi, pid;
-  map_tile(blockIdx.x, ntile, grp.count, pi, pid);
+  int pi, m0, n0;
+  locate_tile<BM, BN>(grp, blockIdx.x, pi, m0, n0);
   const GemmArgs& g = grp.p[pi];
-  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  (void)total_tiles;
-  const int per_group = GROUP_M * tiles_n;
-  const int first_m = (pid / per_group) * GROUP_M;
-  const int gsz = min(tiles_m - first_m, GROUP_M);
-  const int tm = first_m + (pid % per_group) % gsz;
-  const int tn = (pid % per_group) / gsz;
-  const int m0 = tm * BM, n0 = tn * BN;
-
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave >> 1) * (32 * TM), wn = (wave & 1) * (32 * TN);
 
@@ -381,9 +393,293 @@ __global__ __launch_bounds__(256, TM * TN >= 16 ? 1 : 2) void gemm_bf16_kernel(G
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same product for problems with too few 256 x 256 tiles for the chip: tiles of 128 WM x 128 WN, of which EVERY
+// wave still accumulates 128 x 128 (256 accumulation registers), the KG = 4 / (WM WN) waves of one part of the tile
+// taking the k steps of a slice between them.  What bounds a small tile is LDS bandwidth, not the matrix pipe: four
+// waves of 64 x 64 read 32 fragments per 16 MFMAs, a wave of 128 x 128 reads 8, and the waves' sums meet once, in LDS,
+// behind the loop.  Per slice of 64 k (128 x 128 tile, X k-contiguous, W row-contiguous, transpose reads at half rate): 768
+// LDS cycles of reads + 256 of arriving data with four 64 x 64 waves, 384 + 256 this way, against 512 of MFMA.
+// And a small tile's slice is over in some 700 cycles, less than a trip to memory: the slices go through a ring of NST
+// LDS stages (four of 32 KB, or three of 48 KB), requested NST slices ahead, with explicit LDS reads and counted
+// waits (the compiler would wait for every request before any LDS read).  Fragments of the next step are read behind
+// the MFMAs of the current one; one barrier per slice.
+// ---------------------------------------------------------------------------
+template <int WM, int WN, bool XK, bool WK, bool F32OUT>
+__global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp) {
+  constexpr int BM = 128 * WM, BN = 128 * WN;
+  constexpr int KG = 4 / (WM * WN), KS = 4 / KG;    // waves per tile part; k steps of a slice per wave
+  constexpr int XE = BM * BK, WE = BN * BK, SE = XE + WE;
+  constexpr int NST = SE * 2 * 4 <= 128 * 1024 ? 4 : 3;
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[NST * SE];
+
+  int pi, m0, n0;
+  locate_tile<BM, BN>(grp, blockIdx.x, pi, m0, n0);
+  const GemmArgs& g = grp.p[pi];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wave % KG, wmn = wave / KG;
+  const int wm = (WM == 2 ? wmn : 0) * 128, wn = (WN == 2 ? wmn : 0) * 128;
+
+  // ---- request side: a cursor over the slices of both k segments.  The descriptors start at the current slice, so the
+  // lanes' offsets are constants of the tile and a slice costs scalar arithmetic only; past the last slice they are empty.
+  const int nk1 = (g.K + BK - 1) / BK, nk = nk1 + (g.A2 ? (g.K2 + BK - 1) / BK : 0);
+  constexpr int XLD = BM / 32, WLD = BN / 32;        // requests per thread and slice
+  const int ldx = (int)g.lda, ldw = (int)g.ldb;
+  int xoff[XLD], woff[WLD];
+#pragma unroll
+  for (int i = 0; i < XLD; ++i) {
+    const int q = tid + 256 * i;
+    if (XK) { const int r = q >> 3; xoff[i] = (r * ldx + 8 * ((q & 7) ^ ((r >> 1) & 7))) * 2; }
+    else { constexpr int CPR = BM / 8; const int k = q / CPR; xoff[i] = (k * ldx + 8 * ((q % CPR) ^ ((k & 3) << 2))) * 2; }
+  }
+#pragma unroll
+  for (int i = 0; i < WLD; ++i) {
+    const int q = tid + 256 * i;
+    if (WK) { const int r = q >> 3; woff[i] = (r * ldw + 8 * ((q & 7) ^ ((r >> 1) & 7))) * 2; }
+    else { constexpr int CPR = BN / 8; const int k = q / CPR; woff[i] = (k * ldw + 8 * ((q % CPR) ^ ((k & 3) << 2))) * 2; }
+  }
+  const char *fx, *fw;                               // current slice of this tile's rows
+  int64_t xleft, wleft;                              // bytes from there to the operand's end
+  auto seek = [&](const void* X, const void* W, int K) BEAGLE_INLINE_LAMBDA {
+    const int64_t xo = XK ? (int64_t)m0 * ldx * 2 : (int64_t)m0 * 2, wo = WK ? (int64_t)n0 * ldw * 2 : (int64_t)n0 * 2;
+    fx = (const char*)X + xo; xleft = (int64_t)(XK ? g.M : K) * ldx * 2 - xo;
+    fw = (const char*)W + wo; wleft = (int64_t)(WK ? g.N : K) * ldw * 2 - wo;
+  };
+  seek(g.A, g.B, g.K);
+  const int64_t xstep = XK ? BK * 2 : (int64_t)BK * ldx * 2, wstep = WK ? BK * 2 : (int64_t)BK * ldw * 2;
+  int f_t = 0, f_st = 0;                             // next slice to request, its stage
+  __amdgpu_buffer_rsrc_t xrs, wrs;
+  bf16_t* f_dst;
+  auto f_begin = [&]() BEAGLE_INLINE_LAMBDA {
+    if (f_t == nk1 && f_t < nk) seek(g.A2, g.B2, g.K2);
+    xrs = make_rsrc(fx, f_t < nk && xleft > 0 ? xleft : 0);
+    wrs = make_rsrc(fw, f_t < nk && wleft > 0 ? wleft : 0);
+    f_dst = smem + f_st * SE + wave * 512;
+    fx += xstep; xleft -= xstep; fw += wstep; wleft -= wstep;
+    ++f_t; f_st = f_st + 1 == NST ? 0 : f_st + 1;
+  };
+  auto f_issue = [&](auto i_) BEAGLE_INLINE_LAMBDA {
+    constexpr int i = decltype(i_)::value;
+    if constexpr (i < XLD) request16(xrs, f_dst + i * 2048, xoff[i]);
+    else request16(wrs, f_dst + XE + (i - XLD) * 2048, woff[i - XLD]);
+  };
+  constexpr int NLD = XLD + WLD;
+
+  // ---- fragment addresses (bytes from the start of a stage); everything else is an immediate
+  typedef __attribute__((address_space(3))) bf16_t* lds_bf16_ptr;
+  const uint32_t base = (uint32_t)(uintptr_t)(lds_bf16_ptr)smem;
+  const int ql = lane & 31, hf = lane >> 5;
+  // Accumulator row i of wave kg is row block (i + kg OWN) % 4 of its part: every wave then keeps its rows 0 .. OWN - 1 at
+  // the exchange behind the loop, and no branch ever picks accumulators by wave.
+  constexpr int OWN = 4 / KG;                        // 32-row blocks a wave keeps
+  constexpr int NWA = WK ? KS : 4;
+  uint32_t xa[XK ? KS : 1][4], wa[NWA];
+  int xblk[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) xblk[i] = (i + kg * OWN) & 3;
+  {
+    const int gi = lane >> 4, r16 = lane & 15, kr = 8 * (gi >> 1) + (r16 >> 2);
+    auto kmaj = [&](int r0, int s) BEAGLE_INLINE_LAMBDA { return ((r0 + ql) * BK + (((2 * (kg * KS + s) + hf) ^ ((ql >> 1) & 7)) << 3)) * 2; };
+    auto rmaj = [&](int rows, int r0, int b) BEAGLE_INLINE_LAMBDA {
+      const int col = r0 + 32 * b + 16 * (gi & 1) + 4 * (r16 & 3);
+      return ((kg * KS * 16 + kr) * rows + ((((col >> 3) ^ ((kr & 3) << 2)) << 3) | (col & 7))) * 2;
+    };
+#pragma unroll
+    for (int s = 0; s < (XK ? KS : 1); ++s)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) xa[s][i] = base + (XK ? kmaj(wm + 32 * xblk[i], s) : rmaj(BM, wm, xblk[i]));
+#pragma unroll
+    for (int i = 0; i < NWA; ++i) wa[i] = base + 2 * XE + (WK ? kmaj(wn, i) : rmaj(BN, wn, i));
+  }
+  union frag_t { lds_u32x4_t u; struct { lds_u32x2_t a, b; } s; bf16x8_t v; };
+  frag_t xf[2][4], wf[2][4];
+  // LDS read n of a step: X fragments first (one read each, or two transpose reads), then W's
+  constexpr int NXR = XK ? 4 : 8, NWR = WK ? 4 : 8;
+  auto read_one = [&](auto fb_, auto s_, auto n_, uint32_t st) BEAGLE_INLINE_LAMBDA {
+    constexpr int fb = decltype(fb_)::value, s = decltype(s_)::value, n = decltype(n_)::value;
+    if constexpr (n < NXR) {
+      if constexpr (XK) lds_read_b128<0>(xf[fb][n].u, xa[s][n] + st);
+      else if constexpr (n & 1) lds_read_tr16_b64<s * 16 * BM * 2 + 4 * BM * 2>(xf[fb][n >> 1].s.b, xa[0][n >> 1] + st);
+      else lds_read_tr16_b64<s * 16 * BM * 2>(xf[fb][n >> 1].s.a, xa[0][n >> 1] + st);
+    } else {
+      constexpr int k = n - NXR;
+      if constexpr (WK) lds_read_b128<k * 32 * BK * 2>(wf[fb][k].u, wa[s] + st);
+      else if constexpr (k & 1) lds_read_tr16_b64<s * 16 * BN * 2 + 4 * BN * 2>(wf[fb][k >> 1].s.b, wa[k >> 1] + st);
+      else lds_read_tr16_b64<s * 16 * BN * 2>(wf[fb][k >> 1].s.a, wa[k >> 1] + st);
+    }
+  };
+  auto frags_wait = [&](auto fb_) BEAGLE_INLINE_LAMBDA {                  // the step's fragments are in registers; nothing that uses them moves up
+    constexpr int fb = decltype(fb_)::value;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { lds_tie(xf[fb][i].u); lds_tie(wf[fb][i].u); }
+  };
+
+  f32x16_t acc[4][4];
+  // f(j, q) for the 16 groups of four consecutive columns that a lane holds of a 32-row block
+  auto quads = [&](auto f) BEAGLE_INLINE_LAMBDA {
+    static_for<0, 16>([&](auto b_) BEAGLE_INLINE_LAMBDA { f(int_c<(decltype(b_)::value >> 2)>{}, int_c<(decltype(b_)::value & 3)>{}); });
+  };
+  // the first NST slices; the accumulators are cleared while they travel
+#pragma unroll 1
+  for (int t = 0; t < NST; ++t) { f_begin(); static_for<0, NLD>(f_issue); }
+  __builtin_amdgcn_sched_barrier(0);
+  static_for<0, 16>([&](auto b_) BEAGLE_INLINE_LAMBDA {
+    constexpr int b = decltype(b_)::value;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[b >> 2][b & 3][e] = 0.f;
+  });
+  __builtin_amdgcn_sched_barrier(0);
+
+  auto wait_slice = [&]() BEAGLE_INLINE_LAMBDA {                          // all but the NST - 2 youngest slices have landed, for every wave
+    constexpr int n = (NST - 2) * NLD;
+    __builtin_amdgcn_s_waitcnt((n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  uint32_t rst = 0;                                  // stage of the slice being read, in bytes
+  // One slice; on entry its first step's fragments are in registers (parity P).  In its last step the next slice has
+  // landed for everybody, every wave has this slice's fragments in registers, and this slice's stage is requested anew.
+  auto slice = [&](auto par_) BEAGLE_INLINE_LAMBDA {
+    constexpr int P = decltype(par_)::value;
+    static_for<0, KS>([&](auto s_) BEAGLE_INLINE_LAMBDA {
+      constexpr int s = decltype(s_)::value, fb = (P + s) & 1;
+      constexpr bool last = s + 1 == KS;
+      constexpr int ns = last ? 0 : s + 1;
+      if constexpr (last) {
+        wait_slice();
+        f_begin();
+        rst = rst + 2 * SE == NST * 2 * SE ? 0 : rst + 2 * SE;
+      }
+      const uint32_t st = rst;
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<0, 16>([&](auto m_) BEAGLE_INLINE_LAMBDA {
+        constexpr int m = decltype(m_)::value, i = m >> 2, j = m & 3;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[fb][j].v, xf[fb][i].v, acc[i][j], 0, 0, 0);
+        // the next step's reads behind the first eight MFMAs, the requests behind the last ones
+        constexpr int r0 = m * (NXR + NWR) / 8, r1 = (m + 1) * (NXR + NWR) / 8;
+        if constexpr (m < 8) static_for<r0, r1>([&](auto n_) BEAGLE_INLINE_LAMBDA { read_one(int_c<(fb ^ 1)>{}, int_c<ns>{}, n_, st); });
+        // one request every KS * 16 / NLD MFMAs, from the barrier on: a wave gets rid of a request in about a hundred
+        // cycles, and issued faster than that it only stands in front of the MFMAs behind it
+        constexpr int mm = last ? m : 16 + 16 * s + m;
+        constexpr int d0 = (mm * NLD + 16 * KS - 1) / (16 * KS), d1 = ((mm + 1) * NLD + 16 * KS - 1) / (16 * KS);
+        if constexpr (d1 > d0) f_issue(int_c<d0>{});
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      frags_wait(int_c<(fb ^ 1)>{});
+    });
+  };
+  static_assert(NLD <= 16, "at most one request per MFMA");
+
+  {
+    constexpr int n = (NST - 1) * NLD;               // slice 0
+    __builtin_amdgcn_s_waitcnt((n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    static_for<0, NXR + NWR>([&](auto n_) BEAGLE_INLINE_LAMBDA { read_one(int_c<0>{}, int_c<0>{}, n_, 0u); });
+    frags_wait(int_c<0>{});
+  }
+  int t = 0;
+  if constexpr (KS % 2 == 0) {
+#pragma unroll 1
+    for (; t < nk; ++t) slice(int_c<0>{});
+  } else {
+#pragma unroll 1
+    for (; t + 2 <= nk; t += 2) { slice(int_c<0>{}); slice(int_c<1>{}); }
+    if (t < nk) slice(int_c<0>{});
+  }
+
+  // ---- the KG waves of a tile part exchange sums: each ends up with 128 / KG of the rows, summed in a fixed order
+  constexpr int SLOT = OWN * 4096;                   // floats of one wave's slot
+  __builtin_amdgcn_s_waitcnt(0x0F70);                // the requests past the end (they write zeros) have landed
+  __syncthreads();
+  float* slot = nullptr;
+  static_for<1, KG>([&](auto p_) BEAGLE_INLINE_LAMBDA {
+    constexpr int p = decltype(p_)::value;           // rows p OWN .. go to the wave p further round, which keeps those blocks
+    float* half = (float*)smem + (KG == 4 && (p & 1) == 0 ? 4 * SLOT : 0);
+    float* out = half + (wmn * KG + (kg + p) % KG) * SLOT;
+    static_for<0, OWN>([&](auto i_) BEAGLE_INLINE_LAMBDA {
+      constexpr int i = decltype(i_)::value;
+      quads([&](auto j_, auto q_) BEAGLE_INLINE_LAMBDA {
+        constexpr int j = decltype(j_)::value, q = decltype(q_)::value;
+        const f32x16_t& c = acc[p * OWN + i][j];
+        *(float4*)(out + i * 4096 + ((4 * j + q) * 64 + lane) * 4) = float4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+      });
+    });
+    __syncthreads();
+    slot = half + wave * SLOT;
+    static_for<0, OWN>([&](auto i_) BEAGLE_INLINE_LAMBDA {
+      constexpr int i = decltype(i_)::value;
+      quads([&](auto j_, auto q_) BEAGLE_INLINE_LAMBDA {
+        constexpr int j = decltype(j_)::value, q = decltype(q_)::value;
+        const float4 v = *(const float4*)(slot + i * 4096 + ((4 * j + q) * 64 + lane) * 4);
+        f32x16_t& c = acc[i][j];
+        c[4 * q] += v.x; c[4 * q + 1] += v.y; c[4 * q + 2] += v.z; c[4 * q + 3] += v.w;
+      });
+    });
+  });
+  static_assert((KG == 4 ? 2 : 1) * 4 * SLOT * 4 <= NST * SE * 2, "the exchange must fit in the stages");
+
+  // ---- rows out, through the wave's own slot of the last phase (nobody else touches it any more): whole row segments.
+  // Chunk c (16 bytes) of patch row r sits at c ^ (r % chunks), which spreads the column-wise writes over the banks.
+  static_for<0, OWN>([&](auto i_) BEAGLE_INLINE_LAMBDA {
+    constexpr int i = decltype(i_)::value;
+    const int mb = m0 + wm + 32 * (i + kg * OWN), nb = n0 + wn;
+    if constexpr (F32OUT) {
+      float* patch = slot + i * 4096;        // 32 rows x 128 floats: chunks of four, 32 per row
+      quads([&](auto j_, auto q_) BEAGLE_INLINE_LAMBDA {
+        constexpr int j = decltype(j_)::value, q = decltype(q_)::value;
+        *(float4*)(patch + ql * 128 + (((8 * j + 2 * q + hf) ^ ql) << 2)) =
+            float4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+      });
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int it = 0; it < 16; ++it) {
+        const int r = 2 * it + hf, p = ql, m = mb + r, n = nb + 4 * (p ^ r);
+        const float4 v = *(const float4*)(patch + r * 128 + 4 * p);
+        if (m < g.M && n < g.N) *(float4*)((float*)g.C + (int64_t)m * g.ldc + n) = v;
+      }
+    } else {
+      bf16_t* patch = (bf16_t*)(slot + i * 4096);   // 32 rows x 128: 16 chunks of eight per row
+      const int rr = lane >> 4, p = lane & 15;
+      if (g.R) {                                     // residual: its rows in, the lanes' pieces out, added before the rounding
+#pragma unroll
+        for (int it = 0; it < 8; ++it) {
+          const int r = 4 * it + rr, m = mb + r, n = nb + 8 * (p ^ (r & 15));
+          uint4 v = {0, 0, 0, 0};
+          if (m < g.M && n < g.N) v = *(const uint4*)((const bf16_t*)g.R + (int64_t)m * g.ldr + n);
+          *(uint4*)(patch + r * 128 + 8 * p) = v;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        quads([&](auto j_, auto q_) BEAGLE_INLINE_LAMBDA {
+          constexpr int j = decltype(j_)::value, q = decltype(q_)::value;
+          const uint2 r = *(const uint2*)(patch + ql * 128 + (((4 * j + q) ^ (ql & 15)) << 3) + 4 * hf);
+          acc[i][j][4 * q] += __uint_as_float(r.x << 16); acc[i][j][4 * q + 1] += __uint_as_float(r.x & 0xffff0000u);
+          acc[i][j][4 * q + 2] += __uint_as_float(r.y << 16); acc[i][j][4 * q + 3] += __uint_as_float(r.y & 0xffff0000u);
+        });
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      }
+      quads([&](auto j_, auto q_) BEAGLE_INLINE_LAMBDA {
+        constexpr int j = decltype(j_)::value, q = decltype(q_)::value;
+        *(uint2*)(patch + ql * 128 + (((4 * j + q) ^ (ql & 15)) << 3) + 4 * hf) =
+            uint2{pack_bf16x2(acc[i][j][4 * q], acc[i][j][4 * q + 1]), pack_bf16x2(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3])};
+      });
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int it = 0; it < 8; ++it) {
+        const int r = 4 * it + rr, m = mb + r, n = nb + 8 * (p ^ (r & 15));
+        const uint4 v = *(const uint4*)(patch + r * 128 + 8 * p);
+        if (m < g.M && n < g.N) *(uint4*)((bf16_t*)g.C + (int64_t)m * g.ldc + n) = v;
+      }
+    }
+  });
+}
+
 template <int TM, int TN, bool XK, bool WK, bool F32OUT, bool RES = false>
 static void launch_variant(const GemmGroup& grp, int total, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, XK, WK, F32OUT, RES>), dim3(total), dim3(256), 0, s, grp, total);
+  hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, XK, WK, F32OUT, RES>), dim3(total), dim3(256), 0, s, grp);
 }
 
 // What the MFMA kernel needs of a group (checked by the entry points before anything is enqueued, see
@@ -400,12 +696,22 @@ static bool group_fits(const GemmGroup& grp) {
     if (q.R) { res = true; if ((int64_t)q.M * q.ldr * 2 >= lim) return false; }
     if ((xk || wk) && (q.K % BK || (q.A2 && q.K2 % BK))) return false;
     if ((int64_t)(xk ? q.M : q.K) * q.lda * 2 >= lim || (int64_t)(wk ? q.N : q.K) * q.ldb * 2 >= lim) return false;
+    if (q.A2 && (q.lda2 != q.lda || q.ldb2 != q.ldb)) return false;
     if (q.A2 && ((int64_t)(xk ? q.M : q.K2) * q.lda2 * 2 >= lim || (int64_t)(wk ? q.N : q.K2) * q.ldb2 * 2 >= lim)) return false;
   }
   if (res) return xk && !f32;
   return (xk && !f32) || (!xk && !wk);
 }
 bool gemm_bf16_supported(const GemmGroup& grp) { return group_fits(grp); }
+
+static void check_group(const GemmGroup& grp) {
+  if (!group_fits(grp)) {
+    // The entry points refuse such problems with BEAGLE_ERR_UNSUPPORTED before they enqueue anything; there is no
+    // slower kernel to fall back to.  Getting here is a bug in the library's own host code.
+    fprintf(stderr, "beagle_xattn: internal error: GEMM group outside the MFMA kernel's domain reached the launcher\n");
+    abort();
+  }
+}
 
 template <int TM, int TN>
 static void launch_tiles(const GemmGroup& grp, hipStream_t s) {
@@ -417,12 +723,6 @@ static void launch_tiles(const GemmGroup& grp, hipStream_t s) {
   const bool xk = grp.p[0].a_kmajor, wk = grp.p[0].b_kmajor, f32 = grp.p[0].c_is_f32;
   bool res = false;
   for (int i = 0; i < grp.count; ++i) if (grp.p[i].R) res = true;
-  if (!group_fits(grp)) {
-    // The entry points refuse such problems with BEAGLE_ERR_UNSUPPORTED before they enqueue anything; there is no
-    // slower kernel to fall back to.  Getting here is a bug in the library's own host code.
-    fprintf(stderr, "beagle_xattn: internal error: GEMM group outside the MFMA kernel's domain reached the launcher\n");
-    abort();
-  }
   if (res && !wk) launch_variant<TM, TN, true, false, false, true>(grp, total, s);
   else if (res) launch_variant<TM, TN, true, true, false, true>(grp, total, s);
   else if (xk && !wk) launch_variant<TM, TN, true, false, false>(grp, total, s);
@@ -431,17 +731,63 @@ static void launch_tiles(const GemmGroup& grp, hipStream_t s) {
   else launch_variant<TM, TN, false, false, true>(grp, total, s);
 }
 
+template <int WM, int WN>
+static void launch_ksplit(const GemmGroup& grp, hipStream_t s) {
+  constexpr int BM = 128 * WM, BN = 128 * WN;
+  int total = 0;
+  for (int i = 0; i < grp.count; ++i)
+    total += ((grp.p[i].M + BM - 1) / BM) * ((grp.p[i].N + BN - 1) / BN);
+  if (total == 0) return;
+  const bool xk = grp.p[0].a_kmajor, wk = grp.p[0].b_kmajor, f32 = grp.p[0].c_is_f32;
+  const dim3 grid(total), wg(256);
+  if (xk && !wk) hipLaunchKernelGGL((gemm_bf16_ksplit_kernel<WM, WN, true, false, false>), grid, wg, 0, s, grp);
+  else if (xk) hipLaunchKernelGGL((gemm_bf16_ksplit_kernel<WM, WN, true, true, false>), grid, wg, 0, s, grp);
+  else if (!f32) hipLaunchKernelGGL((gemm_bf16_ksplit_kernel<WM, WN, false, false, false>), grid, wg, 0, s, grp);
+  else hipLaunchKernelGGL((gemm_bf16_ksplit_kernel<WM, WN, false, false, true>), grid, wg, 0, s, grp);
+}
+
+// Tile choice: what a launch takes with each tile size, from the number of tiles, the depth of each problem and how full
+// the rounds of 256 workgroups (one per CU) are.  A round costs a fixed part (first slices, exchange, stores) and so much
+// per slice of 64 k, less when part of the chip is idle.  Fitted to launches timed on their own, microseconds:
+//   256 x 256: K 777 full 28; K 4096 full 107-122, a quarter full 76; K 11008 three quarters full 243
+//   256 x 128, 128 x 256: K 777 full 20; K 4096 full 64-70, half full 52
+//   128 x 128: K 777 full 13; K 4096 full 40, 7/8 full 36 (four waves of 64 x 64 per tile took 59)
+// Large problems come out at 256 x 256 by their operand traffic alone (1.30 PFLOP/s against 0.95 and 0.80).
+enum TileSize { TILE_256, TILE_256x128, TILE_128x256, TILE_128 };
+static TileSize choose_tile(const GemmGroup& grp) {
+  struct Cost { int bm, bn; double fixed, slice, slice_full; };
+  static const Cost costs[] = {{256, 256, 8.8, 0.90, 0.65}, {256, 128, 8.3, 0.57, 0.38}, {128, 256, 8.3, 0.57, 0.38}, {128, 128, 6.1, 0.38, 0.16}};
+  int best = 0;
+  double best_us = 0.0;
+  for (int c = 0; c < 4; ++c) {
+    double tiles = 0.0, slices = 0.0;               // slices: over all tiles
+    for (int i = 0; i < grp.count; ++i) {
+      const GemmArgs& q = grp.p[i];
+      const double t = (double)((q.M + costs[c].bm - 1) / costs[c].bm) * ((q.N + costs[c].bn - 1) / costs[c].bn);
+      tiles += t;
+      slices += t * ((q.K + BK - 1) / BK + (q.A2 ? (q.K2 + BK - 1) / BK : 0));
+    }
+    if (tiles == 0.0) continue;
+    const double depth = slices / tiles, full = floor(tiles / 256.0), rest = tiles / 256.0 - full;
+    double us = full * (costs[c].fixed + depth * (costs[c].slice + costs[c].slice_full));
+    if (rest > 0.0) us += costs[c].fixed + depth * (costs[c].slice + costs[c].slice_full * rest);
+    if (c == 0 || us < best_us) { best = c; best_us = us; }
+  }
+  return (TileSize)best;
+}
+
 // Every GEMM of a group must share storage orders and output type; the hot
 // path only forms such groups.  Supported: X k-major with W either order
 // (forward projections, input gradients), both row-major-in-k (weight grads).
 void launch_gemm_bf16(const GemmGroup& grp, hipStream_t s, const char* name) {
   ProfScope ps(name, s);
-  // tile choice: 256 x 256 when that still yields at least one tile per CU
-  long tiles256 = 0;
-  for (int i = 0; i < grp.count; ++i)
-    tiles256 += (long)((grp.p[i].M + 255) / 256) * ((grp.p[i].N + 255) / 256);
-  if (tiles256 >= 256) launch_tiles<4, 4>(grp, s);
-  else launch_tiles<2, 2>(grp, s);
+  check_group(grp);
+  switch (choose_tile(grp)) {
+    case TILE_256: return launch_tiles<4, 4>(grp, s);
+    case TILE_256x128: return launch_ksplit<2, 1>(grp, s);
+    case TILE_128x256: return launch_ksplit<1, 2>(grp, s);
+    case TILE_128: return launch_ksplit<1, 1>(grp, s);
+  }
 }
 
 template <bool F32OUT>
