@@ -204,6 +204,30 @@ void xattn_fwd_run(const Dims& d, const void* xq, const void* xkv, const void* w
   run_gemm(d, group1(out), s, "proj_out");
 }
 
+// dO = dY Wo^T ; dWo = O^T dY
+static void run_bwd_out(const Dims& d, const void* dy, const void* wo, const void* o_save, void* dO, void* dwo, bool wf32,
+                        hipStream_t s) {
+  GemmGroup g = group1(gemm_nt(dy, wo, dO, d.Tq, d.HD, d.D));
+  const GemmArgs w = gemm_tn(o_save, dy, dwo, d.HD, d.D, d.Tq, wf32);
+  if (d.bf16) {
+    run_gemm(d, g, s, "bwd_dout");
+    run_gemm(d, group1(w), s, "bwd_dwo");
+  } else {
+    g.p[g.count++] = w;
+    run_gemm(d, g, s, "bwd_dout_dwo");
+  }
+}
+// The last gradients, input ones and weight ones: the float kernel takes both groups in one launch
+static void run_bwd_last(const Dims& d, GemmGroup dx, const GemmGroup& dw, hipStream_t s) {
+  if (d.bf16) {
+    run_gemm(d, dx, s, "bwd_dx");
+    run_gemm(d, dw, s, "bwd_dw");
+  } else {
+    for (int i = 0; i < dw.count; ++i) dx.p[dx.count++] = dw.p[i];
+    run_gemm(d, dx, s, "bwd_dx_dw");
+  }
+}
+
 // All gradients of the attention op; `base` is a workspace of BEAGLE_WS_BWD bytes.  dxq_res, if given, is added
 // to dxq in the epilogue of its GEMM.
 void xattn_bwd_run(const Dims& d, bool need_dxkv, bool wf32, const void* dy, const void* xq, const void* xkv,
@@ -216,9 +240,7 @@ void xattn_bwd_run(const Dims& d, bool need_dxkv, bool wf32, const void* dy, con
   float* delta = (float*)(base + w.delta);
   const int64_t Mq = d.Tq, Mk = d.Tk;
 
-  // dO = dY Wo^T ; dWo = O^T dY
-  run_gemm(d, group1(gemm_nt(dy, wo, dO, Mq, d.HD, d.D)), s, "bwd_dout");
-  run_gemm(d, group1(gemm_tn(o_save, dy, dwo, d.HD, d.D, Mq, wf32)), s, "bwd_dwo");
+  run_bwd_out(d, dy, wo, o_save, dO, dwo, wf32, s);
 
   AttnArgs a = attn_args(d);
   a.q = q_save; a.k = k_save; a.v = v_save; a.o = (void*)o_save; a.lse = (float*)lse;
@@ -232,22 +254,20 @@ void xattn_bwd_run(const Dims& d, bool need_dxkv, bool wf32, const void* dy, con
   }
 
   // input gradients
-  {
-    GemmGroup g; memset(&g, 0, sizeof(g));
-    g.count = 1;
-    g.p[0] = gemm_nt(dQ, wq, dxq, Mq, d.D, d.HD);
-    g.p[0].R = dxq_res; g.p[0].ldr = d.D;
-    if (need_dxkv) {
-      // deeper problem first: dXkv contracts over the K and the V columns
-      g.count = 2;
-      g.p[1] = g.p[0];
-      g.p[0] = gemm_nt(dK, wk, dxkv, Mk, d.D, d.GD);
-      g.p[0].A2 = dV; g.p[0].B2 = wv; g.p[0].K2 = (int32_t)d.GD; g.p[0].lda2 = d.GD; g.p[0].ldb2 = d.GD;
-    }
-    run_gemm(d, g, s, "bwd_dx");
+  GemmGroup dx; memset(&dx, 0, sizeof(dx));
+  dx.count = 1;
+  dx.p[0] = gemm_nt(dQ, wq, dxq, Mq, d.D, d.HD);
+  dx.p[0].R = dxq_res; dx.p[0].ldr = d.D;
+  if (need_dxkv) {
+    // deeper problem first: dXkv contracts over the K and the V columns
+    dx.count = 2;
+    dx.p[1] = dx.p[0];
+    dx.p[0] = gemm_nt(dK, wk, dxkv, Mk, d.D, d.GD);
+    dx.p[0].A2 = dV; dx.p[0].B2 = wv; dx.p[0].K2 = (int32_t)d.GD; dx.p[0].lda2 = d.GD; dx.p[0].ldb2 = d.GD;
   }
   // weight gradients
   if (split_kv_wgrad(d)) {
+    run_gemm(d, dx, s, "bwd_dx");
     run_gemm(d, group1(gemm_tn(xq, dQ, dwq, d.D, d.HD, Mq, wf32)), s, "bwd_dwq");
     const int64_t kh = (Mk / 2) & ~(int64_t)63, pe = d.D * d.GD;      // rows of the first half; elements of a partial
     float* part = (float*)(base + w.dwpart);
@@ -272,7 +292,7 @@ void xattn_bwd_run(const Dims& d, bool need_dxkv, bool wf32, const void* dy, con
     g.p[0] = gemm_tn(xq, dQ, dwq, d.D, d.HD, Mq, wf32);
     g.p[1] = gemm_tn(xkv, dK, dwk, d.D, d.GD, Mk, wf32);
     g.p[2] = gemm_tn(xkv, dV, dwv, d.D, d.GD, Mk, wf32);
-    run_gemm(d, g, s, "bwd_dw");
+    run_bwd_last(d, dx, g, s);
   }
 }
 
@@ -328,8 +348,7 @@ void xattn_bwd_sim_run(const Dims& d, bool need_dxkv, bool wf32, const void* dy,
   void* dVp = (char*)dKp + kvb;
   const int64_t Mq = d.Tq, Mk = d.Tk;
 
-  run_gemm(d, group1(gemm_nt(dy, wo, dO, Mq, d.HD, d.D)), s, "bwd_dout");
-  run_gemm(d, group1(gemm_tn(o_save, dy, dwo, d.HD, d.D, Mq, wf32)), s, "bwd_dwo");
+  run_bwd_out(d, dy, wo, o_save, dO, dwo, wf32, s);
 
   // true-key part: the main kernels, given the merged LSE and delta = rowsum(dO * O) of the merged O
   SimArgs sa; memset(&sa, 0, sizeof(sa));
@@ -348,31 +367,26 @@ void xattn_bwd_sim_run(const Dims& d, bool need_dxkv, bool wf32, const void* dy,
     launch_rope(d.bf16, r, s, "bwd_rope_qk");
   }
 
-  {
-    GemmGroup g; memset(&g, 0, sizeof(g));
-    g.count = 2;
-    g.p[0] = gemm_nt(dKp, wk, dxpred, Mk, d.D, d.GD);
-    g.p[0].A2 = dVp; g.p[0].B2 = wv; g.p[0].K2 = (int32_t)d.GD; g.p[0].lda2 = d.GD; g.p[0].ldb2 = d.GD;
-    g.p[1] = gemm_nt(dQ, wq, dxq, Mq, d.D, d.HD);
-    g.p[1].R = dxq_res; g.p[1].ldr = d.D;
-    if (need_dxkv) {
-      g.count = 3;
-      g.p[2] = g.p[1];
-      g.p[1] = gemm_nt(dK, wk, dxkv, Mk, d.D, d.GD);
-      g.p[1].A2 = dV; g.p[1].B2 = wv; g.p[1].K2 = (int32_t)d.GD; g.p[1].lda2 = d.GD; g.p[1].ldb2 = d.GD;
-    }
-    run_gemm(d, g, s, "bwd_dx");
+  GemmGroup dx; memset(&dx, 0, sizeof(dx));
+  dx.count = 2;
+  dx.p[0] = gemm_nt(dKp, wk, dxpred, Mk, d.D, d.GD);
+  dx.p[0].A2 = dVp; dx.p[0].B2 = wv; dx.p[0].K2 = (int32_t)d.GD; dx.p[0].lda2 = d.GD; dx.p[0].ldb2 = d.GD;
+  dx.p[1] = gemm_nt(dQ, wq, dxq, Mq, d.D, d.HD);
+  dx.p[1].R = dxq_res; dx.p[1].ldr = d.D;
+  if (need_dxkv) {
+    dx.count = 3;
+    dx.p[2] = dx.p[1];
+    dx.p[1] = gemm_nt(dK, wk, dxkv, Mk, d.D, d.GD);
+    dx.p[1].A2 = dV; dx.p[1].B2 = wv; dx.p[1].K2 = (int32_t)d.GD; dx.p[1].lda2 = d.GD; dx.p[1].ldb2 = d.GD;
   }
-  {
-    GemmGroup g; memset(&g, 0, sizeof(g));
-    g.count = 3;
-    g.p[0] = gemm_tn(xkv, dK, dwk, d.D, d.GD, Mk, wf32);        // two k segments: true and predicted rows
-    g.p[0].A2 = xpred; g.p[0].B2 = dKp; g.p[0].K2 = (int32_t)Mk; g.p[0].lda2 = d.D; g.p[0].ldb2 = d.GD;
-    g.p[1] = gemm_tn(xkv, dV, dwv, d.D, d.GD, Mk, wf32);
-    g.p[1].A2 = xpred; g.p[1].B2 = dVp; g.p[1].K2 = (int32_t)Mk; g.p[1].lda2 = d.D; g.p[1].ldb2 = d.GD;
-    g.p[2] = gemm_tn(xq, dQ, dwq, d.D, d.HD, Mq, wf32);
-    run_gemm(d, g, s, "bwd_dw");
-  }
+  GemmGroup g; memset(&g, 0, sizeof(g));
+  g.count = 3;
+  g.p[0] = gemm_tn(xkv, dK, dwk, d.D, d.GD, Mk, wf32);        // two k segments: true and predicted rows
+  g.p[0].A2 = xpred; g.p[0].B2 = dKp; g.p[0].K2 = (int32_t)Mk; g.p[0].lda2 = d.D; g.p[0].ldb2 = d.GD;
+  g.p[1] = gemm_tn(xkv, dV, dwv, d.D, d.GD, Mk, wf32);
+  g.p[1].A2 = xpred; g.p[1].B2 = dVp; g.p[1].K2 = (int32_t)Mk; g.p[1].lda2 = d.D; g.p[1].ldb2 = d.GD;
+  g.p[2] = gemm_tn(xq, dQ, dwq, d.D, d.HD, Mq, wf32);
+  run_bwd_last(d, dx, g, s);
 }
 
 // K / V rows of the n = d.S new states into cache rows pos .. pos + n - 1 (+ rotary embedding of the K rows).

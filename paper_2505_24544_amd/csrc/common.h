@@ -73,10 +73,10 @@ struct GemmArgs {
   const void* R;         // optional residual added in the epilogue: C = A B (+ A2 B2) + R; storage type of A,
   int64_t ldr;           // row stride ldr; not with c_is_f32
 };
-// Up to 4 independent GEMMs in one launch (they share one grid).
+// Independent GEMMs in one launch (they share one grid): up to 4 of the same storage orders in bf16, up to 6 of any in float.
 struct GemmGroup {
   int32_t count;
-  GemmArgs p[4];
+  GemmArgs p[6];
 };
 void launch_gemm_f32(const GemmGroup& g, hipStream_t s, const char* name);
 void launch_gemm_bf16(const GemmGroup& g, hipStream_t s, const char* name);

@@ -1,0 +1,436 @@
+// The fp32 path (io_dtype == BEAGLE_F32): projections and masked attention in
+// float throughout, on the float matrix instruction v_mfma_f32_32x32x2_f32 (an
+// ordinary float multiply-add chain: results stay within 1e-5 of float64).
+//
+// The problems this path sees are small (the reference problem is 128 rows of
+// 256), so what bounds it is latency: launches, trips to memory and serial
+// chains, not arithmetic.  Hence:
+//   * No LDS staging.  Operand fragments go from L2 straight into registers in
+//     the matrix instruction's layout: lane l supplies row (column) l % 32, and
+//     since the two operands only have to agree on what k a lane half stands
+//     for, half h takes k = 8 i + 4 h + e of instruction (i, e): one 16-byte load
+//     where k is contiguous in memory, four coalesced 4-byte loads where it is not.
+//   * Small tiles (32 x 32) whose four waves split the contraction, so that a
+//     128 x 256 output still occupies 32 workgroups and a contraction of 256 is
+//     one trip to memory and 32 instructions per wave; the four sums meet in LDS.
+//   * Everything independent shares a launch: problems of different storage
+//     orders in one GEMM group, dQ with dK / dV in one attention launch.
+// One training step at 128 rows, hidden 256, 4 heads of 64: 367 us with the
+// scalar kernels that were here (nine launches of 27 - 87 us), 46 us now.
+#include "common.h"
+
+namespace beagle {
+namespace {
+
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
+
+__device__ __forceinline__ f32x16_t mfma(float a, float b, const f32x16_t& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16_t zero16() {
+  f32x16_t z;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) z[e] = 0.f;
+  return z;
+}
+// row (A operand) or column of the 32 x 32 output that accumulator register e of lane half hf belongs to
+__device__ __forceinline__ int acc_row(int e, int hf) { return 8 * (e >> 2) + 4 * hf + (e & 3); }
+
+// ---------------------------------------------------------------------------
+// GEMM.  KG = 4: a 32 x 32 tile per workgroup, the four waves take chunks of 32 k in turn.  KG = 1: a 64 x 64 tile, a
+// 32 x 32 quarter per wave, for problems with tiles enough (half the operand traffic per flop).
+// ---------------------------------------------------------------------------
+template <int KG>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmGroup grp) {
+  constexpr int T = KG == 4 ? 32 : 64;
+  __shared__ float red[KG == 4 ? 4 : 1][32][33];
+  int t = blockIdx.x, pi = 0;
+  for (; pi + 1 < grp.count; ++pi) {
+    const int n = ((grp.p[pi].M + T - 1) / T) * ((grp.p[pi].N + T - 1) / T);
+    if (t < n) break;
+    t -= n;
+  }
+  const GemmArgs& g = grp.p[pi];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hf = lane >> 5, ql = lane & 31;
+  const int tn = (g.N + T - 1) / T;
+  const int m0 = (t / tn) * T + (KG == 1 ? (wave >> 1) * 32 : 0), n0 = (t % tn) * T + (KG == 1 ? (wave & 1) * 32 : 0);
+  const int mr = min(m0 + ql, g.M - 1), nc = min(n0 + ql, g.N - 1);    // rows and columns past the end repeat the last one
+  f32x16_t acc = zero16();
+
+  // one k segment; AK / BK: k contiguous in memory
+  auto segment = [&](auto ak_, auto bk_, const float* A, const float* B, int K, int64_t lda, int64_t ldb) BEAGLE_INLINE_LAMBDA {
+    constexpr bool AK = decltype(ak_)::value, BK = decltype(bk_)::value;
+    const float* ap = AK ? A + mr * lda : A + mr;
+    const float* bp = BK ? B + nc * ldb : B + nc;
+    // 32 k of both operands: register 4 i + e is k = k0 + 8 i + 4 hf + e; past K: zeros on the A side
+    auto load = [&](int k0, float (&a)[16], float (&b)[16]) BEAGLE_INLINE_LAMBDA {
+      if (k0 + 32 <= K) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int k = k0 + 8 * i + 4 * hf;
+          if (AK) { const float4 v = *(const float4*)(ap + k); a[4 * i] = v.x; a[4 * i + 1] = v.y; a[4 * i + 2] = v.z; a[4 * i + 3] = v.w; }
+          if (BK) { const float4 v = *(const float4*)(bp + k); b[4 * i] = v.x; b[4 * i + 1] = v.y; b[4 * i + 2] = v.z; b[4 * i + 3] = v.w; }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (!AK) a[4 * i + e] = ap[(k + e) * lda];
+            if (!BK) b[4 * i + e] = bp[(k + e) * ldb];
+          }
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int k = k0 + 8 * (i >> 2) + 4 * hf + (i & 3), kc = min(k, K - 1);
+          const float v = AK ? ap[kc] : ap[kc * lda];
+          a[i] = k < K ? v : 0.f;
+          b[i] = BK ? bp[kc] : bp[kc * ldb];
+        }
+      }
+    };
+    auto compute = [&](const float (&a)[16], const float (&b)[16]) BEAGLE_INLINE_LAMBDA {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc = mfma(a[i], b[i], acc);
+    };
+    // two chunks in flight; a contraction of up to 256 (64 with one wave) is loaded whole before the first product
+    float a0[16], b0[16], a1[16], b1[16];
+    int k = KG == 4 ? 32 * wave : 0;
+    constexpr int STEP = 32 * KG;
+    if (k < K) load(k, a0, b0);
+    if (k + STEP < K) load(k + STEP, a1, b1);
+    for (; k < K; k += 2 * STEP) {
+      compute(a0, b0);
+      if (k + 2 * STEP < K) load(k + 2 * STEP, a0, b0);
+      if (k + STEP < K) {
+        compute(a1, b1);
+        if (k + 3 * STEP < K) load(k + 3 * STEP, a1, b1);
+      }
+    }
+  };
+  auto both = [&](auto ak_, auto bk_) BEAGLE_INLINE_LAMBDA {
+    segment(ak_, bk_, (const float*)g.A, (const float*)g.B, g.K, g.lda, g.ldb);
+    if (g.A2) segment(ak_, bk_, (const float*)g.A2, (const float*)g.B2, g.K2, g.lda2, g.ldb2);
+  };
+  if (g.a_kmajor && g.b_kmajor) both(int_c<1>{}, int_c<1>{});
+  else if (g.a_kmajor) both(int_c<1>{}, int_c<0>{});
+  else both(int_c<0>{}, int_c<0>{});
+
+  float* C = (float*)g.C;
+  const float* R = (const float*)g.R;
+  if (KG == 4) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) red[wave][acc_row(e, hf)][ql] = acc[e];
+    __syncthreads();
+    const int r = tid >> 3, c = (tid & 7) * 4, m = m0 + r;
+    if (m < g.M) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int n = n0 + c + u;
+        if (n >= g.N) break;
+        float v = ((red[0][r][c + u] + red[KG == 4 ? 1 : 0][r][c + u]) + red[KG == 4 ? 2 : 0][r][c + u]) + red[KG == 4 ? 3 : 0][r][c + u];
+        if (R) v += R[m * g.ldr + n];
+        C[m * g.ldc + n] = v;
+      }
+    }
+  } else {
+    const int n = n0 + ql;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int m = m0 + acc_row(e, hf);
+      if (m < g.M && n < g.N) C[m * g.ldc + n] = acc[e] + (R ? R[m * g.ldr + n] : 0.f);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Attention.  A workgroup owns 32 queries (keys) of one head; its four waves take blocks of 32 keys (queries) in turn
+// and their results are merged in LDS in wave order.  As in the bf16 kernels a lane owns one query (key): scores come
+// out of the matrix instruction with it as the column, and the probabilities go back in as the second product's operand
+// without leaving their registers.  NC: 32-channel blocks of the head width.
+// ---------------------------------------------------------------------------
+// operand fragment of a row: channels 8 i + 4 hf + e at f[4 i + e], zeros past d
+template <int NC>
+__device__ __forceinline__ void row_frag(const float* row, int d, int hf, float (&f)[16 * NC]) {
+#pragma unroll
+  for (int i = 0; i < 4 * NC; ++i) {
+    const int c = 8 * i + 4 * hf;
+    const float4 v = *(const float4*)(row + min(c, d - 4));
+    const bool in = c < d;
+    f[4 * i] = in ? v.x : 0.f; f[4 * i + 1] = in ? v.y : 0.f; f[4 * i + 2] = in ? v.z : 0.f; f[4 * i + 3] = in ? v.w : 0.f;
+  }
+}
+// rows r0 + acc_row(e, hf) (clamped to n - 1) of channel c, for the product over rows; c is clamped by the caller
+__device__ __forceinline__ void col_frag(const float* base, int64_t stride, int r0, int n, int c, int hf, float (&f)[16]) {
+#pragma unroll
+  for (int e = 0; e < 16; ++e) f[e] = base[min(r0 + acc_row(e, hf), n - 1) * stride + c];
+}
+template <int NC>
+__device__ __forceinline__ f32x16_t dot_frags(const float (&a)[16 * NC], const float (&b)[16 * NC]) {
+  f32x16_t s = zero16();
+#pragma unroll
+  for (int i = 0; i < 16 * NC; ++i) s = mfma(a[i], b[i], s);
+  return s;
+}
+__device__ __forceinline__ float pair_sum(float v) { return v + __shfl_xor(v, 32, 64); }
+__device__ __forceinline__ float pair_max(float v) { return fmaxf(v, __shfl_xor(v, 32, 64)); }
+
+// A wave's accumulators [channel 32 cb + acc_row][row ql] -> LDS[row][channel], rows padded by one float
+template <int NC>
+__device__ __forceinline__ void park(float* buf, const f32x16_t (&o)[NC], int ql, int hf) {
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) buf[ql * (32 * NC + 1) + 32 * cb + acc_row(e, hf)] = o[cb][e];
+}
+
+template <int NC>
+__global__ __launch_bounds__(256, 1) void attn_fwd_f32_kernel(AttnArgs a) {
+  __shared__ float ob[4][32 * (32 * NC + 1)];
+  __shared__ float ms[4][32], ls[4][32];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hf = lane >> 5, ql = lane & 31;
+  const int h = blockIdx.y, b = blockIdx.z, g = h / (a.H / a.G), d = a.d;
+  const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * 32;          // the queries that see the most keys first
+  const SeqView sv = seq_view(a, b);
+  if (q0 >= sv.S) return;                               // packed batch: a shorter entry
+  const int q = q0 + ql, qc = min(q, sv.S - 1);
+  const float* K = (const float*)a.k + (sv.kv0 * a.G + g) * d;
+  const float* V = (const float*)a.v + (sv.kv0 * a.G + g) * d;
+  const int64_t kvs = (int64_t)a.G * d;
+  float qf[16 * NC];
+  row_frag<NC>((const float*)a.q + ((sv.q0 + qc) * a.H + h) * d, d, hf, qf);
+  const MaskParams mk = sample_mask(a, b);
+  const int lim = q < sv.S ? row_limit(q, mk) : 0;
+  const int wg_lim = row_limit(min(q0 + 32, sv.S) - 1, mk);            // limits never decrease with the query
+  // draft-tree decode: keys at or past n_true are visible only where the query's tree row has a bit
+  const uint32_t* trow = a.tree ? a.tree + (int64_t)qc * a.tree_words : nullptr;
+
+  f32x16_t o[NC];
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb) o[cb] = zero16();
+  float m = -INFINITY, l = 0.f;
+  for (int j0 = 32 * wave; j0 < wg_lim; j0 += 128) {
+    float kf[16 * NC], vf[NC][16];
+    row_frag<NC>(K + min(j0 + ql, sv.L - 1) * kvs, d, hf, kf);
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) col_frag(V, kvs, j0, sv.L, min(32 * cb + ql, d - 1), hf, vf[cb]);
+    f32x16_t s = dot_frags<NC>(kf, qf);                 // [key acc_row(e, hf)][query ql]
+    float mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int j = j0 + acc_row(e, hf);
+      bool vis = j < lim;
+      if (trow && j >= a.n_true && vis) { const int t = j - a.n_true; vis = ((trow[t >> 5] >> (t & 31)) & 1u) != 0; }
+      s[e] = vis ? a.scale * s[e] : -INFINITY;
+      mx = fmaxf(mx, s[e]);
+    }
+    const float mn = fmaxf(m, pair_max(mx));
+    const float mb = mn == -INFINITY ? 0.f : mn;        // nothing visible so far: every p is exp(-inf) = 0
+    const float alpha = expf(m - mb);
+    float rs = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) { s[e] = expf(s[e] - mb); rs += s[e]; }
+    l = l * alpha + pair_sum(rs);
+    m = mn;
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[cb][e] *= alpha;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[cb] = mfma(vf[cb][e], s[e], o[cb]);
+    }
+  }
+  park<NC>(ob[wave], o, ql, hf);
+  if (hf == 0) { ms[wave][ql] = m; ls[wave][ql] = l; }
+  __syncthreads();
+  // 8 threads per query, every eighth channel each
+  const int r = tid >> 3, p = q0 + r;
+  if (p >= sv.S) return;
+  float mm = fmaxf(fmaxf(ms[0][r], ms[1][r]), fmaxf(ms[2][r], ms[3][r])), w[4], lt = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { w[i] = ms[i][r] == -INFINITY ? 0.f : expf(ms[i][r] - mm); lt += ls[i][r] * w[i]; }
+  const float inv = lt > 0.f ? 1.f / lt : 0.f;
+  float* O = (float*)a.o + ((sv.q0 + p) * a.H + h) * d;
+  for (int c = tid & 7; c < d; c += 8) {
+    const int i = r * (32 * NC + 1) + c;
+    O[c] = (((ob[0][i] * w[0] + ob[1][i] * w[1]) + ob[2][i] * w[2]) + ob[3][i] * w[3]) * inv;
+  }
+  if ((tid & 7) == 0) a.lse[sv.lse0 + h * sv.lse_hs + p] = lt > 0.f ? mm + logf(lt) : -INFINITY;
+}
+
+// Both halves of the backward in one launch (they are independent: each forms delta = rowsum(dO * O) for itself).
+//   blocks [0, n_dq)  : dQ of 32 queries of one head, over the keys they see; also stores delta
+//   the rest          : dK, dV of 32 keys of one key/value head, over the (head, query block) pairs that see them
+template <int NC>
+__global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_dq) {
+  __shared__ float ob[4][32 * (32 * NC + 1)];
+  __shared__ float st[4][2][32];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hf = lane >> 5, ql = lane & 31;
+  const int d = a.d, rep = a.H / a.G;
+  const int64_t kvs = (int64_t)a.G * d, qs = (int64_t)a.H * d;
+  // the merged sums of the four waves, rows r0 .. of a tensor whose rows are `stride` apart
+  auto rows_out = [&](float* out, int64_t stride, int rows, float scale) BEAGLE_INLINE_LAMBDA {
+    __syncthreads();
+    const int r = tid >> 3;
+    if (r < rows)
+      for (int c = tid & 7; c < d; c += 8) {
+        const int i = r * (32 * NC + 1) + c;
+        out[r * stride + c] = (((ob[0][i] + ob[1][i]) + ob[2][i]) + ob[3][i]) * scale;
+      }
+    __syncthreads();
+  };
+  if ((int)blockIdx.x < n_dq) {
+    const int nq = (a.S + 31) / 32;
+    const int row = blockIdx.x / nq, q0 = (nq - 1 - (int)blockIdx.x % nq) * 32;
+    const int h = row % a.H, b = row / a.H, g = h / rep;
+    const SeqView sv = seq_view(a, b);
+    if (q0 >= sv.S) return;
+    const int q = q0 + ql, qc = min(q, sv.S - 1);
+    const int64_t qrow = ((sv.q0 + qc) * a.H + h) * d, li = sv.lse0 + h * sv.lse_hs + qc;
+    const float* K = (const float*)a.k + (sv.kv0 * a.G + g) * d;
+    const float* V = (const float*)a.v + (sv.kv0 * a.G + g) * d;
+    float qf[16 * NC], gf[16 * NC];
+    float part = 0.f;
+    {
+      float of[16 * NC];
+      row_frag<NC>((const float*)a.q + qrow, d, hf, qf);
+      row_frag<NC>((const float*)a.dout + qrow, d, hf, gf);
+      row_frag<NC>((const float*)a.o + qrow, d, hf, of);
+#pragma unroll
+      for (int i = 0; i < 16 * NC; ++i) part = fmaf(gf[i], of[i], part);
+    }
+    const float lse = a.lse[li], delta = pair_sum(part);
+    if (wave == 0 && hf == 0 && q < sv.S) a.delta[li] = delta;
+    const MaskParams mk = sample_mask(a, b);
+    const int lim = q < sv.S ? row_limit(q, mk) : 0;
+    const int wg_lim = row_limit(min(q0 + 32, sv.S) - 1, mk);
+    f32x16_t dq[NC];
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) dq[cb] = zero16();
+    for (int j0 = 32 * wave; j0 < wg_lim; j0 += 128) {
+      float kf[16 * NC], vf[16 * NC], kc[NC][16];
+      const int64_t jr = min(j0 + ql, sv.L - 1) * kvs;
+      row_frag<NC>(K + jr, d, hf, kf);
+      row_frag<NC>(V + jr, d, hf, vf);
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) col_frag(K, kvs, j0, sv.L, min(32 * cb + ql, d - 1), hf, kc[cb]);
+      f32x16_t s = dot_frags<NC>(kf, qf);
+      const f32x16_t dp = dot_frags<NC>(vf, gf);
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        s[e] = j0 + acc_row(e, hf) < lim ? expf(a.scale * s[e] - lse) * (dp[e] - delta) : 0.f;
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) dq[cb] = mfma(kc[cb][e], s[e], dq[cb]);
+    }
+    park<NC>(ob[wave], dq, ql, hf);
+    rows_out((float*)a.dq + ((sv.q0 + q0) * a.H + h) * d, qs, min(32, sv.S - q0), a.scale);
+  } else {
+    const int nk = (a.L + 31) / 32, n = (int)blockIdx.x - n_dq;
+    const int row = n / nk, j0 = (n % nk) * 32, g = row % a.G, b = row / a.G;
+    const SeqView sv = seq_view(a, b);
+    if (j0 >= sv.L) return;
+    const int j = j0 + ql;
+    const int64_t kvrow = ((sv.kv0 + min(j, sv.L - 1)) * a.G + g) * d;
+    float kf[16 * NC], vf[16 * NC];
+    row_frag<NC>((const float*)a.k + kvrow, d, hf, kf);
+    row_frag<NC>((const float*)a.v + kvrow, d, hf, vf);
+    const MaskParams mk = sample_mask(a, b);
+    const int fq = j < sv.L ? first_query_seeing(j, mk) : sv.S;         // this lane's key is seen from here on
+    const int qb0 = first_query_seeing(j0, mk) / 32, nqb = (sv.S + 31) / 32, per = nqb > qb0 ? nqb - qb0 : 0;
+    f32x16_t dk[NC], dv[NC];
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) { dk[cb] = zero16(); dv[cb] = zero16(); }
+    for (int it = wave; it < per * rep; it += 4) {
+      const int hh = it / per, p0 = (qb0 + it % per) * 32, h = g * rep + hh;
+      const float* Q = (const float*)a.q + (sv.q0 * a.H + h) * d;
+      const float* dO = (const float*)a.dout + (sv.q0 * a.H + h) * d;
+      const int pc = min(p0 + ql, sv.S - 1);
+      float qf[16 * NC], gf[16 * NC];
+      row_frag<NC>(Q + pc * qs, d, hf, qf);
+      row_frag<NC>(dO + pc * qs, d, hf, gf);
+      float part = 0.f;
+      {
+        float of[16 * NC];
+        row_frag<NC>((const float*)a.o + (sv.q0 * a.H + h) * d + pc * qs, d, hf, of);
+#pragma unroll
+        for (int i = 0; i < 16 * NC; ++i) part = fmaf(gf[i], of[i], part);
+      }
+      part = pair_sum(part);
+      if (hf == 0) { st[wave][0][ql] = a.lse[sv.lse0 + h * sv.lse_hs + pc]; st[wave][1][ql] = part; }
+      __builtin_amdgcn_wave_barrier();                  // (written and read by this wave only)
+      // the second products' operands: requested here where registers allow (head width up to 64)
+      constexpr bool EARLY = NC <= 2;
+      float cg[EARLY ? NC : 1][16], cq[EARLY ? NC : 1][16];
+      if constexpr (EARLY) {
+#pragma unroll
+        for (int cb = 0; cb < NC; ++cb) {
+          col_frag(dO, qs, p0, sv.S, min(32 * cb + ql, d - 1), hf, cg[cb]);
+          col_frag(Q, qs, p0, sv.S, min(32 * cb + ql, d - 1), hf, cq[cb]);
+        }
+      }
+      f32x16_t s = dot_frags<NC>(qf, kf);               // [query acc_row(e, hf)][key ql]
+      f32x16_t dp = dot_frags<NC>(gf, vf);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int r = acc_row(e, hf), p = p0 + r;
+        const bool vis = p >= fq && p < sv.S;           // a blind query (LSE -inf) is below fq of every key
+        s[e] = vis ? expf(a.scale * s[e] - st[wave][0][r]) : 0.f;
+        dp[e] = vis ? s[e] * (dp[e] - st[wave][1][r]) : 0.f;
+      }
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) {
+        constexpr int CB = EARLY ? 1 : 0;
+        if constexpr (!EARLY) {
+          col_frag(dO, qs, p0, sv.S, min(32 * cb + ql, d - 1), hf, cg[0]);
+          col_frag(Q, qs, p0, sv.S, min(32 * cb + ql, d - 1), hf, cq[0]);
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { dv[cb] = mfma(cg[CB * cb][e], s[e], dv[cb]); dk[cb] = mfma(cq[CB * cb][e], dp[e], dk[cb]); }
+      }
+    }
+    const int64_t out0 = ((sv.kv0 + j0) * a.G + g) * d;
+    park<NC>(ob[wave], dk, ql, hf);
+    rows_out((float*)a.dk + out0, kvs, min(32, sv.L - j0), a.scale);
+    park<NC>(ob[wave], dv, ql, hf);
+    rows_out((float*)a.dv + out0, kvs, min(32, sv.L - j0), 1.f);
+  }
+}
+
+}  // namespace
+
+// 32 x 32 tiles while they are fewer than fit the chip twice over at four workgroups per CU; 64 x 64 beyond
+void launch_gemm_f32(const GemmGroup& g, hipStream_t s, const char* name) {
+  int64_t t32 = 0, t64 = 0;
+  for (int i = 0; i < g.count; ++i) {
+    t32 += (int64_t)((g.p[i].M + 31) / 32) * ((g.p[i].N + 31) / 32);
+    t64 += (int64_t)((g.p[i].M + 63) / 64) * ((g.p[i].N + 63) / 64);
+  }
+  if (t32 == 0) return;
+  ProfScope ps(name, s);
+  if (t32 < 2048) hipLaunchKernelGGL(gemm_f32_kernel<4>, dim3((unsigned)t32), dim3(256), 0, s, g);
+  else hipLaunchKernelGGL(gemm_f32_kernel<1>, dim3((unsigned)t64), dim3(256), 0, s, g);
+}
+
+void launch_attn_fwd_f32(const AttnArgs& a, hipStream_t s) {
+  ProfScope ps("attn_fwd_f32", s);
+  const dim3 grid((a.S + 31) / 32, a.H, a.B), wg(256);
+  switch ((a.d + 31) / 32) {
+    case 1: hipLaunchKernelGGL(attn_fwd_f32_kernel<1>, grid, wg, 0, s, a); break;
+    case 2: hipLaunchKernelGGL(attn_fwd_f32_kernel<2>, grid, wg, 0, s, a); break;
+    case 3: hipLaunchKernelGGL(attn_fwd_f32_kernel<3>, grid, wg, 0, s, a); break;
+    default: hipLaunchKernelGGL(attn_fwd_f32_kernel<4>, grid, wg, 0, s, a); break;
+  }
+}
+
+void launch_attn_bwd_f32(const AttnArgs& a, hipStream_t s) {
+  ProfScope ps("attn_bwd_f32", s);
+  const int n_dq = ((a.S + 31) / 32) * a.H * a.B, n_dkv = ((a.L + 31) / 32) * a.G * a.B;
+  const dim3 grid(n_dq + n_dkv), wg(256);
+  switch ((a.d + 31) / 32) {
+    case 1: hipLaunchKernelGGL(attn_bwd_f32_kernel<1>, grid, wg, 0, s, a, n_dq); break;
+    case 2: hipLaunchKernelGGL(attn_bwd_f32_kernel<2>, grid, wg, 0, s, a, n_dq); break;
+    case 3: hipLaunchKernelGGL(attn_bwd_f32_kernel<3>, grid, wg, 0, s, a, n_dq); break;
+    default: hipLaunchKernelGGL(attn_bwd_f32_kernel<4>, grid, wg, 0, s, a, n_dq); break;
+  }
+}
+
+}  // namespace beagle
