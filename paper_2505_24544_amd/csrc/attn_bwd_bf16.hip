@@ -208,9 +208,19 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
 namespace dkv {
 constexpr int BJ = 128, BQ = 64;
 constexpr int TILE = BQ * HD;            // one Q or dO tile
+constexpr int SLOT = 2 * BJ * HD;        // floats of one partial result: dK, then dV of a key tile
+// SPLIT: a key tile's (head, query tile) pairs are cut into chunks of `per_chunk`, up to `chunks` workgroups per tile
+struct Split { float* part; int32_t chunks, per_chunk; };
+// pairs of key tile j0, and the workgroups that share them (at least one: it writes the zeros of unseen keys)
+__device__ __forceinline__ int tile_pairs(int j0, const MaskParams& mk, int S, int rep) {
+  const int qt0 = first_query_seeing(j0, mk) / BQ, nqt = (S + BQ - 1) / BQ;
+  return nqt > qt0 ? (nqt - qt0) * rep : 0;
+}
+__device__ __forceinline__ int tile_chunks(int pairs, int per_chunk) { return pairs > per_chunk ? (pairs + per_chunk - 1) / per_chunk : 1; }
 }  // namespace dkv
 
-__global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a) {
+template <bool SPLIT>
+__global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, dkv::Split sp) {
   using namespace dkv;
   args_at_hand(a);
   __shared__ __attribute__((aligned(1024))) bf16_t stage0[2 * TILE];
@@ -222,6 +232,9 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hf = lane >> 5, jl = lane & 31;
   int row, jt;                                    // key tile 0 is seen by the most queries: heaviest first
   map_block(blockIdx.x, a.G * a.B, row, jt);
+  int chunk = 0;
+  // (chunk by chunk over all tiles: the workgroups that run together then share the query tiles of the same heads in L2)
+  if (SPLIT) { const int ntile = (a.L + BJ - 1) / BJ; chunk = jt / ntile; jt %= ntile; }
   const int g = row % a.G, b = row / a.G;
   const int rep = a.H / a.G;
   const int j0 = jt * BJ, jw0 = j0 + wave * 32, j = jw0 + jl;
@@ -250,7 +263,15 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a) {
   const int qt0 = wg_first / BQ;
   const int nqt = (sv.S + BQ - 1) / BQ;
   const int per_head = nqt > qt0 ? nqt - qt0 : 0;
-  const int iters = per_head * rep;                 // (head, query tile) pairs, head-major
+  int iters = per_head * rep;                       // (head, query tile) pairs, head-major
+  int first = 0;                                    // this workgroup's first
+  bool whole = true;                                // no other workgroup shares the key tile
+  if (SPLIT) {
+    whole = tile_chunks(iters, sp.per_chunk) == 1;
+    first = chunk * sp.per_chunk;
+    if (chunk > 0 && first >= iters) return;
+    iters = min(iters - first, sp.per_chunk);
+  }
   int fq, wave_first, wave_all;                     // set behind the first tile's requests
   const float c2 = a.scale * LOG2E;
   const FragOffs fo = make_frag_offs(lane);
@@ -264,11 +285,12 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a) {
   // Q / dO rows and the LSE / delta entries of tile `it`; rows and entries past
   // the sequence end arrive as zeros (zero Q and dO rows contribute nothing).
   int f_hh = 0, f_qt = qt0;                         // fetch cursor: head within the group, query tile
-  int c_qt = qt0;                                   // compute cursor: query tile
-  const int64_t head0 = sv.q0 * a.H + g * rep;
+  if (SPLIT && first > 0) { f_hh = first / per_head; f_qt = qt0 + first % per_head; }
+  int c_qt = f_qt;                                  // compute cursor: query tile
+  const int64_t head0 = sv.q0 * a.H + g * rep + f_hh;
   const bf16_t* f_q = (const bf16_t*)a.q + head0 * HD;           // row 0 of the fetch cursor's head
   const bf16_t* f_do = (const bf16_t*)a.dout + head0 * HD;
-  const float* f_stat = ((wave & 1) == 0 ? a.nlse2 : a.delta) + sv.lse0 + (g * rep) * sv.lse_hs;
+  const float* f_stat = ((wave & 1) == 0 ? a.nlse2 : a.delta) + sv.lse0 + (g * rep + f_hh) * sv.lse_hs;
   const int tile_bytes = sv.S > 0 ? (int)((((int64_t)sv.S - 1) * qs + HD) * 2) : 0;   // one head's Q (dO) rows of this entry
   auto fetch = [&](bf16_t* st, float* stat) {
     const int q0 = f_qt * BQ;
@@ -401,6 +423,18 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a) {
   }
   if (it < iters) tile_step(stage0, stat0, stage1, stat1);
 
+  if (SPLIT && !whole) {
+    // a share of the sums: as the accumulators lie, 1 KB per store instruction; sum_dkv_kernel adds the shares in order
+    float* slot = sp.part + (((int64_t)row * ((a.L + BJ - 1) / BJ) + jt) * sp.chunks + chunk) * SLOT + wave * 4096 + lane * 4;
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd) {
+        *(float4*)(slot + (4 * cb + qd) * 256) = float4{dk[cb][4 * qd], dk[cb][4 * qd + 1], dk[cb][4 * qd + 2], dk[cb][4 * qd + 3]};
+        *(float4*)(slot + BJ * HD + (4 * cb + qd) * 256) = float4{dv[cb][4 * qd], dv[cb][4 * qd + 1], dv[cb][4 * qd + 2], dv[cb][4 * qd + 3]};
+      }
+    return;
+  }
   // ---- dK, dV rows out, through LDS (both stages are free: the last step ended with the requests landed and a barrier)
   {
     uint2 pk[16], pv[16];
@@ -419,8 +453,80 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a) {
   }
 }
 
-// workspace: the pre-scaled LSE array, as large as delta
-size_t attn_bwd_bf16_ws_bytes(const AttnArgs& a) { return (size_t)a.B * a.H * a.S * sizeof(float); }
+// dK, dV of the key tiles that several workgroups shared: the sum of their shares, in chunk order.  One workgroup per
+// (32 keys of a tile, matrix): 16 KB per share, summed as they lie, turned into rows in LDS.
+__global__ __launch_bounds__(256) void sum_dkv_kernel(AttnArgs a, dkv::Split sp) {
+  using namespace dkv;
+  __shared__ __attribute__((aligned(16))) bf16_t rows[32][HD + 8];
+  const int tid = threadIdx.x, ntile = (a.L + BJ - 1) / BJ;
+  const int w = blockIdx.x & 3, mat = (blockIdx.x >> 2) & 1, tile = blockIdx.x >> 3;
+  const int jt = tile % ntile, row = tile / ntile, g = row % a.G, b = row / a.G;
+  const SeqView sv = seq_view(a, b);
+  const int j0 = jt * BJ, jw0 = j0 + 32 * w;
+  if (jw0 >= sv.L) return;
+  const int n = tile_chunks(tile_pairs(j0, sample_mask(a, b), sv.S, a.H / a.G), sp.per_chunk);
+  if (n == 1) return;
+  const float* src = sp.part + (int64_t)tile * sp.chunks * SLOT + mat * BJ * HD + w * 4096;
+  const float scale = mat == 0 ? a.scale : 1.f;
+  float4 acc[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc[i] = float4{0.f, 0.f, 0.f, 0.f};
+  for (int c0 = 0; c0 < n; c0 += 4) {                // four shares (16 loads) in flight; past the last one: it again, unused
+    float4 t[4][4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t[c][i] = *(const float4*)(src + (int64_t)min(c0 + c, n - 1) * SLOT + (tid + 256 * i) * 4);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (c0 + c < n) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { acc[i].x += t[c][i].x; acc[i].y += t[c][i].y; acc[i].z += t[c][i].z; acc[i].w += t[c][i].w; }
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int idx = tid + 256 * i, piece = idx >> 6, lane = idx & 63;
+    *(uint2*)&rows[lane & 31][8 * piece + 4 * (lane >> 5)] =
+        make_uint2(cvt_pk(acc[i].x * scale, acc[i].y * scale), cvt_pk(acc[i].z * scale, acc[i].w * scale));
+  }
+  __syncthreads();
+  bf16_t* out = (bf16_t*)(mat == 0 ? a.dk : a.dv) + ((sv.kv0 + jw0) * a.G + g) * HD;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int idx = tid + 256 * i, r = idx >> 4, c = idx & 15;
+    if (jw0 + r < sv.L) *(uint4*)(out + (int64_t)r * a.G * HD + 8 * c) = *(const uint4*)&rows[r][8 * c];
+  }
+}
+
+// Workgroups of the dK/dV kernel per key tile.  A tile's pairs are one serial chain of 1.9 us each; under grouped-query
+// attention the heads of a group multiply it, and a short batch ends up with a few long chains on a few CUs.  With up to
+// 256 tiles (one workgroup per CU) the chains are cut so that about one round of workgroups has work: tiles are seen by
+// half of the queries on average, so n chunks make tiles (n + 1) / 2 of them.  Measured with 32 heads in 8 groups, us, one
+// workgroup per tile -> n chunks + their sum: 300 positions (24 tiles) 42 -> 23, 777 (56) 93 -> 38, 1300 (88) 144 -> 60, 2048
+// (128) 222 -> 106, 4096 (256) 448 -> 332.  Beyond that the shares cost what the balance gains (5546: 636 -> 614 at best, 8192:
+// 574 -> 608), and so they do where the chain is short (777 positions, 32 groups: 34 -> 39).
+static dkv::Split dkv_split(const AttnArgs& a) {
+  dkv::Split sp = {nullptr, 1, 0x7fffffff};
+  const int64_t tiles = (int64_t)((a.L + dkv::BJ - 1) / dkv::BJ) * a.G * a.B;
+  const int64_t longest = (int64_t)((a.S + dkv::BQ - 1) / dkv::BQ) * (a.H / a.G);
+  if (tiles > 256) return sp;
+  int64_t n = tiles > 128 ? 2 : (448 + tiles / 2) / tiles - 1;
+  if (n > 16) n = 16;
+  const int64_t per = (longest + n - 1) / n;
+  if (longest - per < 10) return sp;
+  sp.chunks = (int32_t)((longest + per - 1) / per);
+  sp.per_chunk = (int32_t)per;
+  return sp;
+}
+
+// workspace: the pre-scaled LSE array, as large as delta, and the shares of split key tiles
+static size_t nlse_bytes(const AttnArgs& a) { return ((size_t)a.B * a.H * a.S * sizeof(float) + 255) / 256 * 256; }
+size_t attn_bwd_bf16_ws_bytes(const AttnArgs& a) {
+  const dkv::Split sp = dkv_split(a);
+  const size_t tiles = (size_t)((a.L + dkv::BJ - 1) / dkv::BJ) * a.G * a.B;
+  return nlse_bytes(a) + (sp.chunks > 1 ? tiles * sp.chunks * dkv::SLOT * sizeof(float) : 0);
+}
 
 void launch_attn_bwd_bf16(const AttnArgs& args, void* ws, hipStream_t s) {
   AttnArgs a = args;
@@ -430,10 +536,17 @@ void launch_attn_bwd_bf16(const AttnArgs& args, void* ws, hipStream_t s) {
     dim3 grid(((a.S + dqk::BQ - 1) / dqk::BQ) * a.H * a.B);
     hipLaunchKernelGGL(attn_bwd_dq_bf16_kernel, grid, dim3(256), 0, s, a);
   }
+  dkv::Split sp = dkv_split(a);
+  sp.part = (float*)((char*)ws + nlse_bytes(a));
+  const int tiles = ((a.L + dkv::BJ - 1) / dkv::BJ) * a.G * a.B;
   {
     ProfScope ps("attn_bwd_dkv_bf16", s);
-    dim3 grid(((a.L + dkv::BJ - 1) / dkv::BJ) * a.G * a.B);
-    hipLaunchKernelGGL(attn_bwd_dkv_bf16_kernel, grid, dim3(256), 0, s, a);
+    if (sp.chunks > 1) hipLaunchKernelGGL(attn_bwd_dkv_bf16_kernel<true>, dim3(tiles * sp.chunks), dim3(256), 0, s, a, sp);
+    else hipLaunchKernelGGL(attn_bwd_dkv_bf16_kernel<false>, dim3(tiles), dim3(256), 0, s, a, sp);
+  }
+  if (sp.chunks > 1) {
+    ProfScope ps("attn_bwd_dkv_sum", s);
+    hipLaunchKernelGGL(sum_dkv_kernel, dim3(tiles * 8), dim3(256), 0, s, a, sp);
   }
 }
 
