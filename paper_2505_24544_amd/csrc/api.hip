@@ -168,7 +168,7 @@ const void* states_in(const Dims& d, const void* xkv, void* workspace, size_t ne
 RopeArgs rope_args(const Dims& d, bool inverse) {
   RopeArgs r; memset(&r, 0, sizeof(r));
   r.nb = (int32_t)d.B;
-  r.d = (int32_t)d.d; r.base = d.rope_base; r.inverse = inverse ? 1 : 0;
+  r.d = (int32_t)d.d; r.l2base = log2((double)d.rope_base); r.inverse = inverse ? 1 : 0;
   return r;
 }
 void rope_add(RopeArgs& r, void* x, int64_t rows, int64_t period, int64_t heads, int32_t pos0, const int32_t* pos,
@@ -396,7 +396,10 @@ void kv_append_run(const Dims& d, const void* x_new, const void* wk, const void*
   char* kdst = (char*)k_cache + (size_t)pos * d.GD * d.esz;
   char* vdst = (char*)v_cache + (size_t)pos * d.GD * d.esz;
   if (packed_norm_eps == packed_norm_eps) {      // not NaN: packed weights (the caller has checked strip_gemm_fits)
-    launch_kv_append_strip_bf16(x_new, wk, wv, kdst, vdst, (int32_t)d.S, (int32_t)d.GD, (int32_t)d.D, packed_norm_eps, s);
+    // (the rotary embedding of the K rows is applied to the finished sums)
+    const RopeRows rope = {d.rope_pos, pos, d.rope ? log2((double)d.rope_base) : 0.0, nullptr, d.rope ? 1 : 0};
+    launch_kv_append_strip_bf16(x_new, wk, wv, kdst, vdst, (int32_t)d.S, (int32_t)d.GD, (int32_t)d.D, packed_norm_eps, rope, s);
+    return;
   } else if (d.bf16 && kv_append_bf16_fits((int32_t)d.S, (int32_t)d.GD, (int32_t)d.D)) {
     // a handful of states: HBM-bound on Wk and Wv, so the split-k streaming projection of the draft step
     launch_kv_append_bf16(x_new, wk, wv, kdst, vdst, (int32_t)d.S, (int32_t)d.GD, (int32_t)d.D, workspace, s);

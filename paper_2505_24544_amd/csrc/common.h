@@ -103,7 +103,24 @@ void launch_silu_mul_fwd(bool bf16, const void* u, const void* w, void* m, int64
 void launch_silu_mul_bwd(bool bf16, const void* dm, const void* u, const void* w, void* du, void* dw, int64_t n,
                          hipStream_t s);
 
-// ---- rotary position embedding, in place, of up to three [rows, heads, d] tensors in one launch ----
+// ---- rotary position embedding ----
+// (cos, sin) of position * base^(-2c/d), l2base = log2(base).  In double throughout: with float angles the fp32 path
+// misses 1e-5 at positions in the thousands.  The angle is taken in turns, reduced to an eighth of one exactly, and
+// the two Taylor series run to x^15 / x^14 (below 1e-13 at pi / 4): some 25 double instructions where the library's sincos,
+// which has to reduce any argument, takes an order of magnitude more.
+__device__ __forceinline__ float2 rope_cos_sin(int32_t pos, int c, int d, double l2base) {
+  const double turns = (double)pos * exp2(-2.0 * c / d * l2base) * 0.15915494309189533577;
+  const double r = turns - rint(turns), q = rint(4.0 * r), x = (r - 0.25 * q) * 6.28318530717958647693, z = x * x;
+  const double s = x * (1.0 + z * (-1.0 / 6 + z * (1.0 / 120 + z * (-1.0 / 5040 + z * (1.0 / 362880 + z * (-1.0 / 39916800 +
+                   z * (1.0 / 6227020800.0 + z * (-1.0 / 1307674368000.0))))))));
+  const double k = 1.0 + z * (-0.5 + z * (1.0 / 24 + z * (-1.0 / 720 + z * (1.0 / 40320 + z * (-1.0 / 3628800 +
+                   z * (1.0 / 479001600.0 + z * (-1.0 / 87178291200.0)))))));
+  const int iq = (int)q & 3;                       // quarter turns: q = -2 .. 2
+  const double cs = iq == 0 ? k : iq == 1 ? -s : iq == 2 ? -k : s, sn = iq == 0 ? s : iq == 1 ? k : iq == 2 ? -s : -k;
+  return make_float2((float)cs, (float)sn);
+}
+
+// In place, of up to three [rows, heads, d] tensors in one launch.
 // Row r of tensor t stands at position pos[t] ? pos[t][r % period[t]] : pos0[t] + r % period[t].
 struct RopeArgs {
   int32_t n;                    // tensors
@@ -114,7 +131,7 @@ struct RopeArgs {
   const int32_t* cu[3];         // packed batch: row r of tensor t is row r - cu[b] of the entry b that holds it
   int32_t nb;                   // entries (cu has nb + 1 values)
   int32_t d;                    // head width, d % 4 == 0, d <= 128
-  float base;
+  double l2base;                // log2 of the frequency base
   int32_t inverse;              // rotate by -angle (gradients)
 };
 void launch_rope(bool bf16, const RopeArgs& r, hipStream_t s, const char* name);
@@ -234,8 +251,15 @@ void launch_block_mlp_bf16(const void* z, const void* w_gate, const void* w_up, 
                            void* h, int32_t M, int32_t D, int32_t F, void* ws, hipStream_t s);
 // the same on packed weights: two strip launches, gate fused;
 // needs strip_gemm_fits(M, F, D) and strip_gemm_fits(M, D, F); ws: M * F bf16
+// rope: null, or the rotary embedding of the K rows (pos / pos0, l2base), applied to the finished sums
+struct RopeRows {
+  const int32_t* pos; int32_t pos0;  // row i stands at pos ? pos[i] : pos0 (+ i where the rows are consecutive)
+  double l2base;
+  float2* tab;                       // where a launch that prepares the angles puts (cos, sin): [rows][64]
+  int32_t on;
+};
 void launch_kv_append_strip_bf16(const void* x, const void* wk_pk, const void* wv_pk, void* kdst, void* vdst, int32_t n,
-                                 int32_t N, int32_t K, float norm_eps, hipStream_t s);
+                                 int32_t N, int32_t K, float norm_eps, const RopeRows& rope, hipStream_t s);
 void launch_block_mlp_strip_bf16(const void* z, const void* w_gate_pk, const void* w_up_pk, const void* w_down_pk,
                                  const void* y_res, void* h, int32_t M, int32_t D, int32_t F, float z_norm_eps, void* ws,
                                  hipStream_t s);

@@ -71,12 +71,25 @@ constexpr int COMB_MAXM = 4, COMB_MAXR = 8;
 
 typedef unsigned int xload_t __attribute__((ext_vector_type(4)));
 
+// (cos, sin) of the rotary angles of a step's M queries, tab[m * 64 + c] for channel pair c: written by workgroups of their
+// own in the query projection's launch (a launch of its own for it cost 3 us).
+__device__ __forceinline__ void rope_table(const RopeRows& r, int M, int first, int stride) {
+  for (int i = first; i < M * 64; i += stride) r.tab[i] = rope_cos_sin(r.pos ? r.pos[i >> 6] : r.pos0, i & 63, HD, r.l2base);
+}
+
 template <bool COMBINE>
 __global__ __launch_bounds__(256, 2) void skinny_gemm_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ W,
                                                              float* __restrict__ part, int M, int N, int K, CombineArgs cb,
                                                              const bf16_t* __restrict__ W_z1, float* __restrict__ part_z1,
-                                                             int x_chunked) {
+                                                             int x_chunked, RopeRows rope) {
   using namespace dec;
+  // (all arguments at hand after one trip to the constant cache, see sum_slices_kernel)
+  asm volatile("" :: "s"(x), "s"(W), "s"(part), "s"(M), "s"(N), "s"(K), "s"(W_z1), "s"(part_z1), "s"(x_chunked), "s"(cb.opart),
+               "s"(cb.mlpart), "s"(cb.lse), "s"(cb.lse_stride), "s"(cb.Mpad), "s"(cb.R), "s"(cb.scale));
+  if (!COMBINE && (int)blockIdx.x == N / SG_N) {            // (one more column of workgroups when there is a table to write)
+    rope_table(rope, M, blockIdx.y * 256 + threadIdx.x, gridDim.y * 256);
+    return;
+  }
   if (blockIdx.z == 1) { W = W_z1; part = part_z1; }        // second weight matrix of the launch (same x)
   // The 64 KB tile as four quarters of 128 k-rows, one LDS variable each: requests land in the order they were
   // issued, so quarter c is complete when all but the 12 - 4c youngest have landed, and its transpose reads
@@ -375,7 +388,7 @@ __global__ __launch_bounds__(256) void sum_gate_kernel(const float* __restrict__
 // workgroup 0 writes the LSE.
 // MODE 2 (feed-forward layer, Eq. 1): two weight matrices share the activations, and the strip's result is
 // silu(a W) * (a W2): the gate needs no launch of its own.
-// MODE 3 (cache append): two weight matrices share the activations, each with an output of its own (K and V rows).
+// MODE 3 (cache append): K and V rows.  Every workgroup works on two strips of one of the two matrices.
 // ---------------------------------------------------------------------------
 namespace dec {
 constexpr int ST_N = 16;                 // output columns per workgroup
@@ -390,10 +403,15 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
                                                             const bf16_t* __restrict__ Wt2, void* __restrict__ yout,
                                                             bf16_t* __restrict__ yout2, const bf16_t* __restrict__ res,
                                                             int M, int N, int K, CombineArgs cb, int out_f32,
-                                                            float norm_eps) {
+                                                            float norm_eps, RopeRows rope) {
   using namespace dec;
   asm volatile("" :: "s"(a), "s"(Wt), "s"(Wt2), "s"(yout), "s"(yout2), "s"(res), "s"(M), "s"(N), "s"(K), "s"(out_f32), "s"(norm_eps),
-               "s"(cb.opart), "s"(cb.mlpart), "s"(cb.lse), "s"(cb.lse_stride), "s"(cb.Mpad), "s"(cb.R), "s"(cb.scale));
+               "s"(cb.opart), "s"(cb.mlpart), "s"(cb.lse), "s"(cb.lse_stride), "s"(cb.Mpad), "s"(cb.R), "s"(cb.scale), "s"(rope.pos),
+               "s"(rope.pos0), "s"(rope.l2base), "s"(rope.on));
+  if (MODE == 0 && (int)blockIdx.x == N / ST_N) {           // (one more workgroup when there is a table to write)
+    rope_table(rope, M, threadIdx.x, 64 * WAVES);
+    return;
+  }
   constexpr int ROWS = ROWS16 ? 16 : 8;             // activation rows kept per macro-step
   constexpr int ST_CH = ROWS16 ? 2 : 4;             // macro-steps per activation chunk
   constexpr int LPS = ROWS / 4;                     // loads per macro-step (1 KB = 4 rows each)
@@ -408,13 +426,18 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
   __shared__ float winv[MODE == 1 ? WAVES : 1][8];
   __shared__ float ssw[WAVES][16];                  // RMSNorm: each wave's share of the rows' sums of squares
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n0 = blockIdx.x * ST_N;
+  // MODE 3: even workgroups work on Wk, odd ones on Wv, each on two strips 64 columns apart, i.e. on both halves of 16
+  // channel pairs of a head, so that the rotary embedding of the K rows can be applied to the finished sums
+  const bool second = MODE == 3 && (blockIdx.x & 1);
+  const int strip = MODE == 3 ? 8 * (blockIdx.x >> 3) + ((blockIdx.x >> 1) & 3) : blockIdx.x;
+  const int n0 = strip * ST_N;
   const int S = K >> 7;                             // macro-steps; wave w takes s = w, w + 8, ...
   const int nst = (S - wave + WAVES - 1) / WAVES;
   const int nl = lane & 15, kg = lane >> 4;
   unsigned char* aw0 = abuf[0] + wave * (ST_CH * ROWS * 256);
   unsigned char* aw1 = abuf[1] + wave * (ST_CH * ROWS * 256);
 
+  __shared__ float2 rot[MODE == 3 ? ST_MAXM : 1][16];
   float lse_out = -INFINITY;
   f32x4_t acc[NW];
 #pragma unroll
@@ -423,6 +446,15 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
 #pragma unroll
   for (int g = 0; g < LPS; ++g) ssl[g] = 0.f;
   const bool rownorm = norm_eps >= 0.f;
+  // MODE 3: thread (row, pair) evaluates the angle of one of the workgroup's 16 channel pairs for one row.  Its position is
+  // the wave's first request (requests complete in order: behind the weights it would be waited for with them).
+  const bool turns = MODE == 3 && rope.on && !second && tid < M * 16;
+  int tpos = rope.pos0 + (tid >> 4);
+  if (turns && rope.pos) tpos = rope.pos[tid >> 4];
+  auto angles = [&]() {
+    if (turns) rot[tid >> 4][tid & 15] = rope_cos_sin(tpos, 16 * ((blockIdx.x >> 1) & 3) + (tid & 15), HD, rope.l2base);
+  };
+  __builtin_amdgcn_sched_barrier(0);
   if (nst > 0) {                        // (a wave without a macro-step, K < 1024, only adds zeros below)
   // ---- activations.  Load q of chunk c covers rows 4 g + kg of step c ST_CH + i, (i, g) = divmod(q, LPS):
   // lane (kg, nl) reads chunk nl ^ row of its row and parks it at chunk nl, i.e. at lane * 16 of the 1 KB piece.
@@ -476,9 +508,10 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
   __builtin_amdgcn_sched_barrier(0);
 
   // ---- the first ST_RING macro-steps of weights (one matrix at K = 4096: all of them)
-  const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void*)Wt, 0, (int)((int64_t)N * K * 2), 0x00020000);
-  const __amdgpu_buffer_rsrc_t wrs2 = __builtin_amdgcn_make_buffer_rsrc((void*)(MODE >= 2 ? Wt2 : Wt), 0, (int)((int64_t)N * K * 2), 0x00020000);
-  const int wbase = blockIdx.x * 4096 + lane * 16;          // this strip's block of macro-step 0, this lane's 16 bytes
+  const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void*)(second ? Wt2 : Wt), 0, (int)((int64_t)N * K * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t wrs2 = MODE == 3 ? wrs : __builtin_amdgcn_make_buffer_rsrc((void*)(MODE == 2 ? Wt2 : Wt), 0, (int)((int64_t)N * K * 2), 0x00020000);
+  constexpr int W2OFF = MODE == 3 ? 4 * 4096 : 0;           // from the first strip's block to the second's
+  const int wbase = strip * 4096 + lane * 16;               // this strip's block of macro-step 0, this lane's 16 bytes
   const int wstep = (N / ST_N) * 4096;                      // from one macro-step's blocks to the next's
   union frag_t { xload_t u; bf16x8_t v; };
   frag_t bw[NW][ST_RING][4];
@@ -487,10 +520,12 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
     for (int w = 0; w < NW; ++w)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        bw[w][u][j].u = __builtin_amdgcn_raw_buffer_load_b128(w == 0 ? wrs : wrs2, i < nst ? wbase + (wave + WAVES * i) * wstep + j * 1024 : (int)0x80000000, 0, 0);
+        bw[w][u][j].u = __builtin_amdgcn_raw_buffer_load_b128(w == 0 ? wrs : wrs2, i < nst ? wbase + w * W2OFF + (wave + WAVES * i) * wstep + j * 1024 : (int)0x80000000, 0, 0);
   };
 #pragma unroll
   for (int u = 0; u < ST_RING; ++u) load_b(u, u);
+  __builtin_amdgcn_sched_barrier(0);
+  angles();                                         // while the first requests travel
   __builtin_amdgcn_sched_barrier(0);
 
   if constexpr (MODE == 1) {
@@ -560,6 +595,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
       i0 += ST_ROUND;
     } while (i0 < nst);
   }
+  } else {
+    angles();
   }
 
   // ---- the waves' k shares, added in wave order; output row 4 kg + e, column nl
@@ -597,7 +634,20 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
 #pragma unroll
       for (int wv = 1; wv < WAVES; ++wv) g += red[NW - 1][wv][m][n];
       if (MODE == 2) v = v / (1.f + expf(-v)) * (g * rn);      // silu(gate) * up
-      else yout2[o] = (bf16_t)(cvt_pk(g * rn, 0.f) & 0xffffu); // the second matrix has its own output
+      else {                                                   // columns n and n + 64 of a head's row
+        g *= rn;
+        if (rope.on && !second) {                              // the rows an append without it stores, rotated
+          const float2 t = rot[m][n];
+          v = bf16_to_f32(f32_to_bf16(v)); g = bf16_to_f32(f32_to_bf16(g));
+          const float lo = v * t.x - g * t.y;
+          g = g * t.x + v * t.y;
+          v = lo;
+        }
+        bf16_t* out = second ? yout2 : (bf16_t*)yout;
+        out[o] = (bf16_t)(cvt_pk(v, 0.f) & 0xffffu);
+        out[o + 64] = (bf16_t)(cvt_pk(g, 0.f) & 0xffffu);
+        return;
+      }
     }
     if (res) v += __uint_as_float((uint32_t)res[o] << 16);
     if (out_f32) ((float*)yout)[o] = v;                       // the queries: the attention kernel wants them unrounded
@@ -651,17 +701,6 @@ struct DecAttnArgs {
   const float2* rope_tab;
 };
 
-// (cos, sin) of the rotary angles of M queries, evaluated in double: query m stands at pos[m] (or pos0), channel
-// pair c < 64 turns by position * base^(-2c/128).
-__global__ __launch_bounds__(256) void rope_table_kernel(const int32_t* pos, int pos0, int M, float base, float2* tab) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= M * 64) return;
-  const int m = i >> 6, c = i & 63;
-  double sn, cs;
-  sincos((double)(pos ? pos[m] : pos0) * exp2(-2.0 * c / 128.0 * log2((double)base)), &sn, &cs);
-  tab[i] = make_float2((float)cs, (float)sn);
-}
-
 typedef lds_u32x2_t u32x2_t;
 
 // One workgroup per (head, key range, block of 32 NQB queries): grid (H, R, ceil(M / (32 NQB))).
@@ -675,7 +714,9 @@ typedef lds_u32x2_t u32x2_t;
 // loop is as free of barriers as with one block.  (Waves 0, 1 on the first block and waves 2, 3 on the second, each
 // with 64 keys of a step, was the earlier shape: stages shared between waves, hence a barrier per step with the
 // refill issued only behind it -- 4 400 cycles of arithmetic and 2 700 of request issue per step, one after the other.)
-template <int NQB>
+// QS: k-slices of q that are requested at once: one on packed weights, where q comes as a single slice (asked for as eight,
+// seven of them past the buffer's end, they took the summing wave another 28 requests), else eight; more in further trips.
+template <int NQB, int QS>
 __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
   using namespace dec;
   // two stages of one K and one V step tile each: tile t (0: K, 1: V) of stage i at (2 t + i) * TILE, so that the
@@ -750,32 +791,32 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
   const __amdgpu_buffer_rsrc_t qrs =
       __builtin_amdgcn_make_buffer_rsrc((void*)a.qpart, 0, (int)(a.KSq * slice * 4), 0x00020000);
   const int oob = 0x7fffff00;
-  auto q_issue = [&](int qb, int mrows, int qwaves, int k0, u32x4_t (&t)[4][8]) {
+  auto q_issue = [&](int qb, int mrows, int qwaves, int k0, u32x4_t (&t)[4][QS]) {
     const int mb = m0 + 32 * qb;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int idx = tid + 64 * qwaves * i, m = idx >> 5, c4 = idx & 31;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
+      for (int k = 0; k < QS; ++k) {
         const int off = (int)((((int64_t)(k0 + k) * a.M + mb + m) * HDt + h * HD + 4 * c4) * 4);
         t[i][k] = __builtin_amdgcn_raw_buffer_load_b128(qrs, (wave < qwaves && m < mrows && k0 + k < a.KSq) ? off : oob, 0, 0);
       }
     }
   };
-  auto q_add = [&](const u32x4_t (&t)[4][8], float4 (&acc)[4]) {
+  auto q_add = [&](const u32x4_t (&t)[4][QS], float4 (&acc)[4]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
+      for (int k = 0; k < QS; ++k) {
         acc[i].x += __uint_as_float(t[i][k][0]); acc[i].y += __uint_as_float(t[i][k][1]);
         acc[i].z += __uint_as_float(t[i][k][2]); acc[i].w += __uint_as_float(t[i][k][3]);
       }
   };
-  // slices past the first eight (model widths above 4096), and the rotary embedding: this thread's four channels of
+  // slices past the first QS (eight: model widths above 4096), and the rotary embedding: this thread's four channels of
   // query m pair with the four that lane ^ 16 holds (float4 slot c4 ^ 16 of the same query)
   auto q_finish = [&](int qb, int mrows, int qwaves, float4 (&acc)[4]) {
-    for (int k0 = 8; k0 < a.KSq; k0 += 8) {
-      u32x4_t t[4][8];
+    for (int k0 = QS; k0 < a.KSq; k0 += QS) {
+      u32x4_t t[4][QS];
       q_issue(qb, mrows, qwaves, k0, t);
       q_add(t, acc);
     }
@@ -857,7 +898,7 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
     // 21 of them).  q is there long before the first step has landed.
     shared_first_steps = true;
     if (wave == 0) {
-      u32x4_t t[4][8];
+      u32x4_t t[4][QS];
       float4 acc[4] = {zero4, zero4, zero4, zero4};
       q_issue(0, mtot, 1, 0, t);
       q_add(t, acc);
@@ -895,7 +936,7 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
     // its rows of step 1 -- the K/V stream starts with the kernel, and q (loads return in order) is complete when
     // step 0 has landed, which the arithmetic has to wait for anyway.
     const int qwaves = mtot <= 16 ? 2 : 4;
-    u32x4_t t[4][8];
+    u32x4_t t[4][QS];
     float4 acc[4] = {zero4, zero4, zero4, zero4};
     fetch_own(0, 0);
     q_issue(0, mtot, qwaves, 0, t);
@@ -921,14 +962,14 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
     // 33 .. 64 queries, all four waves sum both blocks: own rows of step 0, block 0's slices, own rows of step 1,
     // block 1's slices -- the last of these only issue as the oldest requests retire (a wave holds at most 63), which
     // is when step 0 lands, and are back soon after step 1.
-    u32x4_t t0[4][8], t1[4][8];
+    u32x4_t t0[4][QS], t1[4][QS];
     float4 acc[4] = {zero4, zero4, zero4, zero4};
     fetch_own(0, 0);
     q_issue(0, 32, 4, 0, t0);
     fetch_own(1, 1);
     q_issue(1, mtot - 32, 4, 0, t1);                           // rows past the last query: zeros
     __builtin_amdgcn_sched_barrier(0);
-    wait_vmem_n<48>();                                         // step 0 and block 0's slices
+    wait_vmem_n<16 + 4 * QS>();                                         // step 0 and block 0's slices
     q_add(t0, acc);
     q_finish(0, 32, 4, acc);
     q_store(0, 4, acc);
@@ -1329,15 +1370,15 @@ bool strip_gemm_fits(int32_t M, int32_t N, int32_t K) {
 }
 // y = a W (+ res) on packed W; with wt2: y = silu(a W) * (a W2); with merge: a is merged from the attention partials (M = 1)
 void launch_strip_gemm(const bf16_t* a, const bf16_t* wt, const bf16_t* wt2, void* y, bf16_t* y2, const bf16_t* res, int M,
-                       int N, int K, const CombineArgs* merge, bool out_f32, float norm_eps, hipStream_t s) {
+                       int N, int K, const CombineArgs* merge, bool out_f32, float norm_eps, const RopeRows& rope, hipStream_t s) {
   using namespace dec;
-  const dim3 grid(N / ST_N);
+  const dim3 grid(N / ST_N + (rope.tab ? 1 : 0));
   const CombineArgs cb = merge ? *merge : CombineArgs{};
   const int f = out_f32 ? 1 : 0;
   // one matrix: eight waves, one workgroup per CU (N / 16 is about the number of CUs for the attention's projections);
   // the feed-forward pair has several strips per CU: four waves and two workgroups per CU, so that one's start and
   // final reduction hide behind the other's stream; the K/V pair of the cache append (y2 given) is as wide as one matrix
-#define STRIP_ARGS a, wt, wt2, y, y2, res, M, N, K, cb, f, norm_eps
+#define STRIP_ARGS a, wt, wt2, y, y2, res, M, N, K, cb, f, norm_eps, rope
   if (merge) hipLaunchKernelGGL((strip_gemm_kernel<1, false, 8>), grid, dim3(512), 0, s, STRIP_ARGS);
   else if (wt2 && y2 && M <= 8) hipLaunchKernelGGL((strip_gemm_kernel<3, false, 8>), grid, dim3(512), 0, s, STRIP_ARGS);
   else if (wt2 && y2) hipLaunchKernelGGL((strip_gemm_kernel<3, true, 8>), grid, dim3(512), 0, s, STRIP_ARGS);
@@ -1363,21 +1404,19 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
   bf16_t* o = (bf16_t*)(base + w.o);
   float* ypart = (float*)(base + w.ypart);
   float2* ropetab = a.rope ? (float2*)(base + w.ropetab) : nullptr;
-  if (a.rope) {
-    ProfScope ps("draft_rope_table", s);
-    hipLaunchKernelGGL(rope_table_kernel, dim3((a.M * 64 + 255) / 256), dim3(256), 0, s, a.rope_pos, a.L, a.M,
-                       a.rope_base, ropetab);
-  }
+  const double l2base = a.rope ? log2((double)a.rope_base) : 0.0;
   for (int m0 = 0; m0 < a.M; m0 += MAXM) {
     const int Mp = a.M - m0 < MAXM ? a.M - m0 : MAXM;
     const bf16_t* x = (const bf16_t*)a.x + (int64_t)m0 * a.D;
+    // the angles of this pass's queries, at rope_pos or all behind the cached rows
+    const RopeRows rope = {a.rope_pos ? a.rope_pos + m0 : nullptr, a.L, l2base, ropetab ? ropetab + (int64_t)m0 * 64 : nullptr, a.rope};
     if (a.wq_pk) {                    // packed Wq: the whole of k in one strip, so q arrives as a single slice
       ProfScope ps("draft_proj_q", s);
-      launch_strip_gemm(x, (const bf16_t*)a.wq_pk, nullptr, qpart, nullptr, nullptr, Mp, HDt, a.D, nullptr, true, a.x_norm_eps, s);
+      launch_strip_gemm(x, (const bf16_t*)a.wq_pk, nullptr, qpart, nullptr, nullptr, Mp, HDt, a.D, nullptr, true, a.x_norm_eps, rope, s);
     } else {
       ProfScope ps("draft_proj_q", s);
-      hipLaunchKernelGGL(skinny_gemm_kernel<false>, dim3(HDt / SG_N, w.KSq), dim3(256), 0, s, x, (const bf16_t*)a.wq, qpart,
-                         Mp, HDt, a.D, CombineArgs{}, (const bf16_t*)nullptr, (float*)nullptr, 0);
+      hipLaunchKernelGGL(skinny_gemm_kernel<false>, dim3(HDt / SG_N + (a.rope ? 1 : 0), w.KSq), dim3(256), 0, s, x, (const bf16_t*)a.wq,
+                         qpart, Mp, HDt, a.D, CombineArgs{}, (const bf16_t*)nullptr, (float*)nullptr, 0, rope);
     }
     {
       DecAttnArgs t;
@@ -1386,10 +1425,12 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
       t.M = Mp; t.Mpad = w.Mpad; t.L = a.L; t.H = a.H; t.G = a.G; t.R = w.R; t.range = w.range;
       t.scale = a.scale;
       t.tree = a.tree ? a.tree + (int64_t)m0 * a.tree_words : nullptr; t.n_true = a.n_true; t.tree_words = a.tree_words;
-      t.rope_tab = ropetab ? ropetab + (int64_t)m0 * 64 : nullptr;
+      t.rope_tab = rope.tab;
       ProfScope ps("draft_attn", s);
-      if (Mp > 32) hipLaunchKernelGGL(decode_attn_kernel<2>, dim3(a.H, w.R, (Mp + 63) / 64), dim3(256), 0, s, t);
-      else hipLaunchKernelGGL(decode_attn_kernel<1>, dim3(a.H, w.R, 1), dim3(256), 0, s, t);
+      const dim3 grid(a.H, w.R, 1), wg(256);
+      if (Mp > 32) hipLaunchKernelGGL((decode_attn_kernel<2, 8>), grid, wg, 0, s, t);
+      else if (t.KSq == 1) hipLaunchKernelGGL((decode_attn_kernel<1, 1>), grid, wg, 0, s, t);
+      else hipLaunchKernelGGL((decode_attn_kernel<1, 8>), grid, wg, 0, s, t);
     }
     if (a.wo_pk) {
       // out-projection on the transposed weights: no k split, so no partial sums and no launch to add them
@@ -1400,7 +1441,7 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
       const bf16_t* yr = a.y_res ? (const bf16_t*)a.y_res + (int64_t)m0 * a.D : (const bf16_t*)nullptr;
       if (Mp == 1 && w.R <= COMB_MAXR && HDt / HD <= 32) {
         ProfScope ps("draft_proj_out", s);
-        launch_strip_gemm(nullptr, (const bf16_t*)a.wo_pk, nullptr, yo, nullptr, yr, Mp, a.D, HDt, &cb, false, -1.f, s);
+        launch_strip_gemm(nullptr, (const bf16_t*)a.wo_pk, nullptr, yo, nullptr, yr, Mp, a.D, HDt, &cb, false, -1.f, RopeRows{}, s);
       } else {
         {
           ProfScope ps("draft_combine", s);
@@ -1408,7 +1449,7 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
                              w.Mpad, a.H, w.R, a.scale, 0);
         }
         ProfScope ps("draft_proj_out", s);
-        launch_strip_gemm(o, (const bf16_t*)a.wo_pk, nullptr, yo, nullptr, yr, Mp, a.D, HDt, nullptr, false, -1.f, s);
+        launch_strip_gemm(o, (const bf16_t*)a.wo_pk, nullptr, yo, nullptr, yr, Mp, a.D, HDt, nullptr, false, -1.f, RopeRows{}, s);
       }
       continue;
     }
@@ -1419,7 +1460,7 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
       cb.scale = a.scale;
       ProfScope ps("draft_proj_out", s);
       hipLaunchKernelGGL(skinny_gemm_kernel<true>, dim3(a.D / SG_N, w.KSo), dim3(256), 0, s, (const bf16_t*)nullptr,
-                         (const bf16_t*)a.wo, ypart, Mp, a.D, HDt, cb, (const bf16_t*)nullptr, (float*)nullptr, 0);
+                         (const bf16_t*)a.wo, ypart, Mp, a.D, HDt, cb, (const bf16_t*)nullptr, (float*)nullptr, 0, RopeRows{});
     } else {
       {
         ProfScope ps("draft_combine", s);
@@ -1428,7 +1469,7 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
       }
       ProfScope ps("draft_proj_out", s);
       hipLaunchKernelGGL(skinny_gemm_kernel<false>, dim3(a.D / SG_N, w.KSo), dim3(256), 0, s, (const bf16_t*)o,
-                         (const bf16_t*)a.wo, ypart, Mp, a.D, HDt, CombineArgs{}, (const bf16_t*)nullptr, (float*)nullptr, 1);
+                         (const bf16_t*)a.wo, ypart, Mp, a.D, HDt, CombineArgs{}, (const bf16_t*)nullptr, (float*)nullptr, 1, RopeRows{});
     }
     {
       ProfScope ps("draft_sum_out", s);
@@ -1458,7 +1499,7 @@ void launch_kv_append_bf16(const void* x, const void* wk, const void* wv, void* 
   {
     ProfScope ps("kv_append_proj", s);
     hipLaunchKernelGGL(skinny_gemm_kernel<false>, dim3(N / SG_N, KS, 2), dim3(256), 0, s, (const bf16_t*)x,
-                       (const bf16_t*)wk, kpart, n, N, K, CombineArgs{}, (const bf16_t*)wv, vpart, 0);
+                       (const bf16_t*)wk, kpart, n, N, K, CombineArgs{}, (const bf16_t*)wv, vpart, 0, RopeRows{});
   }
   {
     ProfScope ps("kv_append_sum", s);
@@ -1508,7 +1549,7 @@ void launch_block_mlp_bf16(const void* z, const void* w_gate, const void* w_up, 
     {
       ProfScope ps("draft_mlp_gate_up", s);
       hipLaunchKernelGGL(skinny_gemm_kernel<false>, dim3(F / SG_N, w.KSg, 2), dim3(256), 0, s, zr, (const bf16_t*)w_gate,
-                         upart, Mp, F, D, CombineArgs{}, (const bf16_t*)w_up, wpart, 0);
+                         upart, Mp, F, D, CombineArgs{}, (const bf16_t*)w_up, wpart, 0, RopeRows{});
     }
     {
       ProfScope ps("draft_mlp_gate", s);
@@ -1518,7 +1559,7 @@ void launch_block_mlp_bf16(const void* z, const void* w_gate, const void* w_up, 
     {
       ProfScope ps("draft_mlp_down", s);
       hipLaunchKernelGGL(skinny_gemm_kernel<false>, dim3(D / SG_N, w.KSd), dim3(256), 0, s, (const bf16_t*)mbuf,
-                         (const bf16_t*)w_down, dpart, Mp, D, F, CombineArgs{}, (const bf16_t*)nullptr, (float*)nullptr, 0);
+                         (const bf16_t*)w_down, dpart, Mp, D, F, CombineArgs{}, (const bf16_t*)nullptr, (float*)nullptr, 0, RopeRows{});
     }
     {
       ProfScope ps("draft_mlp_sum", s);
@@ -1533,10 +1574,10 @@ void launch_block_mlp_bf16(const void* z, const void* w_gate, const void* w_up, 
 // K and V rows of up to 16 new states on packed Wk, Wv (norm_eps >= 0: the RMSNorm in front of them, gain folded into
 // the matrices): one strip launch, no workspace
 void launch_kv_append_strip_bf16(const void* x, const void* wk_pk, const void* wv_pk, void* kdst, void* vdst, int32_t n,
-                                 int32_t N, int32_t K, float norm_eps, hipStream_t s) {
+                                 int32_t N, int32_t K, float norm_eps, const RopeRows& rope, hipStream_t s) {
   ProfScope ps("kv_append_proj", s);
   launch_strip_gemm((const bf16_t*)x, (const bf16_t*)wk_pk, (const bf16_t*)wv_pk, kdst, (bf16_t*)vdst, nullptr, n, N, K, nullptr,
-                    false, norm_eps, s);
+                    false, norm_eps, rope, s);
 }
 
 void launch_block_mlp_strip_bf16(const void* z, const void* w_gate_pk, const void* w_up_pk, const void* w_down_pk,
@@ -1545,11 +1586,11 @@ void launch_block_mlp_strip_bf16(const void* z, const void* w_gate_pk, const voi
   bf16_t* mbuf = (bf16_t*)ws;
   {
     ProfScope ps("draft_mlp_gate_up", s);
-    launch_strip_gemm((const bf16_t*)z, (const bf16_t*)w_gate_pk, (const bf16_t*)w_up_pk, mbuf, nullptr, nullptr, M, F, D, nullptr, false, z_norm_eps, s);
+    launch_strip_gemm((const bf16_t*)z, (const bf16_t*)w_gate_pk, (const bf16_t*)w_up_pk, mbuf, nullptr, nullptr, M, F, D, nullptr, false, z_norm_eps, RopeRows{}, s);
   }
   {
     ProfScope ps("draft_mlp_down", s);
-    launch_strip_gemm(mbuf, (const bf16_t*)w_down_pk, nullptr, (bf16_t*)h, nullptr, (const bf16_t*)y_res, M, D, F, nullptr, false, -1.f, s);
+    launch_strip_gemm(mbuf, (const bf16_t*)w_down_pk, nullptr, (bf16_t*)h, nullptr, (const bf16_t*)y_res, M, D, F, nullptr, false, -1.f, RopeRows{}, s);
   }
 }
 
