@@ -574,7 +574,7 @@ size_t beagle_xattn_workspace_bytes(const beagle_xattn_desc* desc, int which) {
       return w.total + align_up(extra) + states_ws(d);
     }
     case BEAGLE_WS_DRAFT:
-      if (d.bf16) return align_up(decode_bf16_ws_bytes((int32_t)d.S, (int32_t)d.L, (int32_t)d.H, (int32_t)d.d, (int32_t)d.D));
+      if (d.bf16) return align_up(decode_bf16_ws_bytes((int32_t)d.S, (int32_t)d.L, (int32_t)d.H, (int32_t)d.G, (int32_t)d.d, (int32_t)d.D));
       return align_up((size_t)(2 * d.S * d.HD) * d.esz);
     case BEAGLE_WS_BWD_SIM: {
       BwdWs w = bwd_layout(d);

@@ -238,7 +238,7 @@ struct DecodeArgs {
 bool strip_gemm_fits(int32_t M, int32_t N, int32_t K);
 // W [K][N] row-major -> the packed layout that strip_gemm_kernel streams (K % 128 == 0, N % 16 == 0)
 void launch_pack_strips_bf16(const void* in, void* out, int32_t K, int32_t N, const void* gain, hipStream_t s);
-size_t decode_bf16_ws_bytes(int32_t M, int32_t L, int32_t H, int32_t d, int32_t D);
+size_t decode_bf16_ws_bytes(int32_t M, int32_t L, int32_t H, int32_t G, int32_t d, int32_t D);
 void launch_decode_bf16(const DecodeArgs& a, hipStream_t s);
 void launch_read_probe(const void* buf, int64_t bytes, int wgs, uint32_t* sink, hipStream_t s);
 void launch_clock_probe(uint64_t* out, hipStream_t s);

@@ -31,6 +31,7 @@
 // device-scope fence inside a kernel writes back a whole L2 (the XCDs' L2s are
 // not coherent with each other), which costs far more than a launch.  All sums
 // run in a fixed order, so results are bitwise reproducible.
+#include <algorithm>
 #include <type_traits>
 #include "attn_tiles.h"
 
@@ -693,6 +694,7 @@ struct DecAttnArgs {
   const bf16_t* kc; const bf16_t* vc;     // [L][G][128]
   float* opart; float* mlpart;            // [H][R][Mpad][128], [H][R][Mpad][2]
   int M, Mpad, L, H, G, R, range;
+  int hs_log2, row_log2;                  // a workgroup's rows: 2^hs_log2 heads of one K/V head, 2^row_log2 >= M rows each
   float scale;
   // draft tree (nullptr: all rows visible): rows >= n_true are visible to query m iff bit (row - n_true) of
   // tree[m * tree_words ...] is set
@@ -703,7 +705,8 @@ struct DecAttnArgs {
 
 typedef lds_u32x2_t u32x2_t;
 
-// One workgroup per (head, key range, block of 32 NQB queries): grid (H, R, ceil(M / (32 NQB))).
+// One workgroup per (2^hs_log2 query heads of one K/V head, key range): grid (H >> hs_log2, R).  Row i of its 32 NQB rows
+// is query i % 2^row_log2 of head i >> row_log2 ("query" below); rows whose query is past M read zeros and are not stored.
 // NQB = 1 (up to 32 queries): the four waves split each 128-key step by rows, 32 keys each.  A wave requests, reads
 // and refills only its own 32 rows of the two stages, so the step loop has no barrier; a stage half (the wave's K
 // rows, then its V rows) is refilled for the step after next as soon as its fragments sit in registers, i.e. BEFORE
@@ -733,14 +736,14 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
   ml_t& s_mm = *(ml_t*)((float*)qbuf + 4 * NQB * 3 * 32);               // merged max, sum per block
   static_assert((4 * NQB * 3 * 32 + NQB * 2 * 32) * sizeof(float) <= sizeof(qbuf), "merge arrays must fit in the q planes");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hf = lane >> 5, ql = lane & 31;
-  const int h = blockIdx.x, r = blockIdx.y;
-  const int m0 = 32 * NQB * blockIdx.z;                      // first query of the workgroup
-  const int mtot = min(32 * NQB, a.M - m0);                  // its queries
+  const int h = blockIdx.x << a.hs_log2, r = blockIdx.y;     // first head
+  const int row_mask = (1 << a.row_log2) - 1;
+  const int mtot = a.hs_log2 ? 1 << (a.hs_log2 + a.row_log2) : a.M;   // the workgroup's rows
   // every field at hand after one trip to the constant cache (the compiler otherwise fetches them where they are first
   // used, two dependent trips before the first K/V request); no division for the common one head per group
   asm volatile("" :: "s"(a.qpart), "s"(a.KSq), "s"(a.kc), "s"(a.vc), "s"(a.opart), "s"(a.mlpart), "s"(a.M), "s"(a.Mpad), "s"(a.L),
-               "s"(a.H), "s"(a.G), "s"(a.R), "s"(a.range), "s"(a.scale), "s"(a.tree), "s"(a.n_true), "s"(a.tree_words),
-               "s"(a.rope_tab));
+               "s"(a.H), "s"(a.G), "s"(a.R), "s"(a.range), "s"(a.hs_log2), "s"(a.row_log2), "s"(a.scale), "s"(a.tree), "s"(a.n_true),
+               "s"(a.tree_words), "s"(a.rope_tab));
   const int g = a.H == a.G ? h : h / (a.H / a.G);
   const int HDt = a.H * HD;
   const int j_begin = r * a.range, j_end = min(j_begin + a.range, a.L);
@@ -792,14 +795,15 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
       __builtin_amdgcn_make_buffer_rsrc((void*)a.qpart, 0, (int)(a.KSq * slice * 4), 0x00020000);
   const int oob = 0x7fffff00;
   auto q_issue = [&](int qb, int mrows, int qwaves, int k0, u32x4_t (&t)[4][QS]) {
-    const int mb = m0 + 32 * qb;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int idx = tid + 64 * qwaves * i, m = idx >> 5, c4 = idx & 31;
+      const int idx = tid + 64 * qwaves * i, row = 32 * qb + (idx >> 5), c4 = idx & 31;
+      const int m = row & row_mask, hh = h + (row >> a.row_log2);
+      const bool there = wave < qwaves && (idx >> 5) < mrows && m < a.M;
 #pragma unroll
       for (int k = 0; k < QS; ++k) {
-        const int off = (int)((((int64_t)(k0 + k) * a.M + mb + m) * HDt + h * HD + 4 * c4) * 4);
-        t[i][k] = __builtin_amdgcn_raw_buffer_load_b128(qrs, (wave < qwaves && m < mrows && k0 + k < a.KSq) ? off : oob, 0, 0);
+        const int off = (int)((((int64_t)(k0 + k) * a.M + m) * HDt + hh * HD + 4 * c4) * 4);
+        t[i][k] = __builtin_amdgcn_raw_buffer_load_b128(qrs, (there && k0 + k < a.KSq) ? off : oob, 0, 0);
       }
     }
   };
@@ -821,11 +825,10 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
       q_add(t, acc);
     }
     if (a.rope_tab) {
-      const int mb = m0 + 32 * qb;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int idx = tid + 64 * qwaves * i, m = min(idx >> 5, mrows - 1), c4 = idx & 15;
-        const float4* tp = (const float4*)(a.rope_tab + (int64_t)(mb + m) * 64 + 4 * c4);
+        const int idx = tid + 64 * qwaves * i, m = min((32 * qb + (idx >> 5)) & row_mask, a.M - 1), c4 = idx & 15;
+        const float4* tp = (const float4*)(a.rope_tab + (int64_t)m * 64 + 4 * c4);
         const float4 cs0 = tp[0], cs1 = tp[1];                 // (cos, sin) of pairs 4 c4 .. 4 c4 + 3
         const bool upper = (tid & 16) != 0;                    // channels 64 .. 127: x2 of the pair
         const float4 own = acc[i];
@@ -1108,8 +1111,9 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
           // drafted rows: bit i of `vis` says whether this lane's query sees key jw + i (true rows: yes)
           const int off = jw - a.n_true;                       // tree bit of key jw; negative inside the true rows
           const int w0 = off >> 5, sh = off & 31;              // floor division: -1 for the straddling block
-          const uint32_t* row = a.tree + (int64_t)(m0 + 32 * b + ql) * a.tree_words;
-          const bool real = 32 * b + ql < mtot;
+          const int m = (32 * b + ql) & row_mask;
+          const uint32_t* row = a.tree + (int64_t)m * a.tree_words;
+          const bool real = 32 * b + ql < mtot && m < a.M;
           const uint32_t lo = w0 < 0 ? 0xffffffffu : (real && w0 < a.tree_words ? row[w0] : 0u);
           const uint32_t hi = real && w0 + 1 < a.tree_words ? row[w0 + 1] : 0u;
           const uint32_t vis = (uint32_t)((((uint64_t)hi << 32) | lo) >> sh);
@@ -1195,7 +1199,6 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
   // further round its row, so that neither the per-query writes nor the per-channel reads conflict.
   __syncthreads();
   static_assert(NQB * 4 * 32 * HD * sizeof(float) <= sizeof(kvt), "the merge buffers must fit in the stages");
-  const int64_t pbase = ((int64_t)h * a.R + r) * a.Mpad + m0;
 #pragma unroll
   for (int b = 0; b < NQB; ++b) {
     float* ob = (float*)kvt + b * 4 * 32 * HD;
@@ -1227,7 +1230,9 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
   }
   __syncthreads();
   for (int i = tid; i < mtot * 32; i += 256) {                 // padding rows are never read
-    const int c4 = i & 31, qq = i >> 5, qb = qq >> 5, q = qq & 31;
+    const int c4 = i & 31, qq = i >> 5, qb = qq >> 5, q = qq & 31, m = qq & row_mask;
+    if (m >= a.M) continue;
+    const int64_t out = ((int64_t)(h + (qq >> a.row_log2)) * a.R + r) * a.Mpad + m;
     const float* ob = (const float*)kvt + qb * 4 * 32 * HD;
     float4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1236,12 +1241,14 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
       const float4 v = *(const float4*)(ob + (wv * 32 + q) * HD + ((4 * c4 + 4 * q) & (HD - 1)));
       acc.x += v.x * sc; acc.y += v.y * sc; acc.z += v.z * sc; acc.w += v.w * sc;
     }
-    *(float4*)(a.opart + (pbase + qq) * HD + 4 * c4) = acc;
-    if (c4 == 0) { a.mlpart[(pbase + qq) * 2] = s_mm[qb][0][q]; a.mlpart[(pbase + qq) * 2 + 1] = s_mm[qb][1][q]; }
+    *(float4*)(a.opart + out * HD + 4 * c4) = acc;
+    if (c4 == 0) { a.mlpart[out * 2] = s_mm[qb][0][q]; a.mlpart[out * 2 + 1] = s_mm[qb][1][q]; }
   }
 }
 
 // ---- (C) merge the key ranges (fixed order): o (bf16) and LSE ------------------
+// RB: ranges loaded at a time
+template <int RB>
 __global__ __launch_bounds__(128) void decode_combine_kernel(const float* __restrict__ opart, const float* __restrict__ mlpart,
                                                              bf16_t* __restrict__ o, float* __restrict__ lse,
                                                              int lse_stride, int Mpad, int H, int R, float scale,
@@ -1250,14 +1257,14 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float* __rest
   const int m = blockIdx.x, h = blockIdx.y, c = threadIdx.x;
   const float c2 = scale * LOG2E;
   const int64_t p0 = (int64_t)h * R * Mpad + m;              // range s sits at p0 + s * Mpad
-  // Eight ranges are loaded at a time before any is used, maxima, sums and outputs together: with up to eight ranges
+  // RB ranges are loaded at a time before any is used, maxima, sums and outputs together: with up to RB ranges
   // the whole merge is one round trip to memory (the kernel is nothing but round trips: a pass over the maxima first
   // and the rest behind it cost a second one).  A batch that reaches past the last range repeats it, which changes
   // neither the maximum nor (weight 0) the sums.
-  float ms[8], ls[8], ov[8];
+  float ms[RB], ls[RB], ov[RB];
   auto load_batch = [&](int s0) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k < RB; ++k) {
       const int64_t pb = p0 + (int64_t)min(s0 + k, R - 1) * Mpad;
       ms[k] = mlpart[pb * 2]; ls[k] = mlpart[pb * 2 + 1]; ov[k] = opart[pb * HD + c];
     }
@@ -1265,19 +1272,19 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float* __rest
   load_batch(0);
   float mm = -INFINITY;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) mm = fmaxf(mm, ms[k]);
-  for (int s0 = 8; s0 < R; s0 += 8) {                          // more than eight ranges: the remaining maxima first
-    float t[8];
+  for (int k = 0; k < RB; ++k) mm = fmaxf(mm, ms[k]);
+  for (int s0 = RB; s0 < R; s0 += RB) {                          // more than RB ranges: the remaining maxima first
+    float t[RB];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) t[k] = mlpart[(p0 + (int64_t)min(s0 + k, R - 1) * Mpad) * 2];
+    for (int k = 0; k < RB; ++k) t[k] = mlpart[(p0 + (int64_t)min(s0 + k, R - 1) * Mpad) * 2];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) mm = fmaxf(mm, t[k]);
+    for (int k = 0; k < RB; ++k) mm = fmaxf(mm, t[k]);
   }
   float acc = 0.f, lt = 0.f;
-  for (int s0 = 0; s0 < R; s0 += 8) {
+  for (int s0 = 0; s0 < R; s0 += RB) {
     if (s0 > 0) load_batch(s0);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {                              // fixed order
+    for (int k = 0; k < RB; ++k) {                              // fixed order
       const float sc = (s0 + k < R && ms[k] > -INFINITY) ? __builtin_amdgcn_exp2f((ms[k] - mm) * c2) : 0.f;
       acc += ov[k] * sc;
       lt += ls[k] * sc;
@@ -1333,28 +1340,46 @@ void launch_clock_probe(uint64_t* out, hipStream_t s) {
 // ---- host side ----------------------------------------------------------------
 namespace {
 struct DecLayout {
-  int KSq, KSo, R, range, Mpad;
+  int KSq, KSo, R, range, hs_log2, row_log2;
   size_t qpart, opart, mlpart, o, ypart, ropetab, total;
 };
 size_t up256(size_t v) { return (v + 255) / 256 * 256; }
-DecLayout dec_layout(int M, int L, int H, int d, int D) {
+DecLayout dec_layout(int M, int L, int H, int G, int d, int D, bool packed) {
   DecLayout w;
   const int Mp = M < dec::MAXM ? M : dec::MAXM;             // queries per pass
   const int64_t HDt = (int64_t)H * d;
   w.KSq = (D + dec::SG_K - 1) / dec::SG_K;
   w.KSo = (int)((HDt + dec::SG_K - 1) / dec::SG_K);
-  // key ranges per head: about one workgroup per CU over all heads, whole 128-key steps
-  int R = 256 / H;
-  if (R < 1) R = 1;
-  const int max_r = (L + dec::KSTEP - 1) / dec::KSTEP;
-  if (R > max_r) R = max_r;
-  w.range = ((L + R - 1) / R + dec::KSTEP - 1) / dec::KSTEP * dec::KSTEP;
-  w.R = (L + w.range - 1) / w.range;
-  w.Mpad = (Mp + 31) / 32 * 32;
+  // key ranges per workgroup row: about one workgroup per CU over all heads, whole 128-key steps
+  const int per_head = H < 256 ? 256 / H : 1;
+  auto split = [&](int hs_log2, int& range) {
+    const int R = std::min(per_head << hs_log2, (L + dec::KSTEP - 1) / dec::KSTEP);
+    range = ((L + R - 1) / R + dec::KSTEP - 1) / dec::KSTEP * dec::KSTEP;
+    return (L + range - 1) / range;
+  };
+  w.hs_log2 = 0; w.row_log2 = 6;
+  w.R = split(0, w.range);
+  // Grouped queries: heads that share a K/V head share a workgroup too (up to 32 rows in all, padded to a power of two per
+  // head), so the cache rows are fetched once for them and a head's keys split over as many more ranges.  The fewest heads
+  // that give the shortest ranges; without a step less nothing is gained (6 queries over 619 keys, packed: 25.5 us as
+  // before, 26.7 with four heads).  32 heads in 8 groups, packed weights: 8 queries over 8192 keys 43.7 -> 35.5 us, 1 over
+  // 4096 31.0 -> 28.3, 8 over 1500 28.5 -> 27.8.  Where the merge of up to 8 ranges otherwise rides in the output
+  // projection, one step less does not pay for its launch (1 query over 1500 keys 25.7 -> 26.1; over 2600 28.0 -> 27.7).
+  int row_log2 = 0;
+  while ((1 << row_log2) < Mp) ++row_log2;
+  const int least = Mp <= (packed ? 1 : 2) && w.R <= COMB_MAXR ? 2 : 1;   // steps to save
+  int bound = w.range - least * dec::KSTEP;
+  for (int hs = 1; hs + row_log2 <= 5 && H / G % (1 << hs) == 0; ++hs) {
+    int range;
+    const int R = split(hs, range);
+    if (range > bound) continue;
+    w.hs_log2 = hs; w.row_log2 = row_log2; w.range = range; w.R = R;
+    bound = range - dec::KSTEP;
+  }
   size_t o = 0;
   w.qpart = o; o += up256((size_t)w.KSq * Mp * HDt * 4);
-  w.opart = o; o += up256((size_t)H * w.R * w.Mpad * tiles::HD * 4);
-  w.mlpart = o; o += up256((size_t)H * w.R * w.Mpad * 2 * 4);
+  w.opart = o; o += up256((size_t)H * w.R * Mp * tiles::HD * 4);
+  w.mlpart = o; o += up256((size_t)H * w.R * Mp * 2 * 4);
   w.o = o; o += up256((size_t)Mp * HDt * 2);
   w.ypart = o; o += up256((size_t)w.KSo * Mp * D * 4);
   w.ropetab = o; o += up256((size_t)M * 64 * sizeof(float2));
@@ -1389,13 +1414,22 @@ void launch_strip_gemm(const bf16_t* a, const bf16_t* wt, const bf16_t* wt2, voi
 #undef STRIP_ARGS
 }
 
-size_t decode_bf16_ws_bytes(int32_t M, int32_t L, int32_t H, int32_t d, int32_t D) {
-  return dec_layout(M, L, H, d, D).total;
+size_t decode_bf16_ws_bytes(int32_t M, int32_t L, int32_t H, int32_t G, int32_t d, int32_t D) {
+  return std::max(dec_layout(M, L, H, G, d, D, false).total, dec_layout(M, L, H, G, d, D, true).total);
+}
+
+static void launch_combine(int M, const DecodeArgs& a, const DecLayout& w, const float* opart, const float* mlpart, bf16_t* o,
+                           float* lse, int chunked_rows, hipStream_t s) {
+#define COMBINE_ARGS opart, mlpart, o, lse, a.M, M, a.H, w.R, a.scale, chunked_rows
+  if (w.R <= 8) hipLaunchKernelGGL(decode_combine_kernel<8>, dim3(M, a.H), dim3(128), 0, s, COMBINE_ARGS);
+  else if (w.R <= 16) hipLaunchKernelGGL(decode_combine_kernel<16>, dim3(M, a.H), dim3(128), 0, s, COMBINE_ARGS);
+  else hipLaunchKernelGGL(decode_combine_kernel<32>, dim3(M, a.H), dim3(128), 0, s, COMBINE_ARGS);
+#undef COMBINE_ARGS
 }
 
 void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
   using namespace dec;
-  const DecLayout w = dec_layout(a.M, a.L, a.H, a.d, a.D);
+  const DecLayout w = dec_layout(a.M, a.L, a.H, a.G, a.d, a.D, a.wq_pk && a.wo_pk);
   const int HDt = a.H * HD;
   char* base = (char*)a.ws;
   float* qpart = (float*)(base + w.qpart);
@@ -1422,12 +1456,12 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
       DecAttnArgs t;
       t.qpart = qpart; t.KSq = a.wq_pk ? 1 : w.KSq; t.kc = (const bf16_t*)a.kc; t.vc = (const bf16_t*)a.vc;
       t.opart = opart; t.mlpart = mlpart;
-      t.M = Mp; t.Mpad = w.Mpad; t.L = a.L; t.H = a.H; t.G = a.G; t.R = w.R; t.range = w.range;
+      t.M = Mp; t.Mpad = Mp; t.hs_log2 = w.hs_log2; t.row_log2 = w.row_log2; t.L = a.L; t.H = a.H; t.G = a.G; t.R = w.R; t.range = w.range;
       t.scale = a.scale;
       t.tree = a.tree ? a.tree + (int64_t)m0 * a.tree_words : nullptr; t.n_true = a.n_true; t.tree_words = a.tree_words;
       t.rope_tab = rope.tab;
       ProfScope ps("draft_attn", s);
-      const dim3 grid(a.H, w.R, 1), wg(256);
+      const dim3 grid(a.H >> w.hs_log2, w.R), wg(256);
       if (Mp > 32) hipLaunchKernelGGL((decode_attn_kernel<2, 8>), grid, wg, 0, s, t);
       else if (t.KSq == 1) hipLaunchKernelGGL((decode_attn_kernel<1, 1>), grid, wg, 0, s, t);
       else hipLaunchKernelGGL((decode_attn_kernel<1, 8>), grid, wg, 0, s, t);
@@ -1435,7 +1469,7 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
     if (a.wo_pk) {
       // out-projection on the transposed weights: no k split, so no partial sums and no launch to add them
       CombineArgs cb;
-      cb.opart = opart; cb.mlpart = mlpart; cb.lse = a.lse + m0; cb.lse_stride = a.M; cb.Mpad = w.Mpad; cb.R = w.R;
+      cb.opart = opart; cb.mlpart = mlpart; cb.lse = a.lse + m0; cb.lse_stride = a.M; cb.Mpad = Mp; cb.R = w.R;
       cb.scale = a.scale;
       bf16_t* yo = (bf16_t*)a.y + (int64_t)m0 * a.D;
       const bf16_t* yr = a.y_res ? (const bf16_t*)a.y_res + (int64_t)m0 * a.D : (const bf16_t*)nullptr;
@@ -1445,8 +1479,7 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
       } else {
         {
           ProfScope ps("draft_combine", s);
-          hipLaunchKernelGGL(decode_combine_kernel, dim3(Mp, a.H), dim3(128), 0, s, opart, mlpart, o, a.lse + m0, a.M,
-                             w.Mpad, a.H, w.R, a.scale, 0);
+          launch_combine(Mp, a, w, opart, mlpart, o, a.lse + m0, 0, s);
         }
         ProfScope ps("draft_proj_out", s);
         launch_strip_gemm(o, (const bf16_t*)a.wo_pk, nullptr, yo, nullptr, yr, Mp, a.D, HDt, nullptr, false, -1.f, RopeRows{}, s);
@@ -1456,7 +1489,7 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
     if (Mp <= COMB_MAXM && w.R <= COMB_MAXR && HDt % SG_K == 0) {
       // few queries: the merge of the key ranges rides in the projection's prologue
       CombineArgs cb;
-      cb.opart = opart; cb.mlpart = mlpart; cb.lse = a.lse + m0; cb.lse_stride = a.M; cb.Mpad = w.Mpad; cb.R = w.R;
+      cb.opart = opart; cb.mlpart = mlpart; cb.lse = a.lse + m0; cb.lse_stride = a.M; cb.Mpad = Mp; cb.R = w.R;
       cb.scale = a.scale;
       ProfScope ps("draft_proj_out", s);
       hipLaunchKernelGGL(skinny_gemm_kernel<true>, dim3(a.D / SG_N, w.KSo), dim3(256), 0, s, (const bf16_t*)nullptr,
@@ -1464,8 +1497,7 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
     } else {
       {
         ProfScope ps("draft_combine", s);
-        hipLaunchKernelGGL(decode_combine_kernel, dim3(Mp, a.H), dim3(128), 0, s, opart, mlpart, o, a.lse + m0, a.M,
-                           w.Mpad, a.H, w.R, a.scale, Mp);
+        launch_combine(Mp, a, w, opart, mlpart, o, a.lse + m0, Mp, s);
       }
       ProfScope ps("draft_proj_out", s);
       hipLaunchKernelGGL(skinny_gemm_kernel<false>, dim3(a.D / SG_N, w.KSo), dim3(256), 0, s, (const bf16_t*)o,
