@@ -45,12 +45,16 @@ __device__ __forceinline__ float dot8(bf16x8_t a, bf16x8_t b) {
 // (1) dQ and delta
 // ===========================================================================
 namespace dqk {
-constexpr int BQ = 128, BJ = 64;
+constexpr int BJ = 64;
 constexpr int TILE = BJ * HD;            // one K or V tile
 }  // namespace dqk
 
+// KH: key halves, as in the forward: with 2 a workgroup has 64 queries and two waves per 32 of them, one for either half of
+// every tile; their dQ are added in LDS
+template <int KH>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
   using namespace dqk;
+  constexpr int BQ = 128 / KH, NJB = 2 / KH;      // queries per workgroup, 32-key blocks of a tile per wave
   args_at_hand(a);
   __shared__ __attribute__((aligned(1024))) bf16_t stage0[2 * TILE];
   __shared__ __attribute__((aligned(1024))) bf16_t stage1[2 * TILE];
@@ -60,7 +64,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
   map_block(blockIdx.x, a.H * a.B, row, tpos);
   const int qt = nqt - 1 - tpos;                  // heaviest (latest) query tiles first
   const int h = row % a.H, b = row / a.H, g = h / (a.H / a.G);
-  const int q0 = qt * BQ, qw0 = q0 + wave * 32, q = qw0 + ql;
+  const int qw = wave % (4 / KH), kw = wave / (4 / KH) * 32;   // this wave's queries, and its first key in a tile
+  const int q0 = qt * BQ, qw0 = q0 + qw * 32, q = qw0 + ql;
   const SeqView sv = seq_view(a, b);
   if (q0 >= sv.S) return;                         // packed batch: this entry is shorter than the longest one
   const bool q_ok = q < sv.S;
@@ -105,7 +110,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
 #pragma unroll
   for (int s = 0; s < 8; ++s) part += bwd::dot8(dof[s], of[s]);
   const float delta = half_pair_sum(part);
-  if (q_ok && hf == 0) { a.delta[li] = delta; a.nlse2[li] = -LOG2E * lse; }   // blind rows: +inf, masked in the dK/dV kernel
+  if (q_ok && hf == 0 && kw == 0) { a.delta[li] = delta; a.nlse2[li] = -LOG2E * lse; }   // blind rows: +inf, masked in the dK/dV kernel
   const float c2 = a.scale * LOG2E;
   const float lse2 = (lim > 0 ? lse : 0.f) * LOG2E;    // blind rows are fully masked below
   const FragOffs fo = make_frag_offs(lane);
@@ -117,15 +122,15 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
     for (int e = 0; e < 16; ++e) dq[i][e] = 0.f;
 
   auto tile_step = [&](const bf16_t* cur, bf16_t* nxt, int jt) {
-    const int j0 = jt * BJ;
+    const int j0 = jt * BJ + kw;
     if (j0 >= wave_hi) fetch(nxt, jt + 1);        // a wave that sees nothing of the tile only requests its share of the next
     if (j0 < wave_hi) {
       fetch(nxt, jt + 1);                         // issued between the MFMAs below
-      const bf16_t* ks = cur;
-      const bf16_t* vs = cur + TILE;
-      f32x16_t st[2], dp[2];
+      const bf16_t* ks = cur + kw * HD;
+      const bf16_t* vs = cur + TILE + kw * HD;
+      f32x16_t st[NJB], dp[NJB];
 #pragma unroll
-      for (int jb = 0; jb < 2; ++jb) {
+      for (int jb = 0; jb < NJB; ++jb) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) { st[jb][e] = 0.f; dp[jb][e] = 0.f; }
 #pragma unroll
@@ -134,34 +139,34 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
           dp[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag(vs, fo, jb, s), dof[s], dp[jb], 0, 0, 0);
         }
       }
-      pipeline_reads_mfma_loads<32, 1, 8>();
+      pipeline_reads_mfma_loads<32 / KH, 1, 8>();
       __builtin_amdgcn_sched_barrier(0);
       // dS = P (dP - delta); key offsets inside the tile are compile-time constants, and only tiles that reach
       // past the smallest limit of the wave run the compares and selects (a scalar branch around them alone)
-      float dsv[2][16];
+      float dsv[NJB][16];
 #pragma unroll
-      for (int jb = 0; jb < 2; ++jb)
+      for (int jb = 0; jb < NJB; ++jb)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const float p = __builtin_amdgcn_exp2f(st[jb][e] * c2 - lse2);
           dsv[jb][e] = p * (dp[jb][e] - delta);
         }
-      if (j0 + BJ > wave_lo) {
+      if (j0 + 32 * NJB > wave_lo) {
         const int rel = lim - j0 - 4 * hf;
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb)
+        for (int jb = 0; jb < NJB; ++jb)
 #pragma unroll
           for (int e = 0; e < 16; ++e)
             if (32 * jb + 8 * (e >> 2) + (e & 3) >= rel) dsv[jb][e] = 0.f;
       }
-      uint32_t pk[2][8];
+      uint32_t pk[NJB][8];
 #pragma unroll
-      for (int jb = 0; jb < 2; ++jb)
+      for (int jb = 0; jb < NJB; ++jb)
 #pragma unroll
         for (int e = 0; e < 16; e += 2) pk[jb][e >> 1] = cvt_pk(dsv[jb][e], dsv[jb][e + 1]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int jb = 0; jb < 2; ++jb)
+      for (int jb = 0; jb < NJB; ++jb)
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
           union { uint32_t u[4]; bf16x8_t v; } sf;
@@ -171,7 +176,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
           for (int cb = 0; cb < 4; ++cb)
             dq[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag(ks, fo, 32 * jb + 16 * t, cb), sf.v, dq[cb], 0, 0, 0);
         }
-      pipeline_reads_mfma<16, 2>();
+      pipeline_reads_mfma<16 / KH, 2>();
       __builtin_amdgcn_sched_barrier(0);
     }
     wait_vmem();
@@ -188,6 +193,23 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
   }
   if (jt < ntiles) tile_step(stage0, stage1, jt);
 
+  if constexpr (KH == 2) {
+    float4* po = (float4*)stage0 + qw * 64 + lane;               // [16][2 waves][64 lanes]: 32 KB
+    if (kw) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) po[128 * i] = float4{dq[i >> 2][4 * (i & 3)], dq[i >> 2][4 * (i & 3) + 1], dq[i >> 2][4 * (i & 3) + 2], dq[i >> 2][4 * (i & 3) + 3]};
+    }
+    __syncthreads();
+    if (kw) return;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float4 v = po[128 * i];
+      const float w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dq[i >> 2][4 * (i & 3) + e] += w[e];
+    }
+  }
+
   // ---- dQ rows out, through LDS (the stages are free: the last step, or the prologue, ended with a barrier)
   {
     uint2 pq[16];
@@ -197,7 +219,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
       for (int qd = 0; qd < 4; ++qd)
         pq[4 * cb + qd] = make_uint2(cvt_pk(dq[cb][4 * qd] * a.scale, dq[cb][4 * qd + 1] * a.scale),
                                      cvt_pk(dq[cb][4 * qd + 2] * a.scale, dq[cb][4 * qd + 3] * a.scale));
-    store_rows_via_lds(stage0 + wave * 32 * HD, pq, lane, (bf16_t*)a.dq + ((sv.q0 + qw0) * a.H + h) * HD, (int64_t)a.H * HD,
+    store_rows_via_lds((KH == 1 ? stage0 : stage1) + qw * 32 * HD, pq, lane, (bf16_t*)a.dq + ((sv.q0 + qw0) * a.H + h) * HD, (int64_t)a.H * HD,
                        sv.S - qw0);
   }
 }
@@ -533,8 +555,8 @@ void launch_attn_bwd_bf16(const AttnArgs& args, void* ws, hipStream_t s) {
   a.nlse2 = (float*)ws;
   {
     ProfScope ps("attn_bwd_dq_bf16", s);
-    dim3 grid(((a.S + dqk::BQ - 1) / dqk::BQ) * a.H * a.B);
-    hipLaunchKernelGGL(attn_bwd_dq_bf16_kernel, grid, dim3(256), 0, s, a);
+    if (attn_key_halves(a)) hipLaunchKernelGGL(attn_bwd_dq_bf16_kernel<2>, dim3((a.S + 63) / 64 * a.H * a.B), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(attn_bwd_dq_bf16_kernel<1>, dim3((a.S + 127) / 128 * a.H * a.B), dim3(256), 0, s, a);
   }
   dkv::Split sp = dkv_split(a);
   sp.part = (float*)((char*)ws + nlse_bytes(a));

@@ -29,14 +29,18 @@ namespace beagle {
 using namespace tiles;
 
 namespace fwd {
-constexpr int BQ = 128;           // queries per workgroup
 constexpr int BJ = 64;            // keys per tile
 constexpr int TILE = BJ * HD;     // elements of one K or V tile
 constexpr float RESCALE_LOG2 = 8.f;
 }  // namespace fwd
 
+// KH: key halves.  1: the four waves own 32 queries each (128 per workgroup) against whole tiles.  2: two waves own 32
+// queries each (64 per workgroup) against the first half of every tile, the other two the same queries against the second
+// half, and the two partial results are merged in LDS.  See launch_attn_fwd_bf16 for when.
+template <int KH>
 __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
   using namespace fwd;
+  constexpr int BQ = 128 / KH, NJB = 2 / KH;      // queries per workgroup, 32-key blocks of a tile per wave
   args_at_hand(a);
   __shared__ __attribute__((aligned(1024))) bf16_t stage0[2 * TILE];
   __shared__ __attribute__((aligned(1024))) bf16_t stage1[2 * TILE];
@@ -50,7 +54,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
   const int q0 = qt * BQ;
   const SeqView sv = seq_view(a, b);
   if (q0 >= sv.S) return;                         // packed batch: this entry is shorter than the longest one
-  const int qw0 = q0 + wave * 32;                 // first query of this wave
+  const int qw = wave % (4 / KH), kw = wave / (4 / KH) * 32;   // this wave's queries, and its first key in a tile
+  const int qw0 = q0 + qw * 32;                   // first query of this wave
   const int q = qw0 + ql;                         // this lane's query
   const bool q_ok = q < sv.S;
   const int qc = q_ok ? q : sv.S - 1;
@@ -93,23 +98,23 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
   const FragOffs fo = make_frag_offs(lane);
 
   auto tile_step = [&](const bf16_t* cur, bf16_t* nxt, int jt) {
-    const int j0 = jt * BJ;
+    const int j0 = jt * BJ + kw;
     if (j0 >= wave_hi) fetch(nxt, jt + 1);        // a wave that sees nothing of the tile only requests its share of the next
     if (j0 < wave_hi) {                           // wave-uniform: this wave sees part of the tile
       fetch(nxt, jt + 1);                         // past the last tile: zeros / unused, harmless; issued between the MFMAs below
-      const bf16_t* ks = cur;
-      const bf16_t* vs = cur + TILE;
-      // ---- S^T = K Q^T  (two blocks of 32 keys)
-      f32x16_t st[2];
+      const bf16_t* ks = cur + kw * HD;
+      const bf16_t* vs = cur + TILE + kw * HD;
+      // ---- S^T = K Q^T  (blocks of 32 keys)
+      f32x16_t st[NJB];
 #pragma unroll
-      for (int jb = 0; jb < 2; ++jb) {
+      for (int jb = 0; jb < NJB; ++jb) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) st[jb][e] = 0.f;
 #pragma unroll
         for (int s = 0; s < HD / 16; ++s)
           st[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag(ks, fo, jb, s), qf[s], st[jb], 0, 0, 0);
       }
-      pipeline_reads_mfma_loads<16, 1, 8>();
+      pipeline_reads_mfma_loads<16 / KH, 1, KH == 1 ? 8 : 4>();
       __builtin_amdgcn_sched_barrier(0);
       // ---- mask + tile maximum (register e of block jb is key j0 + 32 jb + 8 (e/4) + 4 hf + e%4).
       // Only tiles that straddle a limit of this wave evaluate the per-element predicate.
@@ -118,7 +123,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
       auto tile_max = [&](auto masked) {
         if (decltype(masked)::value) {
 #pragma unroll
-          for (int jb = 0; jb < 2; ++jb)
+          for (int jb = 0; jb < NJB; ++jb)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
               if (32 * jb + 8 * (e >> 2) + (e & 3) >= rel) st[jb][e] = -INFINITY;
@@ -126,11 +131,11 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
         }
         mx = st[0][0];
 #pragma unroll
-        for (int jb = 0; jb < 2; ++jb)
+        for (int jb = 0; jb < NJB; ++jb)
 #pragma unroll
           for (int e = 0; e < 16; ++e) mx = fmaxf(mx, st[jb][e]);
       };
-      if (j0 + BJ > wave_lo) tile_max(std::true_type{}); else tile_max(std::false_type{});
+      if (j0 + 32 * NJB > wave_lo) tile_max(std::true_type{}); else tile_max(std::false_type{});
       mx = half_pair_max(mx);
       // ---- online softmax for this lane's query.  The running reference m only moves when the
       // tile maximum exceeds it by more than 2^RESCALE_LOG2 in the exponent, so that most tiles
@@ -149,9 +154,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
       }
       const float mc = (m == -INFINITY ? 0.f : m) * c2;
       float rs = 0.f;
-      uint32_t pk[2][8];
+      uint32_t pk[NJB][8];
 #pragma unroll
-      for (int jb = 0; jb < 2; ++jb)
+      for (int jb = 0; jb < NJB; ++jb)
 #pragma unroll
         for (int e = 0; e < 16; e += 2) {
           const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(st[jb][e], c2, -mc));
@@ -164,7 +169,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
       // ---- O^T += V^T P^T ; step t of block jb uses S^T registers 8t .. 8t+7
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int jb = 0; jb < 2; ++jb)
+      for (int jb = 0; jb < NJB; ++jb)
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
           union { uint32_t u[4]; bf16x8_t v; } pf;
@@ -174,7 +179,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
           for (int cb = 0; cb < 4; ++cb)
             o[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag(vs, fo, 32 * jb + 16 * t, cb), pf.v, o[cb], 0, 0, 0);
         }
-      pipeline_reads_mfma<16, 2>();
+      pipeline_reads_mfma<16 / KH, 2>();
       __builtin_amdgcn_sched_barrier(0);
     }
     wait_vmem();
@@ -191,6 +196,31 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
   }
   if (jt < ntiles) tile_step(stage0, stage1, jt);
 
+  if constexpr (KH == 2) {          // the second half's partial result joins the first's
+    float4* po = (float4*)stage0 + qw * 64 + lane;               // [16][2 waves][64 lanes]: 32 KB
+    float2* pml = (float2*)(stage1 + TILE) + qw * 64 + lane;     // (the first tile of stage1 takes the rows out below)
+    if (kw) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) po[128 * i] = float4{o[i >> 2][4 * (i & 3)], o[i >> 2][4 * (i & 3) + 1], o[i >> 2][4 * (i & 3) + 2], o[i >> 2][4 * (i & 3) + 3]};
+      *pml = float2{m, l};
+    }
+    __syncthreads();
+    if (kw) return;
+    const float2 ml = *pml;
+    const float mm = fmaxf(m, ml.x);
+    const float w0 = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - mm) * c2);
+    const float w1 = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ml.x - mm) * c2);
+    m = mm;
+    l = l * w0 + ml.y * w1;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float4 v = po[128 * i];
+      const float w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[i >> 2][4 * (i & 3) + e] = o[i >> 2][4 * (i & 3) + e] * w0 + w[e] * w1;
+    }
+  }
+
   // ---- normalise and store: register e of block cb is channel 32 cb + 8 (e/4) + 4 hf + e%4
   // The rows go out through LDS (the stages are free: the last step, or the prologue, ended with a barrier).
   {
@@ -202,7 +232,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
       for (int qd = 0; qd < 4; ++qd)
         po[4 * cb + qd] = make_uint2(cvt_pk(o[cb][4 * qd] * inv, o[cb][4 * qd + 1] * inv),
                                      cvt_pk(o[cb][4 * qd + 2] * inv, o[cb][4 * qd + 3] * inv));
-    store_rows_via_lds(stage0 + wave * 32 * HD, po, lane, (bf16_t*)a.o + ((sv.q0 + qw0) * a.H + h) * HD, (int64_t)a.H * HD,
+    store_rows_via_lds((KH == 1 ? stage0 : stage1) + qw * 32 * HD, po, lane, (bf16_t*)a.o + ((sv.q0 + qw0) * a.H + h) * HD, (int64_t)a.H * HD,
                        sv.S - qw0);
     if (q_ok && hf == 0)
       a.lse[sv.lse0 + h * sv.lse_hs + q] = l > 0.f ? m * a.scale + __logf(l) : -INFINITY;
@@ -211,8 +241,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_kernel(AttnArgs a) {
 
 void launch_attn_fwd_bf16(const AttnArgs& a, hipStream_t s) {
   ProfScope ps("attn_fwd_bf16", s);
-  dim3 grid(((a.S + fwd::BQ - 1) / fwd::BQ) * a.H * a.B);
-  hipLaunchKernelGGL(attn_fwd_bf16_kernel, grid, dim3(256), 0, s, a);
+  if (attn_key_halves(a)) hipLaunchKernelGGL(attn_fwd_bf16_kernel<2>, dim3((a.S + 63) / 64 * a.H * a.B), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(attn_fwd_bf16_kernel<1>, dim3((a.S + 127) / 128 * a.H * a.B), dim3(256), 0, s, a);
 }
 
 }  // namespace beagle

@@ -123,6 +123,17 @@ __device__ __forceinline__ void map_block(int n, int rows, int& row, int& tpos) 
   }
 }
 
+// Whether the forward and the dQ kernel halve their workgroups to 64 queries and give 32 of them to two waves, one per
+// half of every key tile.  A workgroup's walk over the key tiles is a serial chain whose longest is twice the average; with
+// up to one workgroup of 128 queries per CU that chain is the launch, and half as long with twice the workgroups.  The
+// price is that K and V pass through LDS twice as often.  Training step, whole -> half tiles, us (32 heads, 8 groups): one
+// sequence of 300 243 -> 238, 777 357 -> 345, 1300 551 -> 538, 2048 725 -> 719; 2 of 512 382 -> 374; but 2 of 800 551 -> 553,
+// 4 of 512 596 -> 606: between 256 and 512 workgroups it takes a chain of more than 16 tiles.
+inline bool attn_key_halves(const AttnArgs& a) {
+  const int64_t n = (int64_t)((a.S + 127) / 128) * a.H * a.B;
+  return n <= 256 || (n <= 512 && a.S > 1024);
+}
+
 // Issue-order hints for a run of N MFMAs that each consume RPM LDS reads (1 for
 // a whole-row fragment, 2 for a transpose fragment): keep four fragments in
 // flight ahead of the MFMA that uses them instead of read-wait-MFMA per step.
