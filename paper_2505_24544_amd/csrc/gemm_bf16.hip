@@ -40,6 +40,7 @@
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
+#include <string.h>
 #include "common.h"
 
 namespace beagle {
@@ -754,7 +755,8 @@ static void launch_ksplit(const GemmGroup& grp, hipStream_t s) {
 //   128 x 128: K 777 full 13; K 4096 full 40, 7/8 full 36 (four waves of 64 x 64 per tile took 59)
 // Large problems come out at 256 x 256 by their operand traffic alone (1.30 PFLOP/s against 0.95 and 0.80).
 enum TileSize { TILE_256, TILE_256x128, TILE_128x256, TILE_128 };
-static TileSize choose_tile(const GemmGroup& grp) {
+struct TileChoice { TileSize tile; double us; };
+static TileChoice choose_tile(const GemmGroup& grp) {
   struct Cost { int bm, bn; double fixed, slice, slice_full; };
   static const Cost costs[] = {{256, 256, 8.8, 0.90, 0.65}, {256, 128, 8.3, 0.57, 0.38}, {128, 256, 8.3, 0.57, 0.38}, {128, 128, 6.1, 0.38, 0.16}};
   int best = 0;
@@ -773,7 +775,52 @@ static TileSize choose_tile(const GemmGroup& grp) {
     if (rest > 0.0) us += costs[c].fixed + depth * (costs[c].slice + costs[c].slice_full * rest);
     if (c == 0 || us < best_us) { best = c; best_us = us; }
   }
-  return (TileSize)best;
+  return {(TileSize)best, best_us};
+}
+
+static void launch_chosen(const GemmGroup& grp, TileSize tile, hipStream_t s) {
+  switch (tile) {
+    case TILE_256: return launch_tiles<4, 4>(grp, s);
+    case TILE_256x128: return launch_ksplit<2, 1>(grp, s);
+    case TILE_128x256: return launch_ksplit<1, 2>(grp, s);
+    case TILE_128: return launch_ksplit<1, 1>(grp, s);
+  }
+}
+
+// A few 256 x 256 tiles past a whole number of rounds hold the chip for most of another round (3048 x 11008 x 4096: 516 tiles,
+// by the costs above 66 us for the last four after two rounds of 108).  The bottom tile rows of one problem that make up the
+// excess then go into a launch of their own, on small tiles that spread them over the chip (37 us).  The same costs decide,
+// with CUT_US for the second launch and for what the fit is off.  Whole calls, us: training step of 4100 positions, 32 heads
+// 2134 -> 2057, of 4224 in 8 groups 1835 -> 1790, of 3400 at 5120 channels 2535 -> 2503; draft block on 3048 packed rows
+// 4341 -> 4277.  Past half a round of excess the costs find nothing (7.5 rounds of 8192 positions at 5120 channels stay whole).
+constexpr double CUT_US = 8.0;
+static bool cut_excess(const GemmGroup& grp, double whole_us, GemmGroup* main, GemmGroup* rest) {
+  int tiles = 0;
+  for (int i = 0; i < grp.count; ++i) tiles += ((grp.p[i].M + 255) / 256) * ((grp.p[i].N + 255) / 256);
+  const int excess = tiles % 256;
+  if (tiles < 256 || excess == 0 || excess > 128) return false;
+  double best_us = whole_us - CUT_US;
+  bool found = false;
+  for (int i = 0; i < grp.count; ++i) {
+    const GemmArgs& q = grp.p[i];
+    const int rows = (q.M + 255) / 256, cols = (q.N + 255) / 256, r = (excess + cols - 1) / cols;
+    // a row-contiguous X read from the middle of its rows: only whole tiles stay inside the matrix in its last k row
+    if (r >= rows || (!q.a_kmajor && q.M % 256)) continue;
+    GemmGroup a = grp, b; memset(&b, 0, sizeof(b));
+    const int64_t m0 = (int64_t)(rows - r) * 256;
+    a.p[i].M = (int32_t)m0;
+    b.count = 1;
+    GemmArgs& t = b.p[0];
+    t = q;
+    t.M = (int32_t)(q.M - m0);
+    t.A = (const bf16_t*)q.A + m0 * (q.a_kmajor ? q.lda : 1);
+    if (q.A2) t.A2 = (const bf16_t*)q.A2 + m0 * (q.a_kmajor ? q.lda2 : 1);
+    t.C = (char*)q.C + m0 * q.ldc * (q.c_is_f32 ? 4 : 2);
+    if (q.R) t.R = (const bf16_t*)q.R + m0 * q.ldr;
+    const double us = choose_tile(a).us + choose_tile(b).us;
+    if (us < best_us) { best_us = us; *main = a; *rest = b; found = true; }
+  }
+  return found;
 }
 
 // Every GEMM of a group must share storage orders and output type; the hot
@@ -782,12 +829,14 @@ static TileSize choose_tile(const GemmGroup& grp) {
 void launch_gemm_bf16(const GemmGroup& grp, hipStream_t s, const char* name) {
   ProfScope ps(name, s);
   check_group(grp);
-  switch (choose_tile(grp)) {
-    case TILE_256: return launch_tiles<4, 4>(grp, s);
-    case TILE_256x128: return launch_ksplit<2, 1>(grp, s);
-    case TILE_128x256: return launch_ksplit<1, 2>(grp, s);
-    case TILE_128: return launch_ksplit<1, 1>(grp, s);
+  const TileChoice whole = choose_tile(grp);
+  GemmGroup main, rest;
+  if (whole.tile == TILE_256 && cut_excess(grp, whole.us, &main, &rest)) {
+    launch_chosen(main, choose_tile(main).tile, s);
+    launch_chosen(rest, choose_tile(rest).tile, s);
+    return;
   }
+  launch_chosen(grp, whole.tile, s);
 }
 
 template <bool F32OUT>

@@ -39,6 +39,8 @@ def reference(t, S, D, H, G, k):
     (1300, 1024, 32, 8, True),       # 256 | 128 | 128 x 256 | 128 | 128 | 128 x 256
     (900, 3072, 24, 12, False),      # 128 x 256 | 128 | 128 | 256 | 128 x 256 | 256
     (513, 4096, 8, 2, True),         # 128 | 128 | 128 | 128 | 128 x 256 | 128 x 256
+    (4200, 4352, 32, 2, False),      # 256 with the tile rows past whole rounds in a second launch, ragged rows among them ...
+    (4200, 4352, 32, 2, True),       # ... and weight gradients with rows of X cut off, float output
 ])
 def test_step_against_float32(S, D, H, G, wf32):
     gen = torch.Generator(device="cuda").manual_seed(S + D)
@@ -69,7 +71,8 @@ def test_step_against_float32(S, D, H, G, wf32):
         assert rel(g["d" + n], gr[n]) <= 3e-2, n
 
 
-@pytest.mark.parametrize("S,D,H", [(70, 512, 4), (1500, 4096, 32), (2900, 4096, 8)])     # 128 x 128, 256 x 128, 256 x 256
+@pytest.mark.parametrize("S,D,H", [(70, 512, 4), (1500, 4096, 32), (2900, 4096, 8),      # 128 x 128, 256 x 128, 256 x 256
+                                   (4200, 4096, 32)])                                    # 256 x 256, the last tile row apart
 def test_residual_operand(S, D, H):
     """y = o Wo + e of the block's forward, from its own saved o: the residual is added before the one rounding."""
     gen = torch.Generator(device="cuda").manual_seed(S)
