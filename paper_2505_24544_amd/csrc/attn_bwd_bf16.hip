@@ -10,7 +10,7 @@
 //      S^T = K Q^T and dP^T = V dO^T come out with column q = lane % 32, so LSE
 //      and delta are per-lane scalars, and dS^T goes straight from the
 //      accumulator registers into the B operand of dQ^T += K^T dS^T.  The kernel
-//      also computes delta and stores -delta and -log2(e) * LSE for kernel (2).
+//      also computes delta and stores it, with -log2(e) * LSE, for kernel (2).
 //
 //  (2) dkv kernel  one workgroup = 128 keys of one (b, kv head), loop over the
 //      H/G query heads of the group and over the query tiles that can see those
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
 #pragma unroll
   for (int s = 0; s < 8; ++s) part += bwd::dot8(dof[s], of[s]);
   const float delta = half_pair_sum(part);
-  if (q_ok && hf == 0 && kw == 0) { a.delta[li] = -delta; a.nlse2[li] = -LOG2E * lse; }   // blind rows: +inf, masked in the dK/dV kernel
+  if (q_ok && hf == 0 && kw == 0) { a.delta[li] = delta; a.nlse2[li] = -LOG2E * lse; }   // blind rows: +inf, masked in the dK/dV kernel
   const float c2 = a.scale * LOG2E;
   const float lse2 = (lim > 0 ? lse : 0.f) * LOG2E;    // blind rows are fully masked below
   const FragOffs fo = make_frag_offs(lane);
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
   args_at_hand(a);
   __shared__ __attribute__((aligned(1024))) bf16_t stage0[2 * TILE];
   __shared__ __attribute__((aligned(1024))) bf16_t stage1[2 * TILE];
-  // [-log2(e) lse 64 | -delta 64] of the stage's queries; waves 2 and 3 repeat the two requests into the second half,
+  // [-log2(e) lse 64 | delta 64] of the stage's queries; waves 2 and 3 repeat the two requests into the second half,
   // which nobody reads, so that the request sequence has no branch and can be issued between MFMAs
   __shared__ __attribute__((aligned(256))) float stat0[4 * BQ];
   __shared__ __attribute__((aligned(256))) float stat1[4 * BQ];
@@ -346,24 +346,19 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
       {
         constexpr int VPM = 10;   // vector instructions of one block slotted in per MFMA of the other
         f32x16_t s2[2], dp[2];
-        float4 l4[4];
+        float4 l4[4], d4[4];
         uint32_t pp[2][8], pd[2][8];
         auto stats = [&](int qb) {
 #pragma unroll
           for (int e4 = 0; e4 < 4; ++e4) {
             const int r = 32 * qb + 8 * e4 + 4 * hf;
             l4[e4] = *(const float4*)(sl + r);
+            d4[e4] = *(const float4*)(sl + BQ + r);
           }
         };
-        // -delta of the block's queries is what dP starts from, read from LDS into the accumulators: sixteen subtractions
-        // per block less in a kernel bound by instruction issue (4 x 2048 364 -> 357 us, 2 x 4096 in 8 groups 584 -> 574)
         auto scores = [&](int qb) {
 #pragma unroll
-          for (int e4 = 0; e4 < 4; ++e4) {
-            const float4 nd = *(const float4*)(sl + BQ + 32 * qb + 8 * e4 + 4 * hf);
-            s2[qb][4 * e4] = s2[qb][4 * e4 + 1] = s2[qb][4 * e4 + 2] = s2[qb][4 * e4 + 3] = 0.f;
-            dp[qb][4 * e4] = nd.x; dp[qb][4 * e4 + 1] = nd.y; dp[qb][4 * e4 + 2] = nd.z; dp[qb][4 * e4 + 3] = nd.w;
-          }
+          for (int e = 0; e < 16; ++e) { s2[qb][e] = 0.f; dp[qb][e] = 0.f; }
 #pragma unroll
           for (int s = 0; s < 8; ++s) {
             s2[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag(qsm, fo, qb, s), kf[s], s2[qb], 0, 0, 0);
@@ -389,9 +384,10 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
           }
 #pragma unroll
           for (int e4 = 0; e4 < 4; ++e4) {
+            const float dl[4] = {d4[e4].x, d4[e4].y, d4[e4].z, d4[e4].w};
             float dsv[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) dsv[u] = pv[4 * e4 + u] * dp[qb][4 * e4 + u];
+            for (int u = 0; u < 4; ++u) dsv[u] = pv[4 * e4 + u] * (dp[qb][4 * e4 + u] - dl[u]);
             pp[qb][2 * e4] = cvt_pk(pv[4 * e4], pv[4 * e4 + 1]); pp[qb][2 * e4 + 1] = cvt_pk(pv[4 * e4 + 2], pv[4 * e4 + 3]);
             pd[qb][2 * e4] = cvt_pk(dsv[0], dsv[1]); pd[qb][2 * e4 + 1] = cvt_pk(dsv[2], dsv[3]);
           }
@@ -410,7 +406,6 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
           }
         };
         scores(0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
         pipeline_reads_mfma_loads<16, 1, 9>();
         __builtin_amdgcn_sched_barrier(0);
         stats(0);
@@ -422,7 +417,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
         stats(1);
         accum(0);
         probs(1);
-        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
         pipeline_reads_mfma_valu<16, 2, VPM>();
         __builtin_amdgcn_sched_barrier(0);
         accum(1);

@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256) void sim_band_bwd_dq_bf16_kernel(SimArgs s) {
     const Chunk q = load_chunk((const bf16_t*)a.q + row, c);
     const Chunk go = load_chunk((const bf16_t*)a.dout + row, c);
     Chunk dq = load_chunk((const bf16_t*)a.dq + row, c);
-    const float lse = a.lse[li], ndelta = a.delta[li];
+    const float lse = a.lse[li], delta = a.delta[li];
     Chunk acc;
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc.f[i] = 0.f;
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256) void sim_band_bwd_dq_bf16_kernel(SimArgs s) {
       const Chunk kk = load_chunk(Kp + (int64_t)j * a.G * BD, c);
       const Chunk vv = load_chunk(Vp + (int64_t)j * a.G * BD, c);
       const float pj = expf(a.scale * row16_sum(dot8(q, kk)) - lse);
-      const float ds = pj * (row16_sum(dot8(go, vv)) + ndelta);
+      const float ds = pj * (row16_sum(dot8(go, vv)) - delta);
 #pragma unroll
       for (int i = 0; i < 8; ++i) acc.f[i] = fmaf(ds, kk.f[i], acc.f[i]);
     }
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(256) void sim_band_bwd_dkv_bf16_kernel(SimArgs s) {
           const Chunk q = load_chunk((const bf16_t*)a.q + row, c);
           const Chunk go = load_chunk((const bf16_t*)a.dout + row, c);
           const float pj = expf(a.scale * row16_sum(dot8(q, kk)) - a.lse[li]);
-          const float ds = pj * (row16_sum(dot8(go, vv)) + a.delta[li]);
+          const float ds = pj * (row16_sum(dot8(go, vv)) - a.delta[li]);
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
             dk.f[i] = fmaf(ds, q.f[i], dk.f[i]);
