@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmGroup grp) {
     constexpr bool AK = decltype(ak_)::value, BK = decltype(bk_)::value;
     const float* ap = AK ? A + mr * lda : A + mr;
     const float* bp = BK ? B + nc * ldb : B + nc;
-    // 32 k of both operands: register 4 i + e is k = k0 + 8 i + 4 hf + e; past K: zeros on the A side
+    // 32 k of both operands: register 4 i + e is k = k0 + 8 i + 4 hf + e; past K: zeros on both sides (0 * inf is a NaN)
     auto load = [&](int k0, float (&a)[16], float (&b)[16]) BEAGLE_INLINE_LAMBDA {
       if (k0 + 32 <= K) {
 #pragma unroll
@@ -80,9 +80,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmGroup grp) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int k = k0 + 8 * (i >> 2) + 4 * hf + (i & 3), kc = min(k, K - 1);
-          const float v = AK ? ap[kc] : ap[kc * lda];
+          const float v = AK ? ap[kc] : ap[kc * lda], w = BK ? bp[kc] : bp[kc * ldb];
           a[i] = k < K ? v : 0.f;
-          b[i] = BK ? bp[kc] : bp[kc * ldb];
+          b[i] = k < K ? w : 0.f;
         }
       }
     };
@@ -172,6 +172,41 @@ __device__ __forceinline__ f32x16_t dot_frags(const float (&a)[16 * NC], const f
 __device__ __forceinline__ float pair_sum(float v) { return v + __shfl_xor(v, 32, 64); }
 __device__ __forceinline__ float pair_max(float v) { return fmaxf(v, __shfl_xor(v, 32, 64)); }
 
+// Infinities and NaN behind the mask.  The second products multiply the rows that a query (key) must not see by a zero weight,
+// which leaves nothing behind unless such a row is not finite.  Over the tiles that hold hidden pairs the waves therefore sum
+// v * 0 over the fragments (a step of 128 rows takes 48 us with and without); where that is a NaN at the end, the wave starts over
+// on plain code that reads only what each query (key) sees: the functions *_plain below, for which a lane keeps the row and the
+// channels of its accumulators.
+template <int N>
+__device__ __forceinline__ void note_nonfinite(float& nf, const float (&f)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) nf = fmaf(f[i], 0.f, nf);
+}
+__device__ __forceinline__ bool any_nonfinite(float nf) { return __builtin_amdgcn_ballot_w64(nf != 0.f) != 0; }
+// x . y over a head's channels, a lane pair's halves together
+__device__ __forceinline__ float row_dot(const float* x, const float* y, int d, int hf) {
+  float t = 0.f;
+  for (int c = 4 * hf; c < d; c += 8) {
+    const float4 u = *(const float4*)(x + c), v = *(const float4*)(y + c);
+    t = fmaf(u.x, v.x, t); t = fmaf(u.y, v.y, t); t = fmaf(u.z, v.z, t); t = fmaf(u.w, v.w, t);
+  }
+  return pair_sum(t);
+}
+// o = o * keep + w * row where `take`
+template <int NC>
+__device__ __forceinline__ void add_row(f32x16_t (&o)[NC], bool take, float keep, float w, const float* row, int d, int hf) {
+#pragma unroll
+  for (int i = 0; i < 4 * NC; ++i) {
+    const float4 x4 = *(const float4*)(row + min(8 * i + 4 * hf, d - 4));
+    const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float v = o[i >> 2][4 * (i & 3) + u];
+      o[i >> 2][4 * (i & 3) + u] = take ? fmaf(w, x[u], v * keep) : v;
+    }
+  }
+}
+
 // A wave's accumulators [channel 32 cb + acc_row][row ql] -> LDS[row][channel], rows padded by one float
 template <int NC>
 __device__ __forceinline__ void park(float* buf, const f32x16_t (&o)[NC], int ql, int hf) {
@@ -179,6 +214,27 @@ __device__ __forceinline__ void park(float* buf, const f32x16_t (&o)[NC], int ql
   for (int cb = 0; cb < NC; ++cb)
 #pragma unroll
     for (int e = 0; e < 16; ++e) buf[ql * (32 * NC + 1) + 32 * cb + acc_row(e, hf)] = o[cb][e];
+}
+
+template <int NC>
+__device__ __forceinline__ void fwd_plain(const AttnArgs& a, const float* q, const float* K, const float* V, int64_t kvs, int first,
+                                          int wg_lim, int lim, const uint32_t* trow, int hf, f32x16_t (&o)[NC], float& m, float& l) {
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb) o[cb] = zero16();
+  m = -INFINITY; l = 0.f;
+#pragma unroll 1
+  for (int j0 = first; j0 < wg_lim; j0 += 128)
+#pragma unroll 1
+    for (int j = j0; j < min(j0 + 32, wg_lim); ++j) {
+      bool vis = j < lim;
+      if (trow && j >= a.n_true && vis) { const int t = j - a.n_true; vis = ((trow[t >> 5] >> (t & 31)) & 1u) != 0; }
+      const float s = a.scale * row_dot(q, K + j * kvs, a.d, hf);
+      const float mn = vis ? fmaxf(m, s) : m, mb = mn == -INFINITY ? 0.f : mn;
+      const float keep = expf(m - mb), p = expf(s - mb);
+      l = vis ? l * keep + p : l;
+      add_row<NC>(o, vis, keep, p, V + j * kvs, a.d, hf);
+      m = mn;
+    }
 }
 
 template <int NC>
@@ -194,18 +250,20 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_f32_kernel(AttnArgs a) {
   const float* K = (const float*)a.k + (sv.kv0 * a.G + g) * d;
   const float* V = (const float*)a.v + (sv.kv0 * a.G + g) * d;
   const int64_t kvs = (int64_t)a.G * d;
+  const float* Q = (const float*)a.q + ((sv.q0 + qc) * a.H + h) * d;
   float qf[16 * NC];
-  row_frag<NC>((const float*)a.q + ((sv.q0 + qc) * a.H + h) * d, d, hf, qf);
+  row_frag<NC>(Q, d, hf, qf);
   const MaskParams mk = sample_mask(a, b);
   const int lim = q < sv.S ? row_limit(q, mk) : 0;
   const int wg_lim = row_limit(min(q0 + 32, sv.S) - 1, mk);            // limits never decrease with the query
+  const int all_lim = min(row_limit(q0, mk), a.tree ? a.n_true : sv.L);   // keys below are seen by every query
   // draft-tree decode: keys at or past n_true are visible only where the query's tree row has a bit
   const uint32_t* trow = a.tree ? a.tree + (int64_t)qc * a.tree_words : nullptr;
 
   f32x16_t o[NC];
 #pragma unroll
   for (int cb = 0; cb < NC; ++cb) o[cb] = zero16();
-  float m = -INFINITY, l = 0.f;
+  float m = -INFINITY, l = 0.f, nf = 0.f;
   for (int j0 = 32 * wave; j0 < wg_lim; j0 += 128) {
     float kf[16 * NC], vf[NC][16];
     row_frag<NC>(K + min(j0 + ql, sv.L - 1) * kvs, d, hf, kf);
@@ -236,7 +294,12 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_f32_kernel(AttnArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[cb] = mfma(vf[cb][e], s[e], o[cb]);
     }
+    if (j0 + 32 > all_lim) {
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) note_nonfinite(nf, vf[cb]);
+    }
   }
+  if (any_nonfinite(nf)) fwd_plain<NC>(a, Q, K, V, kvs, 32 * wave, wg_lim, lim, trow, hf, o, m, l);
   park<NC>(ob[wave], o, ql, hf);
   if (hf == 0) { ms[wave][ql] = m; ls[wave][ql] = l; }
   __syncthreads();
@@ -253,6 +316,41 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_f32_kernel(AttnArgs a) {
     O[c] = (((ob[0][i] * w[0] + ob[1][i] * w[1]) + ob[2][i] * w[2]) + ob[3][i] * w[3]) * inv;
   }
   if ((tid & 7) == 0) a.lse[sv.lse0 + h * sv.lse_hs + p] = lt > 0.f ? mm + logf(lt) : -INFINITY;
+}
+
+template <int NC>
+__device__ __forceinline__ void dq_plain(const AttnArgs& a, const float* q, const float* g, float lse, float delta, const float* K,
+                                         const float* V, int64_t kvs, int first, int wg_lim, int lim, int hf, f32x16_t (&dq)[NC]) {
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb) dq[cb] = zero16();
+#pragma unroll 1
+  for (int j0 = first; j0 < wg_lim; j0 += 128)
+#pragma unroll 1
+    for (int j = j0; j < min(j0 + 32, wg_lim); ++j) {
+      const float p = expf(a.scale * row_dot(q, K + j * kvs, a.d, hf) - lse);
+      add_row<NC>(dq, j < lim, 1.f, p * (row_dot(g, V + j * kvs, a.d, hf) - delta), K + j * kvs, a.d, hf);
+    }
+}
+// the (head, query block) pairs first, first + 4, ... of one key/value head, whose heads' query rows start at Q, dO, O
+template <int NC>
+__device__ __forceinline__ void dkv_plain(const AttnArgs& a, const SeqView& sv, const float* k, const float* v, const float* Q,
+                                          const float* dO, const float* O, const float* lse, int64_t qs, int first, int pairs, int per,
+                                          int qb0, int fq, int hf, f32x16_t (&dk)[NC], f32x16_t (&dv)[NC]) {
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb) { dk[cb] = zero16(); dv[cb] = zero16(); }
+#pragma unroll 1
+  for (int it = first; it < pairs; it += 4) {
+    const int hh = it / per, p0 = (qb0 + it % per) * 32;
+#pragma unroll 1
+    for (int p = p0; p < min(p0 + 32, sv.S); ++p) {
+      const int64_t r = (int64_t)hh * a.d + p * qs;
+      const float delta = row_dot(dO + r, O + r, a.d, hf);
+      const float w = expf(a.scale * row_dot(Q + r, k, a.d, hf) - lse[hh * sv.lse_hs + p]);
+      const float ds = w * (row_dot(dO + r, v, a.d, hf) - delta);
+      add_row<NC>(dv, p >= fq, 1.f, w, dO + r, a.d, hf);
+      add_row<NC>(dk, p >= fq, 1.f, ds, Q + r, a.d, hf);
+    }
+  }
 }
 
 // Both halves of the backward in one launch (they are independent: each forms delta = rowsum(dO * O) for itself).
@@ -300,10 +398,11 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
     if (wave == 0 && hf == 0 && q < sv.S) a.delta[li] = delta;
     const MaskParams mk = sample_mask(a, b);
     const int lim = q < sv.S ? row_limit(q, mk) : 0;
-    const int wg_lim = row_limit(min(q0 + 32, sv.S) - 1, mk);
+    const int wg_lim = row_limit(min(q0 + 32, sv.S) - 1, mk), all_lim = row_limit(q0, mk);
     f32x16_t dq[NC];
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb) dq[cb] = zero16();
+    float nf = 0.f;
     for (int j0 = 32 * wave; j0 < wg_lim; j0 += 128) {
       float kf[16 * NC], vf[16 * NC], kc[NC][16];
       const int64_t jr = min(j0 + ql, sv.L - 1) * kvs;
@@ -320,7 +419,13 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
       for (int cb = 0; cb < NC; ++cb)
 #pragma unroll
         for (int e = 0; e < 16; ++e) dq[cb] = mfma(kc[cb][e], s[e], dq[cb]);
+      if (j0 + 32 > all_lim) {
+#pragma unroll
+        for (int cb = 0; cb < NC; ++cb) note_nonfinite(nf, kc[cb]);
+      }
     }
+    if (any_nonfinite(nf))
+      dq_plain<NC>(a, (const float*)a.q + qrow, (const float*)a.dout + qrow, lse, delta, K, V, kvs, 32 * wave, wg_lim, lim, hf, dq);
     park<NC>(ob[wave], dq, ql, hf);
     rows_out((float*)a.dq + ((sv.q0 + q0) * a.H + h) * d, qs, min(32, sv.S - q0), a.scale);
   } else {
@@ -335,10 +440,12 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
     row_frag<NC>((const float*)a.v + kvrow, d, hf, vf);
     const MaskParams mk = sample_mask(a, b);
     const int fq = j < sv.L ? first_query_seeing(j, mk) : sv.S;         // this lane's key is seen from here on
+    const int all_q = first_query_seeing(min(j0 + 32, sv.L) - 1, mk);   // the workgroup's keys are all seen from here on
     const int qb0 = first_query_seeing(j0, mk) / 32, nqb = (sv.S + 31) / 32, per = nqb > qb0 ? nqb - qb0 : 0;
     f32x16_t dk[NC], dv[NC];
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb) { dk[cb] = zero16(); dv[cb] = zero16(); }
+    float nf = 0.f;
     for (int it = wave; it < per * rep; it += 4) {
       const int hh = it / per, p0 = (qb0 + it % per) * 32, h = g * rep + hh;
       const float* Q = (const float*)a.q + (sv.q0 * a.H + h) * d;
@@ -385,7 +492,13 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e) { dv[cb] = mfma(cg[CB * cb][e], s[e], dv[cb]); dk[cb] = mfma(cq[CB * cb][e], dp[e], dk[cb]); }
+        if (p0 < all_q || p0 + 32 > sv.S) { note_nonfinite(nf, cg[CB * cb]); note_nonfinite(nf, cq[CB * cb]); }
       }
+    }
+    if (any_nonfinite(nf)) {
+      const int64_t qh = (sv.q0 * a.H + g * rep) * d;                   // query 0 of the group's first head
+      dkv_plain<NC>(a, sv, (const float*)a.k + kvrow, (const float*)a.v + kvrow, (const float*)a.q + qh, (const float*)a.dout + qh,
+                    (const float*)a.o + qh, a.lse + sv.lse0 + g * rep * sv.lse_hs, qs, wave, per * rep, per, qb0, fq, hf, dk, dv);
     }
     const int64_t out0 = ((sv.kv0 + j0) * a.G + g) * d;
     park<NC>(ob[wave], dk, ql, hf);
