@@ -101,6 +101,13 @@ BwdWs bwd_layout(const Dims& d) {
   return w;
 }
 
+size_t bwd_need(const Dims& d, bool sim) {
+  const size_t attn = d.bf16 ? align_up(attn_bwd_bf16_ws_bytes(attn_args(d))) : 0;
+  const size_t pred = sim ? 2 * align_up((size_t)(d.Tk * d.GD) * d.esz) : 0;    // dKp, dVp
+  return bwd_layout(d).total + attn + pred + states_ws(d);
+}
+size_t bwd_spare_bytes(const Dims& d) { return d.bf16 ? attn_bwd_bf16_share_bytes(attn_args(d)) : 0; }
+
 // The three weight gradients dWq, dWk, dWv are one grouped launch of 256 x 256 tiles.  Under grouped-query attention dWk
 // and dWv are narrow, and the launch can end in a round of tiles that fills a fraction of the 256 compute units (H 32 /
 // G 8 at D 4096: 256 + 64 + 64 tiles, i.e. a full round and a half-empty one of the same length).  Then dWq goes alone
@@ -228,13 +235,13 @@ static void run_bwd_last(const Dims& d, GemmGroup dx, const GemmGroup& dw, hipSt
   }
 }
 
-// All gradients of the attention op; `base` is a workspace of BEAGLE_WS_BWD bytes.  dxq_res, if given, is added
+// All gradients of the attention op; `base` is a workspace of bwd_need bytes.  dxq_res, if given, is added
 // to dxq in the epilogue of its GEMM.
 void xattn_bwd_run(const Dims& d, bool need_dxkv, bool wf32, const void* dy, const void* xq, const void* xkv,
                    const void* wq, const void* wk, const void* wv, const void* wo, const void* q_save,
                    const void* k_save, const void* v_save, const void* o_save, const float* lse, void* dxq,
-                   void* dxkv, void* dwq, void* dwk, void* dwv, void* dwo, char* base, const void* dxq_res,
-                   hipStream_t s) {
+                   void* dxkv, void* dwq, void* dwk, void* dwv, void* dwo, char* base, Spare spare,
+                   const void* dxq_res, hipStream_t s) {
   const BwdWs w = bwd_layout(d);
   void* dO = base + w.dO; void* dQ = base + w.dQ; void* dK = base + w.dK; void* dV = base + w.dV;
   float* delta = (float*)(base + w.delta);
@@ -245,7 +252,7 @@ void xattn_bwd_run(const Dims& d, bool need_dxkv, bool wf32, const void* dy, con
   AttnArgs a = attn_args(d);
   a.q = q_save; a.k = k_save; a.v = v_save; a.o = (void*)o_save; a.lse = (float*)lse;
   a.dout = dO; a.dq = dQ; a.dk = dK; a.dv = dV; a.delta = delta;
-  if (d.bf16) launch_attn_bwd_bf16(a, base + w.attn, s); else launch_attn_bwd_f32(a, s);
+  if (d.bf16) launch_attn_bwd_bf16(a, base + w.attn, spare.p, spare.bytes, s); else launch_attn_bwd_f32(a, s);
   if (d.rope) {   // dQ, dK are gradients of the rotated rows: rotate them back
     RopeArgs r = rope_args(d, true);
     rope_add(r, dQ, Mq, d.S, d.H, 0, nullptr, d.cu_q);
@@ -331,18 +338,17 @@ void xattn_fwd_sim_run(const Dims& d, const void* xq, const void* xkv, const voi
   run_gemm(d, group1(out), s, "proj_out");
 }
 
-// The simulation step's backward; `base` is a workspace of BEAGLE_WS_BWD_SIM bytes (without the converted states).
+// The simulation step's backward; `base` is a workspace of bwd_need bytes (without the converted states).
 void xattn_bwd_sim_run(const Dims& d, bool need_dxkv, bool wf32, const void* dy, const void* xq, const void* xkv,
                        const void* xpred, const void* wq, const void* wk, const void* wv, const void* wo,
                        const void* q_save, const void* k_save, const void* v_save, const void* kp_save,
                        const void* vp_save, const void* o_save, const float* lse, int32_t sim_step, void* dxq, void* dxkv,
-                       void* dxpred, void* dwq, void* dwk, void* dwv, void* dwo, char* base, const void* dxq_res,
-                       hipStream_t s) {
+                       void* dxpred, void* dwq, void* dwk, void* dwv, void* dwo, char* base, Spare spare,
+                       const void* dxq_res, hipStream_t s) {
   const BwdWs w = bwd_layout(d);
   void* dO = base + w.dO; void* dQ = base + w.dQ; void* dK = base + w.dK; void* dV = base + w.dV;
   float* delta = (float*)(base + w.delta);
-  size_t extra = 0;
-  if (d.bf16) { AttnArgs t = attn_args(d); extra = attn_bwd_bf16_ws_bytes(t); }
+  const size_t extra = d.bf16 ? attn_bwd_bf16_ws_bytes(attn_args(d)) : 0;
   const size_t kvb = align_up((size_t)(d.Tk * d.GD) * d.esz);
   void* dKp = base + w.total + align_up(extra);
   void* dVp = (char*)dKp + kvb;
@@ -356,7 +362,7 @@ void xattn_bwd_sim_run(const Dims& d, bool need_dxkv, bool wf32, const void* dy,
   sa.a.q = q_save; sa.a.k = k_save; sa.a.v = v_save; sa.a.o = (void*)o_save; sa.a.lse = (float*)lse;
   sa.a.dout = dO; sa.a.dq = dQ; sa.a.dk = dK; sa.a.dv = dV; sa.a.delta = delta;
   sa.kp = kp_save; sa.vp = vp_save; sa.dkp = dKp; sa.dvp = dVp; sa.t = sim_step; sa.is_bf16 = d.bf16 ? 1 : 0;
-  if (d.bf16) launch_attn_bwd_bf16(sa.a, base + w.attn, s); else launch_attn_bwd_f32(sa.a, s);
+  if (d.bf16) launch_attn_bwd_bf16(sa.a, base + w.attn, spare.p, spare.bytes, s); else launch_attn_bwd_f32(sa.a, s);
   // predicted-key band: adds to dQ, writes dKp and dVp (zeros where nothing is seen)
   launch_sim_band_bwd(sa, s);
   if (d.rope) {
@@ -567,21 +573,11 @@ size_t beagle_xattn_workspace_bytes(const beagle_xattn_desc* desc, int which) {
     return 0;
   switch (which) {
     case BEAGLE_WS_FWD: return WS_ALIGN + states_ws(d);   // nothing beyond the saved tensors (and the converted states)
-    case BEAGLE_WS_BWD: {
-      BwdWs w = bwd_layout(d);
-      size_t extra = 0;
-      if (d.bf16) { AttnArgs a = attn_args(d); extra = attn_bwd_bf16_ws_bytes(a); }
-      return w.total + align_up(extra) + states_ws(d);
-    }
+    case BEAGLE_WS_BWD: return bwd_need(d, false) + bwd_spare_bytes(d);
     case BEAGLE_WS_DRAFT:
       if (d.bf16) return align_up(decode_bf16_ws_bytes((int32_t)d.S, (int32_t)d.L, (int32_t)d.H, (int32_t)d.G, (int32_t)d.d, (int32_t)d.D));
       return align_up((size_t)(2 * d.S * d.HD) * d.esz);
-    case BEAGLE_WS_BWD_SIM: {
-      BwdWs w = bwd_layout(d);
-      size_t extra = 0;
-      if (d.bf16) { AttnArgs a = attn_args(d); extra = attn_bwd_bf16_ws_bytes(a); }
-      return w.total + align_up(extra) + 2 * align_up((size_t)(d.Tk * d.GD) * d.esz) + states_ws(d);   // + dKp, dVp
-    }
+    case BEAGLE_WS_BWD_SIM: return bwd_need(d, true) + bwd_spare_bytes(d);
     case BEAGLE_WS_APPEND:
     case BEAGLE_WS_BLOCK_APPEND: {
       size_t n = WS_ALIGN;
@@ -635,13 +631,15 @@ beagle_status beagle_xattn_bwd(const beagle_xattn_desc* desc,
   for (const void* p : ptrs) if (!aligned16(p)) return BEAGLE_ERR_ALIGN;
   if (dxkv && !aligned16(dxkv)) return BEAGLE_ERR_ALIGN;
   if (((uintptr_t)workspace) % WS_ALIGN) return BEAGLE_ERR_ALIGN;
-  if (workspace_bytes < beagle_xattn_workspace_bytes(desc, BEAGLE_WS_BWD)) return BEAGLE_ERR_WORKSPACE;
+  const size_t need = bwd_need(d, false);
+  if (workspace_bytes < need) return BEAGLE_ERR_WORKSPACE;
   hipStream_t s = (hipStream_t)hip_stream;
   (void)hipGetLastError();
 
-  xkv = states_in(d, xkv, workspace, beagle_xattn_workspace_bytes(desc, BEAGLE_WS_BWD), s);
+  xkv = states_in(d, xkv, workspace, need, s);
   xattn_bwd_run(d, need_dxkv, d.bf16 && (desc->flags & BEAGLE_FLAG_WGRAD_F32), dy, xq, xkv, wq, wk, wv, wo, q_save, k_save,
-                v_save, o_save, lse, dxq, dxkv, dwq, dwk, dwv, dwo, (char*)workspace, nullptr, s);
+                v_save, o_save, lse, dxq, dxkv, dwq, dwk, dwv, dwo, (char*)workspace,
+                {(char*)workspace + need, workspace_bytes - need}, nullptr, s);
   return hip_status();
 }
 
@@ -702,15 +700,16 @@ beagle_status beagle_xattn_bwd_sim(const beagle_xattn_desc* desc,
   for (const void* p : ptrs) if (!aligned16(p)) return BEAGLE_ERR_ALIGN;
   if (dxkv && !aligned16(dxkv)) return BEAGLE_ERR_ALIGN;
   if (((uintptr_t)workspace) % WS_ALIGN) return BEAGLE_ERR_ALIGN;
-  if (workspace_bytes < beagle_xattn_workspace_bytes(desc, BEAGLE_WS_BWD_SIM)) return BEAGLE_ERR_WORKSPACE;
+  const size_t need = bwd_need(d, true);
+  if (workspace_bytes < need) return BEAGLE_ERR_WORKSPACE;
   if (sim_step < 0 || d.S != d.L || d.Tq != d.Tk) return BEAGLE_ERR_SHAPE;
   hipStream_t s = (hipStream_t)hip_stream;
   (void)hipGetLastError();
-  xkv = states_in(d, xkv, workspace, beagle_xattn_workspace_bytes(desc, BEAGLE_WS_BWD_SIM), s);
+  xkv = states_in(d, xkv, workspace, need, s);
 
   xattn_bwd_sim_run(d, need_dxkv, d.bf16 && (desc->flags & BEAGLE_FLAG_WGRAD_F32), dy, xq, xkv, xpred, wq, wk, wv, wo, q_save,
                     k_save, v_save, kp_save, vp_save, o_save, lse, sim_step, dxq, dxkv, dxpred, dwq, dwk, dwv, dwo,
-                    (char*)workspace, nullptr, s);
+                    (char*)workspace, {(char*)workspace + need, workspace_bytes - need}, nullptr, s);
   return hip_status();
 }
 

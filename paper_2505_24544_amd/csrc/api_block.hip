@@ -30,6 +30,11 @@ BlockWs block_bwd_layout(const Dims& d, int64_t F) {
   return w;
 }
 
+// what the block's backward needs; simulation: with the gradient of the normalised predicted states
+size_t block_bwd_need(const Dims& d, int64_t F, bool sim) {
+  return block_bwd_layout(d, F).total + (sim ? align_up((size_t)(d.Tk * d.D) * d.esz) : 0) + bwd_need(d, sim);
+}
+
 beagle_status check_block(const beagle_xattn_desc* desc, const beagle_block_params* p, Dims* d, bool draft = false) {
   beagle_status st = check_desc(desc, draft, d);
   if (st != BEAGLE_OK) return st;
@@ -78,11 +83,8 @@ size_t beagle_xattn_block_workspace_bytes(const beagle_xattn_desc* desc, int32_t
   }
   if (check_desc(desc, false, &d) != BEAGLE_OK || ffn < 1 || ffn % (d.bf16 ? 64 : 4)) return 0;
   if (which == BEAGLE_WS_BLOCK_FWD) return WS_ALIGN + states_ws(d);
-  if (which == BEAGLE_WS_BLOCK_BWD)
-    return block_bwd_layout(d, ffn).total + beagle_xattn_workspace_bytes(desc, BEAGLE_WS_BWD);
-  if (which == BEAGLE_WS_BLOCK_BWD_SIM)   // + the gradient of the normalised predicted states
-    return block_bwd_layout(d, ffn).total + align_up((size_t)(d.Tk * d.D) * d.esz) +
-           beagle_xattn_workspace_bytes(desc, BEAGLE_WS_BWD_SIM);
+  if (which == BEAGLE_WS_BLOCK_BWD || which == BEAGLE_WS_BLOCK_BWD_SIM)
+    return block_bwd_need(d, ffn, which == BEAGLE_WS_BLOCK_BWD_SIM) + bwd_spare_bytes(d);
   return 0;
 }
 
@@ -162,7 +164,6 @@ beagle_status block_bwd_impl(const beagle_xattn_desc* desc, const beagle_block_p
     for (const void* q : more) if (q && !aligned16(q)) return BEAGLE_ERR_ALIGN;
     if (sim_step < 0 || d.S != d.L || d.Tq != d.Tk) return BEAGLE_ERR_SHAPE;
   }
-  const int ws_kind = sim ? BEAGLE_WS_BLOCK_BWD_SIM : BEAGLE_WS_BLOCK_BWD;
   const bool need_dhs = desc->flags & BEAGLE_FLAG_NEED_DXKV;
   const void* req[] = {dh, e, hs, p->wq, p->wk, p->wv, p->wo, p->w_gate, p->w_up, p->w_down,
                        sv->q, sv->k, sv->v, sv->o, sv->lse, sv->y, sv->u, sv->w, sv->m,
@@ -178,14 +179,16 @@ beagle_status block_bwd_impl(const beagle_xattn_desc* desc, const beagle_block_p
                        gr->dw_gate, gr->dw_up, gr->dw_down, gr->dg_q, gr->dg_kv, gr->dg_mlp};
   for (const void* q : all) if (q && !aligned16(q)) return BEAGLE_ERR_ALIGN;
   if (((uintptr_t)workspace) % WS_ALIGN) return BEAGLE_ERR_ALIGN;
-  if (workspace_bytes < beagle_xattn_block_workspace_bytes(desc, p->ffn, ws_kind)) return BEAGLE_ERR_WORKSPACE;
+  const size_t need = block_bwd_need(d, p->ffn, sim);
+  if (workspace_bytes < need) return BEAGLE_ERR_WORKSPACE;
+  const Spare spare = {(char*)workspace + need, workspace_bytes - need};
   hipStream_t s = (hipStream_t)hip_stream;
   (void)hipGetLastError();
   const int64_t Mq = d.Tq, Mk = d.Tk, F = p->ffn;
   const int D = (int)d.D;
   const BlockWs w = block_bwd_layout(d, F);
   char* base = (char*)workspace;
-  hs = states_in(d, hs, workspace, beagle_xattn_block_workspace_bytes(desc, p->ffn, ws_kind), s);
+  hs = states_in(d, hs, workspace, need, s);
   void* dm = base + w.dm; void* dwp = base + w.dw; void* dz = base + w.dz; void* dy = base + w.dy;
   void* dxq_n = base + w.dxq; void* dxkv_n = base + w.dxkv; float* part = (float*)(base + w.part);
 
@@ -223,10 +226,10 @@ beagle_status block_bwd_impl(const beagle_xattn_desc* desc, const beagle_block_p
     char* attn_ws = base + w.attn + align_up((size_t)(Mk * d.D) * d.esz);
     xattn_bwd_sim_run(d, need_dxkv, false, dy, xq, xkv, p->g_kv ? sv->xp_n : xpred, p->wq, p->wk, p->wv, p->wo, sv->q, sv->k,
                       sv->v, sv->kp, sv->vp, sv->o, sv->lse, sim_step, dxq_out, dxkv_out, p->g_kv ? dxp_n : gr->dxpred,
-                      gr->dwq, gr->dwk, gr->dwv, gr->dwo, attn_ws, p->g_q ? nullptr : dy, s);
+                      gr->dwq, gr->dwk, gr->dwv, gr->dwo, attn_ws, spare, p->g_q ? nullptr : dy, s);
   } else {
     xattn_bwd_run(d, need_dxkv, false, dy, xq, xkv, p->wq, p->wk, p->wv, p->wo, sv->q, sv->k, sv->v, sv->o, sv->lse,
-                  dxq_out, dxkv_out, gr->dwq, gr->dwk, gr->dwv, gr->dwo, base + w.attn, p->g_q ? nullptr : dy, s);
+                  dxq_out, dxkv_out, gr->dwq, gr->dwk, gr->dwv, gr->dwo, base + w.attn, spare, p->g_q ? nullptr : dy, s);
   }
   if (p->g_q)     // de = dy + dRMSNorm(dxq)
     launch_rmsnorm_bwd(d.bf16, dxq_n, e, p->g_q, sv->r_q, dy, gr->de, gr->dg_q, part, Mq, D, s, "bwd_norm_q");

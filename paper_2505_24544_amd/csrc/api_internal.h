@@ -28,8 +28,14 @@ struct Dims {
 
 struct BwdWs { size_t dO, dQ, dK, dV, delta, dwpart, attn, total; };   // dwpart: see split_kv_wgrad
 
+// Memory that a backward call can use but does not need: what the workspace holds past the call's need
+struct Spare { void* p; size_t bytes; };
+
 beagle_status check_desc(const beagle_xattn_desc* c, bool draft, Dims* out);
 BwdWs bwd_layout(const Dims& d);
+// what the backward needs (converted states included), and what it can use beyond that
+size_t bwd_need(const Dims& d, bool sim);
+size_t bwd_spare_bytes(const Dims& d);
 bool split_kv_wgrad(const Dims& d);
 AttnArgs attn_args(const Dims& d);
 // C[M,N] = A[M,K] B with B stored [K,N]; ... = A W^T with W stored [N,K]; ... = X^T Y with X [K,M], Y [K,N]
@@ -50,8 +56,8 @@ void xattn_fwd_run(const Dims& d, const void* xq, const void* xkv, const void* w
 void xattn_bwd_run(const Dims& d, bool need_dxkv, bool wf32, const void* dy, const void* xq, const void* xkv,
                    const void* wq, const void* wk, const void* wv, const void* wo, const void* q_save,
                    const void* k_save, const void* v_save, const void* o_save, const float* lse, void* dxq,
-                   void* dxkv, void* dwq, void* dwk, void* dwv, void* dwo, char* base, const void* dxq_res,
-                   hipStream_t s);
+                   void* dxkv, void* dwq, void* dwk, void* dwv, void* dwo, char* base, Spare spare,
+                   const void* dxq_res, hipStream_t s);
 void xattn_fwd_sim_run(const Dims& d, const void* xq, const void* xkv, const void* xpred, const void* wq, const void* wk,
                        const void* wv, const void* wo, int32_t sim_step, void* y, float* lse, void* q_save, void* k_save,
                        void* v_save, void* kp_save, void* vp_save, void* o_save, const void* y_res, hipStream_t s);
@@ -59,8 +65,8 @@ void xattn_bwd_sim_run(const Dims& d, bool need_dxkv, bool wf32, const void* dy,
                        const void* xpred, const void* wq, const void* wk, const void* wv, const void* wo,
                        const void* q_save, const void* k_save, const void* v_save, const void* kp_save,
                        const void* vp_save, const void* o_save, const float* lse, int32_t sim_step, void* dxq, void* dxkv,
-                       void* dxpred, void* dwq, void* dwk, void* dwv, void* dwo, char* base, const void* dxq_res,
-                       hipStream_t s);
+                       void* dxpred, void* dwq, void* dwk, void* dwv, void* dwo, char* base, Spare spare,
+                       const void* dxq_res, hipStream_t s);
 // packed_norm_eps: NaN = wk, wv in their stored layout; otherwise they are packed for strip_gemm_kernel, with (>= 0) or
 // without (< 0) the row factor of an RMSNorm in front of them (its gain folded into the matrices)
 void kv_append_run(const Dims& d, const void* x_new, const void* wk, const void* wv, void* k_cache, void* v_cache,

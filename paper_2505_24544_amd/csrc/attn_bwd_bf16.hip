@@ -527,30 +527,42 @@ __global__ __launch_bounds__(256) void sum_dkv_kernel(AttnArgs a, dkv::Split sp)
 // half of the queries on average, so n chunks make tiles (n + 1) / 2 of them.  Measured with 32 heads in 8 groups, us, one
 // workgroup per tile -> n chunks + their sum: 300 positions (24 tiles) 42 -> 23, 777 (56) 93 -> 38, 1300 (88) 144 -> 60, 2048
 // (128) 222 -> 106, 4096 (256) 448 -> 332.  Beyond that the shares cost what the balance gains (5546: 636 -> 614 at best, 8192:
-// 574 -> 608), and so they do where the chain is short (777 positions, 32 groups: 34 -> 39).
-static dkv::Split dkv_split(const AttnArgs& a) {
-  dkv::Split sp = {nullptr, 1, 0x7fffffff};
-  const int64_t tiles = (int64_t)((a.L + dkv::BJ - 1) / dkv::BJ) * a.G * a.B;
-  const int64_t longest = (int64_t)((a.S + dkv::BQ - 1) / dkv::BQ) * (a.H / a.G);
-  if (tiles > 256) return sp;
+// 574 -> 608), and so they do where the chain is short (777 positions, 32 groups: 34 -> 39).  Fewer where the caller's
+// workspace has no room for as many shares, down to none.
+static int64_t dkv_chunks(int64_t tiles, int64_t longest, int64_t most) {
+  if (tiles > 256) return 1;
   int64_t n = tiles > 128 ? 2 : (448 + tiles / 2) / tiles - 1;
   if (n > 16) n = 16;
+  if (n > most) n = most;
+  return n > 1 && longest - (longest + n - 1) / n >= 10 ? n : 1;
+}
+static int64_t dkv_tiles(const AttnArgs& a) { return (int64_t)((a.L + dkv::BJ - 1) / dkv::BJ) * a.G * a.B; }
+static int64_t dkv_longest(const AttnArgs& a) { return (int64_t)((a.S + dkv::BQ - 1) / dkv::BQ) * (a.H / a.G); }
+constexpr size_t SHARE_BYTES = dkv::SLOT * sizeof(float);
+static dkv::Split dkv_split(const AttnArgs& a, void* shares, size_t share_bytes) {
+  const int64_t tiles = dkv_tiles(a), longest = dkv_longest(a);
+  const int64_t n = dkv_chunks(tiles, longest, (int64_t)(share_bytes / (tiles * SHARE_BYTES)));
+  if (n == 1) return {nullptr, 1, 0x7fffffff};
   const int64_t per = (longest + n - 1) / n;
-  if (longest - per < 10) return sp;
-  sp.chunks = (int32_t)((longest + per - 1) / per);
-  sp.per_chunk = (int32_t)per;
-  return sp;
+  return {(float*)shares, (int32_t)((longest + per - 1) / per), (int32_t)per};
 }
 
-// workspace: the pre-scaled LSE array, as large as delta, and the shares of split key tiles
-static size_t nlse_bytes(const AttnArgs& a) { return ((size_t)a.B * a.H * a.S * sizeof(float) + 255) / 256 * 256; }
-size_t attn_bwd_bf16_ws_bytes(const AttnArgs& a) {
-  const dkv::Split sp = dkv_split(a);
-  const size_t tiles = (size_t)((a.L + dkv::BJ - 1) / dkv::BJ) * a.G * a.B;
-  return nlse_bytes(a) + (sp.chunks > 1 ? tiles * sp.chunks * dkv::SLOT * sizeof(float) : 0);
+// workspace: the pre-scaled LSE array, as large as delta
+size_t attn_bwd_bf16_ws_bytes(const AttnArgs& a) { return (size_t)a.B * a.H * a.S * sizeof(float); }
+// ... and what the shares of split key tiles take at most, for this problem or any that is no larger in batch and lengths
+// (of equal lengths if this one's are): a program that sizes its workspace by its largest batch has the smaller ones split too
+size_t attn_bwd_bf16_share_bytes(const AttnArgs& a) {
+  const int64_t ltiles = (a.L + dkv::BJ - 1) / dkv::BJ, rep = a.H / a.G, all = dkv_longest(a);
+  int64_t n = 0;
+  for (int64_t u = 1; u * a.G <= 256 && u <= ltiles * a.B; ++u) {      // key tiles per group
+    const int64_t own = (u < ltiles ? u : ltiles) * (dkv::BJ / dkv::BQ) * rep;
+    const int64_t c = dkv_chunks(u * a.G, a.S == a.L && own < all ? own : all, 16);
+    if (c > 1 && u * a.G * c > n) n = u * a.G * c;
+  }
+  return (size_t)n * SHARE_BYTES;
 }
 
-void launch_attn_bwd_bf16(const AttnArgs& args, void* ws, hipStream_t s) {
+void launch_attn_bwd_bf16(const AttnArgs& args, void* ws, void* shares, size_t share_bytes, hipStream_t s) {
   AttnArgs a = args;
   a.nlse2 = (float*)ws;
   {
@@ -558,9 +570,8 @@ void launch_attn_bwd_bf16(const AttnArgs& args, void* ws, hipStream_t s) {
     if (attn_key_halves(a)) hipLaunchKernelGGL(attn_bwd_dq_bf16_kernel<2>, dim3((a.S + 63) / 64 * a.H * a.B), dim3(256), 0, s, a);
     else hipLaunchKernelGGL(attn_bwd_dq_bf16_kernel<1>, dim3((a.S + 127) / 128 * a.H * a.B), dim3(256), 0, s, a);
   }
-  dkv::Split sp = dkv_split(a);
-  sp.part = (float*)((char*)ws + nlse_bytes(a));
-  const int tiles = ((a.L + dkv::BJ - 1) / dkv::BJ) * a.G * a.B;
+  const dkv::Split sp = dkv_split(a, shares, share_bytes);
+  const int tiles = (int)dkv_tiles(a);
   {
     ProfScope ps("attn_bwd_dkv_bf16", s);
     if (sp.chunks > 1) hipLaunchKernelGGL(attn_bwd_dkv_bf16_kernel<true>, dim3(tiles * sp.chunks), dim3(256), 0, s, a, sp);

@@ -216,8 +216,11 @@ void launch_sim_band_bwd_bf16(const SimArgs& s, hipStream_t st);
 void launch_attn_fwd_f32(const AttnArgs& a, hipStream_t s);
 void launch_attn_bwd_f32(const AttnArgs& a, hipStream_t s);
 void launch_attn_fwd_bf16(const AttnArgs& a, hipStream_t s);
-void launch_attn_bwd_bf16(const AttnArgs& a, void* ws, hipStream_t s);
+// ws: attn_bwd_bf16_ws_bytes; shares: any number of bytes, of which up to attn_bwd_bf16_share_bytes make short grouped
+// batches faster
+void launch_attn_bwd_bf16(const AttnArgs& a, void* ws, void* shares, size_t share_bytes, hipStream_t s);
 size_t attn_bwd_bf16_ws_bytes(const AttnArgs& a);
+size_t attn_bwd_bf16_share_bytes(const AttnArgs& a);
 
 // ---- decode (bf16): split-KV attention of M queries over L cache rows ------
 struct DecodeArgs {
