@@ -1340,7 +1340,7 @@ void launch_clock_probe(uint64_t* out, hipStream_t s) {
 // ---- host side ----------------------------------------------------------------
 namespace {
 struct DecLayout {
-  int KSq, KSo, R, range, hs_log2, row_log2;
+  int KSq, KSo, R, range, hs_log2, row_log2, Mpad;
   size_t qpart, opart, mlpart, o, ypart, ropetab, total;
 };
 size_t up256(size_t v) { return (v + 255) / 256 * 256; }
@@ -1359,6 +1359,8 @@ DecLayout dec_layout(int M, int L, int H, int G, int d, int D, bool packed) {
   };
   w.hs_log2 = 0; w.row_log2 = 6;
   w.R = split(0, w.range);
+  w.Mpad = (Mp + 31) / 32 * 32;                              // rows of a (head, range) partial
+  const size_t rows = (size_t)H * w.R * w.Mpad;
   // Grouped queries: heads that share a K/V head share a workgroup too (up to 32 rows in all, padded to a power of two per
   // head), so the cache rows are fetched once for them and a head's keys split over as many more ranges.  The fewest heads
   // that give the shortest ranges; without a step less nothing is gained (6 queries over 619 keys, packed: 25.5 us as
@@ -1373,13 +1375,15 @@ DecLayout dec_layout(int M, int L, int H, int G, int d, int D, bool packed) {
     int range;
     const int R = split(hs, range);
     if (range > bound) continue;
-    w.hs_log2 = hs; w.row_log2 = row_log2; w.range = range; w.R = R;
+    // 2^hs heads have at most 2^hs times the ranges (both divide the same steps, rounded up), so 32 / 2^hs rows per partial, of
+    // which 2^row_log2 are used, fit the space of the heads alone: grouping takes no more workspace
+    w.hs_log2 = hs; w.row_log2 = row_log2; w.range = range; w.R = R; w.Mpad = 32 >> hs;
     bound = range - dec::KSTEP;
   }
   size_t o = 0;
   w.qpart = o; o += up256((size_t)w.KSq * Mp * HDt * 4);
-  w.opart = o; o += up256((size_t)H * w.R * Mp * tiles::HD * 4);
-  w.mlpart = o; o += up256((size_t)H * w.R * Mp * 2 * 4);
+  w.opart = o; o += up256(rows * tiles::HD * 4);
+  w.mlpart = o; o += up256(rows * 2 * 4);
   w.o = o; o += up256((size_t)Mp * HDt * 2);
   w.ypart = o; o += up256((size_t)w.KSo * Mp * D * 4);
   w.ropetab = o; o += up256((size_t)M * 64 * sizeof(float2));
@@ -1415,12 +1419,12 @@ void launch_strip_gemm(const bf16_t* a, const bf16_t* wt, const bf16_t* wt2, voi
 }
 
 size_t decode_bf16_ws_bytes(int32_t M, int32_t L, int32_t H, int32_t G, int32_t d, int32_t D) {
-  return std::max(dec_layout(M, L, H, G, d, D, false).total, dec_layout(M, L, H, G, d, D, true).total);
+  return dec_layout(M, L, H, G, d, D, false).total;          // (packed or not: the same)
 }
 
 static void launch_combine(int M, const DecodeArgs& a, const DecLayout& w, const float* opart, const float* mlpart, bf16_t* o,
                            float* lse, int chunked_rows, hipStream_t s) {
-#define COMBINE_ARGS opart, mlpart, o, lse, a.M, M, a.H, w.R, a.scale, chunked_rows
+#define COMBINE_ARGS opart, mlpart, o, lse, a.M, w.Mpad, a.H, w.R, a.scale, chunked_rows
   if (w.R <= 8) hipLaunchKernelGGL(decode_combine_kernel<8>, dim3(M, a.H), dim3(128), 0, s, COMBINE_ARGS);
   else if (w.R <= 16) hipLaunchKernelGGL(decode_combine_kernel<16>, dim3(M, a.H), dim3(128), 0, s, COMBINE_ARGS);
   else hipLaunchKernelGGL(decode_combine_kernel<32>, dim3(M, a.H), dim3(128), 0, s, COMBINE_ARGS);
@@ -1456,7 +1460,7 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
       DecAttnArgs t;
       t.qpart = qpart; t.KSq = a.wq_pk ? 1 : w.KSq; t.kc = (const bf16_t*)a.kc; t.vc = (const bf16_t*)a.vc;
       t.opart = opart; t.mlpart = mlpart;
-      t.M = Mp; t.Mpad = Mp; t.hs_log2 = w.hs_log2; t.row_log2 = w.row_log2; t.L = a.L; t.H = a.H; t.G = a.G; t.R = w.R; t.range = w.range;
+      t.M = Mp; t.Mpad = w.Mpad; t.hs_log2 = w.hs_log2; t.row_log2 = w.row_log2; t.L = a.L; t.H = a.H; t.G = a.G; t.R = w.R; t.range = w.range;
       t.scale = a.scale;
       t.tree = a.tree ? a.tree + (int64_t)m0 * a.tree_words : nullptr; t.n_true = a.n_true; t.tree_words = a.tree_words;
       t.rope_tab = rope.tab;
@@ -1469,7 +1473,7 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
     if (a.wo_pk) {
       // out-projection on the transposed weights: no k split, so no partial sums and no launch to add them
       CombineArgs cb;
-      cb.opart = opart; cb.mlpart = mlpart; cb.lse = a.lse + m0; cb.lse_stride = a.M; cb.Mpad = Mp; cb.R = w.R;
+      cb.opart = opart; cb.mlpart = mlpart; cb.lse = a.lse + m0; cb.lse_stride = a.M; cb.Mpad = w.Mpad; cb.R = w.R;
       cb.scale = a.scale;
       bf16_t* yo = (bf16_t*)a.y + (int64_t)m0 * a.D;
       const bf16_t* yr = a.y_res ? (const bf16_t*)a.y_res + (int64_t)m0 * a.D : (const bf16_t*)nullptr;
@@ -1489,7 +1493,7 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
     if (Mp <= COMB_MAXM && w.R <= COMB_MAXR && HDt % SG_K == 0) {
       // few queries: the merge of the key ranges rides in the projection's prologue
       CombineArgs cb;
-      cb.opart = opart; cb.mlpart = mlpart; cb.lse = a.lse + m0; cb.lse_stride = a.M; cb.Mpad = Mp; cb.R = w.R;
+      cb.opart = opart; cb.mlpart = mlpart; cb.lse = a.lse + m0; cb.lse_stride = a.M; cb.Mpad = w.Mpad; cb.R = w.R;
       cb.scale = a.scale;
       ProfScope ps("draft_proj_out", s);
       hipLaunchKernelGGL(skinny_gemm_kernel<true>, dim3(a.D / SG_N, w.KSo), dim3(256), 0, s, (const bf16_t*)nullptr,

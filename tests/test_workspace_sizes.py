@@ -52,3 +52,24 @@ def test_backward_needs_no_more_than_its_tensors(batch, seq, H, G, D):
     assert not _accepts(d, own - 1) and _accepts(d, reported)
     assert _accepts(d, own) or _accepts(d, own + halves)
     assert own <= reported <= own + halves + (64 << 20)
+
+
+def _draft(M, L, H=32, G=8, D=4096):
+    return bx.make_desc(batch=1, seq_q=M, seq_kv=L, hidden=D, n_q_heads=H, n_kv_heads=G, head_dim=128)
+
+
+@pytest.mark.parametrize("H,G,D", [(32, 8, 4096), (32, 32, 4096), (64, 8, 1024), (40, 40, 5120), (24, 4, 128)])
+@pytest.mark.parametrize("L", [128, 619, 1024, 1300, 4096, 9000])
+def test_widest_draft_step_serves_the_narrower_ones(L, H, G, D):
+    size = [bx.beagle_xattn_workspace_bytes(_draft(M, L, H, G, D), bx.BEAGLE_WS_DRAFT) for M in range(1, 130)]
+    assert all(a <= b for a, b in zip(size, size[1:]))
+    # queries in k slices of 512, partial rows padded to 32, merged rows, output slices, rotary table: heads that share a
+    # workgroup take no more than heads alone
+    steps = (L + 127) // 128
+    rng = -(-steps // min(256 // H, steps))
+    for M in (1, 6, 8, 9, 16, 33, 64, 129):
+        m = min(M, 64)
+        rows = H * -(-steps // rng) * ((m + 31) // 32 * 32)
+        need = (up(-(-D // 512) * m * H * 512) + up(rows * 512) + up(rows * 8) + up(m * H * 256) + up(-(-H * 128 // 512) * m * D * 4) +
+                up(M * 512))
+        assert size[M - 1] == need
