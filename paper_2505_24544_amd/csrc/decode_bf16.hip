@@ -399,17 +399,22 @@ constexpr int ST_MAXM = 16;              // rows per launch
 }  // namespace dec
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
-template <int MODE, bool ROWS16, int WAVES>
+// TABLE (MODE 0): the launch also writes the rotary angles.  Launches without it, as those of modes 1 and 2, neither fetch the
+// rotary arguments nor carry the code: with both in every launch a strip launch took 0.1 - 0.25 us longer (packed steps, us: 6
+// queries over 3000 rows 31.8 -> 31.1, 12 over 2000 30.4 -> 29.8, 16 over 700 at 5120 channels 52.7 -> 52.0).
+template <int MODE, bool ROWS16, int WAVES, bool TABLE = false>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const bf16_t* __restrict__ a, const bf16_t* __restrict__ Wt,
                                                             const bf16_t* __restrict__ Wt2, void* __restrict__ yout,
                                                             bf16_t* __restrict__ yout2, const bf16_t* __restrict__ res,
                                                             int M, int N, int K, CombineArgs cb, int out_f32,
                                                             float norm_eps, RopeRows rope) {
   using namespace dec;
-  asm volatile("" :: "s"(a), "s"(Wt), "s"(Wt2), "s"(yout), "s"(yout2), "s"(res), "s"(M), "s"(N), "s"(K), "s"(out_f32), "s"(norm_eps),
-               "s"(cb.opart), "s"(cb.mlpart), "s"(cb.lse), "s"(cb.lse_stride), "s"(cb.Mpad), "s"(cb.R), "s"(cb.scale), "s"(rope.pos),
-               "s"(rope.pos0), "s"(rope.l2base), "s"(rope.on));
-  if (MODE == 0 && (int)blockIdx.x == N / ST_N) {           // (one more workgroup when there is a table to write)
+#define STRIP_AT_HAND "s"(a), "s"(Wt), "s"(Wt2), "s"(yout), "s"(yout2), "s"(res), "s"(M), "s"(N), "s"(K), "s"(out_f32), "s"(norm_eps), \
+    "s"(cb.opart), "s"(cb.mlpart), "s"(cb.lse), "s"(cb.lse_stride), "s"(cb.Mpad), "s"(cb.R), "s"(cb.scale)
+  if constexpr (MODE == 3) asm volatile("" :: STRIP_AT_HAND, "s"(rope.pos), "s"(rope.pos0), "s"(rope.l2base), "s"(rope.on));
+  else asm volatile("" :: STRIP_AT_HAND);
+#undef STRIP_AT_HAND
+  if (TABLE && (int)blockIdx.x == N / ST_N) {               // (one more workgroup when there is a table to write)
     rope_table(rope, M, threadIdx.x, 64 * WAVES);
     return;
   }
@@ -455,7 +460,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
   auto angles = [&]() {
     if (turns) rot[tid >> 4][tid & 15] = rope_cos_sin(tpos, 16 * ((blockIdx.x >> 1) & 3) + (tid & 15), HD, rope.l2base);
   };
-  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (MODE == 3) __builtin_amdgcn_sched_barrier(0);
   if (nst > 0) {                        // (a wave without a macro-step, K < 1024, only adds zeros below)
   // ---- activations.  Load q of chunk c covers rows 4 g + kg of step c ST_CH + i, (i, g) = divmod(q, LPS):
   // lane (kg, nl) reads chunk nl ^ row of its row and parks it at chunk nl, i.e. at lane * 16 of the 1 KB piece.
@@ -526,8 +531,10 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
 #pragma unroll
   for (int u = 0; u < ST_RING; ++u) load_b(u, u);
   __builtin_amdgcn_sched_barrier(0);
-  angles();                                         // while the first requests travel
-  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (MODE == 3) {
+    angles();                                       // while the first requests travel
+    __builtin_amdgcn_sched_barrier(0);
+  }
 
   if constexpr (MODE == 1) {
     const int hl = lane >> 3;
@@ -596,7 +603,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
       i0 += ST_ROUND;
     } while (i0 < nst);
   }
-  } else {
+  } else if constexpr (MODE == 3) {
     angles();
   }
 
@@ -705,8 +712,10 @@ struct DecAttnArgs {
 
 typedef lds_u32x2_t u32x2_t;
 
-// One workgroup per (2^hs_log2 query heads of one K/V head, key range): grid (H >> hs_log2, R).  Row i of its 32 NQB rows
-// is query i % 2^row_log2 of head i >> row_log2 ("query" below); rows whose query is past M read zeros and are not stored.
+// One workgroup per (query head, key range): grid (H, R).  GROUPED: per (2^hs_log2 query heads of one K/V head, key range), grid
+// (H >> hs_log2, R); row i of its 32 rows is query i % 2^row_log2 of head i >> row_log2 ("query" below), and rows whose query is
+// past M read zeros and are not stored.  A kernel of its own: with the rows' arithmetic in it, the one for heads alone took 0.3 -
+// 0.5 us longer (32 queries over 2000 rows 12.7 -> 13.1).
 // NQB = 1 (up to 32 queries): the four waves split each 128-key step by rows, 32 keys each.  A wave requests, reads
 // and refills only its own 32 rows of the two stages, so the step loop has no barrier; a stage half (the wave's K
 // rows, then its V rows) is refilled for the step after next as soon as its fragments sit in registers, i.e. BEFORE
@@ -719,7 +728,7 @@ typedef lds_u32x2_t u32x2_t;
 // refill issued only behind it -- 4 400 cycles of arithmetic and 2 700 of request issue per step, one after the other.)
 // QS: k-slices of q that are requested at once: one on packed weights, where q comes as a single slice (asked for as eight,
 // seven of them past the buffer's end, they took the summing wave another 28 requests), else eight; more in further trips.
-template <int NQB, int QS>
+template <int NQB, int QS, bool GROUPED>
 __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
   using namespace dec;
   // two stages of one K and one V step tile each: tile t (0: K, 1: V) of stage i at (2 t + i) * TILE, so that the
@@ -736,14 +745,17 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
   ml_t& s_mm = *(ml_t*)((float*)qbuf + 4 * NQB * 3 * 32);               // merged max, sum per block
   static_assert((4 * NQB * 3 * 32 + NQB * 2 * 32) * sizeof(float) <= sizeof(qbuf), "merge arrays must fit in the q planes");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hf = lane >> 5, ql = lane & 31;
-  const int h = blockIdx.x << a.hs_log2, r = blockIdx.y;     // first head
-  const int row_mask = (1 << a.row_log2) - 1;
-  const int mtot = a.hs_log2 ? 1 << (a.hs_log2 + a.row_log2) : a.M;   // the workgroup's rows
+  const int h = GROUPED ? blockIdx.x << a.hs_log2 : blockIdx.x, r = blockIdx.y;      // (first) head
+  const int mtot = GROUPED ? 1 << (a.hs_log2 + a.row_log2) : a.M;                    // the workgroup's rows
+  auto row_query = [&](int row) { return GROUPED ? row & ((1 << a.row_log2) - 1) : row; };
+  auto row_head = [&](int row) { return GROUPED ? row >> a.row_log2 : 0; };          // past the first one
   // every field at hand after one trip to the constant cache (the compiler otherwise fetches them where they are first
   // used, two dependent trips before the first K/V request); no division for the common one head per group
-  asm volatile("" :: "s"(a.qpart), "s"(a.KSq), "s"(a.kc), "s"(a.vc), "s"(a.opart), "s"(a.mlpart), "s"(a.M), "s"(a.Mpad), "s"(a.L),
-               "s"(a.H), "s"(a.G), "s"(a.R), "s"(a.range), "s"(a.hs_log2), "s"(a.row_log2), "s"(a.scale), "s"(a.tree), "s"(a.n_true),
-               "s"(a.tree_words), "s"(a.rope_tab));
+#define ATTN_AT_HAND "s"(a.qpart), "s"(a.KSq), "s"(a.kc), "s"(a.vc), "s"(a.opart), "s"(a.mlpart), "s"(a.M), "s"(a.Mpad), "s"(a.L), \
+    "s"(a.H), "s"(a.G), "s"(a.R), "s"(a.range), "s"(a.scale), "s"(a.tree), "s"(a.n_true), "s"(a.tree_words), "s"(a.rope_tab)
+  if constexpr (GROUPED) asm volatile("" :: ATTN_AT_HAND, "s"(a.hs_log2), "s"(a.row_log2));
+  else asm volatile("" :: ATTN_AT_HAND);
+#undef ATTN_AT_HAND
   const int g = a.H == a.G ? h : h / (a.H / a.G);
   const int HDt = a.H * HD;
   const int j_begin = r * a.range, j_end = min(j_begin + a.range, a.L);
@@ -798,8 +810,8 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int idx = tid + 64 * qwaves * i, row = 32 * qb + (idx >> 5), c4 = idx & 31;
-      const int m = row & row_mask, hh = h + (row >> a.row_log2);
-      const bool there = wave < qwaves && (idx >> 5) < mrows && m < a.M;
+      const int m = row_query(row), hh = h + row_head(row);
+      const bool there = wave < qwaves && (idx >> 5) < mrows && (!GROUPED || m < a.M);
 #pragma unroll
       for (int k = 0; k < QS; ++k) {
         const int off = (int)((((int64_t)(k0 + k) * a.M + m) * HDt + hh * HD + 4 * c4) * 4);
@@ -827,7 +839,7 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
     if (a.rope_tab) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int idx = tid + 64 * qwaves * i, m = min((32 * qb + (idx >> 5)) & row_mask, a.M - 1), c4 = idx & 15;
+        const int idx = tid + 64 * qwaves * i, m = min(row_query(32 * qb + (idx >> 5)), a.M - 1), c4 = idx & 15;
         const float4* tp = (const float4*)(a.rope_tab + (int64_t)m * 64 + 4 * c4);
         const float4 cs0 = tp[0], cs1 = tp[1];                 // (cos, sin) of pairs 4 c4 .. 4 c4 + 3
         const bool upper = (tid & 16) != 0;                    // channels 64 .. 127: x2 of the pair
@@ -1111,9 +1123,9 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
           // drafted rows: bit i of `vis` says whether this lane's query sees key jw + i (true rows: yes)
           const int off = jw - a.n_true;                       // tree bit of key jw; negative inside the true rows
           const int w0 = off >> 5, sh = off & 31;              // floor division: -1 for the straddling block
-          const int m = (32 * b + ql) & row_mask;
+          const int m = row_query(32 * b + ql);
           const uint32_t* row = a.tree + (int64_t)m * a.tree_words;
-          const bool real = 32 * b + ql < mtot && m < a.M;
+          const bool real = 32 * b + ql < mtot && (!GROUPED || m < a.M);
           const uint32_t lo = w0 < 0 ? 0xffffffffu : (real && w0 < a.tree_words ? row[w0] : 0u);
           const uint32_t hi = real && w0 + 1 < a.tree_words ? row[w0 + 1] : 0u;
           const uint32_t vis = (uint32_t)((((uint64_t)hi << 32) | lo) >> sh);
@@ -1229,10 +1241,12 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
     s_mm[qb][0][q] = mm; s_mm[qb][1][q] = lt;
   }
   __syncthreads();
+  const int64_t pbase = ((int64_t)h * a.R + r) * a.Mpad;
+  const int hstep = a.R * a.Mpad;                              // from one head's partials to the next one's
   for (int i = tid; i < mtot * 32; i += 256) {                 // padding rows are never read
-    const int c4 = i & 31, qq = i >> 5, qb = qq >> 5, q = qq & 31, m = qq & row_mask;
-    if (m >= a.M) continue;
-    const int64_t out = ((int64_t)(h + (qq >> a.row_log2)) * a.R + r) * a.Mpad + m;
+    const int c4 = i & 31, qq = i >> 5, qb = qq >> 5, q = qq & 31, m = row_query(qq);
+    if (GROUPED && m >= a.M) continue;
+    const int64_t out = pbase + row_head(qq) * hstep + m;
     const float* ob = (const float*)kvt + qb * 4 * 32 * HD;
     float4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1340,7 +1354,7 @@ void launch_clock_probe(uint64_t* out, hipStream_t s) {
 // ---- host side ----------------------------------------------------------------
 namespace {
 struct DecLayout {
-  int KSq, KSo, R, range, hs_log2, row_log2, Mpad;
+  int KSq, KSo, R, range, hs_log2, row_log2;
   size_t qpart, opart, mlpart, o, ypart, ropetab, total;
 };
 size_t up256(size_t v) { return (v + 255) / 256 * 256; }
@@ -1357,10 +1371,11 @@ DecLayout dec_layout(int M, int L, int H, int G, int d, int D, bool packed) {
     range = ((L + R - 1) / R + dec::KSTEP - 1) / dec::KSTEP * dec::KSTEP;
     return (L + range - 1) / range;
   };
-  w.hs_log2 = 0; w.row_log2 = 6;
+  w.hs_log2 = 0; w.row_log2 = 0;                             // heads alone
   w.R = split(0, w.range);
-  w.Mpad = (Mp + 31) / 32 * 32;                              // rows of a (head, range) partial
-  const size_t rows = (size_t)H * w.R * w.Mpad;
+  // Room for the partials: 32 or 64 rows per (head, range), of which Mp are used.  2^hs heads that share a workgroup have at most
+  // 2^hs times the ranges (both divide the same steps, rounded up) of up to 32 / 2^hs rows: grouping takes no more workspace.
+  const size_t rows = (size_t)H * w.R * ((Mp + 31) / 32 * 32);
   // Grouped queries: heads that share a K/V head share a workgroup too (up to 32 rows in all, padded to a power of two per
   // head), so the cache rows are fetched once for them and a head's keys split over as many more ranges.  The fewest heads
   // that give the shortest ranges; without a step less nothing is gained (6 queries over 619 keys, packed: 25.5 us as
@@ -1375,9 +1390,7 @@ DecLayout dec_layout(int M, int L, int H, int G, int d, int D, bool packed) {
     int range;
     const int R = split(hs, range);
     if (range > bound) continue;
-    // 2^hs heads have at most 2^hs times the ranges (both divide the same steps, rounded up), so 32 / 2^hs rows per partial, of
-    // which 2^row_log2 are used, fit the space of the heads alone: grouping takes no more workspace
-    w.hs_log2 = hs; w.row_log2 = row_log2; w.range = range; w.R = R; w.Mpad = 32 >> hs;
+    w.hs_log2 = hs; w.row_log2 = row_log2; w.range = range; w.R = R;
     bound = range - dec::KSTEP;
   }
   size_t o = 0;
@@ -1413,6 +1426,8 @@ void launch_strip_gemm(const bf16_t* a, const bf16_t* wt, const bf16_t* wt2, voi
   else if (wt2 && y2) hipLaunchKernelGGL((strip_gemm_kernel<3, true, 8>), grid, dim3(512), 0, s, STRIP_ARGS);
   else if (wt2 && M <= 8) hipLaunchKernelGGL((strip_gemm_kernel<2, false, 4>), grid, dim3(256), 0, s, STRIP_ARGS);
   else if (wt2) hipLaunchKernelGGL((strip_gemm_kernel<2, true, 4>), grid, dim3(256), 0, s, STRIP_ARGS);
+  else if (rope.tab && M <= 8) hipLaunchKernelGGL((strip_gemm_kernel<0, false, 8, true>), grid, dim3(512), 0, s, STRIP_ARGS);
+  else if (rope.tab) hipLaunchKernelGGL((strip_gemm_kernel<0, true, 8, true>), grid, dim3(512), 0, s, STRIP_ARGS);
   else if (M <= 8) hipLaunchKernelGGL((strip_gemm_kernel<0, false, 8>), grid, dim3(512), 0, s, STRIP_ARGS);
   else hipLaunchKernelGGL((strip_gemm_kernel<0, true, 8>), grid, dim3(512), 0, s, STRIP_ARGS);
 #undef STRIP_ARGS
@@ -1424,7 +1439,7 @@ size_t decode_bf16_ws_bytes(int32_t M, int32_t L, int32_t H, int32_t G, int32_t 
 
 static void launch_combine(int M, const DecodeArgs& a, const DecLayout& w, const float* opart, const float* mlpart, bf16_t* o,
                            float* lse, int chunked_rows, hipStream_t s) {
-#define COMBINE_ARGS opart, mlpart, o, lse, a.M, w.Mpad, a.H, w.R, a.scale, chunked_rows
+#define COMBINE_ARGS opart, mlpart, o, lse, a.M, M, a.H, w.R, a.scale, chunked_rows
   if (w.R <= 8) hipLaunchKernelGGL(decode_combine_kernel<8>, dim3(M, a.H), dim3(128), 0, s, COMBINE_ARGS);
   else if (w.R <= 16) hipLaunchKernelGGL(decode_combine_kernel<16>, dim3(M, a.H), dim3(128), 0, s, COMBINE_ARGS);
   else hipLaunchKernelGGL(decode_combine_kernel<32>, dim3(M, a.H), dim3(128), 0, s, COMBINE_ARGS);
@@ -1460,20 +1475,23 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
       DecAttnArgs t;
       t.qpart = qpart; t.KSq = a.wq_pk ? 1 : w.KSq; t.kc = (const bf16_t*)a.kc; t.vc = (const bf16_t*)a.vc;
       t.opart = opart; t.mlpart = mlpart;
-      t.M = Mp; t.Mpad = w.Mpad; t.hs_log2 = w.hs_log2; t.row_log2 = w.row_log2; t.L = a.L; t.H = a.H; t.G = a.G; t.R = w.R; t.range = w.range;
+      t.M = Mp; t.Mpad = Mp; t.hs_log2 = w.hs_log2; t.row_log2 = w.row_log2; t.L = a.L; t.H = a.H; t.G = a.G; t.R = w.R; t.range = w.range;
       t.scale = a.scale;
       t.tree = a.tree ? a.tree + (int64_t)m0 * a.tree_words : nullptr; t.n_true = a.n_true; t.tree_words = a.tree_words;
       t.rope_tab = rope.tab;
       ProfScope ps("draft_attn", s);
       const dim3 grid(a.H >> w.hs_log2, w.R), wg(256);
-      if (Mp > 32) hipLaunchKernelGGL((decode_attn_kernel<2, 8>), grid, wg, 0, s, t);
-      else if (t.KSq == 1) hipLaunchKernelGGL((decode_attn_kernel<1, 1>), grid, wg, 0, s, t);
-      else hipLaunchKernelGGL((decode_attn_kernel<1, 8>), grid, wg, 0, s, t);
+      const bool grouped = w.hs_log2 > 0;                    // (up to 32 rows)
+      if (Mp > 32) hipLaunchKernelGGL((decode_attn_kernel<2, 8, false>), grid, wg, 0, s, t);
+      else if (t.KSq == 1 && grouped) hipLaunchKernelGGL((decode_attn_kernel<1, 1, true>), grid, wg, 0, s, t);
+      else if (t.KSq == 1) hipLaunchKernelGGL((decode_attn_kernel<1, 1, false>), grid, wg, 0, s, t);
+      else if (grouped) hipLaunchKernelGGL((decode_attn_kernel<1, 8, true>), grid, wg, 0, s, t);
+      else hipLaunchKernelGGL((decode_attn_kernel<1, 8, false>), grid, wg, 0, s, t);
     }
     if (a.wo_pk) {
       // out-projection on the transposed weights: no k split, so no partial sums and no launch to add them
       CombineArgs cb;
-      cb.opart = opart; cb.mlpart = mlpart; cb.lse = a.lse + m0; cb.lse_stride = a.M; cb.Mpad = w.Mpad; cb.R = w.R;
+      cb.opart = opart; cb.mlpart = mlpart; cb.lse = a.lse + m0; cb.lse_stride = a.M; cb.Mpad = Mp; cb.R = w.R;
       cb.scale = a.scale;
       bf16_t* yo = (bf16_t*)a.y + (int64_t)m0 * a.D;
       const bf16_t* yr = a.y_res ? (const bf16_t*)a.y_res + (int64_t)m0 * a.D : (const bf16_t*)nullptr;
@@ -1493,7 +1511,7 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
     if (Mp <= COMB_MAXM && w.R <= COMB_MAXR && HDt % SG_K == 0) {
       // few queries: the merge of the key ranges rides in the projection's prologue
       CombineArgs cb;
-      cb.opart = opart; cb.mlpart = mlpart; cb.lse = a.lse + m0; cb.lse_stride = a.M; cb.Mpad = w.Mpad; cb.R = w.R;
+      cb.opart = opart; cb.mlpart = mlpart; cb.lse = a.lse + m0; cb.lse_stride = a.M; cb.Mpad = Mp; cb.R = w.R;
       cb.scale = a.scale;
       ProfScope ps("draft_proj_out", s);
       hipLaunchKernelGGL(skinny_gemm_kernel<true>, dim3(a.D / SG_N, w.KSo), dim3(256), 0, s, (const bf16_t*)nullptr,
