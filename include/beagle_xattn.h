@@ -145,10 +145,10 @@ typedef struct {
 } beagle_xattn_desc;
 
 /* Bytes of device workspace for the given entry point and `desc` (`which` is
- * BEAGLE_WS_*).  Returns 0 for an invalid descriptor.  The bytes for one
- * problem serve every problem of the same widths that is not larger in batch
- * and lengths.  The backward entry points run on less: part of what is
- * reported for grouped-query batches (up to 64 MiB) only lets several
+ * BEAGLE_WS_*).  Returns 0 for an invalid descriptor.
+ * Backward entry points: the bytes for one problem serve every problem of the
+ * same widths that is not larger in batch and lengths.  They also run on less:
+ * for grouped-query batches up to 64 MiB of what is reported only let several
  * workgroups share a key tile.  With less of it short batches are slower, and
  * their dK, dV differ in the order of float sums; the same workspace_bytes
  * always give the same bits. */

@@ -1,5 +1,5 @@
 """dK / dV with a key tile's (head, query tile) pairs shared by several workgroups: chunks that cross heads, the last chunk
-short, tiles with a single chunk next to tiles with many, entries shorter than the longest, keys that nobody sees."""
+short, tiles with a single chunk next to tiles with many, keys that nobody sees (packed: test_gpu_attn_split_packed.py)."""
 import numpy as np
 import pytest
 

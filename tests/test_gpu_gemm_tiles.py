@@ -1,4 +1,5 @@
-"""The projection GEMMs at sizes that take each of their tile sizes (128 x 128, 128 x 256, 256 x 128, 256 x 256): a whole
+"""The projection GEMMs at sizes that take each of their tile sizes (128 x 128, 128 x 256, 256 x 128, 256 x 256; with every
+storage order and output type: test_gpu_gemm_variants.py): a whole
 forward + backward against plain float32 PyTorch on the same inputs, rows that end inside a tile, weight gradients over
 row counts that end inside a k slice, both output types; and a residual operand on the large and the small tiles."""
 import pytest
@@ -36,9 +37,9 @@ def reference(t, S, D, H, G, k):
     (60, 256, 2, 1, False),          # 128 x 128 throughout, less than one tile of rows
     (700, 1024, 16, 4, True),        # 128 x 128, ragged rows and k slices
     (1024, 2048, 16, 16, False),     # 256 x 128 | 128 | 128 | 128 | 128 | 256
-    (1300, 1024, 32, 8, True),       # 256 | 128 | 128 x 256 | 128 | 128 | 128 x 256
-    (900, 3072, 24, 12, False),      # 128 x 256 | 128 | 128 | 256 | 128 x 256 | 256
-    (513, 4096, 8, 2, True),         # 128 | 128 | 128 | 128 | 128 x 256 | 128 x 256
+    (1300, 1024, 32, 8, True),       # 256 | 128 | 128 x 256 | 128 | 128 | 256 x 128
+    (900, 3072, 24, 12, False),      # 256 x 128 | 128 | 128 | 256 | 256 x 128 | 256, the excess on 128
+    (513, 4096, 8, 2, True),         # 128 | 128 | 128 | 128 | 128 x 256 | 256 x 128
     (4200, 4352, 32, 2, False),      # 256 with the tile rows past whole rounds in a second launch, ragged rows among them ...
     (4200, 4352, 32, 2, True),       # ... and weight gradients with rows of X cut off, float output
 ])

@@ -1,0 +1,78 @@
+"""Every instantiation of the small-tile GEMM kernel has a whole step against float32 that runs it: tile size, storage orders of
+the operands (nn: X W, nt: X W^T, tn: X^T Y) and output type.  Which tiles a launch takes is computed here from the cost rule
+that gemm_bf16.hip states, so that the sizes are known to reach what they are listed for."""
+import pytest
+
+import test_gpu_gemm_tiles as whole
+
+# (BM, BN, us per round, us per slice of 64 k, and the share of it that grows with how full the round is)
+COSTS = ((256, 256, 8.8, 0.90, 0.65), (256, 128, 8.3, 0.57, 0.38), (128, 256, 8.3, 0.57, 0.38), (128, 128, 6.1, 0.38, 0.16))
+CUT_US = 8.0
+up = lambda a, b: -(-a // b)
+
+
+def _choose(group):
+    """group: (M, N, depths of the k segments) of every product of the launch -> ((BM, BN), microseconds)."""
+    best = None
+    for bm, bn, fixed, each, fuller in COSTS:
+        tiles = [up(m, bm) * up(n, bn) for m, n, _ in group]
+        depth = sum(t * sum(up(k, 64) for k in ks) for t, (_, _, ks) in zip(tiles, group)) / sum(tiles)
+        full, rest = divmod(sum(tiles) / 256.0, 1.0)
+        us = full * (fixed + depth * (each + fuller)) + (fixed + depth * (each + fuller * rest) if rest else 0.0)
+        if best is None or us < best[1]:
+            best = ((bm, bn), us)
+    return best
+
+
+def _launches(group, rows_contiguous):
+    """Tile sizes of the one or two launches that a group becomes."""
+    tile, us = _choose(group)
+    total = sum(up(m, 256) * up(n, 256) for m, n, _ in group)
+    excess = total % 256
+    if tile != (256, 256) or total < 256 or excess == 0 or excess > 128:
+        return [tile]
+    best, found = us - CUT_US, [tile]
+    for i, (m, n, ks) in enumerate(group):
+        rows, r = up(m, 256), up(excess, up(n, 256))
+        if r >= rows or (rows_contiguous and m % 256):
+            continue
+        kept = (rows - r) * 256
+        a, b = _choose(group[:i] + [(kept, n, ks)] + group[i + 1:]), _choose([(m - kept, n, ks)])
+        if a[1] + b[1] < best:
+            best, found = a[1] + b[1], [a[0], b[0]]
+    return found
+
+
+def _variants(S, D, H, G, wf32):
+    """{(tile, orders, output type)} of a step's launches (dWk, dWv not in halves at these sizes)."""
+    W, V = 128 * H, 128 * G
+    assert up(D, 256) * (up(W, 256) + 2 * up(V, 256)) < 256
+    nn, nt = [[(S, W, (D,)), (S, V, (D,)), (S, V, (D,))], [(S, D, (W,))]], [[(S, W, (D,))], [(S, D, (V, V)), (S, D, (W,))]]
+    tn = [[(W, D, (S,))], [(D, W, (S,)), (D, V, (S,)), (D, V, (S,))]]
+    out = set()
+    for orders, groups in (("nn", nn), ("nt", nt), ("tn", tn)):
+        for g in groups:
+            out |= {(t, orders, "f32" if orders == "tn" and wf32 else "bf16") for t in _launches(g, orders == "tn")}
+    return out
+
+
+SHAPES = [
+    (200, 1408, 8, 8, False),      # odd multiples of 128 channels: weight gradients on 128 x 256 ...
+    (200, 1408, 8, 8, True),       # ... in both output types
+    (200, 2176, 16, 16, False),    # dWo on 256 x 128
+    (200, 2560, 13, 1, True),      # dWo on 128 x 256, [dWq, dWk, dWv] on 256 x 128
+    (1152, 2688, 24, 8, False),    # an odd multiple of 128 rows: forward projections and input gradients on 128 x 256
+    (1664, 1664, 13, 13, False),   # input gradients on 256 x 128
+    (1024, 2048, 15, 15, False),   # forward projections on 256 x 128
+]
+
+
+def test_shapes_reach_every_small_tile_variant():
+    want = {((bm, bn), o, t) for bm, bn, *_ in COSTS[1:] for o, t in (("nn", "bf16"), ("nt", "bf16"), ("tn", "bf16"), ("tn", "f32"))}
+    assert want <= set().union(*(_variants(*s) for s in SHAPES)), want - set().union(*(_variants(*s) for s in SHAPES))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("S,D,H,G,wf32", SHAPES)
+def test_step_on_the_variant(S, D, H, G, wf32):
+    whole.test_step_against_float32(S, D, H, G, wf32)
