@@ -3,21 +3,24 @@
 //   delta_p = sum_c dO_pc O_pc          P = exp(s - LSE)        dS = P * (dP - delta)
 //   dQ = scale * dS K      dK = scale * dS^T Q      dV = P^T dO      dP = dO V^T
 //
-// Two kernels, no floating-point atomics (results are bitwise reproducible):
+// No floating-point atomics (results are bitwise reproducible):
 //
-//  (1) dq kernel   one workgroup = 128 queries of one (b, h), loop over the key
-//      tiles those queries can see.  As in the forward, a lane owns ONE query:
-//      S^T = K Q^T and dP^T = V dO^T come out with column q = lane % 32, so LSE
-//      and delta are per-lane scalars, and dS^T goes straight from the
-//      accumulator registers into the B operand of dQ^T += K^T dS^T.  The kernel
-//      also computes delta and stores it, with -log2(e) * LSE, for kernel (2).
+//  (1) dq kernel   one workgroup = 128 queries (64 in short batches, as in the
+//      forward) of one (b, h), loop over the key tiles those queries can see.  A
+//      lane owns ONE query, as in the forward: S^T = K Q^T and dP^T = V dO^T
+//      come out with column q = lane % 32, so LSE and delta are per-lane scalars,
+//      and dS^T goes straight from the accumulator registers into the B operand
+//      of dQ^T += K^T dS^T.  The kernel also computes delta and stores it, with
+//      -log2(e) * LSE, for kernel (2).
 //
 //  (2) dkv kernel  one workgroup = 128 keys of one (b, kv head), loop over the
 //      H/G query heads of the group and over the query tiles that can see those
 //      keys.  A lane owns ONE key: S = Q K^T and dP = dO V^T come out with
 //      column j = lane % 32; P and dS go straight into the B operands of
 //      dV^T += dO^T P and dK^T += Q^T dS.  LSE/delta of the tile's queries are
-//      read from LDS (they index the accumulator registers here).
+//      read from LDS (they index the accumulator registers here).  In short
+//      grouped-query batches several workgroups share a key tile, and a third
+//      kernel adds their sums in order.
 //
 // Tiles go from HBM/L2 straight into one of two LDS stages while the other is
 // consumed; the swizzled tile layout (attn_tiles.h) serves both the whole-row

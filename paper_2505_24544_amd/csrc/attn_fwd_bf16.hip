@@ -1,8 +1,9 @@
 // Flash-style forward of the block-masked cross-attention (Eq. 2 with the
 // window mask of section 4.2) for bf16, head width 128, on gfx950 MFMA.
 //
-// One workgroup (4 waves) owns 128 queries of one (batch, head); each wave owns
-// 32 of them.  Key/value tiles of 64 rows go from HBM/L2 straight into one of
+// One workgroup (4 waves) owns 128 queries of one (batch, head), or 64 where
+// those are too few for the chip; each wave owns 32 of them, in the second case
+// against one half of every key tile.  Key/value tiles of 64 rows go from HBM/L2 straight into one of
 // two LDS stages (see attn_tiles.h) while the other stage is consumed.
 //
 // Everything is computed transposed so that a lane owns ONE query:

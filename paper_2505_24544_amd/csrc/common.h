@@ -58,9 +58,10 @@ struct ProfScope {
 // ---- GEMM:  C[M,N] (+)= op(A) * op(B), float accumulation -----------------
 // a_kmajor: A is stored [M,K] (k fastest, leading dim lda) else [K,M].
 // b_kmajor: B is stored [N,K] (k fastest, leading dim ldb) else [K,N].
-// C is row-major [M,N] with leading dim ldc.  accumulate: C += instead of C =.
-// An optional second k-segment (A2, B2, K2; same storage orders and leading
-// dims lda2/ldb2) is contracted into the same C:  C = A*B + A2*B2.
+// C is row-major [M,N] with leading dim ldc.
+// An optional second k-segment (A2, B2, K2; same storage orders) is contracted
+// into the same C:  C = A*B + A2*B2.  Its leading dims are free in float and
+// those of the first segment in bf16 (lda2 == lda, ldb2 == ldb).
 struct GemmArgs {
   const void* A; const void* B; void* C;
   int32_t M, N, K;
@@ -252,17 +253,18 @@ size_t block_mlp_bf16_ws_bytes(int32_t M, int32_t D, int32_t F);
 bool block_mlp_bf16_fits(int32_t D, int32_t F);
 void launch_block_mlp_bf16(const void* z, const void* w_gate, const void* w_up, const void* w_down, const void* y_res,
                            void* h, int32_t M, int32_t D, int32_t F, void* ws, hipStream_t s);
-// the same on packed weights: two strip launches, gate fused;
-// needs strip_gemm_fits(M, F, D) and strip_gemm_fits(M, D, F); ws: M * F bf16
-// rope: null, or the rotary embedding of the K rows (pos / pos0, l2base), applied to the finished sums
+// the rotary embedding of rows on the decode side
 struct RopeRows {
   const int32_t* pos; int32_t pos0;  // row i stands at pos ? pos[i] : pos0 (+ i where the rows are consecutive)
   double l2base;
   float2* tab;                       // where a launch that prepares the angles puts (cos, sin): [rows][64]
-  int32_t on;
+  int32_t on;                        // 0: none
 };
+// rope: of the K rows, applied to the finished sums
 void launch_kv_append_strip_bf16(const void* x, const void* wk_pk, const void* wv_pk, void* kdst, void* vdst, int32_t n,
                                  int32_t N, int32_t K, float norm_eps, const RopeRows& rope, hipStream_t s);
+// launch_block_mlp_bf16 on packed weights: two strip launches, gate fused;
+// needs strip_gemm_fits(M, F, D) and strip_gemm_fits(M, D, F); ws: M * F bf16
 void launch_block_mlp_strip_bf16(const void* z, const void* w_gate_pk, const void* w_up_pk, const void* w_down_pk,
                                  const void* y_res, void* h, int32_t M, int32_t D, int32_t F, float z_norm_eps, void* ws,
                                  hipStream_t s);

@@ -8,7 +8,8 @@
 //   (A) skinny_gemm   q_part[ks] = x * Wq[k-slice ks]        grid (N/64) x (K/512),
 //                     two workgroups per CU, the whole chip resident at once; the
 //                     64 KB tile is worked on in quarters as they land
-//   (B) decode_attn   one workgroup per (head, key range, block of 32 queries);
+//   (B) decode_attn   one workgroup per (head, key range), or per several query
+//                     heads of a key/value head where grouped queries are few;
 //                     its 4 waves split each 128-key step by rows.  A lane owns
 //                     one query (as in the training forward): online softmax per
 //                     lane, P goes from the accumulator registers straight into

@@ -179,8 +179,9 @@ __device__ __forceinline__ void locate_tile(const GemmGroup& grp, int wg, int& p
 
 // RES: some problem of the group has a residual operand R (a separate instantiation, so that the kernels
 // without one keep their register allocation).
-template <int TM, int TN, bool XK, bool WK, bool F32OUT, bool RES>
-__global__ __launch_bounds__(256, TM * TN >= 16 ? 1 : 2) void gemm_bf16_kernel(GemmGroup grp) {
+template <bool XK, bool WK, bool F32OUT, bool RES>
+__global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmGroup grp) {
+  constexpr int TM = 4, TN = 4;                  // 32 x 32 accumulators per wave
   constexpr int BM = 64 * TM, BN = 64 * TN;
   constexpr int XE = BM * BK, WE = BN * BK;      // elements per operand tile
   __shared__ __attribute__((aligned(1024))) bf16_t stage0[XE + WE];
@@ -678,11 +679,6 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
   });
 }
 
-template <int TM, int TN, bool XK, bool WK, bool F32OUT, bool RES = false>
-static void launch_variant(const GemmGroup& grp, int total, hipStream_t s) {
-  hipLaunchKernelGGL((gemm_bf16_kernel<TM, TN, XK, WK, F32OUT, RES>), dim3(total), dim3(256), 0, s, grp);
-}
-
 // What the MFMA kernel needs of a group (checked by the entry points before anything is enqueued, see
 // gemm_bf16_supported): k-contiguous operands with K a multiple of the k slice, every operand (and the residual)
 // addressable through a 32-bit buffer descriptor, and one of the storage-order combinations instantiated below.
@@ -714,22 +710,20 @@ static void check_group(const GemmGroup& grp) {
   }
 }
 
-template <int TM, int TN>
-static void launch_tiles(const GemmGroup& grp, hipStream_t s) {
-  constexpr int BM = 64 * TM, BN = 64 * TN;
+static void launch_256(const GemmGroup& grp, hipStream_t s) {
   int total = 0;
-  for (int i = 0; i < grp.count; ++i)
-    total += ((grp.p[i].M + BM - 1) / BM) * ((grp.p[i].N + BN - 1) / BN);
+  for (int i = 0; i < grp.count; ++i) total += ((grp.p[i].M + 255) / 256) * ((grp.p[i].N + 255) / 256);
   if (total == 0) return;
   const bool xk = grp.p[0].a_kmajor, wk = grp.p[0].b_kmajor, f32 = grp.p[0].c_is_f32;
   bool res = false;
   for (int i = 0; i < grp.count; ++i) if (grp.p[i].R) res = true;
-  if (res && !wk) launch_variant<TM, TN, true, false, false, true>(grp, total, s);
-  else if (res) launch_variant<TM, TN, true, true, false, true>(grp, total, s);
-  else if (xk && !wk) launch_variant<TM, TN, true, false, false>(grp, total, s);
-  else if (xk) launch_variant<TM, TN, true, true, false>(grp, total, s);
-  else if (!f32) launch_variant<TM, TN, false, false, false>(grp, total, s);
-  else launch_variant<TM, TN, false, false, true>(grp, total, s);
+  const dim3 grid(total), wg(256);
+  if (res && !wk) hipLaunchKernelGGL((gemm_bf16_kernel<true, false, false, true>), grid, wg, 0, s, grp);
+  else if (res) hipLaunchKernelGGL((gemm_bf16_kernel<true, true, false, true>), grid, wg, 0, s, grp);
+  else if (xk && !wk) hipLaunchKernelGGL((gemm_bf16_kernel<true, false, false, false>), grid, wg, 0, s, grp);
+  else if (xk) hipLaunchKernelGGL((gemm_bf16_kernel<true, true, false, false>), grid, wg, 0, s, grp);
+  else if (!f32) hipLaunchKernelGGL((gemm_bf16_kernel<false, false, false, false>), grid, wg, 0, s, grp);
+  else hipLaunchKernelGGL((gemm_bf16_kernel<false, false, true, false>), grid, wg, 0, s, grp);
 }
 
 template <int WM, int WN>
@@ -780,7 +774,7 @@ static TileChoice choose_tile(const GemmGroup& grp) {
 
 static void launch_chosen(const GemmGroup& grp, TileSize tile, hipStream_t s) {
   switch (tile) {
-    case TILE_256: return launch_tiles<4, 4>(grp, s);
+    case TILE_256: return launch_256(grp, s);
     case TILE_256x128: return launch_ksplit<2, 1>(grp, s);
     case TILE_128x256: return launch_ksplit<1, 2>(grp, s);
     case TILE_128: return launch_ksplit<1, 1>(grp, s);

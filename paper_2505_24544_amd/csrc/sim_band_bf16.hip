@@ -1,6 +1,6 @@
 // Late-stage simulation band (section 4.2, second half) for bf16 storage and
-// head width 128.  Same arithmetic as the one-wave-per-row kernels of the
-// scalar path, laid out for memory throughput: the band is at most t keys per
+// head width 128.  Same arithmetic as the one-wave-per-row float
+// kernels (sim_band_f32.hip), laid out for memory throughput: the band is at most t keys per
 // query, so these kernels are pure streaming over Q / O / dO / dQ.  A row of 128
 // channels is owned by 16 lanes with one 16-byte chunk each (a wavefront covers
 // four consecutive rows = 1 KB contiguous), dot products are reduced inside a
