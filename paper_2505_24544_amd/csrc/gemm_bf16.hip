@@ -385,12 +385,15 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmGroup grp) {
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own writes have landed; no other wave touches its patch
     const int pp = lane % CPW, rsub = lane / CPW;
+    // (the bounds in registers: otherwise every one of the 32 stores fetches them again from the arguments and waits)
+    int gm = g.M, gn = g.N;
+    asm volatile("" : "+s"(gm), "+s"(gn));
 #pragma unroll
     for (int it = 0; it < PROWS / RPI; ++it) {
       const int pr = it * RPI + rsub;
       const uint4 v = *(const uint4*)(patch + pr * (CPW * 8) + pp * 8);
       const int m = m0 + wm + pr, n = n0 + wn + 8 * (pp ^ (pr & (CPW - 1)));
-      if (m < g.M && n < g.N) { typedef unsigned int nt_u32x4 __attribute__((ext_vector_type(4))); const nt_u32x4 w = {v.x, v.y, v.z, v.w}; __builtin_nontemporal_store(w, (nt_u32x4*)((bf16_t*)g.C + (int64_t)m * g.ldc + n)); }
+      if (m < gm && n < gn) { typedef unsigned int nt_u32x4 __attribute__((ext_vector_type(4))); const nt_u32x4 w = {v.x, v.y, v.z, v.w}; __builtin_nontemporal_store(w, (nt_u32x4*)((bf16_t*)g.C + (int64_t)m * g.ldc + n)); }
     }
   }
 }
