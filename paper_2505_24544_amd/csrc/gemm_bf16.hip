@@ -3,9 +3,9 @@
 // projection-shaped contraction of the backward pass.
 //
 // Design
-//   * One workgroup of 4 wavefronts (2 x 2) owns a BM x BN tile of C; each
-//     wave owns (32*TM) x (32*TN) of it as TM x TN accumulators of the
-//     v_mfma_f32_32x32x16_bf16 instruction.
+//   * One workgroup of 4 wavefronts (2 x 2) owns a 256 x 256 tile of C (128 x
+//     128 for a few shallow products); each wave owns a quarter of it as T x T
+//     accumulators of the v_mfma_f32_32x32x16_bf16 instruction.
 //   * The k loop walks BK = 64 at a time through two LDS stages.  Slices go
 //     from HBM/L2 straight into LDS (buffer_load ... lds, 16 bytes per lane):
 //     no staging registers, no ds_write, and out-of-range chunks arrive as
@@ -179,9 +179,9 @@ __device__ __forceinline__ void locate_tile(const GemmGroup& grp, int wg, int& p
 
 // RES: some problem of the group has a residual operand R (a separate instantiation, so that the kernels
 // without one keep their register allocation).
-template <bool XK, bool WK, bool F32OUT, bool RES>
-__global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(GemmGroup grp) {
-  constexpr int TM = 4, TN = 4;                  // 32 x 32 accumulators per wave
+template <int T, bool XK, bool WK, bool F32OUT, bool RES>
+__global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGroup grp) {
+  constexpr int TM = T, TN = T;                  // 32 x 32 accumulators per wave
   constexpr int BM = 64 * TM, BN = 64 * TN;
   constexpr int XE = BM * BK, WE = BN * BK;      // elements per operand tile
   __shared__ __attribute__((aligned(1024))) bf16_t stage0[XE + WE];
@@ -713,20 +713,22 @@ static void check_group(const GemmGroup& grp) {
   }
 }
 
-static void launch_256(const GemmGroup& grp, hipStream_t s) {
+template <int T>
+static void launch_square(const GemmGroup& grp, hipStream_t s) {
+  constexpr int BM = 64 * T;
   int total = 0;
-  for (int i = 0; i < grp.count; ++i) total += ((grp.p[i].M + 255) / 256) * ((grp.p[i].N + 255) / 256);
+  for (int i = 0; i < grp.count; ++i) total += ((grp.p[i].M + BM - 1) / BM) * ((grp.p[i].N + BM - 1) / BM);
   if (total == 0) return;
   const bool xk = grp.p[0].a_kmajor, wk = grp.p[0].b_kmajor, f32 = grp.p[0].c_is_f32;
   bool res = false;
   for (int i = 0; i < grp.count; ++i) if (grp.p[i].R) res = true;
   const dim3 grid(total), wg(256);
-  if (res && !wk) hipLaunchKernelGGL((gemm_bf16_kernel<true, false, false, true>), grid, wg, 0, s, grp);
-  else if (res) hipLaunchKernelGGL((gemm_bf16_kernel<true, true, false, true>), grid, wg, 0, s, grp);
-  else if (xk && !wk) hipLaunchKernelGGL((gemm_bf16_kernel<true, false, false, false>), grid, wg, 0, s, grp);
-  else if (xk) hipLaunchKernelGGL((gemm_bf16_kernel<true, true, false, false>), grid, wg, 0, s, grp);
-  else if (!f32) hipLaunchKernelGGL((gemm_bf16_kernel<false, false, false, false>), grid, wg, 0, s, grp);
-  else hipLaunchKernelGGL((gemm_bf16_kernel<false, false, true, false>), grid, wg, 0, s, grp);
+  if (res && !wk) hipLaunchKernelGGL((gemm_bf16_kernel<T, true, false, false, true>), grid, wg, 0, s, grp);
+  else if (res) hipLaunchKernelGGL((gemm_bf16_kernel<T, true, true, false, true>), grid, wg, 0, s, grp);
+  else if (xk && !wk) hipLaunchKernelGGL((gemm_bf16_kernel<T, true, false, false, false>), grid, wg, 0, s, grp);
+  else if (xk) hipLaunchKernelGGL((gemm_bf16_kernel<T, true, true, false, false>), grid, wg, 0, s, grp);
+  else if (!f32) hipLaunchKernelGGL((gemm_bf16_kernel<T, false, false, false, false>), grid, wg, 0, s, grp);
+  else hipLaunchKernelGGL((gemm_bf16_kernel<T, false, false, true, false>), grid, wg, 0, s, grp);
 }
 
 template <int WM, int WN>
@@ -751,13 +753,17 @@ static void launch_ksplit(const GemmGroup& grp, hipStream_t s) {
 //   256 x 128, 128 x 256: K 777 full 20; K 4096 full 64-70, half full 52
 //   128 x 128: K 777 full 13; K 4096 full 40, 7/8 full 36 (four waves of 64 x 64 per tile took 59)
 // Large problems come out at 256 x 256 by their operand traffic alone (1.30 PFLOP/s against 0.95 and 0.80).
-enum TileSize { TILE_256, TILE_256x128, TILE_128x256, TILE_128 };
+// Tiles of 128 x 128 over a short contraction take four waves of 64 x 64 instead (TILE_128_SHALLOW): no ring to fill and no sums
+// to exchange, and half the accumulators to clear.  Two products of 768 x 1024 over K 128 / 512 / 1024, us: 10.2 / 12.6 / 15.8 with waves
+// that split k -> 5.9 / 8.7 / 12.3; at K 1536 both take 19.3, at 2048 22.7 -> 24.5.
+constexpr int SHALLOW = 16;                         // slices of 64 k
+enum TileSize { TILE_256, TILE_256x128, TILE_128x256, TILE_128, TILE_128_SHALLOW };
 struct TileChoice { TileSize tile; double us; };
 static TileChoice choose_tile(const GemmGroup& grp) {
   struct Cost { int bm, bn; double fixed, slice, slice_full; };
   static const Cost costs[] = {{256, 256, 8.8, 0.90, 0.65}, {256, 128, 8.3, 0.57, 0.38}, {128, 256, 8.3, 0.57, 0.38}, {128, 128, 6.1, 0.38, 0.16}};
   int best = 0;
-  double best_us = 0.0;
+  double best_us = 0.0, best_depth = 0.0;
   for (int c = 0; c < 4; ++c) {
     double tiles = 0.0, slices = 0.0;               // slices: over all tiles
     for (int i = 0; i < grp.count; ++i) {
@@ -770,17 +776,19 @@ static TileChoice choose_tile(const GemmGroup& grp) {
     const double depth = slices / tiles, full = floor(tiles / 256.0), rest = tiles / 256.0 - full;
     double us = full * (costs[c].fixed + depth * (costs[c].slice + costs[c].slice_full));
     if (rest > 0.0) us += costs[c].fixed + depth * (costs[c].slice + costs[c].slice_full * rest);
-    if (c == 0 || us < best_us) { best = c; best_us = us; }
+    if (c == 0 || us < best_us) { best = c; best_us = us; best_depth = depth; }
   }
+  if (best == TILE_128 && best_depth <= SHALLOW) best = TILE_128_SHALLOW;
   return {(TileSize)best, best_us};
 }
 
 static void launch_chosen(const GemmGroup& grp, TileSize tile, hipStream_t s) {
   switch (tile) {
-    case TILE_256: return launch_256(grp, s);
+    case TILE_256: return launch_square<4>(grp, s);
     case TILE_256x128: return launch_ksplit<2, 1>(grp, s);
     case TILE_128x256: return launch_ksplit<1, 2>(grp, s);
     case TILE_128: return launch_ksplit<1, 1>(grp, s);
+    case TILE_128_SHALLOW: return launch_square<2>(grp, s);
   }
 }
 

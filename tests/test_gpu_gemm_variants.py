@@ -1,5 +1,6 @@
-"""Every instantiation of the small-tile GEMM kernel has a whole step against float32 that runs it: tile size, storage orders of
-the operands (nn: X W, nt: X W^T, tn: X^T Y) and output type.  Which tiles a launch takes is computed here from the cost rule
+"""Every instantiation of the small-tile GEMM kernels has a whole step against float32 that runs it: tile size, storage orders of
+the operands (nn: X W, nt: X W^T, tn: X^T Y) and output type; tiles of 128 x 128 over up to 16 slices of 64 k ("shallow") have a
+kernel of their own.  Which tiles a launch takes is computed here from the cost rule
 that gemm_bf16.hip states, so that the sizes are known to reach what they are listed for."""
 import pytest
 
@@ -8,11 +9,12 @@ import test_gpu_gemm_tiles as whole
 # (BM, BN, us per round, us per slice of 64 k, and the share of it that grows with how full the round is)
 COSTS = ((256, 256, 8.8, 0.90, 0.65), (256, 128, 8.3, 0.57, 0.38), (128, 256, 8.3, 0.57, 0.38), (128, 128, 6.1, 0.38, 0.16))
 CUT_US = 8.0
+SHALLOW = 16
 up = lambda a, b: -(-a // b)
 
 
 def _choose(group):
-    """group: (M, N, depths of the k segments) of every product of the launch -> ((BM, BN), microseconds)."""
+    """group: (M, N, depths of the k segments) of every product of the launch -> ((BM, BN) or "shallow", microseconds)."""
     best = None
     for bm, bn, fixed, each, fuller in COSTS:
         tiles = [up(m, bm) * up(n, bn) for m, n, _ in group]
@@ -20,7 +22,7 @@ def _choose(group):
         full, rest = divmod(sum(tiles) / 256.0, 1.0)
         us = full * (fixed + depth * (each + fuller)) + (fixed + depth * (each + fuller * rest) if rest else 0.0)
         if best is None or us < best[1]:
-            best = ((bm, bn), us)
+            best = ("shallow" if (bm, bn) == (128, 128) and depth <= SHALLOW else (bm, bn), us)
     return best
 
 
@@ -64,11 +66,15 @@ SHAPES = [
     (1152, 2688, 24, 8, False),    # an odd multiple of 128 rows: forward projections and input gradients on 128 x 256
     (1664, 1664, 13, 13, False),   # input gradients on 256 x 128
     (1024, 2048, 15, 15, False),   # forward projections on 256 x 128
+    (60, 256, 2, 1, False),        # all shallow: less than a tile of rows
+    (1030, 1024, 8, 2, False),     # shallow forward and dO, weight gradients over 17 slices: just past it
+    (1030, 1024, 8, 2, True),
 ]
 
 
 def test_shapes_reach_every_small_tile_variant():
-    want = {((bm, bn), o, t) for bm, bn, *_ in COSTS[1:] for o, t in (("nn", "bf16"), ("nt", "bf16"), ("tn", "bf16"), ("tn", "f32"))}
+    tiles = [(bm, bn) for bm, bn, *_ in COSTS[1:]] + ["shallow"]
+    want = {(tile, o, t) for tile in tiles for o, t in (("nn", "bf16"), ("nt", "bf16"), ("tn", "bf16"), ("tn", "f32"))}
     assert want <= set().union(*(_variants(*s) for s in SHAPES)), want - set().union(*(_variants(*s) for s in SHAPES))
 
 
@@ -76,3 +82,9 @@ def test_shapes_reach_every_small_tile_variant():
 @pytest.mark.parametrize("S,D,H,G,wf32", SHAPES)
 def test_step_on_the_variant(S, D, H, G, wf32):
     whole.test_step_against_float32(S, D, H, G, wf32)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("S,D,H", [(70, 2048, 16), (130, 1088, 9)])       # past 16 slices on tiles of 128 x 128: with a residual
+def test_residual_on_the_variant(S, D, H):
+    whole.test_residual_operand(S, D, H)
