@@ -759,23 +759,67 @@ static void launch_ksplit(const GemmGroup& grp, hipStream_t s) {
 constexpr int SHALLOW = 16;                         // slices of 64 k
 enum TileSize { TILE_256, TILE_256x128, TILE_128x256, TILE_128, TILE_128_SHALLOW };
 struct TileChoice { TileSize tile; double us; };
+struct TileCost { int bm, bn; double fixed, slice, slice_full; };
+
+// Problems of different depth (dXkv contracts over two matrices, dXq over one): their tiles are dealt out in problem order,
+// each to the CU that is free first, so shallow tiles fill up behind deep ones, and a launch of less than a round lasts as long
+// as its deepest tile.  By the mean depth 1024 positions at 5120 channels took 160 large tiles for their input gradients (whole
+// backward 628 us, now 256 x 128 and 557), and the 320 tiles of 2500 positions were cut although their shallow half fills up the
+// second round (866 -> 839); simulation step of 3048 positions 1386 -> 1351, 3 of 500 at 2048 channels 239 -> 226.
+// `tiles` and `depth` of each of `count` problems; less than 0: too many rounds for the depths to matter.
+static double uneven_us(const TileCost& c, const double* tiles, const double* depth, int count) {
+  double total = 0.0;
+  for (int i = 0; i < count; ++i) total += tiles[i];
+  if (total > 4096.0) return -1.0;
+  const double fill = total < 256.0 ? total / 256.0 : 1.0;
+  struct { double at, cus; } free_at[64];            // CUs by the time they are free
+  int n = 1;
+  free_at[0] = {0.0, 256.0};
+  double end = 0.0;
+  for (int i = 0; i < count; ++i) {
+    const double us = c.fixed + depth[i] * (c.slice + c.slice_full * fill);
+    for (double left = tiles[i]; left > 0.0;) {
+      int e = 0;
+      for (int k = 1; k < n; ++k) if (free_at[k].at < free_at[e].at) e = k;
+      const double at = free_at[e].at + us, some = left < free_at[e].cus ? left : free_at[e].cus;
+      left -= some;
+      free_at[e].cus -= some;
+      if (free_at[e].cus == 0.0) free_at[e] = free_at[--n];
+      int k = 0;
+      while (k < n && free_at[k].at != at) ++k;
+      if (k == 64) return -1.0;
+      if (k == n) free_at[n++] = {at, some}; else free_at[k].cus += some;
+      if (at > end) end = at;
+    }
+  }
+  return end;
+}
+
 static TileChoice choose_tile(const GemmGroup& grp) {
-  struct Cost { int bm, bn; double fixed, slice, slice_full; };
-  static const Cost costs[] = {{256, 256, 8.8, 0.90, 0.65}, {256, 128, 8.3, 0.57, 0.38}, {128, 256, 8.3, 0.57, 0.38}, {128, 128, 6.1, 0.38, 0.16}};
+  static const TileCost costs[] = {{256, 256, 8.8, 0.90, 0.65}, {256, 128, 8.3, 0.57, 0.38}, {128, 256, 8.3, 0.57, 0.38}, {128, 128, 6.1, 0.38, 0.16}};
   int best = 0;
   double best_us = 0.0, best_depth = 0.0;
   for (int c = 0; c < 4; ++c) {
     double tiles = 0.0, slices = 0.0;               // slices: over all tiles
+    double each[4], deep[4];                        // tiles and depth of each problem
+    bool even = true;
     for (int i = 0; i < grp.count; ++i) {
       const GemmArgs& q = grp.p[i];
       const double t = (double)((q.M + costs[c].bm - 1) / costs[c].bm) * ((q.N + costs[c].bn - 1) / costs[c].bn);
+      each[i] = t;
+      deep[i] = (q.K + BK - 1) / BK + (q.A2 ? (q.K2 + BK - 1) / BK : 0);
+      even = even && deep[i] == deep[0];
       tiles += t;
-      slices += t * ((q.K + BK - 1) / BK + (q.A2 ? (q.K2 + BK - 1) / BK : 0));
+      slices += t * deep[i];
     }
     if (tiles == 0.0) continue;
     const double depth = slices / tiles, full = floor(tiles / 256.0), rest = tiles / 256.0 - full;
     double us = full * (costs[c].fixed + depth * (costs[c].slice + costs[c].slice_full));
     if (rest > 0.0) us += costs[c].fixed + depth * (costs[c].slice + costs[c].slice_full * rest);
+    if (!even) {
+      const double uneven = uneven_us(costs[c], each, deep, grp.count);
+      if (uneven >= 0.0) us = uneven;
+    }
     if (c == 0 || us < best_us) { best = c; best_us = us; best_depth = depth; }
   }
   if (best == TILE_128 && best_depth <= SHALLOW) best = TILE_128_SHALLOW;

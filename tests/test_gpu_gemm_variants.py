@@ -2,6 +2,8 @@
 the operands (nn: X W, nt: X W^T, tn: X^T Y) and output type; tiles of 128 x 128 over up to 16 slices of 64 k ("shallow") have a
 kernel of their own.  Which tiles a launch takes is computed here from the cost rule
 that gemm_bf16.hip states, so that the sizes are known to reach what they are listed for."""
+import heapq
+
 import pytest
 
 import test_gpu_gemm_tiles as whole
@@ -13,6 +15,19 @@ SHALLOW = 16
 up = lambda a, b: -(-a // b)
 
 
+def _uneven(fixed, each, fuller, tiles, depths):
+    """Makespan of tiles of different depth, dealt out in order to whichever of the 256 CUs is free first."""
+    fill = min(1.0, sum(tiles) / 256.0)
+    free = [0.0] * 256
+    end = 0.0
+    for t, d in zip(tiles, depths):
+        for _ in range(t):
+            at = heapq.heappop(free) + fixed + d * (each + fuller * fill)
+            heapq.heappush(free, at)
+            end = max(end, at)
+    return end
+
+
 def _choose(group):
     """group: (M, N, depths of the k segments) of every product of the launch -> ((BM, BN) or "shallow", microseconds)."""
     best = None
@@ -21,6 +36,9 @@ def _choose(group):
         depth = sum(t * sum(up(k, 64) for k in ks) for t, (_, _, ks) in zip(tiles, group)) / sum(tiles)
         full, rest = divmod(sum(tiles) / 256.0, 1.0)
         us = full * (fixed + depth * (each + fuller)) + (fixed + depth * (each + fuller * rest) if rest else 0.0)
+        depths = [sum(up(k, 64) for k in ks) for _, _, ks in group]
+        if len(set(depths)) > 1 and sum(tiles) <= 4096:
+            us = _uneven(fixed, each, fuller, tiles, depths)
         if best is None or us < best[1]:
             best = ("shallow" if (bm, bn) == (128, 128) and depth <= SHALLOW else (bm, bn), us)
     return best
@@ -64,7 +82,7 @@ SHAPES = [
     (200, 2176, 16, 16, False),    # dWo on 256 x 128
     (200, 2560, 13, 1, True),      # dWo on 128 x 256, [dWq, dWk, dWv] on 256 x 128
     (1152, 2688, 24, 8, False),    # an odd multiple of 128 rows: forward projections and input gradients on 128 x 256
-    (1664, 1664, 13, 13, False),   # input gradients on 256 x 128
+    (700, 3072, 8, 4, False),      # input gradients on 256 x 128
     (1024, 2048, 15, 15, False),   # forward projections on 256 x 128
     (60, 256, 2, 1, False),        # all shallow: less than a tile of rows
     (1030, 1024, 8, 2, False),     # shallow forward and dO, weight gradients over 17 slices: just past it
