@@ -32,7 +32,7 @@ def reference(t, S, D, H, G, k):
     return y.detach(), {n: x.grad for n, x in p.items()}
 
 
-# (rows, D, H, G): tiles taken by [q, k, v] | output | dO | dWo | [dXkv, dXq] | [dWq, dWk, dWv]
+# (rows, D, H, G): tiles taken by [q, k, v] | output | dO | dWo | [dXkv, dXq] | [dWq, dWk, dWv] (128: either kernel of that size)
 @pytest.mark.parametrize("S,D,H,G,wf32", [
     (60, 256, 2, 1, False),          # 128 x 128 throughout, less than one tile of rows
     (700, 1024, 16, 4, True),        # 128 x 128, ragged rows and k slices
