@@ -4,39 +4,44 @@
 //
 // Design
 //   * One workgroup of 4 wavefronts (2 x 2) owns a 256 x 256 tile of C (128 x
-//     128 for a few shallow products); each wave owns a quarter of it as T x T
-//     accumulators of the v_mfma_f32_32x32x16_bf16 instruction.
-//   * The k loop walks BK = 64 at a time through two LDS stages.  Slices go
-//     from HBM/L2 straight into LDS (buffer_load ... lds, 16 bytes per lane):
-//     no staging registers, no ds_write, and out-of-range chunks arrive as
-//     zeros through the buffer descriptor's range check.  The loads of slice
-//     t+1 are issued before the MFMAs of slice t; one vmcnt wait + barrier per
-//     slice.  The two stages are two separate __shared__ arrays so that the
-//     compiler can tell a fragment read of one stage from an in-flight load
-//     into the other.
+//     128 for shallow products); each wave owns a quarter of it as accumulators
+//     of v_mfma_f32_16x16x32_bf16, which the power limit lets run 6 % faster on
+//     random operands than 32x32x16 (bare loops: 1.90 against 1.80 PFLOP/s; it
+//     reads and writes half the accumulators per product).
+//   * The k loop walks 32 k at a time.  Slices go from HBM/L2 straight into LDS
+//     (buffer_load ... lds, 16 bytes per lane): no staging registers, no
+//     ds_write, and out-of-range chunks arrive as zeros through the buffer
+//     descriptor's range check.
+//   * What bounded it was the trip to memory: two stages of 64 k left a request
+//     1000 - 2000 cycles, and a slice of 64 k took 2900 - 3300 cycles with loads
+//     from memory, 2340 with loads that always hit L2, 2048 of MFMAs.  All 160 KB
+//     of LDS now hold stages, each is requested anew as soon as every wave has
+//     its fragments, and the requests are spread evenly over the MFMAs: 2000 -
+//     4000 cycles from request to use, 2240 - 2380 cycles per 64 k.
+//   * k-contiguous operands are requested 64 k (a 128-byte line) at a time: by
+//     halves of lines L2 served twice the requests, and X * W^T took 2900 cycles
+//     per 64 k instead of 2290.  Row-contiguous ones come 32 k at a time.
 //   * Each operand tile sits in LDS in the order it has in HBM (a lane's 16
 //     bytes land at wave_base + 16 * lane), with an XOR swizzle chosen on the
 //     GLOBAL side (which chunk a lane fetches) so that reads are conflict free:
-//       k-contiguous operand  -> rows of 128 B; chunk c of row r is stored at
-//                                chunk c ^ ((r >> 1) & 7); a fragment is one
-//                                ds_read_b128;
-//       row-contiguous operand-> k-rows of ROWS*2 B; chunk c of k-row k is
-//                                stored at chunk c ^ ((k & 3) << 2); a fragment
-//                                is two ds_read_b64_tr_b16 (the LDS transpose
-//                                read), which hand every lane four consecutive
-//                                k of its own row.
-//   * Fragments are double-buffered in registers: those of k step s+1 are read
-//     from LDS before the MFMAs of step s are issued.
+//     a k-contiguous fragment is one ds_read_b128, a row-contiguous one two
+//     ds_read_b64_tr_b16 (the LDS transpose read), which hand every lane four
+//     consecutive k of its own row.
+//   * Fragments are double-buffered in registers: those of the next step are
+//     read from LDS between the MFMAs of this one.  Reads, requests and scalar
+//     arithmetic each have their place behind an MFMA; one barrier per step.
 //   * The MFMA is issued "transposed" (A operand = W rows, B operand = X rows)
 //     so that a lane ends up with 4 consecutive n of one C row in 4 consecutive
-//     accumulator registers: the epilogue stores 8 (bf16) or 16 (float) bytes
-//     per lane per instruction.
+//     accumulator registers.
 //   * Workgroup ids are remapped so that each XCD (ids are dealt round-robin
 //     to the 8 XCDs) works on a contiguous run of tiles, and tiles are walked
 //     in groups of GROUP_M tile-rows so that the run shares X and W tiles in
 //     that XCD's L2.
 //   * Several independent GEMMs can share one launch (Q, K, V projections;
 //     the three weight gradients) so that small ones do not leave CUs idle.
+// Measured against the kernel of two stages and 32x32x16 MFMAs, us (operands in
+// HBM): 8192 x 4096 x 4096 X W 211 -> 187, X W^T 221 -> 183, X^T Y over 8192 k 204 ->
+// 181; 3048 x 4096 x 11008 (192 tiles) 262 -> 214.
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -47,11 +52,13 @@ namespace beagle {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4_t;
 typedef s16x4_t __attribute__((address_space(3))) * lds_s16x4_ptr;
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
 constexpr int BK = 64;
+constexpr int KB = 32;                               // k per step of gemm_bf16_kernel
 constexpr int GROUP_M = 4;
 constexpr int NUM_XCD = 8;
 
@@ -64,77 +71,19 @@ __device__ __forceinline__ void request16(__amdgpu_buffer_rsrc_t rsrc, bf16_t* d
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)dst, 16, off, 0, 0, 0);
 }
 
-// One BK slice of one operand, HBM -> LDS.  Chunk q = tid + 256 i of the tile
-// (16 bytes) lands at tile + 16 q; which global chunk it is follows from the
-// swizzle.
-//   KMAJOR : element (row r, k) at base[r * ld + k]   (buffer = rows * ld elements)
-//   !KMAJOR: element (row r, k) at base[k * ld + r]   (buffer = K * ld elements)
-// k beyond K must read as zero: for !KMAJOR that is past the end of the buffer;
-// for KMAJOR the launcher requires K % BK == 0.  Rows beyond the matrix only
-// feed output rows/columns that are never stored, so whatever they read (zero
-// past the end, or a neighbouring row) is harmless.
-template <int ROWS, bool KMAJOR>
-__device__ __forceinline__ void load_slice(bf16_t* tile, __amdgpu_buffer_rsrc_t rsrc, int64_t ld, int row0, int k0,
-                                           int tid) {
-  constexpr int PER_THREAD = ROWS * BK / 8 / 256;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-#pragma unroll
-  for (int i = 0; i < PER_THREAD; ++i) {
-    const int q = tid + 256 * i;
-    int off;
-    if (KMAJOR) {
-      const int r = q >> 3, c = (q & 7) ^ ((r >> 1) & 7);
-      off = (int)(((int64_t)(row0 + r) * ld + k0 + 8 * c) * 2);
-    } else {
-      constexpr int CPR = ROWS / 8;
-      const int k = q / CPR, c = (q % CPR) ^ ((k & 3) << 2);
-      off = (int)(((int64_t)(k0 + k) * ld + row0 + 8 * c) * 2);
-    }
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(tile + (i * 4 + wave) * 512), 16, off, 0, 0, 0);
-  }
-}
+// Tiles of operands whose rows are contiguous: chunk c of k-row k sits at chunk c ^ krow_swizzle(k).
+__device__ __forceinline__ int krow_swizzle(int k) { return ((k & 3) << 2) ^ ((k >> 2) & 2); }
+// Tiles of k-contiguous operands, 64 bytes per row: chunk c of row r sits at chunk c ^ row_swizzle(r).  A 16-byte read serves lanes
+// 0-3, 12-15, 20-27 together, then 4-11, 16-19, 28-31, and so on: rows 0-3 and 12-15 of one k group with rows 4-11 of the next.
+__device__ __forceinline__ int row_swizzle(int r) { return ((r >> 2) & 3) ^ ((r >> 1) & 2); }
 
-// Per-lane element offsets of an operand's fragments inside its tile, computed
-// once per kernel.  Everything that varies inside the k loop (the 32-row block
-// for k-contiguous tiles, the k step for both) is then a compile-time constant
-// added to one of these, i.e. an immediate offset of the LDS read.
-//   KMAJOR : o[ks]  = row (l % 32), swizzled chunk of k step ks       (+ 32-row block * BK)
-//   !KMAJOR: o[blk] = k-row (8 (l/32) + (l%16)/4), swizzled column of block blk   (+ k step * 16 * ROWS)
-template <int ROWS, bool KMAJOR, int NBLK>
-struct FragOffs {
-  int o[KMAJOR ? BK / 16 : NBLK];
-  __device__ __forceinline__ void init(int lane, int r0) {
-    if (KMAJOR) {
-      const int ql = lane & 31, hf = lane >> 5;
-#pragma unroll
-      for (int ks = 0; ks < BK / 16; ++ks) o[ks] = (r0 + ql) * BK + (((2 * ks + hf) ^ ((ql >> 1) & 7)) << 3);
-    } else {
-      const int gi = lane >> 4, r16 = lane & 15;
-      const int kr = 8 * (gi >> 1) + (r16 >> 2);
-#pragma unroll
-      for (int b = 0; b < NBLK; ++b) {
-        const int col = r0 + 32 * b + 16 * (gi & 1) + 4 * (r16 & 3);
-        o[b] = kr * ROWS + ((((col >> 3) ^ ((kr & 3) << 2)) << 3) | (col & 7));
-      }
-    }
-  }
-};
-
-// MFMA operand fragment: lane l gets row (r0 + 32 blk + l % 32), k = 16 ks + 8 * (l / 32) .. + 7.
-template <int ROWS, bool KMAJOR, int NBLK>
-__device__ __forceinline__ bf16x8_t read_frag(const bf16_t* tile, const FragOffs<ROWS, KMAJOR, NBLK>& f, int blk, int ks) {
-  if (KMAJOR) {
-    return *(const bf16x8_t*)(tile + blk * 32 * BK + f.o[ks]);
-  } else {
-    // transpose read: the 16 lanes of a group pass the addresses of 4 k-rows x
-    // 4 pieces of 4 rows; lane l of the group receives k-rows 0..3 of row l.
-    const bf16_t* p = tile + ks * 16 * ROWS + f.o[blk];
-    union { struct { s16x4_t a, b; } s; bf16x8_t v; } u;
-    u.s.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)p);
-    u.s.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * ROWS));
-    return u.v;
-  }
+// The matrix instruction on accumulators that stay where they are: with 256 of them and the fragments of two steps, the compiler's
+// own form of it (result and addend in different registers) left 80 - 170 register copies per slice of 128 instructions.
+// Whoever reads the accumulators afterwards waits the instruction's latency first (mfma_drain).
+__device__ __forceinline__ void mfma16(f32x4_t& acc, const bf16x8_t& a, const bf16x8_t& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
+__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 
 // Workgroup id -> (problem, tile index inside the problem).  Ids are dealt
 // round-robin to the 8 XCDs; every problem's tiles are split evenly over the
@@ -181,219 +130,288 @@ __device__ __forceinline__ void locate_tile(const GemmGroup& grp, int wg, int& p
 // without one keep their register allocation).
 template <int T, bool XK, bool WK, bool F32OUT, bool RES>
 __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGroup grp) {
-  constexpr int TM = T, TN = T;                  // 32 x 32 accumulators per wave
-  constexpr int BM = 64 * TM, BN = 64 * TN;
-  constexpr int XE = BM * BK, WE = BN * BK;      // elements per operand tile
-  __shared__ __attribute__((aligned(1024))) bf16_t stage0[XE + WE];
-  __shared__ __attribute__((aligned(1024))) bf16_t stage1[XE + WE];
+  constexpr int NB = 2 * T;                          // 16 x 16 accumulators per wave: NB x NB
+  constexpr int BM = 64 * T, BN = 64 * T;
+  // steps of KB k per slice of X and of W, stages of either: 160 KB (T = 4) or 80 KB (T = 2) in all
+  constexpr int XS = XK ? 2 : 1, WS = XK && WK ? 2 : 1, NXS = XK ? 3 : 5, NWS = WS == 2 ? 2 : XK ? 4 : 5;
+  constexpr int AHEAD = XK ? 3 : 4;                  // steps from a step's requests to the barrier that wants them
+  constexpr int XE = BM * KB * XS, WE = BN * KB * WS, WBASE = NXS * XE;      // elements per stage; where W's begin
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[NXS * XE + NWS * WE];
 
   int pi, m0, n0;
   locate_tile<BM, BN>(grp, blockIdx.x, pi, m0, n0);
   const GemmArgs& g = grp.p[pi];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = (wave >> 1) * (32 * TM), wn = (wave & 1) * (32 * TN);
+  const int wm = (wave >> 1) * (32 * T), wn = (wave & 1) * (32 * T);
 
-  FragOffs<BM, XK, TM> xo;
-  FragOffs<BN, WK, TN> wo;
-  xo.init(lane, wm);
-  wo.init(lane, wn);
+  f32x4_t acc[NB][NB];
 
-  // The accumulators are cleared behind the first segment's first requests, not ahead of them: 256 register
-  // writes per lane are 2 000 cycles that the first round trip to memory can hide.
-  f32x16_t acc[TM][TN];
-  auto clear_acc = [&]() {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  // ---- request side: for either operand a cursor over the slices of both k segments.  The descriptors start at the current
+  // slice, so the lanes' offsets are constants of the tile and a slice costs scalar arithmetic only, in pieces that fit between
+  // two MFMAs; past the last slice they are empty.
+  constexpr int XLD = BM * XS / 64, WLD = BN * WS / 64, NLD = XLD / XS + WLD / WS;      // requests per thread: an X slice, a W slice, a step
+  const int ldx = (int)g.lda, ldw = (int)g.ldb;
+  int nk = (g.K + KB - 1) / KB + (g.A2 ? (g.K2 + KB - 1) / KB : 0);           // steps
+  auto chunk_off = [&](int q, bool kmajor, int wide, int rows, int ld) BEAGLE_INLINE_LAMBDA {      // 16-byte chunk q of an operand's slice
+    if (kmajor && wide) { const int r = q >> 3; return (r * ld + 8 * ((q & 7) ^ ((r >> 1) & 7))) * 2; }
+    if (kmajor) { const int r = q >> 2; return (r * ld + 8 * ((q & 3) ^ row_swizzle(r))) * 2; }
+    const int cpr = rows / 8, k = q / cpr;
+    return (k * ld + 8 * ((q % cpr) ^ krow_swizzle(k))) * 2;
   };
-  bool fresh = true;
-
-#pragma unroll 1
-  for (int seg = 0; seg < 2; ++seg) {
-    const bf16_t* X = (const bf16_t*)(seg ? g.A2 : g.A);
-    const bf16_t* W = (const bf16_t*)(seg ? g.B2 : g.B);
-    const int K = seg ? g.K2 : g.K;
-    const int64_t ldx = seg ? g.lda2 : g.lda, ldw = seg ? g.ldb2 : g.ldb;
-    if (X == nullptr || K <= 0) continue;
-    const int nk = (K + BK - 1) / BK;
-    const __amdgpu_buffer_rsrc_t xrs = make_rsrc(X, (int64_t)(XK ? g.M : K) * ldx * 2);
-    const __amdgpu_buffer_rsrc_t wrs = make_rsrc(W, (int64_t)(WK ? g.N : K) * ldw * 2);
-
-    bf16x8_t xf[2][TM], wf[2][TN];
-    auto fetch_x = [&](bf16_t* st, int k0) { load_slice<BM, XK>(st, xrs, ldx, m0, k0, tid); };
-    auto fetch_w = [&](bf16_t* st, int k0) { load_slice<BN, WK>(st + XE, wrs, ldw, n0, k0, tid); };
-    auto frags = [&](const bf16_t* st, int fb, int ks) {
+  int xoff[XLD], woff[WLD];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) xf[fb][i] = read_frag<BM, XK, TM>(st, xo, i, ks);
+  for (int i = 0; i < XLD; ++i) xoff[i] = chunk_off(tid + 256 * i, XK, true, BM, ldx);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) wf[fb][j] = read_frag<BN, WK, TN>(st + XE, wo, j, ks);
-    };
-    auto mfmas = [&](int fb) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[fb][j], xf[fb][i], acc[i][j], 0, 0, 0);
-    };
-    constexpr int NSTEP = BK / 16;                                      // k steps per slice (4)
-    constexpr int NREADS = (XK ? TM : 2 * TM) + (WK ? TN : 2 * TN);     // LDS reads per k step
-    constexpr int XLOADS = BM * BK / 8 / 256, WLOADS = BN * BK / 8 / 256;   // HBM->LDS loads per thread per slice
-    static_assert(NSTEP == 4 && NREADS % 2 == 0 && NREADS / 2 <= TM * TN, "issue pattern below assumes this");
-    static_assert(XLOADS <= TM * TN && WLOADS <= TM * TN, "one load per MFMA at most");
-    // One k slice.  On entry: slice kt is visible in `cur` and its step-0 fragments are in
-    // registers; the X half of slice kt+1 is already on its way into `nxt`.
-    //   step 0    : MFMAs + LDS reads of step 1 + the W half of slice kt+1 (one load per MFMA)
-    //   steps 1,2 : MFMAs + LDS reads of the next step
-    //   wait for this thread's loads, barrier: slice kt+1 visible, nobody reads `cur` any more
-    //   step 3    : MFMAs from registers + first fragment reads of slice kt+1 + the X half of
-    //               slice kt+2 into `cur`
-    // so every HBM->LDS load is issued at least two k steps (>= 1000 cycles) before it is
-    // waited for, and the in-order wave never waits on a queue while the MFMA pipe is idle.
-    auto slice = [&](bf16_t* cur, bf16_t* nxt, int kt) {
-      fetch_w(nxt, (kt + 1) * BK);    // past the last slice these fetch zeros / unused rows: harmless
-#pragma unroll
-      for (int ks = 0; ks < NSTEP - 1; ++ks) {
-        const int fb = ks & 1;
-        frags(cur, fb ^ 1, ks + 1);
-        mfmas(fb);
-#pragma unroll
-        for (int t = 0; t < TM * TN; ++t) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          if (t < NREADS / 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-          if (ks == 0 && t < WLOADS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-        }
+  for (int i = 0; i < WLD; ++i) woff[i] = chunk_off(tid + 256 * i, WK, WS == 2, BN, ldw);
+  // STG stages of E elements from `first`; what the loop needs stays in registers: it would fetch it from the arguments again
+  struct Cursor {
+    const char *at, *at2;                            // next slice's first byte; the second segment's
+    int left, left2, step;                           // bytes from there to the operand's end; per slice
+    int t, sw, end;                                  // the slice's number; the number at which the operand changes; of slices
+    bf16_t *first, *dst;                             // where this wave's part of the first stage lies, of the slice's stage
+    __amdgpu_buffer_rsrc_t rsrc;
+  } fx, fw;
+  auto f_init = [&](Cursor& c, const void* p, const void* p2, bool kmajor, int rows, int r0, int ld, int k, bf16_t* first) BEAGLE_INLINE_LAMBDA {
+    const int64_t skip = (kmajor ? (int64_t)r0 * ld : (int64_t)r0) * 2;
+    c.at = (const char*)p + skip; c.at2 = (const char*)p2 + skip;
+    c.left = (int)((int64_t)(kmajor ? rows : g.K) * ld * 2 - skip); c.left2 = (int)((int64_t)(kmajor ? rows : g.K2) * ld * 2 - skip);
+    c.step = kmajor ? k * 2 : k * ld * 2;
+    c.t = 0; c.sw = (g.K + k - 1) / k; c.end = c.sw + (p2 ? (g.K2 + k - 1) / k : 0);
+    c.first = c.dst = first;
+    asm volatile("" : "+s"(c.at2), "+s"(c.left2), "+s"(c.step), "+s"(c.end));
+    if (c.sw == 0) { c.at = c.at2; c.left = c.left2; c.sw = c.end; }
+    if (c.end == 0) c.left = 0;
+  };
+  f_init(fx, g.A, g.A2, XK, g.M, m0, ldx, KB * XS, smem + wave * 512);
+  f_init(fw, g.B, g.B2, WK, g.N, n0, ldw, KB * WS, smem + WBASE + wave * 512);
+  auto f_rsrc = [&](Cursor& c) BEAGLE_INLINE_LAMBDA { c.rsrc = make_rsrc(c.at, max(c.left, 0)); };
+  constexpr int PIECES = 4;
+  auto f_next = [&](auto i_, Cursor& c, int stages, int e) BEAGLE_INLINE_LAMBDA {
+    constexpr int i = decltype(i_)::value;
+    if constexpr (i == 0) { c.at += c.step; c.left -= c.step; }
+    if constexpr (i == 1) c.dst = c.dst == c.first + (stages - 1) * e ? c.first : c.dst + e;
+    if constexpr (i == 2) {
+      if (++c.t == c.sw) {                           // on to the second segment, or past the end: nothing left
+        c.at = c.at2;
+        c.left = c.t < c.end ? c.left2 : 0;
+        c.sw = c.t < c.end ? c.end : -1;
       }
-      __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this thread's chunks of the next slice are in LDS
-      __syncthreads();                      // everyone's are, and everyone is done reading `cur`
-      frags(nxt, 0, 0);
-      fetch_x(cur, (kt + 2) * BK);
-      mfmas((NSTEP - 1) & 1);
-#pragma unroll
-      for (int t = 0; t < TM * TN; ++t) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (t < NREADS / 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        if (t < XLOADS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-      }
+    }
+    if constexpr (i == 3) f_rsrc(c);
+  };
+  auto fx_next = [&](auto i_) BEAGLE_INLINE_LAMBDA { f_next(i_, fx, NXS, XE); };
+  auto fw_next = [&](auto i_) BEAGLE_INLINE_LAMBDA { f_next(i_, fw, NWS, WE); };
+  // Request i of a step.  X and W in turn where W's slices last a step; X's slices may last two, and are then requested half in an
+  // odd step, half in the next one.  Where either's last two, X's in odd steps and W's in even ones.
+  auto f_issue = [&](auto odd_, auto i_) BEAGLE_INLINE_LAMBDA {
+    constexpr int i = decltype(i_)::value, odd = decltype(odd_)::value;
+    constexpr bool of_w = WS == 2 ? !odd : i & 1;
+    constexpr int n = WS == 2 ? i : (!of_w && XS == 2 && !odd ? XLD / 2 : 0) + (i >> 1);
+    if constexpr (of_w) request16(fw.rsrc, fw.dst + n * 2048, woff[n]);
+    else request16(fx.rsrc, fx.dst + n * 2048, xoff[n]);
+  };
+
+  // ---- fragment addresses (bytes) in the stages that are read next; everything else is an immediate
+  typedef __attribute__((address_space(3))) bf16_t* lds_bf16_ptr;
+  const int l16 = lane & 15, gi = lane >> 4;
+  constexpr int NXA = XK ? XS : NB, NWA = WK ? WS : NB;       // one per step of a slice, or per block
+  uint32_t xa[NXA], wa[NWA];
+  {
+    const uint32_t base = (uint32_t)(uintptr_t)(lds_bf16_ptr)smem;
+    auto rows = [&](int steps, int r0, int b) BEAGLE_INLINE_LAMBDA {
+      return ((r0 + l16) * KB * steps + ((steps == 2 ? (4 * b + gi) ^ ((l16 >> 1) & 7) : gi ^ row_swizzle(l16)) << 3)) * 2;
     };
-
-    __syncthreads();                        // previous segment: all reads done, both stages free
-    fetch_x(stage0, 0);
-    fetch_w(stage0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (fresh) { clear_acc(); fresh = false; }
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();
-    frags(stage0, 0, 0);
-    fetch_x(stage1, BK);
-    int kt = 0;
-#pragma unroll 1
-    for (; kt + 2 <= nk; kt += 2) {
-      slice(stage0, stage1, kt);
-      slice(stage1, stage0, kt + 1);
-    }
-    if (kt < nk) slice(stage0, stage1, kt);
-    __builtin_amdgcn_s_waitcnt(0x0F70);     // drain the look-ahead loads before the stages are reused
-  }
-  if (fresh) clear_acc();                   // no segment at all: C = 0 (+ residual)
-
-  // ---- residual operand: its tile goes HBM -> LDS in one burst (both stages are free now), so that the
-  // epilogue below does not pay one HBM round trip per store.  Chunk q = tid + 256 i (16 bytes) of the tile
-  // lands at 16 q; chunk position pc of row r holds global chunk pc ^ (r % CPR), which spreads the epilogue's
-  // same-column reads of 32 different rows over the banks.  The upper half of the rows lives in stage1.
-  constexpr int CPR = BN / 8;                      // 16-byte chunks per tile row
-  constexpr int RLOADS = BM * CPR / 256;           // per thread
-  const bool with_res = RES && !F32OUT && g.R != nullptr;
-  if (with_res) {
-    static_assert((BM / 2) * BN <= XE + WE, "half of the residual tile must fit one stage");
-    __syncthreads();                               // every wave is done reading the operand stages
-    const __amdgpu_buffer_rsrc_t rrs = make_rsrc(g.R, (int64_t)g.M * g.ldr * 2);
+    auto cols = [&](int rows, int r0, int b) BEAGLE_INLINE_LAMBDA {
+      const int kr = 8 * gi + (l16 >> 2), col = r0 + 16 * b + 4 * (l16 & 3);
+      return (kr * rows + ((((col >> 3) ^ krow_swizzle(kr)) << 3) | (col & 7))) * 2;
+    };
 #pragma unroll
-    for (int i = 0; i < RLOADS; ++i) {
-      const int q = tid + 256 * i, r = q / CPR, c = (q % CPR) ^ (r & (CPR - 1));
-      const int off = (int)(((int64_t)(m0 + r) * g.ldr + n0 + 8 * c) * 2);
-      bf16_t* st = i < RLOADS / 2 ? stage0 : stage1;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rrs, (lds_void_ptr)(st + ((i % (RLOADS / 2)) * 4 + wave) * 512), 16, off,
-                                               0, 0, 0);
-    }
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();
+    for (int b = 0; b < NXA; ++b) xa[b] = base + (XK ? rows(XS, wm, b) : cols(BM, wm, b));
+#pragma unroll
+    for (int b = 0; b < NWA; ++b) wa[b] = base + 2 * WBASE + (WK ? rows(WS, wn, b) : cols(BN, wn, b));
   }
+  int rx_st = 0, rx_step = XE * 2, rw_st = 0, rw_step = WE * 2;     // the stage they point into; bytes from there to the next
+  auto rx_next = [&]() BEAGLE_INLINE_LAMBDA { rx_st = rx_st + 1 == NXS ? 0 : rx_st + 1; rx_step = rx_st + 1 == NXS ? -(NXS - 1) * XE * 2 : XE * 2; };
+  auto rw_next = [&]() BEAGLE_INLINE_LAMBDA { rw_st = rw_st + 1 == NWS ? 0 : rw_st + 1; rw_step = rw_st + 1 == NWS ? -(NWS - 1) * WE * 2 : WE * 2; };
+  union frag_t { lds_u32x4_t u; struct { lds_u32x2_t a, b; } s; bf16x8_t v; };
+  // Fragments, in buffers that take turns.  Where W's slices last two steps, both steps' fragments are read in the odd step before,
+  // so that the stage is free a step earlier; three buffers, then, over a period of four steps.
+  frag_t xf[2][NB], wf[WS == 2 ? 3 : 2][NB];
+  constexpr int PERIOD = WS == 2 ? 4 : 2;
+  // LDS read n of step P of a period, X fragments first (one read each, or two transpose reads), then W's; behind the last read of
+  // an address, it moves on to the next stage
+  constexpr int NXR = XK ? NB : 2 * NB, NWR = WK ? NB : 2 * NB;
+  auto wbuf = [](int p) constexpr { return WS == 1 ? p % 2 : p % 2 == 0 ? 0 : p % 4 == 1 ? 1 : 2; };
+  auto read_one = [&](auto p_, auto n_) BEAGLE_INLINE_LAMBDA {
+    constexpr int nxt = decltype(p_)::value + 1, n = decltype(n_)::value, fx_ = nxt % 2;
+    if constexpr (n < NXR) {
+      if constexpr (XK) lds_read_b128<n * 16 * KB * XS * 2>(xf[fx_][n].u, xa[fx_]);
+      else if constexpr (n & 1) lds_read_tr16_b64<4 * BM * 2>(xf[fx_][n >> 1].s.b, xa[n >> 1]);
+      else lds_read_tr16_b64<0>(xf[fx_][n >> 1].s.a, xa[n >> 1]);
+      if constexpr (XK ? n == NXR - 1 : n & 1) xa[XK ? fx_ : n >> 1] += rx_step;
+    } else {
+      constexpr int half = (n - NXR) / NWR, k = (n - NXR) % NWR, fw_ = wbuf(nxt + half);
+      if constexpr (WK) lds_read_b128<k * 16 * KB * WS * 2>(wf[fw_][k].u, wa[half]);
+      else if constexpr (k & 1) lds_read_tr16_b64<4 * BN * 2>(wf[fw_][k >> 1].s.b, wa[k >> 1]);
+      else lds_read_tr16_b64<0>(wf[fw_][k >> 1].s.a, wa[k >> 1]);
+      if constexpr (WK ? k == NWR - 1 : k & 1) wa[WK ? half : k >> 1] += rw_step;
+    }
+  };
+  auto frags_wait = [&](auto p_) BEAGLE_INLINE_LAMBDA {                   // what step P read is in registers; nothing that uses it moves up
+    constexpr int nxt = decltype(p_)::value + 1;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      lds_tie(xf[nxt % 2][i].u);
+      if (WS == 1 || nxt % 2 == 0) lds_tie(wf[wbuf(nxt)][i].u);
+      if (WS == 2 && nxt % 2 == 0) lds_tie(wf[wbuf(nxt + 1)][i].u);
+    }
+  };
+  auto landed = [&](auto n_) BEAGLE_INLINE_LAMBDA {                       // all but the requests of the n youngest steps have landed, for every wave
+    constexpr int n = decltype(n_)::value * NLD;
+    __builtin_amdgcn_s_waitcnt((n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  // Step P of a period, KB k; on entry its fragments are in registers.  Behind the barrier the next step's operands are visible and
+  // every wave has this step's fragments, so the stages they came from are requested anew, two or three steps (of 1024 cycles of
+  // MFMAs) before they are waited for.  Every MFMA is pinned in its place, with at most one read, one request or one piece of a
+  // cursor's arithmetic behind it.
+  auto step = [&](auto p_) BEAGLE_INLINE_LAMBDA {
+    constexpr int P = decltype(p_)::value, odd = P & 1;
+    constexpr int NM = NB * NB, RE = NM / NLD;       // MFMAs, per request
+    constexpr int NR = NXR + (WS == 1 ? NWR : odd ? 2 * NWR : 0);
+    constexpr bool XEND = XS == 1 || (WS == 2 ? odd : !odd), WEND = WS == 1 || !odd;      // this step's requests end a slice
+    constexpr bool XREAD = XS == 1 || !odd, WREAD = WS == 1 || odd;                       // its reads do
+    if constexpr (WS == 1 || odd) landed(int_c<AHEAD - 1>{});
+    else __builtin_amdgcn_s_barrier();               // (an even step reads from slices that the odd one has waited for)
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, NM>([&](auto m_) BEAGLE_INLINE_LAMBDA {
+      constexpr int m = decltype(m_)::value, i = m / NB, j = (i & 1) ? NB - 1 - m % NB : m % NB;
+      mfma16(acc[i][j], wf[wbuf(P)][j].v, xf[odd][i].v);
+      constexpr int r0 = m * NR * 5 / (NM * 4), r1 = (m + 1) * NR * 5 / (NM * 4);      // reads behind the first four fifths
+      if constexpr (r0 < NR) static_for<r0, (r1 < NR ? r1 : NR)>([&](auto n_) BEAGLE_INLINE_LAMBDA { read_one(p_, n_); });
+      if constexpr (m % RE == 0) f_issue(int_c<odd>{}, int_c<m / RE>{});
+      if constexpr (T == 4) {
+        constexpr int px = m - (NM - (WS == 2 ? 1 : 2) * RE + 1), pw = m - (NM - RE + 1);
+        if constexpr (XEND && px >= 0 && px < PIECES) fx_next(int_c<px>{});
+        if constexpr (WEND && pw >= 0 && pw < PIECES) fw_next(int_c<pw>{});
+        if constexpr (XREAD && pw == PIECES) rx_next();
+        if constexpr (WREAD && pw == PIECES + 1) rw_next();
+      } else if constexpr (m == NM - 1) {
+        if constexpr (XEND) static_for<0, PIECES>(fx_next);
+        if constexpr (WEND) static_for<0, PIECES>(fw_next);
+        if constexpr (XREAD) rx_next();
+        if constexpr (WREAD) rw_next();
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    frags_wait(p_);
+  };
 
-  // ---- epilogue: lane holds C row m = .. + lane % 32; register e of tile (i, j)
-  // holds column n = .. + 8 * (e / 4) + 4 * (lane / 32) + e % 4.
+  // the requests of the steps that would have been: AHEAD, and before them the one that brings X's first (half) slice
+  f_rsrc(fx); f_rsrc(fw);
+  auto before = [&](auto odd_, auto with_w_) BEAGLE_INLINE_LAMBDA {
+    constexpr int odd = decltype(odd_)::value;
+    constexpr bool with_w = decltype(with_w_)::value;
+    static_for<0, NLD>([&](auto i_) BEAGLE_INLINE_LAMBDA { if constexpr (with_w || !(decltype(i_)::value & 1)) f_issue(odd_, i_); });
+    if constexpr (XS == 1 || (WS == 2 ? odd : !odd)) static_for<0, PIECES>(fx_next);
+    if constexpr (WS == 2 ? !odd : with_w) static_for<0, PIECES>(fw_next);
+  };
+  if constexpr (XS == 2) before(int_c<1>{}, int_c<(WS == 2)>{});
+  static_for<0, AHEAD + 1>([&](auto t_) BEAGLE_INLINE_LAMBDA { before(int_c<(decltype(t_)::value & 1)>{}, int_c<1>{}); });
+  __builtin_amdgcn_sched_barrier(0);
+  // (cleared behind the first requests, not ahead of them: 256 register writes per lane are 2 000 cycles that the trip hides)
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+  __builtin_amdgcn_sched_barrier(0);
+  landed(int_c<AHEAD>{});
+  static_for<0, NXR + WS * NWR>([&](auto n_) BEAGLE_INLINE_LAMBDA { read_one(int_c<PERIOD - 1>{}, n_); });
+  if constexpr (XS == 1) rx_next();
+  rw_next();
+  frags_wait(int_c<PERIOD - 1>{});
+  int kt = 0;
+#pragma unroll 1
+  for (; kt + PERIOD <= nk; kt += PERIOD) static_for<0, PERIOD>(step);
+  // (k-contiguous operands come in whole slices of BK)
+  if constexpr (WS == 2) { if (kt < nk) { step(int_c<0>{}); step(int_c<1>{}); } }
+  if constexpr (!XK) { if (kt < nk) step(int_c<0>{}); }
+  mfma_drain();
+  __builtin_amdgcn_s_waitcnt(0x0F70);                // the requests past the end (they write zeros) have landed
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- epilogue: lane holds C row m = .. + lane % 16; register e of tile (i, j) holds column n = .. + 4 * (lane / 16) + e.
   if constexpr (F32OUT) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int m = m0 + wm + 32 * i + (lane & 31);
+    for (int i = 0; i < NB; ++i) {
+      const int m = m0 + wm + 16 * i + l16;
       if (m >= g.M) continue;
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int n = n0 + wn + 32 * j + 8 * q + 4 * (lane >> 5);
-          if (n >= g.N) continue;
-          float4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-          *(float4*)((float*)g.C + (int64_t)m * g.ldc + n) = v;
-        }
+      for (int j = 0; j < NB; ++j) {
+        const int n = n0 + wn + 16 * j + 4 * gi;
+        if (n >= g.N) continue;
+        *(float4*)((float*)g.C + (int64_t)m * g.ldc + n) = float4{acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
       }
     }
   } else {
-    // bf16 output.  Straight from the registers a store instruction would carry 16 bytes for each of 32 rows, and
+    // bf16 output.  Straight from the registers a store instruction would carry 8 bytes for each of 64 places, and
     // the workgroup -- the only one on its CU -- spent 15 % of its life issuing them (measured: 27 500 cycles per
     // 256 x 256 tile against 2 350 per k slice).  Each wave therefore transposes its part of the tile through a
     // patch of LDS of its own (the operand stages are free now; two patches per stage) and writes whole row
     // segments: 16 bytes per lane, 64 / CPW rows per instruction.  Patch rows hold CPW 16-byte chunks; chunk c
     // of row r sits at position c ^ (r % CPW), which spreads the column-wise writes over the banks.
-    constexpr int CPW = 4 * TN;                      // chunks per patch row (32 TN columns)
-    constexpr int PROWS = 32 * TM;                   // patch rows
+    constexpr int CPW = 4 * T;                       // chunks per patch row (32 T columns)
+    constexpr int PROWS = 32 * T;                    // patch rows
     constexpr int RPI = 64 / CPW;                    // rows per store instruction
     static_assert(CPW <= 64 && 64 % CPW == 0 && PROWS % RPI == 0, "patch rows must tile a wave");
-    static_assert(2 * PROWS * CPW * 8 <= XE + WE, "two patches per stage");
-    if (with_res) {
-      // the residual tile occupies the stages: take it into the accumulators first, then let go of it
+    static_assert(4 * PROWS * CPW * 8 <= NXS * XE + NWS * WE, "four patches");
+    __syncthreads();                                 // every wave is done reading the stages
+    bf16_t* patch = smem + wave * (PROWS * CPW * 8);
+    const int pp = lane % CPW, rsub = lane / CPW;
+    if constexpr (RES) {
+      // the residual's part of the tile lands in the wave's patch (zeros where a problem has none), where a lane finds its own
+      // pieces and leaves the sums
+      const __amdgpu_buffer_rsrc_t rrs = make_rsrc(g.R, g.R ? (int64_t)g.M * g.ldr * 2 : 0);
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int rt = wm + 32 * i + (lane & 31);      // row inside the tile
-        const bf16_t* rrow = (rt < BM / 2 ? stage0 : stage1) + (rt % (BM / 2)) * BN;
+      for (int it = 0; it < PROWS / RPI; ++it) {
+        const int pr = it * RPI + rsub;
+        request16(rrs, patch + it * 512, (int)(((int64_t)(m0 + wm + pr) * g.ldr + n0 + wn + 8 * (pp ^ (pr & (CPW - 1)))) * 2));
+      }
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      asm volatile("" ::: "memory");
+    }
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+    for (int i = 0; i < NB; ++i) {
+      const int pr = 16 * i + l16;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int ct = wn + 32 * j + 8 * q;        // first column of this 8-column chunk inside the tile
-            const uint2 r = *(const uint2*)(rrow + (((ct >> 3) ^ (rt & (CPR - 1))) << 3) + 4 * (lane >> 5));
-            acc[i][j][4 * q] += __uint_as_float(r.x << 16); acc[i][j][4 * q + 1] += __uint_as_float(r.x & 0xffff0000u);
-            acc[i][j][4 * q + 2] += __uint_as_float(r.y << 16); acc[i][j][4 * q + 3] += __uint_as_float(r.y & 0xffff0000u);
-          }
+      for (int j = 0; j < NB; ++j) {
+        uint2* at = (uint2*)(patch + pr * (CPW * 8) + (((2 * j + (gi >> 1)) ^ (pr & (CPW - 1))) << 3) + 4 * (gi & 1));
+        f32x4_t c = acc[i][j];
+        if constexpr (RES) {
+          const uint2 r = *at;
+          c[0] += __uint_as_float(r.x << 16); c[1] += __uint_as_float(r.x & 0xffff0000u);
+          c[2] += __uint_as_float(r.y << 16); c[3] += __uint_as_float(r.y & 0xffff0000u);
+        }
+        *at = uint2{pack_bf16x2(c[0], c[1]), pack_bf16x2(c[2], c[3])};
       }
     }
-    __syncthreads();                                 // every wave is done reading the stages
-    bf16_t* patch = (wave < 2 ? stage0 : stage1) + (wave & 1) * (PROWS * CPW * 8);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int pr = 32 * i + (lane & 31);
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          uint2 v = {pack_bf16x2(acc[i][j][4 * q], acc[i][j][4 * q + 1]), pack_bf16x2(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3])};
-          *(uint2*)(patch + pr * (CPW * 8) + (((4 * j + q) ^ (pr & (CPW - 1))) << 3) + 4 * (lane >> 5)) = v;
-        }
-    }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own writes have landed; no other wave touches its patch
-    const int pp = lane % CPW, rsub = lane / CPW;
     // (the bounds in registers: otherwise every one of the 32 stores fetches them again from the arguments and waits)
     int gm = g.M, gn = g.N;
-    asm volatile("" : "+s"(gm), "+s"(gn));
+    int64_t ldc = g.ldc;
+    bf16_t* C = (bf16_t*)g.C;
+    asm volatile("" : "+s"(gm), "+s"(gn), "+s"(ldc), "+s"(C));
 #pragma unroll
     for (int it = 0; it < PROWS / RPI; ++it) {
       const int pr = it * RPI + rsub;
       const uint4 v = *(const uint4*)(patch + pr * (CPW * 8) + pp * 8);
       const int m = m0 + wm + pr, n = n0 + wn + 8 * (pp ^ (pr & (CPW - 1)));
-      if (m < gm && n < gn) { typedef unsigned int nt_u32x4 __attribute__((ext_vector_type(4))); const nt_u32x4 w = {v.x, v.y, v.z, v.w}; __builtin_nontemporal_store(w, (nt_u32x4*)((bf16_t*)g.C + (int64_t)m * g.ldc + n)); }
+      if (m < gm && n < gn) { typedef unsigned int nt_u32x4 __attribute__((ext_vector_type(4))); const nt_u32x4 w = {v.x, v.y, v.z, v.w}; __builtin_nontemporal_store(w, (nt_u32x4*)(C + (int64_t)m * ldc + n)); }
     }
   }
 }
