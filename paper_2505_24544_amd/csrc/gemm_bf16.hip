@@ -83,7 +83,50 @@ __device__ __forceinline__ int row_swizzle(int r) { return ((r >> 2) & 3) ^ ((r 
 __device__ __forceinline__ void mfma16(f32x4_t& acc, const bf16x8_t& a, const bf16x8_t& b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
+__device__ __forceinline__ void mfma32(f32x16_t& acc, const bf16x8_t& a, const bf16x8_t& b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
 __device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
+// Where the requests of one operand stand: a slice of both k segments after the other.  The descriptor starts at the current slice,
+// so the lanes' offsets are constants of the tile and a slice costs scalar arithmetic only, in pieces that fit between two MFMAs;
+// past the last slice it is empty.
+struct SliceCursor {
+  const char *at, *at2;                              // the slice's first byte for this tile; the second segment's
+  int left, left2, step;                             // bytes from there to the operand's end; bytes per slice
+  int t, sw, end;                                    // the slice's number; the number at which the operand changes; of slices
+  bf16_t *first, *dst;                               // where this wave's part of stage 0 lies, and of the slice's stage
+  __amdgpu_buffer_rsrc_t rsrc;
+  static constexpr int PIECES = 4;
+
+  // operand (p, then p2) of `rows` rows, tile from row r0, k per slice
+  __device__ __forceinline__ void init(const GemmArgs& g, const void* p, const void* p2, bool kmajor, int rows, int r0, int ld, int k, bf16_t* stage0) {
+    const int64_t skip = (kmajor ? (int64_t)r0 * ld : (int64_t)r0) * 2;
+    at = (const char*)p + skip; at2 = (const char*)p2 + skip;
+    left = (int)((int64_t)(kmajor ? rows : g.K) * ld * 2 - skip); left2 = (int)((int64_t)(kmajor ? rows : g.K2) * ld * 2 - skip);
+    step = kmajor ? k * 2 : k * ld * 2;
+    t = 0; sw = (g.K + k - 1) / k; end = sw + (p2 ? (g.K2 + k - 1) / k : 0);
+    first = dst = stage0;
+    // (in registers: the loop would fetch what it can from the arguments again, and wait for it)
+    asm volatile("" : "+s"(at2), "+s"(left2), "+s"(step), "+s"(end));
+    if (sw == 0) { at = at2; left = left2; sw = end; }
+    if (end == 0) left = 0;
+  }
+  __device__ __forceinline__ void describe() { rsrc = make_rsrc(at, max(left, 0)); }
+  // on to the next slice: pieces 0 .. PIECES - 1 in order; STAGES stages of E elements
+  template <int I, int STAGES, int E> __device__ __forceinline__ void next() {
+    if constexpr (I == 0) { at += step; left -= step; }
+    if constexpr (I == 1) dst = dst == first + (STAGES - 1) * E ? first : dst + E;
+    if constexpr (I == 2) {
+      if (++t == sw) {                               // on to the second segment, or past the end: nothing left
+        at = at2;
+        left = t < end ? left2 : 0;
+        sw = t < end ? end : -1;
+      }
+    }
+    if constexpr (I == 3) describe();
+  }
+};
 
 // Workgroup id -> (problem, tile index inside the problem).  Ids are dealt
 // round-robin to the 8 XCDs; every problem's tiles are split evenly over the
@@ -146,9 +189,7 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGrou
 
   f32x4_t acc[NB][NB];
 
-  // ---- request side: for either operand a cursor over the slices of both k segments.  The descriptors start at the current
-  // slice, so the lanes' offsets are constants of the tile and a slice costs scalar arithmetic only, in pieces that fit between
-  // two MFMAs; past the last slice they are empty.
+  // ---- request side: for either operand a cursor over the slices of both k segments, and the lanes' offsets from there
   constexpr int XLD = BM * XS / 64, WLD = BN * WS / 64, NLD = XLD / XS + WLD / WS;      // requests per thread: an X slice, a W slice, a step
   const int ldx = (int)g.lda, ldw = (int)g.ldb;
   int nk = (g.K + KB - 1) / KB + (g.A2 ? (g.K2 + KB - 1) / KB : 0);           // steps
@@ -163,44 +204,12 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGrou
   for (int i = 0; i < XLD; ++i) xoff[i] = chunk_off(tid + 256 * i, XK, true, BM, ldx);
 #pragma unroll
   for (int i = 0; i < WLD; ++i) woff[i] = chunk_off(tid + 256 * i, WK, WS == 2, BN, ldw);
-  // STG stages of E elements from `first`; what the loop needs stays in registers: it would fetch it from the arguments again
-  struct Cursor {
-    const char *at, *at2;                            // next slice's first byte; the second segment's
-    int left, left2, step;                           // bytes from there to the operand's end; per slice
-    int t, sw, end;                                  // the slice's number; the number at which the operand changes; of slices
-    bf16_t *first, *dst;                             // where this wave's part of the first stage lies, of the slice's stage
-    __amdgpu_buffer_rsrc_t rsrc;
-  } fx, fw;
-  auto f_init = [&](Cursor& c, const void* p, const void* p2, bool kmajor, int rows, int r0, int ld, int k, bf16_t* first) BEAGLE_INLINE_LAMBDA {
-    const int64_t skip = (kmajor ? (int64_t)r0 * ld : (int64_t)r0) * 2;
-    c.at = (const char*)p + skip; c.at2 = (const char*)p2 + skip;
-    c.left = (int)((int64_t)(kmajor ? rows : g.K) * ld * 2 - skip); c.left2 = (int)((int64_t)(kmajor ? rows : g.K2) * ld * 2 - skip);
-    c.step = kmajor ? k * 2 : k * ld * 2;
-    c.t = 0; c.sw = (g.K + k - 1) / k; c.end = c.sw + (p2 ? (g.K2 + k - 1) / k : 0);
-    c.first = c.dst = first;
-    asm volatile("" : "+s"(c.at2), "+s"(c.left2), "+s"(c.step), "+s"(c.end));
-    if (c.sw == 0) { c.at = c.at2; c.left = c.left2; c.sw = c.end; }
-    if (c.end == 0) c.left = 0;
-  };
-  f_init(fx, g.A, g.A2, XK, g.M, m0, ldx, KB * XS, smem + wave * 512);
-  f_init(fw, g.B, g.B2, WK, g.N, n0, ldw, KB * WS, smem + WBASE + wave * 512);
-  auto f_rsrc = [&](Cursor& c) BEAGLE_INLINE_LAMBDA { c.rsrc = make_rsrc(c.at, max(c.left, 0)); };
-  constexpr int PIECES = 4;
-  auto f_next = [&](auto i_, Cursor& c, int stages, int e) BEAGLE_INLINE_LAMBDA {
-    constexpr int i = decltype(i_)::value;
-    if constexpr (i == 0) { c.at += c.step; c.left -= c.step; }
-    if constexpr (i == 1) c.dst = c.dst == c.first + (stages - 1) * e ? c.first : c.dst + e;
-    if constexpr (i == 2) {
-      if (++c.t == c.sw) {                           // on to the second segment, or past the end: nothing left
-        c.at = c.at2;
-        c.left = c.t < c.end ? c.left2 : 0;
-        c.sw = c.t < c.end ? c.end : -1;
-      }
-    }
-    if constexpr (i == 3) f_rsrc(c);
-  };
-  auto fx_next = [&](auto i_) BEAGLE_INLINE_LAMBDA { f_next(i_, fx, NXS, XE); };
-  auto fw_next = [&](auto i_) BEAGLE_INLINE_LAMBDA { f_next(i_, fw, NWS, WE); };
+  SliceCursor fx, fw;
+  fx.init(g, g.A, g.A2, XK, g.M, m0, ldx, KB * XS, smem + wave * 512);
+  fw.init(g, g.B, g.B2, WK, g.N, n0, ldw, KB * WS, smem + WBASE + wave * 512);
+  constexpr int PIECES = SliceCursor::PIECES;
+  auto fx_next = [&](auto i_) BEAGLE_INLINE_LAMBDA { fx.next<decltype(i_)::value, NXS, XE>(); };
+  auto fw_next = [&](auto i_) BEAGLE_INLINE_LAMBDA { fw.next<decltype(i_)::value, NWS, WE>(); };
   // Request i of a step.  X and W in turn where W's slices last a step; X's slices may last two, and are then requested half in an
   // odd step, half in the next one.  Where either's last two, X's in odd steps and W's in even ones.
   auto f_issue = [&](auto odd_, auto i_) BEAGLE_INLINE_LAMBDA {
@@ -311,7 +320,7 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGrou
   };
 
   // the requests of the steps that would have been: AHEAD, and before them the one that brings X's first (half) slice
-  f_rsrc(fx); f_rsrc(fw);
+  fx.describe(); fw.describe();
   auto before = [&](auto odd_, auto with_w_) BEAGLE_INLINE_LAMBDA {
     constexpr int odd = decltype(odd_)::value;
     constexpr bool with_w = decltype(with_w_)::value;
@@ -424,16 +433,19 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGrou
 // behind the loop.  Per slice of 64 k (128 x 128 tile, X k-contiguous, W row-contiguous, transpose reads at half rate): 768
 // LDS cycles of reads + 256 of arriving data with four 64 x 64 waves, 384 + 256 this way, against 512 of MFMA.
 // And a small tile's slice is over in some 700 cycles, less than a trip to memory: the slices go through a ring of NST
-// LDS stages (four of 32 KB, or three of 48 KB), requested NST slices ahead, with explicit LDS reads and counted
-// waits (the compiler would wait for every request before any LDS read).  Fragments of the next step are read behind
-// the MFMAs of the current one; one barrier per slice.
+// LDS stages (five of 32 KB, or three of 48 KB), requested anew as soon as every wave has a slice's fragments, with explicit LDS
+// reads and counted waits (the compiler would wait for every request before any LDS read).  Fragments of the next step are read
+// behind the MFMAs of the current one; one barrier per slice.  Reads, requests and the cursors' scalar arithmetic each have
+// their place behind an MFMA: in front of the barrier and behind it they cost 100 - 190 cycles per step.  Cycles per slice without
+// loads / with loads that hit L2 / from memory, at 777 - 1531 rows of 4096 over 4096: 128 x 128 670 / 810 / 850 - 950 before, 560 /
+// 640 / 690 - 840 now; 256 x 128 1400 / 1430 / 1420 - 1540 before, 1140 / 1090 / 1110 - 1370 now.
 // ---------------------------------------------------------------------------
 template <int WM, int WN, bool XK, bool WK, bool F32OUT>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp) {
   constexpr int BM = 128 * WM, BN = 128 * WN;
   constexpr int KG = 4 / (WM * WN), KS = 4 / KG;    // waves per tile part; k steps of a slice per wave
   constexpr int XE = BM * BK, WE = BN * BK, SE = XE + WE;
-  constexpr int NST = SE * 2 * 4 <= 128 * 1024 ? 4 : 3;
+  constexpr int NST = KG == 4 ? 5 : 3;
   __shared__ __attribute__((aligned(1024))) bf16_t smem[NST * SE];
 
   int pi, m0, n0;
@@ -443,52 +455,35 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
   const int kg = wave % KG, wmn = wave / KG;
   const int wm = (WM == 2 ? wmn : 0) * 128, wn = (WN == 2 ? wmn : 0) * 128;
 
-  // ---- request side: a cursor over the slices of both k segments.  The descriptors start at the current slice, so the
-  // lanes' offsets are constants of the tile and a slice costs scalar arithmetic only; past the last slice they are empty.
-  const int nk1 = (g.K + BK - 1) / BK, nk = nk1 + (g.A2 ? (g.K2 + BK - 1) / BK : 0);
-  constexpr int XLD = BM / 32, WLD = BN / 32;        // requests per thread and slice
+  // ---- request side
+  constexpr int XLD = BM / 32, WLD = BN / 32, NLD = XLD + WLD;      // requests per thread and slice
   const int ldx = (int)g.lda, ldw = (int)g.ldb;
   int xoff[XLD], woff[WLD];
-#pragma unroll
-  for (int i = 0; i < XLD; ++i) {
-    const int q = tid + 256 * i;
-    if (XK) { const int r = q >> 3; xoff[i] = (r * ldx + 8 * ((q & 7) ^ ((r >> 1) & 7))) * 2; }
-    else { constexpr int CPR = BM / 8; const int k = q / CPR; xoff[i] = (k * ldx + 8 * ((q % CPR) ^ ((k & 3) << 2))) * 2; }
-  }
-#pragma unroll
-  for (int i = 0; i < WLD; ++i) {
-    const int q = tid + 256 * i;
-    if (WK) { const int r = q >> 3; woff[i] = (r * ldw + 8 * ((q & 7) ^ ((r >> 1) & 7))) * 2; }
-    else { constexpr int CPR = BN / 8; const int k = q / CPR; woff[i] = (k * ldw + 8 * ((q % CPR) ^ ((k & 3) << 2))) * 2; }
-  }
-  const char *fx, *fw;                               // current slice of this tile's rows
-  int64_t xleft, wleft;                              // bytes from there to the operand's end
-  auto seek = [&](const void* X, const void* W, int K) BEAGLE_INLINE_LAMBDA {
-    const int64_t xo = XK ? (int64_t)m0 * ldx * 2 : (int64_t)m0 * 2, wo = WK ? (int64_t)n0 * ldw * 2 : (int64_t)n0 * 2;
-    fx = (const char*)X + xo; xleft = (int64_t)(XK ? g.M : K) * ldx * 2 - xo;
-    fw = (const char*)W + wo; wleft = (int64_t)(WK ? g.N : K) * ldw * 2 - wo;
+  auto chunk_off = [&](int q, bool kmajor, int rows, int ld) BEAGLE_INLINE_LAMBDA {                // 16-byte chunk q of an operand's slice
+    if (kmajor) { const int r = q >> 3; return (r * ld + 8 * ((q & 7) ^ ((r >> 1) & 7))) * 2; }
+    const int cpr = rows / 8, k = q / cpr;
+    return (k * ld + 8 * ((q % cpr) ^ ((k & 3) << 2))) * 2;
   };
-  seek(g.A, g.B, g.K);
-  const int64_t xstep = XK ? BK * 2 : (int64_t)BK * ldx * 2, wstep = WK ? BK * 2 : (int64_t)BK * ldw * 2;
-  int f_t = 0, f_st = 0;                             // next slice to request, its stage
-  __amdgpu_buffer_rsrc_t xrs, wrs;
-  bf16_t* f_dst;
-  auto f_begin = [&]() BEAGLE_INLINE_LAMBDA {
-    if (f_t == nk1 && f_t < nk) seek(g.A2, g.B2, g.K2);
-    xrs = make_rsrc(fx, f_t < nk && xleft > 0 ? xleft : 0);
-    wrs = make_rsrc(fw, f_t < nk && wleft > 0 ? wleft : 0);
-    f_dst = smem + f_st * SE + wave * 512;
-    fx += xstep; xleft -= xstep; fw += wstep; wleft -= wstep;
-    ++f_t; f_st = f_st + 1 == NST ? 0 : f_st + 1;
-  };
+#pragma unroll
+  for (int i = 0; i < XLD; ++i) xoff[i] = chunk_off(tid + 256 * i, XK, BM, ldx);
+#pragma unroll
+  for (int i = 0; i < WLD; ++i) woff[i] = chunk_off(tid + 256 * i, WK, BN, ldw);
+  int nk = (g.K + BK - 1) / BK + (g.A2 ? (g.K2 + BK - 1) / BK : 0);
+  SliceCursor fx, fw;
+  fx.init(g, g.A, g.A2, XK, g.M, m0, ldx, BK, smem + wave * 512);
+  fw.init(g, g.B, g.B2, WK, g.N, n0, ldw, BK, smem + XE + wave * 512);
+  constexpr int PIECES = SliceCursor::PIECES;
   auto f_issue = [&](auto i_) BEAGLE_INLINE_LAMBDA {
     constexpr int i = decltype(i_)::value;
-    if constexpr (i < XLD) request16(xrs, f_dst + i * 2048, xoff[i]);
-    else request16(wrs, f_dst + XE + (i - XLD) * 2048, woff[i - XLD]);
+    if constexpr (i < XLD) request16(fx.rsrc, fx.dst + i * 2048, xoff[i]);
+    else request16(fw.rsrc, fw.dst + (i - XLD) * 2048, woff[i - XLD]);
   };
-  constexpr int NLD = XLD + WLD;
+  auto f_next = [&](auto i_) BEAGLE_INLINE_LAMBDA {
+    constexpr int i = decltype(i_)::value;
+    if constexpr (i < PIECES) fx.next<i, NST, SE>(); else fw.next<i - PIECES, NST, SE>();
+  };
 
-  // ---- fragment addresses (bytes from the start of a stage); everything else is an immediate
+  // ---- fragment addresses (bytes) in the stage that is read next; everything else is an immediate
   typedef __attribute__((address_space(3))) bf16_t* lds_bf16_ptr;
   const uint32_t base = (uint32_t)(uintptr_t)(lds_bf16_ptr)smem;
   const int ql = lane & 31, hf = lane >> 5;
@@ -516,19 +511,25 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
   }
   union frag_t { lds_u32x4_t u; struct { lds_u32x2_t a, b; } s; bf16x8_t v; };
   frag_t xf[2][4], wf[2][4];
-  // LDS read n of a step: X fragments first (one read each, or two transpose reads), then W's
-  constexpr int NXR = XK ? 4 : 8, NWR = WK ? 4 : 8;
-  auto read_one = [&](auto fb_, auto s_, auto n_, uint32_t st) BEAGLE_INLINE_LAMBDA {
+  int r_st = 0, r_step = SE * 2;                     // the stage the addresses point into; bytes from there to the next
+  auto r_next = [&]() BEAGLE_INLINE_LAMBDA { r_st = r_st + 1 == NST ? 0 : r_st + 1; r_step = r_st + 1 == NST ? -(NST - 1) * SE * 2 : SE * 2; };
+  // LDS read n of step s of a slice: X fragments first (one read each, or two transpose reads), then W's; behind a slice's last read
+  // of an address, it moves on to the next stage
+  constexpr int NXR = XK ? 4 : 8, NWR = WK ? 4 : 8, NR = NXR + NWR;
+  auto read_one = [&](auto fb_, auto s_, auto n_) BEAGLE_INLINE_LAMBDA {
     constexpr int fb = decltype(fb_)::value, s = decltype(s_)::value, n = decltype(n_)::value;
     if constexpr (n < NXR) {
-      if constexpr (XK) lds_read_b128<0>(xf[fb][n].u, xa[s][n] + st);
-      else if constexpr (n & 1) lds_read_tr16_b64<s * 16 * BM * 2 + 4 * BM * 2>(xf[fb][n >> 1].s.b, xa[0][n >> 1] + st);
-      else lds_read_tr16_b64<s * 16 * BM * 2>(xf[fb][n >> 1].s.a, xa[0][n >> 1] + st);
+      if constexpr (XK) lds_read_b128<0>(xf[fb][n].u, xa[s][n]);
+      else if constexpr (n & 1) lds_read_tr16_b64<s * 16 * BM * 2 + 4 * BM * 2>(xf[fb][n >> 1].s.b, xa[0][n >> 1]);
+      else lds_read_tr16_b64<s * 16 * BM * 2>(xf[fb][n >> 1].s.a, xa[0][n >> 1]);
+      if constexpr (XK) xa[s][n] += r_step;
+      else if constexpr (s == KS - 1 && (n & 1)) xa[0][n >> 1] += r_step;
     } else {
       constexpr int k = n - NXR;
-      if constexpr (WK) lds_read_b128<k * 32 * BK * 2>(wf[fb][k].u, wa[s] + st);
-      else if constexpr (k & 1) lds_read_tr16_b64<s * 16 * BN * 2 + 4 * BN * 2>(wf[fb][k >> 1].s.b, wa[k >> 1] + st);
-      else lds_read_tr16_b64<s * 16 * BN * 2>(wf[fb][k >> 1].s.a, wa[k >> 1] + st);
+      if constexpr (WK) lds_read_b128<k * 32 * BK * 2>(wf[fb][k].u, wa[s]);
+      else if constexpr (k & 1) lds_read_tr16_b64<s * 16 * BN * 2 + 4 * BN * 2>(wf[fb][k >> 1].s.b, wa[k >> 1]);
+      else lds_read_tr16_b64<s * 16 * BN * 2>(wf[fb][k >> 1].s.a, wa[k >> 1]);
+      if constexpr (WK ? k == NWR - 1 : s == KS - 1 && (k & 1)) wa[WK ? s : k >> 1] += r_step;
     }
   };
   auto frags_wait = [&](auto fb_) BEAGLE_INLINE_LAMBDA {                  // the step's fragments are in registers; nothing that uses them moves up
@@ -543,9 +544,15 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
   auto quads = [&](auto f) BEAGLE_INLINE_LAMBDA {
     static_for<0, 16>([&](auto b_) BEAGLE_INLINE_LAMBDA { f(int_c<(decltype(b_)::value >> 2)>{}, int_c<(decltype(b_)::value & 3)>{}); });
   };
-  // the first NST slices; the accumulators are cleared while they travel
+  // The requests of a slice go evenly over the MFMAs from a slice's last step to the next one's, but for the place of the cursors'
+  // pieces behind them; FIRST of them fall in that last step.
+  constexpr int SLOTS = 16 * KS, RS = KS == 1 ? SLOTS - 4 : SLOTS - 8, FIRST = KS == 1 ? NLD : 16 * NLD / RS;
+  // the first slices, as far as a last step ahead of them would have come; the accumulators are cleared while they travel
+  fx.describe(); fw.describe();
 #pragma unroll 1
-  for (int t = 0; t < NST; ++t) { f_begin(); static_for<0, NLD>(f_issue); }
+  for (int t = 0; t < NST - 1; ++t) { static_for<0, NLD>(f_issue); static_for<0, 2 * PIECES>(f_next); }
+  static_for<0, FIRST>(f_issue);
+  if constexpr (KS == 1) static_for<0, 2 * PIECES>(f_next);
   __builtin_amdgcn_sched_barrier(0);
   static_for<0, 16>([&](auto b_) BEAGLE_INLINE_LAMBDA {
     constexpr int b = decltype(b_)::value;
@@ -554,56 +561,47 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
   });
   __builtin_amdgcn_sched_barrier(0);
 
-  auto wait_slice = [&]() BEAGLE_INLINE_LAMBDA {                          // all but the NST - 2 youngest slices have landed, for every wave
-    constexpr int n = (NST - 2) * NLD;
+  auto landed = [&](auto n_) BEAGLE_INLINE_LAMBDA {                       // all but the n youngest requests have landed, for every wave
+    constexpr int n = decltype(n_)::value;
     __builtin_amdgcn_s_waitcnt((n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14));
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
-  uint32_t rst = 0;                                  // stage of the slice being read, in bytes
-  // One slice; on entry its first step's fragments are in registers (parity P).  In its last step the next slice has
-  // landed for everybody, every wave has this slice's fragments in registers, and this slice's stage is requested anew.
+  // One slice; on entry its first step's fragments are in registers (parity P).  Before its last step the next slice has
+  // landed for everybody and every wave has this slice's fragments in registers: its stage is requested anew, from that step to
+  // the next slice's last.  Every MFMA is pinned in its place, with at most one or two reads, one request and one piece of the
+  // cursors' arithmetic behind it.
   auto slice = [&](auto par_) BEAGLE_INLINE_LAMBDA {
     constexpr int P = decltype(par_)::value;
     static_for<0, KS>([&](auto s_) BEAGLE_INLINE_LAMBDA {
       constexpr int s = decltype(s_)::value, fb = (P + s) & 1;
       constexpr bool last = s + 1 == KS;
       constexpr int ns = last ? 0 : s + 1;
-      if constexpr (last) {
-        wait_slice();
-        f_begin();
-        rst = rst + 2 * SE == NST * 2 * SE ? 0 : rst + 2 * SE;
-      }
-      const uint32_t st = rst;
+      if constexpr (last) landed(int_c<(NST - 2) * NLD>{});
       __builtin_amdgcn_sched_barrier(0);
       static_for<0, 16>([&](auto m_) BEAGLE_INLINE_LAMBDA {
-        constexpr int m = decltype(m_)::value, i = m >> 2, j = m & 3;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[fb][j].v, xf[fb][i].v, acc[i][j], 0, 0, 0);
-        // the next step's reads behind the first eight MFMAs, the requests behind the last ones
-        constexpr int r0 = m * (NXR + NWR) / 8, r1 = (m + 1) * (NXR + NWR) / 8;
-        if constexpr (m < 8) static_for<r0, r1>([&](auto n_) BEAGLE_INLINE_LAMBDA { read_one(int_c<(fb ^ 1)>{}, int_c<ns>{}, n_, st); });
-        // one request every KS * 16 / NLD MFMAs, from the barrier on: a wave gets rid of a request in about a hundred
-        // cycles, and issued faster than that it only stands in front of the MFMAs behind it
+        constexpr int m = decltype(m_)::value, i = m >> 2, j = (i & 1) ? 3 - (m & 3) : m & 3;
+        mfma32(acc[i][j], wf[fb][j].v, xf[fb][i].v);
+        constexpr int r0 = m * NR * 5 / 64, r1 = (m + 1) * NR * 5 / 64;      // reads behind the first four fifths
+        if constexpr (r0 < NR) static_for<r0, (r1 < NR ? r1 : NR)>([&](auto n_) BEAGLE_INLINE_LAMBDA { read_one(int_c<(fb ^ 1)>{}, int_c<ns>{}, n_); });
         constexpr int mm = last ? m : 16 + 16 * s + m;
-        constexpr int d0 = (mm * NLD + 16 * KS - 1) / (16 * KS), d1 = ((mm + 1) * NLD + 16 * KS - 1) / (16 * KS);
-        if constexpr (d1 > d0) f_issue(int_c<d0>{});
+        constexpr int d0 = mm * NLD / RS, d1 = (mm + 1) * NLD / RS;
+        if constexpr (d0 < NLD) static_for<d0, (d1 < NLD ? d1 : NLD)>(f_issue);
+        constexpr int pc = mm - RS, PP = KS == 1 ? 2 : 1;
+        if constexpr (pc >= 0) { static_for<pc * PP, pc * PP + PP>(f_next); }
+        if constexpr (s == 0 && m == 15) r_next();
         __builtin_amdgcn_sched_barrier(0);
       });
       frags_wait(int_c<(fb ^ 1)>{});
     });
   };
-  static_assert(NLD <= 16, "at most one request per MFMA");
+  static_assert(2 * PIECES == 8, "as many places behind the last request");
 
-  {
-    constexpr int n = (NST - 1) * NLD;               // slice 0
-    __builtin_amdgcn_s_waitcnt((n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14));
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    static_for<0, NXR + NWR>([&](auto n_) BEAGLE_INLINE_LAMBDA { read_one(int_c<0>{}, int_c<0>{}, n_, 0u); });
-    frags_wait(int_c<0>{});
-  }
+  landed(int_c<(NST - 2) * NLD + FIRST>{});          // slice 0
+  static_for<0, NR>([&](auto n_) BEAGLE_INLINE_LAMBDA { read_one(int_c<0>{}, int_c<0>{}, n_); });
+  if constexpr (KS == 1) r_next();
+  frags_wait(int_c<0>{});
   int t = 0;
   if constexpr (KS % 2 == 0) {
 #pragma unroll 1
@@ -613,6 +611,8 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
     for (; t + 2 <= nk; t += 2) { slice(int_c<0>{}); slice(int_c<1>{}); }
     if (t < nk) slice(int_c<0>{});
   }
+  mfma_drain();
+  __builtin_amdgcn_sched_barrier(0);
 
   // ---- the KG waves of a tile part exchange sums: each ends up with 128 / KG of the rows, summed in a fixed order
   constexpr int SLOT = OWN * 4096;                   // floats of one wave's slot
