@@ -355,31 +355,50 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGrou
   __builtin_amdgcn_sched_barrier(0);
 
   // ---- epilogue: lane holds C row m = .. + lane % 16; register e of tile (i, j) holds column n = .. + 4 * (lane / 16) + e.
+  // Straight from the registers a store instruction would carry 8 (float: 64) bytes for each of 64 (16) places, and the workgroup --
+  // the only one on its CU -- spent 15 % of its life issuing them (27 500 cycles per 256 x 256 tile of bf16 against 2 300 per 64 k).
+  // Each wave therefore transposes its part of the tile through a patch of LDS of its own and writes whole row segments, 16
+  // bytes per lane.  Patch rows are made of 16-byte chunks; chunk c of row r sits at position c ^ (r % chunks), which spreads the
+  // column-wise writes over the banks.
+  // (the bounds in registers: otherwise every one of the stores fetches them again from the arguments and waits)
+  int gm = g.M, gn = g.N;
+  int64_t ldc = g.ldc;
+  void* cptr = g.C;
+  asm volatile("" : "+s"(gm), "+s"(gn), "+s"(ldc), "+s"(cptr));
+  typedef unsigned int nt_u32x4 __attribute__((ext_vector_type(4)));
+  __syncthreads();                                   // every wave is done reading the stages
   if constexpr (F32OUT) {
+    constexpr int CPW = 8 * T, PROWS = 64, RPI = 64 / CPW;      // chunks per row, rows of a patch (T / 2 in turn), rows per store
+    static_assert(4 * PROWS * CPW * 8 <= NXS * XE + NWS * WE, "four patches");
+    float* patch = (float*)smem + wave * (PROWS * CPW * 4);
+    const int pp = lane % CPW, rsub = lane / CPW;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int m = m0 + wm + 16 * i + l16;
-      if (m >= g.M) continue;
+    for (int part = 0; part < T / 2; ++part) {
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const int n = n0 + wn + 16 * j + 4 * gi;
-        if (n >= g.N) continue;
-        *(float4*)((float*)g.C + (int64_t)m * g.ldc + n) = float4{acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+      for (int i = 0; i < 4; ++i) {
+        const int pr = 16 * i + l16;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          const f32x4_t& c = acc[4 * part + i][j];
+          *(float4*)(patch + pr * (CPW * 4) + (((4 * j + gi) ^ (pr & (CPW - 1))) << 2)) = float4{c[0], c[1], c[2], c[3]};
+        }
       }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // the wave's own writes have landed; no other wave touches its patch
+#pragma unroll
+      for (int it = 0; it < PROWS / RPI; ++it) {
+        const int pr = it * RPI + rsub;
+        const nt_u32x4 v = *(const nt_u32x4*)(patch + pr * (CPW * 4) + pp * 4);
+        const int m = m0 + wm + 64 * part + pr, n = n0 + wn + 4 * (pp ^ (pr & (CPW - 1)));
+        if (m < gm && n < gn) __builtin_nontemporal_store(v, (nt_u32x4*)((float*)cptr + (int64_t)m * ldc + n));
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
   } else {
-    // bf16 output.  Straight from the registers a store instruction would carry 8 bytes for each of 64 places, and
-    // the workgroup -- the only one on its CU -- spent 15 % of its life issuing them (measured: 27 500 cycles per
-    // 256 x 256 tile against 2 350 per k slice).  Each wave therefore transposes its part of the tile through a
-    // patch of LDS of its own (the operand stages are free now; two patches per stage) and writes whole row
-    // segments: 16 bytes per lane, 64 / CPW rows per instruction.  Patch rows hold CPW 16-byte chunks; chunk c
-    // of row r sits at position c ^ (r % CPW), which spreads the column-wise writes over the banks.
     constexpr int CPW = 4 * T;                       // chunks per patch row (32 T columns)
     constexpr int PROWS = 32 * T;                    // patch rows
     constexpr int RPI = 64 / CPW;                    // rows per store instruction
     static_assert(CPW <= 64 && 64 % CPW == 0 && PROWS % RPI == 0, "patch rows must tile a wave");
     static_assert(4 * PROWS * CPW * 8 <= NXS * XE + NWS * WE, "four patches");
-    __syncthreads();                                 // every wave is done reading the stages
     bf16_t* patch = smem + wave * (PROWS * CPW * 8);
     const int pp = lane % CPW, rsub = lane / CPW;
     if constexpr (RES) {
@@ -410,17 +429,12 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGrou
       }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the wave's own writes have landed; no other wave touches its patch
-    // (the bounds in registers: otherwise every one of the 32 stores fetches them again from the arguments and waits)
-    int gm = g.M, gn = g.N;
-    int64_t ldc = g.ldc;
-    bf16_t* C = (bf16_t*)g.C;
-    asm volatile("" : "+s"(gm), "+s"(gn), "+s"(ldc), "+s"(C));
 #pragma unroll
     for (int it = 0; it < PROWS / RPI; ++it) {
       const int pr = it * RPI + rsub;
-      const uint4 v = *(const uint4*)(patch + pr * (CPW * 8) + pp * 8);
+      const nt_u32x4 v = *(const nt_u32x4*)(patch + pr * (CPW * 8) + pp * 8);
       const int m = m0 + wm + pr, n = n0 + wn + 8 * (pp ^ (pr & (CPW - 1)));
-      if (m < gm && n < gn) { typedef unsigned int nt_u32x4 __attribute__((ext_vector_type(4))); const nt_u32x4 w = {v.x, v.y, v.z, v.w}; __builtin_nontemporal_store(w, (nt_u32x4*)(C + (int64_t)m * ldc + n)); }
+      if (m < gm && n < gn) __builtin_nontemporal_store(v, (nt_u32x4*)((bf16_t*)cptr + (int64_t)m * ldc + n));
     }
   }
 }
