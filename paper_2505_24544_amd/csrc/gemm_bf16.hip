@@ -779,22 +779,20 @@ static void launch_ksplit(const GemmGroup& grp, hipStream_t s) {
 }
 
 // Tile choice: what a launch takes with each tile size, from the number of tiles, the depth of each problem and how full
-// the rounds of 256 workgroups (one per CU) are.  A round costs a fixed part (first slices, exchange, stores) and so much
-// per slice of 64 k, less when part of the chip is idle.  Fitted to launches timed on their own, microseconds:
-//   256 x 256: K 777 full 28; K 4096 full 107-122, a quarter full 76; K 11008 three quarters full 243
-//   256 x 128, 128 x 256: K 777 full 20; K 4096 full 64-70, half full 52
-//   128 x 128: K 777 full 13; K 4096 full 40, 7/8 full 36 (four waves of 64 x 64 per tile took 59)
-// Large problems come out at 256 x 256 by their operand traffic alone (1.30 PFLOP/s against 0.95 and 0.80).
-// Tiles of 128 x 128 over a short contraction take four waves of 64 x 64 instead (TILE_128_SHALLOW): no ring to fill and no sums
-// to exchange, and half the accumulators to clear.  Two products of 768 x 1024 over K 128 / 512 / 1024, us: 10.2 / 12.6 / 15.8 with waves
-// that split k -> 5.9 / 8.7 / 12.3; at K 1536 both take 19.3, at 2048 22.7 -> 24.5.
+// the rounds (one workgroup per CU; two of the smallest kind) are.  A round costs a fixed part (first slices, exchange, stores) and
+// so much per slice of 64 k, less when part of the chip is idle.  Fitted to 98 launches timed on their own (256 - 4096 rows of 4096
+// over 256 - 11008, every storage order), to 6 - 10 % each; the choice is on average 0.6 % above the best tile's time, the worst
+// 10 %.  Large problems come out at 256 x 256 by their operand traffic alone (1.45 PFLOP/s against 1.12 and 0.85).
+// Tiles of 128 x 128 over a short contraction may take four waves of 64 x 64 instead (TILE_128_SHALLOW): no sums to exchange, half the
+// accumulators to clear, and two workgroups per CU; but twice the LDS reads.  256 rows of 4096 over 256 / 1024 / 2048 / 4096, us:
+// 11.9 / 15.6 / 21.0 / 31 with waves that split k, 8.5 / 13.2 / 19.7 / 37; 1024 over 2048 X^T Y 25.6, 25.7.
 constexpr int SHALLOW = 16;                         // slices of 64 k
 enum TileSize { TILE_256, TILE_256x128, TILE_128x256, TILE_128, TILE_128_SHALLOW };
 struct TileChoice { TileSize tile; double us; };
-struct TileCost { int bm, bn; double fixed, slice, slice_full; };
+struct TileCost { int bm, bn; double at_once, fixed, slice, slice_full; };
 
 // Problems of different depth (dXkv contracts over two matrices, dXq over one): their tiles are dealt out in problem order,
-// each to the CU that is free first, so shallow tiles fill up behind deep ones, and a launch of less than a round lasts as long
+// each to the place that is free first, so shallow tiles fill up behind deep ones, and a launch of less than a round lasts as long
 // as its deepest tile.  By the mean depth 1024 positions at 5120 channels took 160 large tiles for their input gradients (whole
 // backward 628 us, now 256 x 128 and 557), and the 320 tiles of 2500 positions were cut although their shallow half fills up the
 // second round (866 -> 839); simulation step of 3048 positions 1386 -> 1351, 3 of 500 at 2048 channels 239 -> 226.
@@ -803,10 +801,10 @@ static double uneven_us(const TileCost& c, const double* tiles, const double* de
   double total = 0.0;
   for (int i = 0; i < count; ++i) total += tiles[i];
   if (total > 4096.0) return -1.0;
-  const double fill = total < 256.0 ? total / 256.0 : 1.0;
+  const double fill = total < c.at_once ? total / c.at_once : 1.0;
   struct { double at, cus; } free_at[64];            // CUs by the time they are free
   int n = 1;
-  free_at[0] = {0.0, 256.0};
+  free_at[0] = {0.0, c.at_once};
   double end = 0.0;
   for (int i = 0; i < count; ++i) {
     const double us = c.fixed + depth[i] * (c.slice + c.slice_full * fill);
@@ -828,10 +826,11 @@ static double uneven_us(const TileCost& c, const double* tiles, const double* de
 }
 
 static TileChoice choose_tile(const GemmGroup& grp) {
-  static const TileCost costs[] = {{256, 256, 8.8, 0.90, 0.65}, {256, 128, 8.3, 0.57, 0.38}, {128, 256, 8.3, 0.57, 0.38}, {128, 128, 6.1, 0.38, 0.16}};
+  static const TileCost costs[] = {{256, 256, 256.0, 7.0, 0.91, 0.46}, {256, 128, 256.0, 6.7, 0.45, 0.38}, {128, 256, 256.0, 6.7, 0.45, 0.38},
+                                   {128, 128, 256.0, 5.9, 0.29, 0.21}, {128, 128, 512.0, 2.7, 0.285, 0.66}};      // by TileSize
   int best = 0;
-  double best_us = 0.0, best_depth = 0.0;
-  for (int c = 0; c < 4; ++c) {
+  double best_us = 0.0;
+  for (int c = 0; c < 5; ++c) {
     double tiles = 0.0, slices = 0.0;               // slices: over all tiles
     double each[4], deep[4];                        // tiles and depth of each problem
     bool even = true;
@@ -845,16 +844,16 @@ static TileChoice choose_tile(const GemmGroup& grp) {
       slices += t * deep[i];
     }
     if (tiles == 0.0) continue;
-    const double depth = slices / tiles, full = floor(tiles / 256.0), rest = tiles / 256.0 - full;
+    const double depth = slices / tiles, full = floor(tiles / costs[c].at_once), rest = tiles / costs[c].at_once - full;
+    if (c == TILE_128_SHALLOW && depth > SHALLOW) continue;
     double us = full * (costs[c].fixed + depth * (costs[c].slice + costs[c].slice_full));
     if (rest > 0.0) us += costs[c].fixed + depth * (costs[c].slice + costs[c].slice_full * rest);
     if (!even) {
       const double uneven = uneven_us(costs[c], each, deep, grp.count);
       if (uneven >= 0.0) us = uneven;
     }
-    if (c == 0 || us < best_us) { best = c; best_us = us; best_depth = depth; }
+    if (c == 0 || us < best_us) { best = c; best_us = us; }
   }
-  if (best == TILE_128 && best_depth <= SHALLOW) best = TILE_128_SHALLOW;
   return {(TileSize)best, best_us};
 }
 

@@ -32,16 +32,19 @@ def reference(t, S, D, H, G, k):
     return y.detach(), {n: x.grad for n, x in p.items()}
 
 
-# (rows, D, H, G): tiles taken by [q, k, v] | output | dO | dWo | [dXkv, dXq] | [dWq, dWk, dWv] (128: either kernel of that size)
+# (rows, D, H, G): tiles taken by [q, k, v] | output | dO | dWo | [dXkv, dXq] | [dWq, dWk, dWv] (s: 128 x 128 by four waves of 64 x 64)
 @pytest.mark.parametrize("S,D,H,G,wf32", [
-    (60, 256, 2, 1, False),          # 128 x 128 throughout, less than one tile of rows
-    (700, 1024, 16, 4, True),        # 128 x 128, ragged rows and k slices
-    (1024, 2048, 16, 16, False),     # 256 x 128 | 128 | 128 | 128 | 128 | 256
-    (1300, 1024, 32, 8, True),       # 256 | 128 | 128 x 256 | 128 | 128 | 256 x 128
-    (900, 3072, 24, 12, False),      # 256 x 128 | 128 | 128 | 256 | 256 x 128 | 256, the excess on 128
-    (513, 4096, 8, 2, True),         # 128 | 128 | 128 | 128 | 128 x 256 | 256 x 128
-    (4200, 4352, 32, 2, False),      # 256 with the tile rows past whole rounds in a second launch, ragged rows among them ...
-    (4200, 4352, 32, 2, True),       # ... and weight gradients with rows of X cut off, float output
+    (60, 256, 2, 1, False),          # s throughout, less than one tile of rows
+    (700, 1024, 16, 4, True),        # s | 128 | s | s | 128 | s, ragged rows and k slices
+    (1024, 2048, 16, 16, False),     # 256 x 128 | 128 | 128 | s | 128 | 256
+    (1300, 1024, 32, 8, True),       # s | 128 | s | 128 | 128 | 256 x 128
+    (900, 3072, 24, 12, False),      # 256 x 128 | 128 | 128 | 256 | 256 x 128 | s
+    (513, 4096, 8, 2, True),         # 128 | s | 128 | s | s | s
+    (4200, 4352, 32, 2, False),      # 128 x 256 | 128 x 256 | 128 x 256 | 256 x 128 | 256 x 128 | 256 x 128, more than a round of each
+    (4200, 4352, 32, 2, True),
+    (5000, 3328, 16, 8, False),      # forward and input gradients on 256 with the tile rows past whole rounds in a second launch
+    (4360, 2560, 24, 24, False),     # the same of input and weight gradients (rows of X cut off) ...
+    (4360, 2560, 24, 24, True),      # ... with float output
 ])
 def test_step_against_float32(S, D, H, G, wf32):
     gen = torch.Generator(device="cuda").manual_seed(S + D)

@@ -1,4 +1,4 @@
-"""Every instantiation of the small-tile GEMM kernels has a whole step against float32 that runs it: tile size, storage orders of
+"""Every instantiation of the GEMM kernels has a whole step against float32 that runs it: tile size, storage orders of
 the operands (nn: X W, nt: X W^T, tn: X^T Y) and output type; tiles of 128 x 128 over up to 16 slices of 64 k ("shallow") have a
 kernel of their own.  Which tiles a launch takes is computed here from the cost rule
 that gemm_bf16.hip states, so that the sizes are known to reach what they are listed for."""
@@ -8,17 +8,18 @@ import pytest
 
 import test_gpu_gemm_tiles as whole
 
-# (BM, BN, us per round, us per slice of 64 k, and the share of it that grows with how full the round is)
-COSTS = ((256, 256, 8.8, 0.90, 0.65), (256, 128, 8.3, 0.57, 0.38), (128, 256, 8.3, 0.57, 0.38), (128, 128, 6.1, 0.38, 0.16))
+# (BM, BN, workgroups of a round, us per round, us per slice of 64 k, and the share of it that grows with how full the round is)
+COSTS = ((256, 256, 256, 7.0, 0.91, 0.46), (256, 128, 256, 6.7, 0.45, 0.38), (128, 256, 256, 6.7, 0.45, 0.38),
+         (128, 128, 256, 5.9, 0.29, 0.21), (128, 128, 512, 2.7, 0.285, 0.66))
 CUT_US = 8.0
 SHALLOW = 16
 up = lambda a, b: -(-a // b)
 
 
-def _uneven(fixed, each, fuller, tiles, depths):
-    """Makespan of tiles of different depth, dealt out in order to whichever of the 256 CUs is free first."""
-    fill = min(1.0, sum(tiles) / 256.0)
-    free = [0.0] * 256
+def _uneven(at_once, fixed, each, fuller, tiles, depths):
+    """Makespan of tiles of different depth, dealt out in order to whichever place is free first."""
+    fill = min(1.0, sum(tiles) / at_once)
+    free = [0.0] * at_once
     end = 0.0
     for t, d in zip(tiles, depths):
         for _ in range(t):
@@ -31,16 +32,18 @@ def _uneven(fixed, each, fuller, tiles, depths):
 def _choose(group):
     """group: (M, N, depths of the k segments) of every product of the launch -> ((BM, BN) or "shallow", microseconds)."""
     best = None
-    for bm, bn, fixed, each, fuller in COSTS:
+    for bm, bn, at_once, fixed, each, fuller in COSTS:
         tiles = [up(m, bm) * up(n, bn) for m, n, _ in group]
         depth = sum(t * sum(up(k, 64) for k in ks) for t, (_, _, ks) in zip(tiles, group)) / sum(tiles)
-        full, rest = divmod(sum(tiles) / 256.0, 1.0)
+        if at_once == 512 and depth > SHALLOW:
+            continue
+        full, rest = divmod(sum(tiles) / at_once, 1.0)
         us = full * (fixed + depth * (each + fuller)) + (fixed + depth * (each + fuller * rest) if rest else 0.0)
         depths = [sum(up(k, 64) for k in ks) for _, _, ks in group]
         if len(set(depths)) > 1 and sum(tiles) <= 4096:
-            us = _uneven(fixed, each, fuller, tiles, depths)
+            us = _uneven(at_once, fixed, each, fuller, tiles, depths)
         if best is None or us < best[1]:
-            best = ("shallow" if (bm, bn) == (128, 128) and depth <= SHALLOW else (bm, bn), us)
+            best = ("shallow" if at_once == 512 else (bm, bn), us)
     return best
 
 
@@ -77,21 +80,30 @@ def _variants(S, D, H, G, wf32):
 
 
 SHAPES = [
-    (200, 1408, 8, 8, False),      # odd multiples of 128 channels: weight gradients on 128 x 256 ...
+    (200, 1408, 8, 8, False),      # odd multiples of 128 channels: shallow weight gradients ...
     (200, 1408, 8, 8, True),       # ... in both output types
-    (200, 2176, 16, 16, False),    # dWo on 256 x 128
-    (200, 2560, 13, 1, True),      # dWo on 128 x 256, [dWq, dWk, dWv] on 256 x 128
+    (200, 2176, 16, 16, False),
+    (200, 2560, 13, 1, True),
     (1152, 2688, 24, 8, False),    # an odd multiple of 128 rows: forward projections and input gradients on 128 x 256
-    (700, 3072, 8, 4, False),      # input gradients on 256 x 128
+    (700, 3072, 8, 4, False),
     (1024, 2048, 15, 15, False),   # forward projections on 256 x 128
     (60, 256, 2, 1, False),        # all shallow: less than a tile of rows
     (1030, 1024, 8, 2, False),     # shallow forward and dO, weight gradients over 17 slices: just past it
     (1030, 1024, 8, 2, True),
+    (1030, 320, 29, 29, False),    # dWo on 128 x 256
+    (1030, 320, 30, 30, True),
+    (900, 2112, 6, 6, False),      # input gradients on 256 x 128
+    (1030, 448, 23, 23, True),     # dWq, dWk, dWv on 256 x 128
+    (1600, 256, 24, 24, False),    # 256 x 256 of few steps: forward projections ...
+    (1600, 320, 24, 24, False),    # ... and dO, whose steps end inside a period of four
+    (1030, 3776, 3, 1, False),     # input gradients on 256 x 256, two segments of 128
+    (200, 1984, 19, 19, False),    # weight gradients on 256 x 256, an odd number of steps ...
+    (200, 1984, 19, 19, True),     # ... in both output types
 ]
 
 
-def test_shapes_reach_every_small_tile_variant():
-    tiles = [(bm, bn) for bm, bn, *_ in COSTS[1:]] + ["shallow"]
+def test_shapes_reach_every_variant():
+    tiles = [(bm, bn) for bm, bn, *_ in COSTS[:4]] + ["shallow"]
     want = {(tile, o, t) for tile in tiles for o, t in (("nn", "bf16"), ("nt", "bf16"), ("tn", "bf16"), ("tn", "f32"))}
     assert want <= set().union(*(_variants(*s) for s in SHAPES)), want - set().union(*(_variants(*s) for s in SHAPES))
 
