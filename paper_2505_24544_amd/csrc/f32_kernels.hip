@@ -146,12 +146,18 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmGroup grp) {
 // out of the matrix instruction with it as the column, and the probabilities go back in as the second product's operand
 // without leaving their registers.  NC: 32-channel blocks of the head width.
 // ---------------------------------------------------------------------------
-// operand fragment of a row: channels 8 i + 4 hf + e at f[4 i + e], zeros past d
-template <int NC>
+// operand fragment of a row: channels 8 i + 4 hf + e at f[4 i + e], zeros past d.  FULL: d = 32 NC, nothing is past it.  (A select on
+// a loaded value makes the wave wait for the load where it stands, ahead of whatever it would have requested next.)
+template <int NC, bool FULL>
 __device__ __forceinline__ void row_frag(const float* row, int d, int hf, float (&f)[16 * NC]) {
 #pragma unroll
   for (int i = 0; i < 4 * NC; ++i) {
     const int c = 8 * i + 4 * hf;
+    if constexpr (FULL) {
+      const float4 v = *(const float4*)(row + c);
+      f[4 * i] = v.x; f[4 * i + 1] = v.y; f[4 * i + 2] = v.z; f[4 * i + 3] = v.w;
+      continue;
+    }
     const float4 v = *(const float4*)(row + min(c, d - 4));
     const bool in = c < d;
     f[4 * i] = in ? v.x : 0.f; f[4 * i + 1] = in ? v.y : 0.f; f[4 * i + 2] = in ? v.z : 0.f; f[4 * i + 3] = in ? v.w : 0.f;
@@ -237,7 +243,7 @@ __device__ __forceinline__ void fwd_plain(const AttnArgs& a, const float* q, con
     }
 }
 
-template <int NC>
+template <int NC, bool FULL>
 __global__ __launch_bounds__(256, 1) void attn_fwd_f32_kernel(AttnArgs a) {
   __shared__ float ob[4][32 * (32 * NC + 1)];
   __shared__ float ms[4][32], ls[4][32];
@@ -251,8 +257,16 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_f32_kernel(AttnArgs a) {
   const float* V = (const float*)a.v + (sv.kv0 * a.G + g) * d;
   const int64_t kvs = (int64_t)a.G * d;
   const float* Q = (const float*)a.q + ((sv.q0 + qc) * a.H + h) * d;
-  float qf[16 * NC];
-  row_frag<NC>(Q, d, hf, qf);
+  // everything the wave's first block needs is requested at once, ahead of the mask's divisions: one trip to memory, not two
+  float qf[16 * NC], kf[16 * NC], vf[NC][16];
+  row_frag<NC, FULL>(Q, d, hf, qf);
+  auto keys = [&](int j0) BEAGLE_INLINE_LAMBDA { row_frag<NC, FULL>(K + min(j0 + ql, sv.L - 1) * kvs, d, hf, kf); };
+  auto values = [&](int j0) BEAGLE_INLINE_LAMBDA {
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) col_frag(V, kvs, j0, sv.L, min(32 * cb + ql, d - 1), hf, vf[cb]);
+  };
+  if (sv.L > 0) { keys(32 * wave); values(32 * wave); }
+  __builtin_amdgcn_sched_barrier(0);
   const MaskParams mk = sample_mask(a, b);
   const int lim = q < sv.S ? row_limit(q, mk) : 0;
   const int wg_lim = row_limit(min(q0 + 32, sv.S) - 1, mk);            // limits never decrease with the query
@@ -265,11 +279,8 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_f32_kernel(AttnArgs a) {
   for (int cb = 0; cb < NC; ++cb) o[cb] = zero16();
   float m = -INFINITY, l = 0.f, nf = 0.f;
   for (int j0 = 32 * wave; j0 < wg_lim; j0 += 128) {
-    float kf[16 * NC], vf[NC][16];
-    row_frag<NC>(K + min(j0 + ql, sv.L - 1) * kvs, d, hf, kf);
-#pragma unroll
-    for (int cb = 0; cb < NC; ++cb) col_frag(V, kvs, j0, sv.L, min(32 * cb + ql, d - 1), hf, vf[cb]);
     f32x16_t s = dot_frags<NC>(kf, qf);                 // [key acc_row(e, hf)][query ql]
+    if (j0 + 128 < wg_lim) keys(j0 + 128);
     float mx = -INFINITY;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -298,6 +309,7 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_f32_kernel(AttnArgs a) {
 #pragma unroll
       for (int cb = 0; cb < NC; ++cb) note_nonfinite(nf, vf[cb]);
     }
+    if (j0 + 128 < wg_lim) values(j0 + 128);
   }
   if (any_nonfinite(nf)) fwd_plain<NC>(a, Q, K, V, kvs, 32 * wave, wg_lim, lim, trow, hf, o, m, l);
   park<NC>(ob[wave], o, ql, hf);
@@ -356,7 +368,7 @@ __device__ __forceinline__ void dkv_plain(const AttnArgs& a, const SeqView& sv, 
 // Both halves of the backward in one launch (they are independent: each forms delta = rowsum(dO * O) for itself).
 //   blocks [0, n_dq)  : dQ of 32 queries of one head, over the keys they see; also stores delta
 //   the rest          : dK, dV of 32 keys of one key/value head, over the (head, query block) pairs that see them
-template <int NC>
+template <int NC, bool FULL>
 __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_dq) {
   __shared__ float ob[4][32 * (32 * NC + 1)];
   __shared__ float st[4][2][32];
@@ -384,17 +396,30 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
     const int64_t qrow = ((sv.q0 + qc) * a.H + h) * d, li = sv.lse0 + h * sv.lse_hs + qc;
     const float* K = (const float*)a.k + (sv.kv0 * a.G + g) * d;
     const float* V = (const float*)a.v + (sv.kv0 * a.G + g) * d;
-    float qf[16 * NC], gf[16 * NC];
+    // (one trip to memory, as in the forward)
+    float qf[16 * NC], gf[16 * NC], kf[16 * NC], vf[16 * NC], kc[NC][16];
+    auto rows = [&](int j0) BEAGLE_INLINE_LAMBDA {
+      const int64_t jr = min(j0 + ql, sv.L - 1) * kvs;
+      row_frag<NC, FULL>(K + jr, d, hf, kf);
+      row_frag<NC, FULL>(V + jr, d, hf, vf);
+    };
+    auto cols = [&](int j0) BEAGLE_INLINE_LAMBDA {
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) col_frag(K, kvs, j0, sv.L, min(32 * cb + ql, d - 1), hf, kc[cb]);
+    };
     float part = 0.f;
+    const float lse = a.lse[li];
     {
       float of[16 * NC];
-      row_frag<NC>((const float*)a.q + qrow, d, hf, qf);
-      row_frag<NC>((const float*)a.dout + qrow, d, hf, gf);
-      row_frag<NC>((const float*)a.o + qrow, d, hf, of);
+      row_frag<NC, FULL>((const float*)a.dout + qrow, d, hf, gf);
+      row_frag<NC, FULL>((const float*)a.o + qrow, d, hf, of);
+      row_frag<NC, FULL>((const float*)a.q + qrow, d, hf, qf);
+      if (sv.L > 0) { rows(32 * wave); cols(32 * wave); }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < 16 * NC; ++i) part = fmaf(gf[i], of[i], part);
     }
-    const float lse = a.lse[li], delta = pair_sum(part);
+    const float delta = pair_sum(part);
     if (wave == 0 && hf == 0 && q < sv.S) a.delta[li] = delta;
     const MaskParams mk = sample_mask(a, b);
     const int lim = q < sv.S ? row_limit(q, mk) : 0;
@@ -404,14 +429,9 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
     for (int cb = 0; cb < NC; ++cb) dq[cb] = zero16();
     float nf = 0.f;
     for (int j0 = 32 * wave; j0 < wg_lim; j0 += 128) {
-      float kf[16 * NC], vf[16 * NC], kc[NC][16];
-      const int64_t jr = min(j0 + ql, sv.L - 1) * kvs;
-      row_frag<NC>(K + jr, d, hf, kf);
-      row_frag<NC>(V + jr, d, hf, vf);
-#pragma unroll
-      for (int cb = 0; cb < NC; ++cb) col_frag(K, kvs, j0, sv.L, min(32 * cb + ql, d - 1), hf, kc[cb]);
       f32x16_t s = dot_frags<NC>(kf, qf);
       const f32x16_t dp = dot_frags<NC>(vf, gf);
+      if (j0 + 128 < wg_lim) rows(j0 + 128);
 #pragma unroll
       for (int e = 0; e < 16; ++e)
         s[e] = j0 + acc_row(e, hf) < lim ? expf(a.scale * s[e] - lse) * (dp[e] - delta) : 0.f;
@@ -423,6 +443,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
 #pragma unroll
         for (int cb = 0; cb < NC; ++cb) note_nonfinite(nf, kc[cb]);
       }
+      if (j0 + 128 < wg_lim) cols(j0 + 128);
     }
     if (any_nonfinite(nf))
       dq_plain<NC>(a, (const float*)a.q + qrow, (const float*)a.dout + qrow, lse, delta, K, V, kvs, 32 * wave, wg_lim, lim, hf, dq);
@@ -436,8 +457,9 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
     const int j = j0 + ql;
     const int64_t kvrow = ((sv.kv0 + min(j, sv.L - 1)) * a.G + g) * d;
     float kf[16 * NC], vf[16 * NC];
-    row_frag<NC>((const float*)a.k + kvrow, d, hf, kf);
-    row_frag<NC>((const float*)a.v + kvrow, d, hf, vf);
+    row_frag<NC, FULL>((const float*)a.k + kvrow, d, hf, kf);
+    row_frag<NC, FULL>((const float*)a.v + kvrow, d, hf, vf);
+    __builtin_amdgcn_sched_barrier(0);
     const MaskParams mk = sample_mask(a, b);
     const int fq = j < sv.L ? first_query_seeing(j, mk) : sv.S;         // this lane's key is seen from here on
     const int all_q = first_query_seeing(min(j0 + 32, sv.L) - 1, mk);   // the workgroup's keys are all seen from here on
@@ -452,18 +474,11 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
       const float* dO = (const float*)a.dout + (sv.q0 * a.H + h) * d;
       const int pc = min(p0 + ql, sv.S - 1);
       float qf[16 * NC], gf[16 * NC];
-      row_frag<NC>(Q + pc * qs, d, hf, qf);
-      row_frag<NC>(dO + pc * qs, d, hf, gf);
-      float part = 0.f;
-      {
-        float of[16 * NC];
-        row_frag<NC>((const float*)a.o + (sv.q0 * a.H + h) * d + pc * qs, d, hf, of);
-#pragma unroll
-        for (int i = 0; i < 16 * NC; ++i) part = fmaf(gf[i], of[i], part);
-      }
-      part = pair_sum(part);
-      if (hf == 0) { st[wave][0][ql] = a.lse[sv.lse0 + h * sv.lse_hs + pc]; st[wave][1][ql] = part; }
-      __builtin_amdgcn_wave_barrier();                  // (written and read by this wave only)
+      row_frag<NC, FULL>(Q + pc * qs, d, hf, qf);
+      row_frag<NC, FULL>(dO + pc * qs, d, hf, gf);
+      const float lse = a.lse[sv.lse0 + h * sv.lse_hs + pc];
+      float of[16 * NC], part = 0.f;
+      row_frag<NC, FULL>((const float*)a.o + (sv.q0 * a.H + h) * d + pc * qs, d, hf, of);
       // the second products' operands: requested here where registers allow (head width up to 64)
       constexpr bool EARLY = NC <= 2;
       float cg[EARLY ? NC : 1][16], cq[EARLY ? NC : 1][16];
@@ -473,9 +488,15 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
           col_frag(dO, qs, p0, sv.S, min(32 * cb + ql, d - 1), hf, cg[cb]);
           col_frag(Q, qs, p0, sv.S, min(32 * cb + ql, d - 1), hf, cq[cb]);
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
       f32x16_t s = dot_frags<NC>(qf, kf);               // [query acc_row(e, hf)][key ql]
       f32x16_t dp = dot_frags<NC>(gf, vf);
+#pragma unroll
+      for (int i = 0; i < 16 * NC; ++i) part = fmaf(gf[i], of[i], part);
+      part = pair_sum(part);
+      if (hf == 0) { st[wave][0][ql] = lse; st[wave][1][ql] = part; }
+      __builtin_amdgcn_wave_barrier();                  // (written and read by this wave only)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int r = acc_row(e, hf), p = p0 + r;
@@ -526,11 +547,16 @@ void launch_gemm_f32(const GemmGroup& g, hipStream_t s, const char* name) {
 void launch_attn_fwd_f32(const AttnArgs& a, hipStream_t s) {
   ProfScope ps("attn_fwd_f32", s);
   const dim3 grid((a.S + 31) / 32, a.H, a.B), wg(256);
+  auto go = [&](auto nc_) {
+    constexpr int NC = decltype(nc_)::value;
+    if (a.d == 32 * NC) hipLaunchKernelGGL((attn_fwd_f32_kernel<NC, true>), grid, wg, 0, s, a);
+    else hipLaunchKernelGGL((attn_fwd_f32_kernel<NC, false>), grid, wg, 0, s, a);
+  };
   switch ((a.d + 31) / 32) {
-    case 1: hipLaunchKernelGGL(attn_fwd_f32_kernel<1>, grid, wg, 0, s, a); break;
-    case 2: hipLaunchKernelGGL(attn_fwd_f32_kernel<2>, grid, wg, 0, s, a); break;
-    case 3: hipLaunchKernelGGL(attn_fwd_f32_kernel<3>, grid, wg, 0, s, a); break;
-    default: hipLaunchKernelGGL(attn_fwd_f32_kernel<4>, grid, wg, 0, s, a); break;
+    case 1: go(int_c<1>{}); break;
+    case 2: go(int_c<2>{}); break;
+    case 3: go(int_c<3>{}); break;
+    default: go(int_c<4>{}); break;
   }
 }
 
@@ -538,11 +564,16 @@ void launch_attn_bwd_f32(const AttnArgs& a, hipStream_t s) {
   ProfScope ps("attn_bwd_f32", s);
   const int n_dq = ((a.S + 31) / 32) * a.H * a.B, n_dkv = ((a.L + 31) / 32) * a.G * a.B;
   const dim3 grid(n_dq + n_dkv), wg(256);
+  auto go = [&](auto nc_) {
+    constexpr int NC = decltype(nc_)::value;
+    if (a.d == 32 * NC) hipLaunchKernelGGL((attn_bwd_f32_kernel<NC, true>), grid, wg, 0, s, a, n_dq);
+    else hipLaunchKernelGGL((attn_bwd_f32_kernel<NC, false>), grid, wg, 0, s, a, n_dq);
+  };
   switch ((a.d + 31) / 32) {
-    case 1: hipLaunchKernelGGL(attn_bwd_f32_kernel<1>, grid, wg, 0, s, a, n_dq); break;
-    case 2: hipLaunchKernelGGL(attn_bwd_f32_kernel<2>, grid, wg, 0, s, a, n_dq); break;
-    case 3: hipLaunchKernelGGL(attn_bwd_f32_kernel<3>, grid, wg, 0, s, a, n_dq); break;
-    default: hipLaunchKernelGGL(attn_bwd_f32_kernel<4>, grid, wg, 0, s, a, n_dq); break;
+    case 1: go(int_c<1>{}); break;
+    case 2: go(int_c<2>{}); break;
+    case 3: go(int_c<3>{}); break;
+    default: go(int_c<4>{}); break;
   }
 }
 
