@@ -230,6 +230,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
 // ===========================================================================
 // (2) dK and dV
 // ===========================================================================
+// The matrix instruction on an accumulator that stays in its accumulation registers.  (The compiler keeps all of a function's
+// accumulators in one register file: with the scores in vector registers, dK and dV were there too, and one LDS fragment was in
+// flight instead of four.)  The compiler does not know its latency: whoever writes the operands with vector instructions, or reads
+// the accumulators, keeps the distance.
+__device__ __forceinline__ void mfma_in_place(f32x16_t& acc, const bf16x8_t& a, const bf16x8_t& b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
 namespace dkv {
 constexpr int BJ = 128, BQ = 64;
 constexpr int TILE = BQ * HD;            // one Q or dO tile
@@ -368,14 +375,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
             dp[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag(dsm, fo, qb, s), vf[s], dp[qb], 0, 0, 0);
           }
         };
-        auto probs = [&](int qb) {
-          float pv[16];
-#pragma unroll
-          for (int e4 = 0; e4 < 4; ++e4) {
-            const float ls[4] = {l4[e4].x, l4[e4].y, l4[e4].z, l4[e4].w};
-#pragma unroll
-            for (int u = 0; u < 4; ++u) pv[4 * e4 + u] = __builtin_amdgcn_exp2f(__builtin_fmaf(s2[qb][4 * e4 + u], c2, ls[u]));
-          }
+        auto hide = [&](int qb, float (&pv)[16]) BEAGLE_INLINE_LAMBDA {
           // The per-element predicate only where some key of the wave is hidden from some query of the block (a
           // scalar branch around the compares and selects alone: the kernel is bound by instruction issue, and a
           // second copy of the whole body made the register allocator shuffle the accumulators).  A blind query
@@ -385,6 +385,16 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
             for (int e = 0; e < 16; ++e)
               if (32 * qb + 8 * (e >> 2) + (e & 3) < relq) pv[e] = 0.f;
           }
+        };
+        auto probs = [&](int qb) {
+          float pv[16];
+#pragma unroll
+          for (int e4 = 0; e4 < 4; ++e4) {
+            const float ls[4] = {l4[e4].x, l4[e4].y, l4[e4].z, l4[e4].w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) pv[4 * e4 + u] = __builtin_amdgcn_exp2f(__builtin_fmaf(s2[qb][4 * e4 + u], c2, ls[u]));
+          }
+          hide(qb, pv);
 #pragma unroll
           for (int e4 = 0; e4 < 4; ++e4) {
             const float dl[4] = {d4[e4].x, d4[e4].y, d4[e4].z, d4[e4].w};
@@ -395,18 +405,27 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
             pd[qb][2 * e4] = cvt_pk(dsv[0], dsv[1]); pd[qb][2 * e4 + 1] = cvt_pk(dsv[2], dsv[3]);
           }
         };
-        auto accum = [&](int qb) {
+        // 16 MFMAs on the block's probabilities (dV, dK in turn), each pinned in its place with the read of the fragment four
+        // ahead and `beside(m)` behind it
+        auto accum = [&](auto qb_, auto beside) {
+          constexpr int qb = decltype(qb_)::value;
+          union { uint32_t u[4]; bf16x8_t v; } pf[2], sf[2];
 #pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            union { uint32_t u[4]; bf16x8_t v; } pf, sf;
+          for (int i = 0; i < 8; ++i) { pf[i >> 2].u[i & 3] = pp[qb][i]; sf[i >> 2].u[i & 3] = pd[qb][i]; }
+          bf16x8_t fr[16];
+          auto read = [&](int m) BEAGLE_INLINE_LAMBDA { fr[m] = tr_frag(m & 1 ? qsm : dsm, fo, 32 * qb + 16 * (m >> 3), (m >> 1) & 3); };
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { pf.u[i] = pp[qb][4 * t + i]; sf.u[i] = pd[qb][4 * t + i]; }
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb) {
-              dv[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag(dsm, fo, 32 * qb + 16 * t, cb), pf.v, dv[cb], 0, 0, 0);
-              dk[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag(qsm, fo, 32 * qb + 16 * t, cb), sf.v, dk[cb], 0, 0, 0);
-            }
-          }
+          for (int m = 0; m < 4; ++m) read(m);
+          beside(int_c<-1>{});
+          __builtin_amdgcn_sched_barrier(0);
+          static_for<0, 16>([&](auto m_) {
+            constexpr int m = decltype(m_)::value;
+            mfma_in_place(m & 1 ? dk[(m >> 1) & 3] : dv[(m >> 1) & 3], fr[m], m & 1 ? sf[m >> 3].v : pf[m >> 3].v);
+            if constexpr (m + 4 < 16) read(m + 4);
+            beside(m_);
+            __builtin_amdgcn_sched_barrier(0);
+          });
         };
         scores(0);
         pipeline_reads_mfma_loads<16, 1, 9>();
@@ -417,15 +436,28 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
         __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
         pipeline_reads_mfma_valu<16, 1, VPM>();
         __builtin_amdgcn_sched_barrier(0);
-        stats(1);
-        accum(0);
-        probs(1);
-        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-        pipeline_reads_mfma_valu<16, 2, VPM>();
-        __builtin_amdgcn_sched_barrier(0);
-        accum(1);
-        pipeline_reads_mfma<16, 2>();
-        __builtin_amdgcn_sched_barrier(0);
+        // block 1's probabilities and products beside block 0's accumulation: two elements per MFMA
+        float pv[16];
+        accum(int_c<0>{}, [&](auto m_) BEAGLE_INLINE_LAMBDA {
+          constexpr int m = decltype(m_)::value;
+          if constexpr (m < 0) {
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) l4[e4] = *(const float4*)(sl + 32 + 8 * e4 + 4 * hf);
+          } else if constexpr (m < 8) {
+            if constexpr (m < 4) d4[m] = *(const float4*)(sl + BQ + 32 + 8 * m + 4 * hf);
+            const float* ls = (const float*)&l4[m >> 1];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+              pv[2 * m + u] = __builtin_amdgcn_exp2f(__builtin_fmaf(s2[1][2 * m + u], c2, ls[2 * (m & 1) + u]));
+            if constexpr (m == 7) hide(1, pv);
+          } else {
+            constexpr int i = m - 8;
+            const float* dl = (const float*)&d4[i >> 1];
+            pp[1][i] = cvt_pk(pv[2 * i], pv[2 * i + 1]);
+            pd[1][i] = cvt_pk(pv[2 * i] * (dp[1][2 * i] - dl[2 * (i & 1)]), pv[2 * i + 1] * (dp[1][2 * i + 1] - dl[2 * (i & 1) + 1]));
+          }
+        });
+        accum(int_c<1>{}, [](auto) BEAGLE_INLINE_LAMBDA {});
       }
     }
     wait_vmem();
@@ -447,6 +479,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
     tile_step(stage1, stat1, stage0, stat0);
   }
   if (it < iters) tile_step(stage0, stat0, stage1, stat1);
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");     // the last MFMAs' results are there
 
   if (SPLIT && !whole) {
     // a share of the sums: as the accumulators lie, 1 KB per store instruction; sum_dkv_kernel adds the shares in order
