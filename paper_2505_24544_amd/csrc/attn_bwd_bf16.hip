@@ -240,6 +240,7 @@ __device__ __forceinline__ void mfma_in_place(f32x16_t& acc, const bf16x8_t& a, 
 namespace dkv {
 constexpr int BJ = 128, BQ = 64;
 constexpr int TILE = BQ * HD;            // one Q or dO tile
+constexpr int AHEAD = 4;                // MFMAs from an LDS fragment's read to its use
 constexpr int SLOT = 2 * BJ * HD;        // floats of one partial result: dK, then dV of a key tile
 // SPLIT: a key tile's (head, query tile) pairs are cut into chunks of `per_chunk`, up to `chunks` workgroups per tile
 struct Split { float* part; int32_t chunks, per_chunk; };
@@ -324,20 +325,27 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
   const bf16_t* f_do = (const bf16_t*)a.dout + head0 * HD;
   const float* f_stat = ((wave & 1) == 0 ? a.nlse2 : a.delta) + sv.lse0 + (g * rep + f_hh) * sv.lse_hs;
   const int tile_bytes = sv.S > 0 ? (int)((((int64_t)sv.S - 1) * qs + HD) * 2) : 0;   // one head's Q (dO) rows of this entry
-  auto fetch = [&](bf16_t* st, float* stat) {
+  // request i of 9, in order; the cursor moves on behind the last one
+  auto fetch_part = [&](int i, bf16_t* st, float* stat) BEAGLE_INLINE_LAMBDA {
     const int q0 = f_qt * BQ;
     const bool live = f_hh < rep;                    // past the last pair: empty descriptors, i.e. zeros
-    const int tbytes = live ? tile_bytes : 0, sbytes = live ? sv.S * 4 : 0;
-    load_rows<BQ>(st, __builtin_amdgcn_make_buffer_rsrc((void*)f_q, 0, tbytes, 0x00020000), qs, q0, tid);
-    load_rows<BQ>(st + TILE, __builtin_amdgcn_make_buffer_rsrc((void*)f_do, 0, tbytes, 0x00020000), qs, q0, tid);
-    const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc((void*)f_stat, 0, sbytes, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(srs, (lds_void_ptr)(stat + wave * BQ), 4, (q0 + lane) * 4, 0, 0, 0);
-    // advance the cursor without branches
-    const bool wrap = f_qt + 1 == nqt;
-    const bool adv = wrap && f_hh + 1 < rep;
-    f_qt = wrap ? qt0 : f_qt + 1;
-    f_hh += wrap ? 1 : 0;
-    f_q += adv ? HD : 0; f_do += adv ? HD : 0; f_stat += adv ? sv.lse_hs : 0;
+    if (i < 4) load_rows_part(st, __builtin_amdgcn_make_buffer_rsrc((void*)f_q, 0, live ? tile_bytes : 0, 0x00020000), qs, q0, tid, i);
+    else if (i < 8)
+      load_rows_part(st + TILE, __builtin_amdgcn_make_buffer_rsrc((void*)f_do, 0, live ? tile_bytes : 0, 0x00020000), qs, q0, tid, i - 4);
+    else {
+      const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc((void*)f_stat, 0, live ? sv.S * 4 : 0, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(srs, (lds_void_ptr)(stat + wave * BQ), 4, (q0 + lane) * 4, 0, 0, 0);
+      // advance the cursor without branches
+      const bool wrap = f_qt + 1 == nqt;
+      const bool adv = wrap && f_hh + 1 < rep;
+      f_qt = wrap ? qt0 : f_qt + 1;
+      f_hh += wrap ? 1 : 0;
+      f_q += adv ? HD : 0; f_do += adv ? HD : 0; f_stat += adv ? sv.lse_hs : 0;
+    }
+  };
+  auto fetch = [&](bf16_t* st, float* stat) {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) fetch_part(i, st, stat);
   };
 
   auto tile_step = [&](const bf16_t* cur, const float* sl, bf16_t* nxt, float* nstat) {
@@ -345,120 +353,82 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
     if (++c_qt == nqt) c_qt = qt0;
     if (q0 + BQ <= wave_first) fetch(nxt, nstat);     // a wave that sees nothing of the tile only requests its share of the next
     if (q0 + BQ > wave_first) {                       // some query of the tile sees some key of the wave
-      fetch(nxt, nstat);                              // issued between the first MFMAs below
       const bf16_t* qsm = cur;
       const bf16_t* dsm = cur + TILE;
       const int relq = fq - q0 - 4 * hf;    // query offsets inside the tile are compile-time constants
-      // The two 32-query blocks of the tile go through  scores -> probabilities -> accumulation  one
-      // phase apart, so that the exponentials and products of one block issue between the MFMAs of
-      // the other (this kernel has one wave per SIMD: nothing else would fill the matrix pipe then).
+      // The tile is one run of 64 MFMAs: the scores (S and dP in turn) of its first block of 32 queries, those of the second, then
+      // either's accumulation (dV and dK in turn).  Each is pinned in its place with, behind it, the read of the LDS fragment that
+      // the one four further on wants, and its share of everything else: the next tile's requests, the statistics' reads, and, one
+      // phase late, the probabilities and products of a block, two elements per MFMA.  This kernel has one wave per SIMD:
+      // whatever is not in its place leaves the matrix pipe idle, and every phase that started with reads of its own did.
       // Register e of block qb is query q0 + 32 qb + 8 (e/4) + 4 hf + e%4 ; column = this lane's key.
-      {
-        constexpr int VPM = 10;   // vector instructions of one block slotted in per MFMA of the other
-        f32x16_t s2[2], dp[2];
-        float4 l4[4], d4[4];
-        uint32_t pp[2][8], pd[2][8];
-        auto stats = [&](int qb) {
+      f32x16_t s2[2], dp[2];
+      float4 l4[2][4], d4[2][4];
+      float pv[2][16];
+      union probs_t { uint32_t u[4]; bf16x8_t v; } pp[2][2], pd[2][2];
+      bf16x8_t fr[64];
+      auto read = [&](int n) BEAGLE_INLINE_LAMBDA {
+        const bf16_t* t = n & 1 ? (n < 32 ? dsm : qsm) : (n < 32 ? qsm : dsm);
+        if (n < 32) fr[n] = row_frag(t, fo, n >> 4, (n >> 1) & 7);
+        else fr[n] = tr_frag(t, fo, 2 * (n - 32) & ~15, (n >> 1) & 3);
+      };
+      auto mfma = [&](int n) BEAGLE_INLINE_LAMBDA {
+        const int i = n >> 1, qb = (n >> 4) & 1;
+        if (n < 32) {
+          f32x16_t& c = n & 1 ? dp[qb] : s2[qb];
+          if ((i & 7) == 0)
 #pragma unroll
-          for (int e4 = 0; e4 < 4; ++e4) {
-            const int r = 32 * qb + 8 * e4 + 4 * hf;
-            l4[e4] = *(const float4*)(sl + r);
-            d4[e4] = *(const float4*)(sl + BQ + r);
-          }
-        };
-        auto scores = [&](int qb) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) { s2[qb][e] = 0.f; dp[qb][e] = 0.f; }
-#pragma unroll
-          for (int s = 0; s < 8; ++s) {
-            s2[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag(qsm, fo, qb, s), kf[s], s2[qb], 0, 0, 0);
-            dp[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag(dsm, fo, qb, s), vf[s], dp[qb], 0, 0, 0);
-          }
-        };
-        auto hide = [&](int qb, float (&pv)[16]) BEAGLE_INLINE_LAMBDA {
+            for (int e = 0; e < 16; ++e) c[e] = 0.f;
+          c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n], n & 1 ? vf[i & 7] : kf[i & 7], c, 0, 0, 0);
+        } else {
+          const int t = (n >> 3) & 1;
+          mfma_in_place(n & 1 ? dk[i & 3] : dv[i & 3], fr[n], n & 1 ? pd[qb][t].v : pp[qb][t].v);
+        }
+      };
+      auto stat = [&](int qb, int i) BEAGLE_INLINE_LAMBDA {
+        const int r = 32 * qb + 8 * (i & 3) + 4 * hf;
+        if (i < 4) l4[qb][i] = *(const float4*)(sl + r);
+        else d4[qb][i & 3] = *(const float4*)(sl + BQ + r);
+      };
+      auto probs = [&](int qb, int m) BEAGLE_INLINE_LAMBDA {        // m: 0 .. 7 probabilities, 8 .. 15 products
+        const int e = 2 * (m & 7);
+        if (m < 8) {
+          const float* ls = (const float*)&l4[qb][e >> 2];
+          pv[qb][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s2[qb][e], c2, ls[e & 3]));
+          pv[qb][e + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s2[qb][e + 1], c2, ls[(e & 3) + 1]));
           // The per-element predicate only where some key of the wave is hidden from some query of the block (a
           // scalar branch around the compares and selects alone: the kernel is bound by instruction issue, and a
           // second copy of the whole body made the register allocator shuffle the accumulators).  A blind query
           // (-log2(e) LSE = +inf, p = +inf) is below fq for every key, so its block always comes through here.
-          if (q0 + 32 * qb < wave_all) {
+          if (m == 7 && q0 + 32 * qb < wave_all) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-              if (32 * qb + 8 * (e >> 2) + (e & 3) < relq) pv[e] = 0.f;
+            for (int k = 0; k < 16; ++k)
+              if (32 * qb + 8 * (k >> 2) + (k & 3) < relq) pv[qb][k] = 0.f;
           }
-        };
-        auto probs = [&](int qb) {
-          float pv[16];
+        } else {
+          const float* dl = (const float*)&d4[qb][e >> 2];
+          const float a0 = pv[qb][e], a1 = pv[qb][e + 1];
+          pp[qb][e >> 3].u[(e >> 1) & 3] = cvt_pk(a0, a1);
+          pd[qb][e >> 3].u[(e >> 1) & 3] = cvt_pk(a0 * (dp[qb][e] - dl[e & 3]), a1 * (dp[qb][e + 1] - dl[(e & 3) + 1]));
+          // (here and not where they are used, which mfma_in_place would not wait for)
+          if ((m & 3) == 3) asm volatile("" : "+v"(pp[qb][e >> 3].v), "+v"(pd[qb][e >> 3].v));
+        }
+      };
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int e4 = 0; e4 < 4; ++e4) {
-            const float ls[4] = {l4[e4].x, l4[e4].y, l4[e4].z, l4[e4].w};
-#pragma unroll
-            for (int u = 0; u < 4; ++u) pv[4 * e4 + u] = __builtin_amdgcn_exp2f(__builtin_fmaf(s2[qb][4 * e4 + u], c2, ls[u]));
-          }
-          hide(qb, pv);
-#pragma unroll
-          for (int e4 = 0; e4 < 4; ++e4) {
-            const float dl[4] = {d4[e4].x, d4[e4].y, d4[e4].z, d4[e4].w};
-            float dsv[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) dsv[u] = pv[4 * e4 + u] * (dp[qb][4 * e4 + u] - dl[u]);
-            pp[qb][2 * e4] = cvt_pk(pv[4 * e4], pv[4 * e4 + 1]); pp[qb][2 * e4 + 1] = cvt_pk(pv[4 * e4 + 2], pv[4 * e4 + 3]);
-            pd[qb][2 * e4] = cvt_pk(dsv[0], dsv[1]); pd[qb][2 * e4 + 1] = cvt_pk(dsv[2], dsv[3]);
-          }
-        };
-        // 16 MFMAs on the block's probabilities (dV, dK in turn), each pinned in its place with the read of the fragment four
-        // ahead and `beside(m)` behind it
-        auto accum = [&](auto qb_, auto beside) {
-          constexpr int qb = decltype(qb_)::value;
-          union { uint32_t u[4]; bf16x8_t v; } pf[2], sf[2];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) { pf[i >> 2].u[i & 3] = pp[qb][i]; sf[i >> 2].u[i & 3] = pd[qb][i]; }
-          bf16x8_t fr[16];
-          auto read = [&](int m) BEAGLE_INLINE_LAMBDA { fr[m] = tr_frag(m & 1 ? qsm : dsm, fo, 32 * qb + 16 * (m >> 3), (m >> 1) & 3); };
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int m = 0; m < 4; ++m) read(m);
-          beside(int_c<-1>{});
-          __builtin_amdgcn_sched_barrier(0);
-          static_for<0, 16>([&](auto m_) {
-            constexpr int m = decltype(m_)::value;
-            mfma_in_place(m & 1 ? dk[(m >> 1) & 3] : dv[(m >> 1) & 3], fr[m], m & 1 ? sf[m >> 3].v : pf[m >> 3].v);
-            if constexpr (m + 4 < 16) read(m + 4);
-            beside(m_);
-            __builtin_amdgcn_sched_barrier(0);
-          });
-        };
-        scores(0);
-        pipeline_reads_mfma_loads<16, 1, 9>();
+      for (int n = 0; n < AHEAD; ++n) read(n);
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<0, 64>([&](auto n_) BEAGLE_INLINE_LAMBDA {
+        constexpr int n = decltype(n_)::value;
+        mfma(n);
+        if constexpr (n + AHEAD < 64) read(n + AHEAD);
+        if constexpr (n < 9) fetch_part(n, nxt, nstat);
+        if constexpr (n >= 8 && n < 16) stat(0, n - 8);
+        if constexpr (n >= 24 && n < 32) stat(1, n - 24);
+        if constexpr (n >= 16 && n < 32) probs(0, n - 16);
+        if constexpr (n >= 32 && n < 48) probs(1, n - 32);
         __builtin_amdgcn_sched_barrier(0);
-        stats(0);
-        scores(1);
-        probs(0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-        pipeline_reads_mfma_valu<16, 1, VPM>();
-        __builtin_amdgcn_sched_barrier(0);
-        // block 1's probabilities and products beside block 0's accumulation: two elements per MFMA
-        float pv[16];
-        accum(int_c<0>{}, [&](auto m_) BEAGLE_INLINE_LAMBDA {
-          constexpr int m = decltype(m_)::value;
-          if constexpr (m < 0) {
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) l4[e4] = *(const float4*)(sl + 32 + 8 * e4 + 4 * hf);
-          } else if constexpr (m < 8) {
-            if constexpr (m < 4) d4[m] = *(const float4*)(sl + BQ + 32 + 8 * m + 4 * hf);
-            const float* ls = (const float*)&l4[m >> 1];
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-              pv[2 * m + u] = __builtin_amdgcn_exp2f(__builtin_fmaf(s2[1][2 * m + u], c2, ls[2 * (m & 1) + u]));
-            if constexpr (m == 7) hide(1, pv);
-          } else {
-            constexpr int i = m - 8;
-            const float* dl = (const float*)&d4[i >> 1];
-            pp[1][i] = cvt_pk(pv[2 * i], pv[2 * i + 1]);
-            pd[1][i] = cvt_pk(pv[2 * i] * (dp[1][2 * i] - dl[2 * (i & 1)]), pv[2 * i + 1] * (dp[1][2 * i + 1] - dl[2 * (i & 1) + 1]));
-          }
-        });
-        accum(int_c<1>{}, [](auto) BEAGLE_INLINE_LAMBDA {});
-      }
+      });
     }
     wait_vmem();
     __syncthreads();

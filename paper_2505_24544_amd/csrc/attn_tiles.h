@@ -35,16 +35,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const bf16_t* base, 
   return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000);
 }
 
-// Fill a tile of R rows (R * 16 chunks, 256 threads) with global rows row0 .. row0 + R - 1.
+// Fill a tile of R rows (R * 16 chunks, 256 threads) with global rows row0 .. row0 + R - 1: request i of R / 16, or all of them.
+__device__ __forceinline__ void load_rows_part(bf16_t* tile, __amdgpu_buffer_rsrc_t rsrc, int64_t stride, int row0, int tid, int i) {
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = tid + 256 * i, r = q >> 4, c = (q & 15) ^ swz(r);
+  const int off = (int)(((int64_t)(row0 + r) * stride + 8 * c) * 2);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(tile + (i * 4 + wave) * 512), 16, off, 0, 0, 0);
+}
 template <int R>
 __device__ __forceinline__ void load_rows(bf16_t* tile, __amdgpu_buffer_rsrc_t rsrc, int64_t stride, int row0, int tid) {
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
-  for (int i = 0; i < R * 16 / 256; ++i) {
-    const int q = tid + 256 * i, r = q >> 4, c = (q & 15) ^ swz(r);
-    const int off = (int)(((int64_t)(row0 + r) * stride + 8 * c) * 2);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)(tile + (i * 4 + wave) * 512), 16, off, 0, 0, 0);
-  }
+  for (int i = 0; i < R * 16 / 256; ++i) load_rows_part(tile, rsrc, stride, row0, tid, i);
 }
 
 // Per-lane element offsets of the two fragment kinds, computed once.  Tile
