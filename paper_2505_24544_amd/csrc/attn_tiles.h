@@ -166,24 +166,6 @@ __device__ __forceinline__ void pipeline_reads_mfma_loads() {
   __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
 }
 
-// The same run with V vector instructions (ordinary or transcendental) of independent work slotted
-// in after every MFMA, so that they issue while the matrix pipe is busy.
-template <int N, int RPM, int V>
-__device__ __forceinline__ void pipeline_reads_mfma_valu() {
-  __builtin_amdgcn_sched_group_barrier(0x100, 4 * RPM, 0);
-#pragma unroll
-  for (int i = 0; i < N - 4; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, RPM, 0);
-    __builtin_amdgcn_sched_group_barrier(0x402, V, 0);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x402, V, 0);
-  }
-}
-
 // A wave's 32 rows x 128 channels from the accumulator layout of a transposed 32x32 MFMA block row (lane = row
 // lane % 32; its registers are groups of four consecutive channels, piece 4 cb + qd = channels 32 cb + 8 qd + 4 hf ..)
 // out as whole rows of a bf16 tensor.  Stored from the registers, every instruction would write 16 bytes into each of
