@@ -419,6 +419,8 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGrou
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
         uint2* at = (uint2*)(patch + pr * (CPW * 8) + (((2 * j + (gi >> 1)) ^ (pr & (CPW - 1))) << 3) + 4 * (gi & 1));
+        // (here, not as soon as the wait is over: taken apart that early, accumulators were moved about and three were spilled)
+        if constexpr (RES) asm volatile("" : "+a"(acc[i][j]));
         f32x4_t c = acc[i][j];
         if constexpr (RES) {
           const uint2 r = *at;
