@@ -31,6 +31,7 @@
 // Key tiles beyond a workgroup's last limit / query tiles before a key tile's
 // first viewer are never visited (whole-tile skipping).
 #include "attn_tiles.h"
+#include "mfma_in_place.h"
 
 namespace beagle {
 using namespace tiles;
@@ -230,14 +231,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
 // ===========================================================================
 // (2) dK and dV
 // ===========================================================================
-// The matrix instruction on an accumulator that stays in its accumulation registers.  (The compiler keeps all of a function's
-// accumulators in one register file: with the scores in vector registers, dK and dV were there too, and one LDS fragment was in
-// flight instead of four.)  With both in accumulation registers the scores' 64 values per tile were copied: 2689 -> 2648 us for 2 x 4096
-// positions in 8 groups, 6684 -> 6566 for 8192 at 5120 channels.  The compiler does not know its latency: whoever writes the operands with vector instructions, or reads
-// the accumulators, keeps the distance.
-__device__ __forceinline__ void mfma_in_place(f32x16_t& acc, const bf16x8_t& a, const bf16x8_t& b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-}
 namespace dkv {
 constexpr int BJ = 128, BQ = 64;
 constexpr int TILE = BQ * HD;            // one Q or dO tile
@@ -310,6 +303,10 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
   const float c2 = a.scale * LOG2E;
   const FragOffs fo = make_frag_offs(lane);
 
+  // In accumulation registers by hand (mfma_in_place), with the scores in vector registers: the compiler keeps all of a function's
+  // accumulators in one register file.  With all in the one, the scores' 64 values were copied in every tile (2689 -> 2648 us for
+  // 2 x 4096 positions in 8 groups, 6684 -> 6566 for 8192 at 5120 channels); with all in the other, one LDS fragment was in flight
+  // instead of four.
   f32x16_t dk[4], dv[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -452,7 +449,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
     tile_step(stage1, stat1, stage0, stat0);
   }
   if (it < iters) tile_step(stage0, stat0, stage1, stat1);
-  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");     // the last MFMAs' results are there
+  mfma_drain();
 
   if (SPLIT && !whole) {
     // a share of the sums: as the accumulators lie, 1 KB per store instruction; sum_dkv_kernel adds the shares in order

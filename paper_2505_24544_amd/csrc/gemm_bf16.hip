@@ -47,12 +47,13 @@
 #include <stdlib.h>
 #include <string.h>
 #include "common.h"
+#include "mfma_in_place.h"
 
 namespace beagle {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
+typedef mfma_bf16x8_t bf16x8_t;
+typedef mfma_f32x16_t f32x16_t;
+typedef mfma_f32x4_t f32x4_t;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s16x4_t;
 typedef s16x4_t __attribute__((address_space(3))) * lds_s16x4_ptr;
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
@@ -76,17 +77,6 @@ __device__ __forceinline__ int krow_swizzle(int k) { return ((k & 3) << 2) ^ ((k
 // Tiles of k-contiguous operands, 64 bytes per row: chunk c of row r sits at chunk c ^ row_swizzle(r).  A 16-byte read serves lanes
 // 0-3, 12-15, 20-27 together, then 4-11, 16-19, 28-31, and so on: rows 0-3 and 12-15 of one k group with rows 4-11 of the next.
 __device__ __forceinline__ int row_swizzle(int r) { return ((r >> 2) & 3) ^ ((r >> 1) & 2); }
-
-// The matrix instruction on accumulators that stay where they are: with 256 of them and the fragments of two steps, the compiler's
-// own form of it (result and addend in different registers) left 80 - 170 register copies per slice of 128 instructions.
-// Whoever reads the accumulators afterwards waits the instruction's latency first (mfma_drain).
-__device__ __forceinline__ void mfma16(f32x4_t& acc, const bf16x8_t& a, const bf16x8_t& b) {
-  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void mfma32(f32x16_t& acc, const bf16x8_t& a, const bf16x8_t& b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 
 // Where the requests of one operand stand: a slice of both k segments after the other.  The descriptor starts at the current slice,
 // so the lanes' offsets are constants of the tile and a slice costs scalar arithmetic only, in pieces that fit between two MFMAs;
@@ -298,7 +288,7 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGrou
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, NM>([&](auto m_) BEAGLE_INLINE_LAMBDA {
       constexpr int m = decltype(m_)::value, i = m / NB, j = (i & 1) ? NB - 1 - m % NB : m % NB;
-      mfma16(acc[i][j], wf[wbuf(P)][j].v, xf[odd][i].v);
+      mfma_in_place(acc[i][j], wf[wbuf(P)][j].v, xf[odd][i].v);
       constexpr int r0 = m * NR * 5 / (NM * 4), r1 = (m + 1) * NR * 5 / (NM * 4);      // reads behind the first four fifths
       if constexpr (r0 < NR) static_for<r0, (r1 < NR ? r1 : NR)>([&](auto n_) BEAGLE_INLINE_LAMBDA { read_one(p_, n_); });
       if constexpr (m % RE == 0) f_issue(int_c<odd>{}, int_c<m / RE>{});
@@ -598,7 +588,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
       __builtin_amdgcn_sched_barrier(0);
       static_for<0, 16>([&](auto m_) BEAGLE_INLINE_LAMBDA {
         constexpr int m = decltype(m_)::value, i = m >> 2, j = (i & 1) ? 3 - (m & 3) : m & 3;
-        mfma32(acc[i][j], wf[fb][j].v, xf[fb][i].v);
+        mfma_in_place(acc[i][j], wf[fb][j].v, xf[fb][i].v);
         constexpr int r0 = m * NR * 5 / 64, r1 = (m + 1) * NR * 5 / 64;      // reads behind the first four fifths
         if constexpr (r0 < NR) static_for<r0, (r1 < NR ? r1 : NR)>([&](auto n_) BEAGLE_INLINE_LAMBDA { read_one(int_c<(fb ^ 1)>{}, int_c<ns>{}, n_); });
         constexpr int mm = last ? m : 16 + 16 * s + m;
@@ -628,7 +618,6 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
     if (t < nk) slice(int_c<0>{});
   }
   mfma_drain();
-  __builtin_amdgcn_sched_barrier(0);
 
   // ---- the KG waves of a tile part exchange sums: each ends up with 128 / KG of the rows, summed in a fixed order
   constexpr int SLOT = OWN * 4096;                   // floats of one wave's slot

@@ -13,8 +13,8 @@ import pytest
 from paper_2505_24544_amd import build
 
 LLVM = "/opt/rocm/llvm/bin/"
-KERNELS = ("gemm_bf16_kernel", "gemm_bf16_ksplit_kernel")
-COUNT = 12 + 12                              # instantiations
+KERNELS = ("attn_bwd_dkv_bf16_kernel", "gemm_bf16_kernel", "gemm_bf16_ksplit_kernel")
+COUNT = 2 + 12 + 12                              # instantiations
 pytestmark = pytest.mark.skipif(not os.path.exists(LLVM + "llvm-objdump"), reason="no llvm-objdump")
 
 
