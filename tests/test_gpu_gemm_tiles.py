@@ -75,8 +75,11 @@ def test_step_against_float32(S, D, H, G, wf32):
         assert rel(g["d" + n], gr[n]) <= 3e-2, n
 
 
-@pytest.mark.parametrize("S,D,H", [(70, 512, 4), (1500, 4096, 32), (2900, 4096, 8),      # 128 x 128, 256 x 128, 256 x 256
-                                   (4200, 4096, 32)])                                    # 256 x 256, the last tile row apart
+# y takes 128 x 128 (s), 256 x 128, 256 x 256, 128 x 256, and 256 x 256 with the last tile rows apart; h always s
+RESIDUAL = [(70, 512, 4), (1500, 4096, 32), (2900, 4096, 8), (4200, 4096, 32), (4100, 4096, 12)]
+
+
+@pytest.mark.parametrize("S,D,H", RESIDUAL)
 def test_residual_operand(S, D, H):
     """y = o Wo + e of the block's forward, from its own saved o: the residual is added before the one rounding."""
     gen = torch.Generator(device="cuda").manual_seed(S)

@@ -1,12 +1,14 @@
 """Every instantiation of the GEMM kernels has a whole step against float32 that runs it: tile size, storage orders of
-the operands (nn: X W, nt: X W^T, tn: X^T Y) and output type; tiles of 128 x 128 over up to 16 slices of 64 k ("shallow") have a
-kernel of their own.  Which tiles a launch takes is computed here from the cost rule
+the operands (nn: X W, nt: X W^T, tn: X^T Y), output type and, where that makes a kernel of its own, a residual; tiles of 128 x 128 over
+up to 16 slices of 64 k ("shallow") have a kernel of their own.  Which tiles a launch takes is computed here from the cost rule
 that gemm_bf16.hip states, so that the sizes are known to reach what they are listed for."""
 import heapq
 
 import pytest
+import torch
 
 import test_gpu_gemm_tiles as whole
+from paper_2505_24544_amd import binding as bx
 
 # (BM, BN, workgroups of a round, us per round, us per slice of 64 k, and the share of it that grows with how full the round is)
 COSTS = ((256, 256, 256, 7.0, 0.91, 0.46), (256, 128, 256, 6.7, 0.45, 0.38), (128, 256, 256, 6.7, 0.45, 0.38),
@@ -114,7 +116,79 @@ def test_step_on_the_variant(S, D, H, G, wf32):
     whole.test_step_against_float32(S, D, H, G, wf32)
 
 
+# ---- with a residual (square tiles: a kernel of their own): y = o Wo + e and h = m W_down + y of the block's forward (nn), and without
+# gains its backward's dy = du W_gate^T + dw W_up^T + dh and de = dq Wq^T + dy (nt), the latter in a launch with dK Wk^T + dV Wv^T
+RESIDUAL_ON_128 = [(70, 2048, 16), (130, 1088, 9)]             # past 16 slices
+RESIDUAL_NT = [(70, 512, 4, 128), (3500, 4096, 2, 128), (4100, 4096, 2, 768)]      # shallow, 256 x 256, and that with rows apart
+
+
+def _nn(S, D, H):
+    return _launches([(S, D, (128 * H,))], False)
+
+
+def _nt(S, D, F):
+    return _launches([(S, D, (F, F))], False)
+
+
+def test_residuals_reach_what_they_are_listed_for():
+    assert [_nn(*s) for s in whole.RESIDUAL] == [["shallow"], [(256, 128)], [(256, 256)], [(128, 256)], [(256, 256), (128, 128)]]
+    assert all(_launches([(S, D, (128,))], False) == ["shallow"] for S, D, _ in whole.RESIDUAL)
+    assert [_nn(*s) for s in RESIDUAL_ON_128] == [[(128, 128)]] * 2
+    assert [_nt(S, D, F) for S, D, _, F in RESIDUAL_NT] == [["shallow"], [(256, 256)], [(256, 256), (128, 128)]]
+
+
+def test_cut_launches_are_cut():
+    """The rows of test_step_against_float32 whose comments say so: a second launch for the last tile rows of one product."""
+    assert _launches([(5000, 2048, (3328,)), (5000, 1024, (3328,)), (5000, 1024, (3328,))], False) == [(256, 256), (128, 128)]
+    assert _launches([(5000, 3328, (1024, 1024)), (5000, 3328, (2048,))], False) == [(256, 256), (128, 128)]
+    assert _launches([(4360, 2560, (3072, 3072)), (4360, 2560, (3072,))], False) == [(256, 256), (128, 256)]
+    assert _launches([(2560, 3072, (4360,))] * 3, True) == [(256, 256), (256, 128)]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("S,D,H", [(70, 2048, 16), (130, 1088, 9)])       # past 16 slices on tiles of 128 x 128: with a residual
+@pytest.mark.parametrize("S,D,H", RESIDUAL_ON_128)
 def test_residual_on_the_variant(S, D, H):
     whole.test_residual_operand(S, D, H)
+
+
+def _block_reference(t, w, S, H, k):
+    """Float32 autograd over Eq. 1 without normalisation; every product is a plain matrix product of contiguous operands."""
+    e, hs = t["e"].float().requires_grad_(), t["hs"].float()
+    w = {n: x.float() for n, x in w.items()}
+    q, kk, v = e @ w["wq"], hs @ w["wk"], hs @ w["wv"]
+    pos = torch.arange(S, device="cuda")
+    see = pos[None, :] < (pos // k * k)[:, None]
+    out = []
+    for h in range(H):
+        cols = slice(h * whole.HEAD, (h + 1) * whole.HEAD)
+        s = (q[:, cols] @ kk[:, cols].t().contiguous()) / whole.HEAD ** 0.5
+        out.append(torch.softmax(s.masked_fill(~see, -1e30), -1) * see @ v[:, cols])
+    y = torch.cat(out, 1) @ w["wo"] + e
+    (torch.nn.functional.silu(y @ w["w_gate"]) * (y @ w["w_up"]) @ w["w_down"] + y).backward(t["dh"].float())
+    return e.grad
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("S,D,H,F", RESIDUAL_NT)
+def test_residual_of_the_input_gradient(S, D, H, F):
+    gen = torch.Generator(device="cuda").manual_seed(S + F)
+    r = lambda *s, std=1.0: (torch.randn(*s, generator=gen, device="cuda") * std).bfloat16()
+    W, k = H * whole.HEAD, 4
+    w = dict(wq=r(D, W, std=0.02), wk=r(D, W, std=0.02), wv=r(D, W, std=0.02), wo=r(W, D, std=0.02), w_gate=r(D, F, std=0.02),
+             w_up=r(D, F, std=0.02), w_down=r(F, D, std=0.02))
+    t = dict(e=r(S, D), hs=r(S, D), dh=r(S, D))
+    d = bx.make_desc(batch=1, seq_q=S, seq_kv=S, hidden=D, n_q_heads=H, n_kv_heads=H, head_dim=whole.HEAD, block_size=k,
+                     flags=bx.BEAGLE_FLAG_NEED_DXKV)
+    nan = lambda *s, dt=torch.bfloat16: torch.full(s, float("nan"), dtype=dt, device="cuda")
+    sv = dict(q=nan(S, W), k=nan(S, W), v=nan(S, W), o=nan(S, W), lse=nan(H, S, dt=torch.float32), y=nan(S, D), u=nan(S, F), w=nan(S, F),
+              m=nan(S, F))
+    g = dict(de=nan(S, D), dhs=nan(S, D), **{"d" + n: nan(*x.shape) for n, x in w.items()})
+    ws = lambda which: torch.empty(max(1, bx.beagle_xattn_block_workspace_bytes(d, F, which)), dtype=torch.uint8, device="cuda")
+    p, saved = bx.make_block_params(F, 1e-5, **w), bx.make_block_saved(**sv)
+    bx.beagle_xattn_block_fwd(d, p, t["e"], t["hs"], nan(S, D), saved, ws(bx.BEAGLE_WS_BLOCK_FWD))
+    bx.beagle_xattn_block_bwd(d, p, t["dh"], t["e"], t["hs"], saved, bx.make_block_grads(**g), ws(bx.BEAGLE_WS_BLOCK_BWD))
+    # the bound of the other gradients (roundings of 2^-9 between the inputs and here); the last tile rows by themselves too, which a
+    # launch of their own may have written
+    ref = _block_reference(t, w, S, H, k)
+    assert whole.rel(g["de"], ref) <= 3e-2
+    assert whole.rel(g["de"][S // 256 * 256:], ref[S // 256 * 256:]) <= 3e-2
