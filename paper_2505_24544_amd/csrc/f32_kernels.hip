@@ -147,7 +147,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmGroup grp) {
 // without leaving their registers.  NC: 32-channel blocks of the head width.
 // ---------------------------------------------------------------------------
 // operand fragment of a row: channels 8 i + 4 hf + e at f[4 i + e], zeros past d.  FULL: d = 32 NC, nothing is past it.  (A select on
-// a loaded value makes the wave wait for the load where it stands, ahead of whatever it would have requested next.)
+// a loaded value makes the wave wait for the load where it stands, ahead of whatever it would have requested next.  Without FULL the
+// kernels therefore request a block where they need it: a block ahead, it saved nothing, cost registers, and at widths of 100 - 124
+// spilled 41.  Steps with and without, us: 128 rows at width 36 47.1, 46.2; at 100 72.6, 71.8; 2 x 300 at 100 183, 178.)
 template <int NC, bool FULL>
 __device__ __forceinline__ void row_frag(const float* row, int d, int hf, float (&f)[16 * NC]) {
 #pragma unroll
@@ -257,7 +259,8 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_f32_kernel(AttnArgs a) {
   const float* V = (const float*)a.v + (sv.kv0 * a.G + g) * d;
   const int64_t kvs = (int64_t)a.G * d;
   const float* Q = (const float*)a.q + ((sv.q0 + qc) * a.H + h) * d;
-  // everything the wave's first block needs is requested at once, ahead of the mask's divisions: one trip to memory, not two
+  // FULL: everything the wave's first block needs is requested at once, ahead of the mask's divisions (one trip to memory, not two),
+  // and a next block's operands as soon as this one's are used
   float qf[16 * NC], kf[16 * NC], vf[NC][16];
   row_frag<NC, FULL>(Q, d, hf, qf);
   auto keys = [&](int j0) BEAGLE_INLINE_LAMBDA { row_frag<NC, FULL>(K + min(j0 + ql, sv.L - 1) * kvs, d, hf, kf); };
@@ -265,8 +268,10 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_f32_kernel(AttnArgs a) {
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb) col_frag(V, kvs, j0, sv.L, min(32 * cb + ql, d - 1), hf, vf[cb]);
   };
-  if (sv.L > 0) { keys(32 * wave); values(32 * wave); }
-  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (FULL) {
+    if (sv.L > 0) { keys(32 * wave); values(32 * wave); }
+    __builtin_amdgcn_sched_barrier(0);
+  }
   const MaskParams mk = sample_mask(a, b);
   const int lim = q < sv.S ? row_limit(q, mk) : 0;
   const int wg_lim = row_limit(min(q0 + 32, sv.S) - 1, mk);            // limits never decrease with the query
@@ -279,8 +284,9 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_f32_kernel(AttnArgs a) {
   for (int cb = 0; cb < NC; ++cb) o[cb] = zero16();
   float m = -INFINITY, l = 0.f, nf = 0.f;
   for (int j0 = 32 * wave; j0 < wg_lim; j0 += 128) {
+    if constexpr (!FULL) { keys(j0); values(j0); }
     f32x16_t s = dot_frags<NC>(kf, qf);                 // [key acc_row(e, hf)][query ql]
-    if (j0 + 128 < wg_lim) keys(j0 + 128);
+    if (FULL && j0 + 128 < wg_lim) keys(j0 + 128);
     float mx = -INFINITY;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -309,7 +315,7 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_f32_kernel(AttnArgs a) {
 #pragma unroll
       for (int cb = 0; cb < NC; ++cb) note_nonfinite(nf, vf[cb]);
     }
-    if (j0 + 128 < wg_lim) values(j0 + 128);
+    if (FULL && j0 + 128 < wg_lim) values(j0 + 128);
   }
   if (any_nonfinite(nf)) fwd_plain<NC>(a, Q, K, V, kvs, 32 * wave, wg_lim, lim, trow, hf, o, m, l);
   park<NC>(ob[wave], o, ql, hf);
@@ -396,7 +402,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
     const int64_t qrow = ((sv.q0 + qc) * a.H + h) * d, li = sv.lse0 + h * sv.lse_hs + qc;
     const float* K = (const float*)a.k + (sv.kv0 * a.G + g) * d;
     const float* V = (const float*)a.v + (sv.kv0 * a.G + g) * d;
-    // (one trip to memory, as in the forward)
+    // (FULL: one trip to memory, as in the forward)
     float qf[16 * NC], gf[16 * NC], kf[16 * NC], vf[16 * NC], kc[NC][16];
     auto rows = [&](int j0) BEAGLE_INLINE_LAMBDA {
       const int64_t jr = min(j0 + ql, sv.L - 1) * kvs;
@@ -414,8 +420,10 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
       row_frag<NC, FULL>((const float*)a.dout + qrow, d, hf, gf);
       row_frag<NC, FULL>((const float*)a.o + qrow, d, hf, of);
       row_frag<NC, FULL>((const float*)a.q + qrow, d, hf, qf);
-      if (sv.L > 0) { rows(32 * wave); cols(32 * wave); }
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (FULL) {
+        if (sv.L > 0) { rows(32 * wave); cols(32 * wave); }
+        __builtin_amdgcn_sched_barrier(0);
+      }
 #pragma unroll
       for (int i = 0; i < 16 * NC; ++i) part = fmaf(gf[i], of[i], part);
     }
@@ -429,9 +437,10 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
     for (int cb = 0; cb < NC; ++cb) dq[cb] = zero16();
     float nf = 0.f;
     for (int j0 = 32 * wave; j0 < wg_lim; j0 += 128) {
+      if constexpr (!FULL) { rows(j0); cols(j0); }
       f32x16_t s = dot_frags<NC>(kf, qf);
       const f32x16_t dp = dot_frags<NC>(vf, gf);
-      if (j0 + 128 < wg_lim) rows(j0 + 128);
+      if (FULL && j0 + 128 < wg_lim) rows(j0 + 128);
 #pragma unroll
       for (int e = 0; e < 16; ++e)
         s[e] = j0 + acc_row(e, hf) < lim ? expf(a.scale * s[e] - lse) * (dp[e] - delta) : 0.f;
@@ -443,7 +452,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
 #pragma unroll
         for (int cb = 0; cb < NC; ++cb) note_nonfinite(nf, kc[cb]);
       }
-      if (j0 + 128 < wg_lim) cols(j0 + 128);
+      if (FULL && j0 + 128 < wg_lim) cols(j0 + 128);
     }
     if (any_nonfinite(nf))
       dq_plain<NC>(a, (const float*)a.q + qrow, (const float*)a.dout + qrow, lse, delta, K, V, kvs, 32 * wave, wg_lim, lim, hf, dq);
@@ -459,7 +468,9 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
     float kf[16 * NC], vf[16 * NC];
     row_frag<NC, FULL>((const float*)a.k + kvrow, d, hf, kf);
     row_frag<NC, FULL>((const float*)a.v + kvrow, d, hf, vf);
-    __builtin_amdgcn_sched_barrier(0);
+    constexpr bool EARLY = NC <= 2;                  // the second products' operands are requested with the first ones'
+    constexpr bool STATS_FIRST = !FULL && EARLY;     // delta is formed ahead of them: the selects have waited for its rows anyway
+    if constexpr (!STATS_FIRST) __builtin_amdgcn_sched_barrier(0);
     const MaskParams mk = sample_mask(a, b);
     const int fq = j < sv.L ? first_query_seeing(j, mk) : sv.S;         // this lane's key is seen from here on
     const int all_q = first_query_seeing(min(j0 + 32, sv.L) - 1, mk);   // the workgroup's keys are all seen from here on
@@ -479,8 +490,16 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
       const float lse = a.lse[sv.lse0 + h * sv.lse_hs + pc];
       float of[16 * NC], part = 0.f;
       row_frag<NC, FULL>((const float*)a.o + (sv.q0 * a.H + h) * d + pc * qs, d, hf, of);
+      // delta, and both statistics to where the wave's other lanes find them (written and read by this wave only)
+      auto stats = [&]() BEAGLE_INLINE_LAMBDA {
+#pragma unroll
+        for (int i = 0; i < 16 * NC; ++i) part = fmaf(gf[i], of[i], part);
+        part = pair_sum(part);
+        if (hf == 0) { st[wave][0][ql] = lse; st[wave][1][ql] = part; }
+        __builtin_amdgcn_wave_barrier();
+      };
+      if constexpr (STATS_FIRST) stats();
       // the second products' operands: requested here where registers allow (head width up to 64)
-      constexpr bool EARLY = NC <= 2;
       float cg[EARLY ? NC : 1][16], cq[EARLY ? NC : 1][16];
       if constexpr (EARLY) {
 #pragma unroll
@@ -488,15 +507,11 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_
           col_frag(dO, qs, p0, sv.S, min(32 * cb + ql, d - 1), hf, cg[cb]);
           col_frag(Q, qs, p0, sv.S, min(32 * cb + ql, d - 1), hf, cq[cb]);
         }
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!STATS_FIRST) __builtin_amdgcn_sched_barrier(0);
       }
       f32x16_t s = dot_frags<NC>(qf, kf);               // [query acc_row(e, hf)][key ql]
       f32x16_t dp = dot_frags<NC>(gf, vf);
-#pragma unroll
-      for (int i = 0; i < 16 * NC; ++i) part = fmaf(gf[i], of[i], part);
-      part = pair_sum(part);
-      if (hf == 0) { st[wave][0][ql] = lse; st[wave][1][ql] = part; }
-      __builtin_amdgcn_wave_barrier();                  // (written and read by this wave only)
+      if constexpr (!STATS_FIRST) stats();
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int r = acc_row(e, hf), p = p0 + r;

@@ -13,6 +13,8 @@ pytestmark = pytest.mark.gpu
     (1, 1, 4, 1, 1, 4, 1, 0),                  # smallest of everything
     (33, 33, 36, 3, 1, 12, 2, 1),              # one past a tile; chunk of 32 plus 4; head width inside a block
     (129, 129, 68, 2, 2, 36, 5, 3),            # second 32-channel block of four channels
+    (140, 140, 96, 2, 1, 72, 4, 1),            # three blocks, the last of eight channels
+    (97, 200, 64, 2, 2, 96, 4, 0),             # three whole blocks
     (200, 200, 256, 4, 2, 100, 4, 2),          # four blocks, the last of four channels
     (150, 97, 128, 2, 1, 128, 3, 0),           # more queries than keys
     (97, 290, 96, 2, 2, 64, 8, 7),             # more keys than queries, three key blocks per wave

@@ -2,7 +2,8 @@
 are compiled: the compiler inserts no wait states around an instruction it cannot see, so the code has to hold them.  Read from the
 built library's own code objects, by control flow: an accumulator is touched by other instructions only behind the two `s_nop 15` that
 outlast the longest of them, no vector instruction writes an operand within two wait states of its use, and nothing is spilled
-(a spill would read an accumulator wherever the register allocator likes)."""
+(a spill would read an accumulator wherever the register allocator likes).  Nor do the float attention kernels spill, which hold the
+operands of two products at once."""
 import os
 import re
 import shutil
@@ -15,6 +16,7 @@ from paper_2505_24544_amd import build
 LLVM = "/opt/rocm/llvm/bin/"
 KERNELS = ("attn_bwd_dkv_bf16_kernel", "gemm_bf16_kernel", "gemm_bf16_ksplit_kernel")
 COUNT = 2 + 12 + 12                              # instantiations
+FLOAT_KERNELS = ("attn_fwd_f32_kernel", "attn_bwd_f32_kernel")      # four widths, whole and ragged, each
 pytestmark = pytest.mark.skipif(not os.path.exists(LLVM + "llvm-objdump"), reason="no llvm-objdump")
 
 
@@ -50,50 +52,56 @@ class Ins:
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """{name: (instructions with their successors, spilled registers)} of KERNELS."""
+def library(tmp_path_factory):
+    """({name: instructions with their successors} of KERNELS, {name: spilled registers} of every kernel)."""
     if not os.path.exists(build.OUT):
         build.build(verbose=False)
     tmp = str(tmp_path_factory.mktemp("co"))
     shutil.copy(build.OUT, os.path.join(tmp, "lib.so"))
     _out(LLVM + "llvm-objdump", "--offloading", "lib.so", cwd=tmp)
-    found = {}
+    found, spilled = {}, {}
     for f in sorted(os.listdir(tmp)):
         if not f.endswith("gfx950"):
             continue
         notes = _out(LLVM + "llvm-readelf", "--notes", f, cwd=tmp)
-        spills = dict(re.findall(r"\.name:\s+(_Z\S+)\n(?:(?!\.name).*\n)*?\s+\.vgpr_spill_count: (\d+)", notes))
-        if not any(k in n for n in spills for k in KERNELS):
+        here = dict(re.findall(r"\.name:\s+(_Z\S+)\n(?:(?!\.name).*\n)*?\s+\.vgpr_spill_count: (\d+)", notes))
+        spilled.update((n, int(s)) for n, s in here.items())
+        if not any(k in n for n in here for k in KERNELS):
             continue
         name, code = None, []
         for line in _out(LLVM + "llvm-objdump", "-d", "--mcpu=gfx950", f, cwd=tmp).splitlines():
             m = re.match(r"[0-9a-f]+ <(\S+)>:", line)
             if m:
-                name = m[1] if any(k in m[1] for k in KERNELS) and m[1] in spills else None
+                name = m[1] if any(k in m[1] for k in KERNELS) and m[1] in here else None
                 if name:
-                    found[name] = (code := [], int(spills[name]))
+                    found[name] = code = []
             elif name and (m := re.match(r"\s+(\S.*?)\s*// ([0-9A-F]+): [0-9A-F ]+?(?: <.*\+0x([0-9a-f]+)>)?\s*$", line)):
                 code.append(Ins(int(m[2], 16), m[1]))
                 code[-1].to = int(m[3], 16) if m[3] else None
-    for code, _ in found.values():
+    for code in found.values():
         at = {i.addr - code[0].addr: n for n, i in enumerate(code)}
         for n, i in enumerate(code):
             if i.op.startswith(("s_cbranch", "s_branch")):
                 i.next.append(at[i.to])
             if n + 1 < len(code) and i.op not in ("s_branch", "s_endpgm", "s_setpc_b64"):
                 i.next.append(n + 1)
-    return found
+    return found, spilled
+
+
+@pytest.fixture(scope="module")
+def kernels(library):
+    return library[0]
 
 
 def test_every_kernel_is_there(kernels):
     assert len(kernels) == COUNT, sorted(kernels)
-    for name, (code, _) in kernels.items():
+    for name, code in kernels.items():
         assert any(i.mfma and i.dst & ACC for i in code), name
 
 
 def test_accumulators_are_read_behind_the_wait(kernels):
     wrong = []
-    for name, (code, _) in kernels.items():
+    for name, code in kernels.items():
         undrained = [None] * len(code)           # accumulators that may be in flight ahead of an instruction
         undrained[0], todo = 0, [0]
         while todo:
@@ -115,7 +123,7 @@ def test_accumulators_are_read_behind_the_wait(kernels):
 
 def test_operands_are_written_in_time(kernels):
     wrong = []
-    for name, (code, _) in kernels.items():
+    for name, code in kernels.items():
         for n, i in enumerate(code):
             if not i.op.startswith("v_") or i.mfma or not i.dst:
                 continue
@@ -131,5 +139,7 @@ def test_operands_are_written_in_time(kernels):
     assert not wrong, (len(wrong), wrong[:5])
 
 
-def test_nothing_is_spilled(kernels):
-    assert {n: s for n, (_, s) in kernels.items() if s} == {}
+def test_nothing_is_spilled(library):
+    spilled = {n: s for n, s in library[1].items() if any(k in n for k in KERNELS + FLOAT_KERNELS)}
+    assert len(spilled) == COUNT + 16
+    assert {n: s for n, s in spilled.items() if s} == {}
