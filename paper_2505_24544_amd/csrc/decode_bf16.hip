@@ -829,32 +829,50 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
         acc[i].z += __uint_as_float(t[i][k][2]); acc[i].w += __uint_as_float(t[i][k][3]);
       }
   };
-  // slices past the first QS (eight: model widths above 4096), and the rotary embedding: this thread's four channels of
-  // query m pair with the four that lane ^ 16 holds (float4 slot c4 ^ 16 of the same query)
-  auto q_finish = [&](int qb, int mrows, int qwaves, float4 (&acc)[4]) {
+  // slices past the first QS (eight: model widths above 4096)
+  auto q_rest = [&](int qb, int mrows, int qwaves, float4 (&acc)[4]) {
     for (int k0 = QS; k0 < a.KSq; k0 += QS) {
       u32x4_t t[4][QS];
       q_issue(qb, mrows, qwaves, k0, t);
       q_add(t, acc);
     }
-    if (a.rope_tab) {
+  };
+  // the rotary embedding: this thread's four channels of query m pair with the four that lane ^ 16 holds (float4 slot c4 ^ 16 of the
+  // same query); (cos, sin) of pairs 4 c4 .. 4 c4 + 3
+  typedef float4 q_angles_t[4][2];
+  auto q_angle = [&](int qb, int qwaves, int i, float4 (&cs)[2]) {
+    const int idx = tid + 64 * qwaves * i, m = min(row_query(32 * qb + (idx >> 5)), a.M - 1), c4 = idx & 15;
+    const float4* tp = (const float4*)(a.rope_tab + (int64_t)m * 64 + 4 * c4);
+    cs[0] = tp[0]; cs[1] = tp[1];
+  };
+  auto q_rotate_one = [&](const float4 (&cs)[2], float4& acc) {
+    const float4 cs0 = cs[0], cs1 = cs[1], own = acc;
+    const bool upper = (tid & 16) != 0;                    // channels 64 .. 127: x2 of the pair
+    float4 oth;
+    oth.x = __shfl_xor(own.x, 16, 64); oth.y = __shfl_xor(own.y, 16, 64);
+    oth.z = __shfl_xor(own.z, 16, 64); oth.w = __shfl_xor(own.w, 16, 64);
+    // x1' = x1 cos - x2 sin ; x2' = x2 cos + x1 sin
+    const float sg = upper ? 1.f : -1.f;
+    acc.x = own.x * cs0.x + sg * oth.x * cs0.y;
+    acc.y = own.y * cs0.z + sg * oth.y * cs0.w;
+    acc.z = own.z * cs1.x + sg * oth.z * cs1.y;
+    acc.w = own.w * cs1.z + sg * oth.w * cs1.w;
+  };
+  auto q_angles = [&](int qb, int qwaves, q_angles_t& cs) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int idx = tid + 64 * qwaves * i, m = min(row_query(32 * qb + (idx >> 5)), a.M - 1), c4 = idx & 15;
-        const float4* tp = (const float4*)(a.rope_tab + (int64_t)m * 64 + 4 * c4);
-        const float4 cs0 = tp[0], cs1 = tp[1];                 // (cos, sin) of pairs 4 c4 .. 4 c4 + 3
-        const bool upper = (tid & 16) != 0;                    // channels 64 .. 127: x2 of the pair
-        const float4 own = acc[i];
-        float4 oth;
-        oth.x = __shfl_xor(own.x, 16, 64); oth.y = __shfl_xor(own.y, 16, 64);
-        oth.z = __shfl_xor(own.z, 16, 64); oth.w = __shfl_xor(own.w, 16, 64);
-        // x1' = x1 cos - x2 sin ; x2' = x2 cos + x1 sin
-        const float sg = upper ? 1.f : -1.f;
-        acc[i].x = own.x * cs0.x + sg * oth.x * cs0.y;
-        acc[i].y = own.y * cs0.z + sg * oth.y * cs0.w;
-        acc[i].z = own.z * cs1.x + sg * oth.z * cs1.y;
-        acc[i].w = own.w * cs1.z + sg * oth.w * cs1.w;
-      }
+    for (int i = 0; i < 4; ++i) q_angle(qb, qwaves, i, cs[i]);
+  };
+  auto q_rotate = [&](const q_angles_t& cs, float4 (&acc)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q_rotate_one(cs[i], acc[i]);
+  };
+  auto q_finish = [&](int qb, int mrows, int qwaves, float4 (&acc)[4]) {
+    q_rest(qb, mrows, qwaves, acc);
+    if (a.rope_tab) {
+      q_angles_t cs;
+      if constexpr (NQB == 1) { q_angles(qb, qwaves, cs); q_rotate(cs, acc); }
+      else                                                   // (no registers for all of them beside both blocks' slices)
+        static_for<0, 4>([&](auto i_) { constexpr int i = decltype(i_)::value; q_angle(qb, qwaves, i, cs[i]); q_rotate_one(cs[i], acc[i]); });
     }
   };
   // hi / lo halves (8 bytes each) of four channels of row m
@@ -916,9 +934,15 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
     if (wave == 0) {
       u32x4_t t[4][QS];
       float4 acc[4] = {zero4, zero4, zero4, zero4};
+      q_angles_t cs;
       q_issue(0, mtot, 1, 0, t);
+      // With q, not a trip behind it.  (6 queries over 619 rows 23.9 -> 23.6 us, 2 over 300 22.9 -> 22.5, 8 over 1024 25.3 -> 24.8.
+      // By the clock this wave is never the last one at the barrier: what moves these times is how soon its q and the others' first
+      // step arrive, which any change of the code ahead of them moves by up to 400 cycles.)
+      if (a.rope_tab) q_angles(0, 1, cs);
       q_add(t, acc);
-      q_finish(0, mtot, 1, acc);
+      q_rest(0, mtot, 1, acc);
+      if (a.rope_tab) q_rotate(cs, acc);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int idx = tid + 64 * i, m = idx >> 5, c4 = idx & 31;
