@@ -72,12 +72,9 @@ __device__ __forceinline__ void request16(__amdgpu_buffer_rsrc_t rsrc, bf16_t* d
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_ptr)dst, 16, off, 0, 0, 0);
 }
 
-// Tiles of operands whose rows are contiguous: chunk c of k-row k sits at chunk c ^ krow_swizzle(k).
+// Tiles of operands whose rows are contiguous: chunk c of k-row k sits at chunk c ^ krow_swizzle(k).  (Of k-contiguous ones, 128 bytes
+// per row: chunk c of row r at chunk c ^ ((r >> 1) & 7).)
 __device__ __forceinline__ int krow_swizzle(int k) { return ((k & 3) << 2) ^ ((k >> 2) & 2); }
-// Tiles of k-contiguous operands, 64 bytes per row: chunk c of row r sits at chunk c ^ row_swizzle(r).  A 16-byte read serves lanes
-// 0-3, 12-15, 20-27 together, then 4-11, 16-19, 28-31, and so on: rows 0-3 and 12-15 of one k group with rows 4-11 of the next.
-__device__ __forceinline__ int row_swizzle(int r) { return ((r >> 2) & 3) ^ ((r >> 1) & 2); }
-
 // Where the requests of one operand stand: a slice of both k segments after the other.  The descriptor starts at the current slice,
 // so the lanes' offsets are constants of the tile and a slice costs scalar arithmetic only, in pieces that fit between two MFMAs;
 // past the last slice it is empty.
@@ -163,6 +160,7 @@ __device__ __forceinline__ void locate_tile(const GemmGroup& grp, int wg, int& p
 // without one keep their register allocation).
 template <int T, bool XK, bool WK, bool F32OUT, bool RES>
 __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGroup grp) {
+  static_assert(XK || !WK, "k-contiguous W comes with k-contiguous X");
   constexpr int NB = 2 * T;                          // 16 x 16 accumulators per wave: NB x NB
   constexpr int BM = 64 * T, BN = 64 * T;
   // steps of KB k per slice of X and of W, stages of either: 160 KB (T = 4) or 80 KB (T = 2) in all
@@ -183,17 +181,16 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGrou
   constexpr int XLD = BM * XS / 64, WLD = BN * WS / 64, NLD = XLD / XS + WLD / WS;      // requests per thread: an X slice, a W slice, a step
   const int ldx = (int)g.lda, ldw = (int)g.ldb;
   int nk = (g.K + KB - 1) / KB + (g.A2 ? (g.K2 + KB - 1) / KB : 0);           // steps
-  auto chunk_off = [&](int q, bool kmajor, int wide, int rows, int ld) BEAGLE_INLINE_LAMBDA {      // 16-byte chunk q of an operand's slice
-    if (kmajor && wide) { const int r = q >> 3; return (r * ld + 8 * ((q & 7) ^ ((r >> 1) & 7))) * 2; }
-    if (kmajor) { const int r = q >> 2; return (r * ld + 8 * ((q & 3) ^ row_swizzle(r))) * 2; }
+  auto chunk_off = [&](int q, bool kmajor, int rows, int ld) BEAGLE_INLINE_LAMBDA {      // 16-byte chunk q of an operand's slice
+    if (kmajor) { const int r = q >> 3; return (r * ld + 8 * ((q & 7) ^ ((r >> 1) & 7))) * 2; }
     const int cpr = rows / 8, k = q / cpr;
     return (k * ld + 8 * ((q % cpr) ^ krow_swizzle(k))) * 2;
   };
   int xoff[XLD], woff[WLD];
 #pragma unroll
-  for (int i = 0; i < XLD; ++i) xoff[i] = chunk_off(tid + 256 * i, XK, true, BM, ldx);
+  for (int i = 0; i < XLD; ++i) xoff[i] = chunk_off(tid + 256 * i, XK, BM, ldx);
 #pragma unroll
-  for (int i = 0; i < WLD; ++i) woff[i] = chunk_off(tid + 256 * i, WK, WS == 2, BN, ldw);
+  for (int i = 0; i < WLD; ++i) woff[i] = chunk_off(tid + 256 * i, WK, BN, ldw);
   SliceCursor fx, fw;
   fx.init(g, g.A, g.A2, XK, g.M, m0, ldx, KB * XS, smem + wave * 512);
   fw.init(g, g.B, g.B2, WK, g.N, n0, ldw, KB * WS, smem + WBASE + wave * 512);
@@ -217,17 +214,15 @@ __global__ __launch_bounds__(256, T == 4 ? 1 : 2) void gemm_bf16_kernel(GemmGrou
   uint32_t xa[NXA], wa[NWA];
   {
     const uint32_t base = (uint32_t)(uintptr_t)(lds_bf16_ptr)smem;
-    auto rows = [&](int steps, int r0, int b) BEAGLE_INLINE_LAMBDA {
-      return ((r0 + l16) * KB * steps + ((steps == 2 ? (4 * b + gi) ^ ((l16 >> 1) & 7) : gi ^ row_swizzle(l16)) << 3)) * 2;
-    };
+    auto rows = [&](int r0, int b) BEAGLE_INLINE_LAMBDA { return ((r0 + l16) * KB * 2 + (((4 * b + gi) ^ ((l16 >> 1) & 7)) << 3)) * 2; };
     auto cols = [&](int rows, int r0, int b) BEAGLE_INLINE_LAMBDA {
       const int kr = 8 * gi + (l16 >> 2), col = r0 + 16 * b + 4 * (l16 & 3);
       return (kr * rows + ((((col >> 3) ^ krow_swizzle(kr)) << 3) | (col & 7))) * 2;
     };
 #pragma unroll
-    for (int b = 0; b < NXA; ++b) xa[b] = base + (XK ? rows(XS, wm, b) : cols(BM, wm, b));
+    for (int b = 0; b < NXA; ++b) xa[b] = base + (XK ? rows(wm, b) : cols(BM, wm, b));
 #pragma unroll
-    for (int b = 0; b < NWA; ++b) wa[b] = base + 2 * WBASE + (WK ? rows(WS, wn, b) : cols(BN, wn, b));
+    for (int b = 0; b < NWA; ++b) wa[b] = base + 2 * WBASE + (WK ? rows(wn, b) : cols(BN, wn, b));
   }
   int rx_st = 0, rx_step = XE * 2, rw_st = 0, rw_step = WE * 2;     // the stage they point into; bytes from there to the next
   auto rx_next = [&]() BEAGLE_INLINE_LAMBDA { rx_st = rx_st + 1 == NXS ? 0 : rx_st + 1; rx_step = rx_st + 1 == NXS ? -(NXS - 1) * XE * 2 : XE * 2; };
