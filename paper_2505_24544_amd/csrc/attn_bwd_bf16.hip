@@ -355,12 +355,13 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_bf16_kernel(AttnArgs a, d
       const bf16_t* dsm = cur + TILE;
       const int relq = fq - q0 - 4 * hf;    // query offsets inside the tile are compile-time constants
       // The tile is one run of 64 MFMAs: the scores (S and dP in turn) of its first block of 32 queries, those of the second, then
-      // either's accumulation (dV and dK in turn).  Each is pinned in its place with, behind it, the read of the LDS fragment that
-      // the one four further on wants, and its share of everything else: the next tile's requests, the statistics' reads, and, one
-      // phase late, the probabilities and products of a block, two elements per MFMA.  This kernel has one wave per SIMD:
-      // whatever is not in its place leaves the matrix pipe idle, and every phase that started with reads of its own did.
-      // Training steps against phases in the compiler's order, us: 4096 positions in 8 groups x 2 2600 -> 2571, 8192 at 5120 channels
-      // 6454 -> 6327; six or eight fragments ahead measure the same.
+      // either's accumulation (dV and dK in turn).  A step is an MFMA and its share of everything else: the read of the LDS fragment
+      // that the MFMA four further on wants, the next tile's requests, the statistics' reads, and, one phase late, the probabilities
+      // and products of a block, two elements at a time.  A fence at its end keeps it apart from the next one; inside a step the
+      // order is the compiler's (a block's first probabilities stand ahead of their step's MFMA and wait for S, two MFMAs back).
+      // This kernel has one wave per SIMD: whatever is not in its place leaves the matrix pipe idle, and every phase that started
+      // with reads of its own did.  Training steps against phases in the compiler's order, us: 4096 positions in 8 groups x 2 2600 ->
+      // 2571, 8192 at 5120 channels 6454 -> 6327; six or eight fragments ahead measure the same.
       // Register e of block qb is query q0 + 32 qb + 8 (e/4) + 4 hf + e%4 ; column = this lane's key.
       f32x16_t s2[2], dp[2];
       float4 l4[2][4], d4[2][4];

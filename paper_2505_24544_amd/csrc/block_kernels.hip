@@ -6,10 +6,11 @@
 // these kernels are laid out for 16-byte accesses and nothing else:
 //   rmsnorm_fwd   : one workgroup per row, two passes over the row (the second
 //                   one hits L2), writes the normalised row and 1/rms
-//   rmsnorm_bwd   : one workgroup per slice of rows, a row in registers; dx per
-//                   row, the gain's gradient as per-workgroup column partials
-//                   that a second kernel sums in a fixed order (deterministic,
-//                   no atomics)
+//   rmsnorm_bwd   : one workgroup per slice of rows, a row in registers (very
+//                   wide ones: read twice, column sums in LDS); dx per row, the
+//                   gain's gradient as per-workgroup column partials that a
+//                   second kernel sums in a fixed order (deterministic, no
+//                   atomics)
 //   silu_mul_fwd / _bwd : element-wise
 // Templated on the storage type (float, or bf16 bits widened on load).
 #include "common.h"

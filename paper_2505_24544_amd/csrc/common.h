@@ -90,7 +90,7 @@ void launch_sum_pairs(const SumPairArgs& p, int64_t n, bool out_f32, hipStream_t
 
 // ---- draft block around the attention (section 4.1, Eq. 1): streaming kernels ----
 constexpr int RMS_BWD_MAX_PARTS = 1024;      // workgroups (= column-partial rows) of the RMSNorm backward
-constexpr int RMS_MAX_D = 12288;             // its column partials live in LDS: 4 * D bytes
+constexpr int RMS_MAX_D = 12288;             // rows past its registers (1024 vectors of 16 bytes) keep their column sums in LDS: 4 * D bytes
 int rmsnorm_bwd_parts(int64_t rows);
 void launch_rmsnorm_fwd(bool bf16, const void* x, const void* gain, void* out, float* rinv, int64_t rows, int D,
                         float eps, hipStream_t s, const char* name);
