@@ -1097,9 +1097,8 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) st[0][e] += st2[e];
       } else {
-        // One chain per block, hi parts first.  q's fragments come from their LDS planes in every step (the two output
-        // accumulators fill the accumulation registers, and 128 more registers of fragments did not survive register
-        // allocation): the lo fragments land during the hi parts' MFMAs, the V fragments during the lo parts'.
+        // One chain per block, hi parts first.  q's fragments come from their LDS planes in every step (128 more registers of
+        // fragments did not survive register allocation while the scores took accumulation registers too): the lo fragments land during the hi parts' MFMAs, the V fragments during the lo parts'.
         qfrag_t qf[NQB][8], ql_[NQB][8];
         static_for<0, NQB>([&](auto b_) {
           constexpr int b = decltype(b_)::value;
