@@ -22,11 +22,10 @@ FLAGS = [
 ]
 # Matrix instructions write either register file.  By default all of a kernel's write accumulation registers as soon as it needs any
 # of those, and every score, probability or sum that vector instructions go on to use is copied over first.  By file, us without / with:
-# dK/dV see attn_bwd_bf16.hip; draft step of 64 queries over 4096 rows 57.3 / 56.4, of one 34.6 / 34.4; float step of 128 rows at head
-# width 64 46.9 / 46.6, at 32 42.6 / 41.9.  But attn_f32_wide.hip: 128 rows at width 100 68.6 / 71.8, 2 x 500 at 96 192 / 195.  The other
-# files' kernels come out the same either way.
+# dK/dV see attn_bwd_bf16.hip; draft step of 64 queries over 4096 rows 57.3 / 56.4, of one 34.6 / 34.4.  The other files' kernels come
+# out the same either way.
 VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-VGPR_FORM_SOURCES = ("attn_bwd_bf16.hip", "decode_bf16.hip", "f32_kernels.hip")
+VGPR_FORM_SOURCES = ("attn_bwd_bf16.hip", "decode_bf16.hip")
 
 
 def sources():

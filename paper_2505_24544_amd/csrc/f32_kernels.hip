@@ -22,6 +22,20 @@
 namespace beagle {
 namespace {
 
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
+
+__device__ __forceinline__ f32x16_t mfma(float a, float b, const f32x16_t& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16_t zero16() {
+  f32x16_t z;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) z[e] = 0.f;
+  return z;
+}
+// row (A operand) or column of the 32 x 32 output that accumulator register e of lane half hf belongs to
+__device__ __forceinline__ int acc_row(int e, int hf) { return 8 * (e >> 2) + 4 * hf + (e & 3); }
+
 // ---------------------------------------------------------------------------
 // GEMM.  KG = 4: a 32 x 32 tile per workgroup, the four waves take chunks of 32 k in turn.  KG = 1: a 64 x 64 tile, a
 // 32 x 32 quarter per wave, for problems with tiles enough (half the operand traffic per flop).
@@ -141,14 +155,26 @@ void launch_gemm_f32(const GemmGroup& g, hipStream_t s, const char* name) {
   else hipLaunchKernelGGL(gemm_f32_kernel<1>, dim3((unsigned)t64), dim3(256), 0, s, g);
 }
 
+// the instantiation of a head width: 32-channel blocks, and whether they are full
+template <class F>
+static void launch_widths(const AttnArgs& a, F&& go) {
+  auto full = [&](auto nc_) { if (a.d == 32 * decltype(nc_)::value) go(nc_, int_c<1>{}); else go(nc_, int_c<0>{}); };
+  if (a.d <= 32) full(int_c<1>{}); else if (a.d <= 64) full(int_c<2>{}); else if (a.d <= 96) full(int_c<3>{}); else full(int_c<4>{});
+}
+
 void launch_attn_fwd_f32(const AttnArgs& a, hipStream_t s) {
   ProfScope ps("attn_fwd_f32", s);
-  if (a.d > 64) launch_attn_fwd_f32_wide(a, s); else launch_fwd<1>(a, s);
+  launch_widths(a, [&](auto nc_, auto full_) {
+    hipLaunchKernelGGL((attn_fwd_f32_kernel<decltype(nc_)::value, decltype(full_)::value>), dim3((a.S + AT - 1) / AT, a.H, a.B), dim3(64 * AW), 0, s, a);
+  });
 }
 
 void launch_attn_bwd_f32(const AttnArgs& a, hipStream_t s) {
   ProfScope ps("attn_bwd_f32", s);
-  if (a.d > 64) launch_attn_bwd_f32_wide(a, s); else launch_bwd<1>(a, s);
+  const int n_dq = ((a.S + AT - 1) / AT) * a.H * a.B, n_dkv = ((a.L + AT - 1) / AT) * a.G * a.B;
+  launch_widths(a, [&](auto nc_, auto full_) {
+    hipLaunchKernelGGL((attn_bwd_f32_kernel<decltype(nc_)::value, decltype(full_)::value>), dim3(n_dq + n_dkv), dim3(64 * AW), 0, s, a, n_dq);
+  });
 }
 
 }  // namespace beagle
