@@ -1,158 +1,180 @@
 // The fp32 path (io_dtype == BEAGLE_F32): projections and masked attention (attn_f32.h) in
-// float throughout, on the float matrix instruction v_mfma_f32_32x32x2_f32 (an
+// float throughout, on the float matrix instruction v_mfma_f32_16x16x4_f32 (an
 // ordinary float multiply-add chain: results stay within 1e-5 of float64).
 //
 // The problems this path sees are small (the reference problem is 128 rows of
 // 256), so what bounds it is latency: launches, trips to memory and serial
 // chains, not arithmetic.  Hence:
 //   * No LDS staging.  Operand fragments go from L2 straight into registers in
-//     the matrix instruction's layout: lane l supplies row (column) l % 32, and
-//     since the two operands only have to agree on what k a lane half stands
-//     for, half h takes k = 8 i + 4 h + e of instruction (i, e): one 16-byte load
-//     where k is contiguous in memory, four coalesced 4-byte loads where it is not.
-//   * Small tiles (32 x 32) whose four waves split the contraction, so that a
-//     128 x 256 output still occupies 32 workgroups and a contraction of 256 is
-//     one trip to memory and 32 instructions per wave; the four sums meet in LDS.
+//     the matrix instruction's layout, 16 bytes at a time: the two operands only
+//     have to agree on what k a lane group stands for, and which of a tile's columns
+//     is an instruction's n-th is free.
+//   * Small tiles (16 x 64, 16 x 16 scores) whose eight waves split the
+//     contraction, so that a 128 x 256 output occupies 32 workgroups and a
+//     contraction of 256 is one trip to memory and 32 instructions of 32 cycles per
+//     wave; the eight sums meet in LDS.
 //   * Everything independent shares a launch: problems of different storage
 //     orders in one GEMM group, dQ with dK / dV in one attention launch.
-// One training step at 128 rows, hidden 256, 4 heads of 64: 367 us with the
-// scalar kernels that were here (nine launches of 27 - 87 us), 48 us now.
+// One training step at 128 rows, hidden 256, 4 heads of 64: 367 us on scalar
+// kernels (nine launches), 46.5 on 32 x 32 x 2 instructions and four waves, 37.6 now.
+#include <string.h>
 #include "attn_f32.h"
 
 namespace beagle {
 namespace {
 
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16_t;
-
-__device__ __forceinline__ f32x16_t mfma(float a, float b, const f32x16_t& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x16_t zero16() {
-  f32x16_t z;
+// A group and where each of its problems' tiles begin.  A workgroup finds its problem in one trip to the kernel's arguments and has all
+// that the problem says in a second one (walking from problem to problem took a trip each).
+struct TiledGroup {
+  int32_t first[6];                                                    // past the last problem: beyond every tile
+  GemmArgs p[6];
+};
+__device__ __forceinline__ const GemmArgs& problem_of(const TiledGroup& grp, int& t) {
+  asm volatile("" :: "s"(grp.first[1]), "s"(grp.first[2]), "s"(grp.first[3]), "s"(grp.first[4]), "s"(grp.first[5]));
+  int pi = 0, f = 0;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) z[e] = 0.f;
-  return z;
+  for (int i = 1; i < 6; ++i)
+    if (t >= grp.first[i]) { pi = i; f = grp.first[i]; }
+  t -= f;
+  const GemmArgs& p = grp.p[pi];
+  asm volatile("" :: "s"(p.A), "s"(p.B), "s"(p.C), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.lda), "s"(p.ldb), "s"(p.ldc), "s"(p.a_kmajor),
+               "s"(p.b_kmajor), "s"(p.A2), "s"(p.B2), "s"(p.K2), "s"(p.lda2), "s"(p.ldb2), "s"(p.R), "s"(p.ldr));
+  return p;
 }
-// row (A operand) or column of the 32 x 32 output that accumulator register e of lane half hf belongs to
-__device__ __forceinline__ int acc_row(int e, int hf) { return 8 * (e >> 2) + 4 * hf + (e & 3); }
 
 // ---------------------------------------------------------------------------
-// GEMM.  KG = 4: a 32 x 32 tile per workgroup, the four waves take chunks of 32 k in turn.  KG = 1: a 64 x 64 tile, a
-// 32 x 32 quarter per wave, for problems with tiles enough (half the operand traffic per flop).
+// GEMM: a tile of 16 x 64 per workgroup, whose eight waves take chunks of 32 k in turn; the eight sums meet in LDS.
+// Bound by one trip to memory and the chain behind it.  Lane (n, g) of a 16 x 16 x 4 instruction supplies row (column) n at k = g, and
+// what it stands for is free: k = 16 j + 4 g + e of a chunk, so that a k-contiguous operand comes 16 bytes at a time, and column
+// 4 n + u of the tile in instruction u, so that a row-contiguous B does too (10 requests per 32 k, and 32 instructions of 32 cycles;
+// 32 x 32 tiles on 32 x 32 x 2 instructions took 20 requests, 16 of them of 4 bytes, and with four waves twice the chain).
+// Every N and leading dimension is a multiple of 4, and so is K where an operand is k-contiguous (the descriptor's checks on widths).
+// AHEAD: two chunks of a wave in flight, which leaves registers for one workgroup per CU; without, two share a CU.
 // ---------------------------------------------------------------------------
-template <int KG>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmGroup grp) {
-  constexpr int T = KG == 4 ? 32 : 64;
-  __shared__ float red[KG == 4 ? 4 : 1][32][33];
-  int t = blockIdx.x, pi = 0;
-  for (; pi + 1 < grp.count; ++pi) {
-    const int n = ((grp.p[pi].M + T - 1) / T) * ((grp.p[pi].N + T - 1) / T);
-    if (t < n) break;
-    t -= n;
-  }
-  const GemmArgs& g = grp.p[pi];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hf = lane >> 5, ql = lane & 31;
-  const int tn = (g.N + T - 1) / T;
-  const int m0 = (t / tn) * T + (KG == 1 ? (wave >> 1) * 32 : 0), n0 = (t % tn) * T + (KG == 1 ? (wave & 1) * 32 : 0);
-  const int mr = min(m0 + ql, g.M - 1), nc = min(n0 + ql, g.N - 1);    // rows and columns past the end repeat the last one
-  f32x16_t acc = zero16();
+constexpr int GW = 8, GM = 16, GN = 64;
+template <bool AHEAD>
+__global__ __launch_bounds__(64 * GW, AHEAD ? 2 : 4) void gemm_f32_kernel(TiledGroup grp) {
+  __shared__ __attribute__((aligned(16))) float red[GW][GM][GN + 4];
+  int t = blockIdx.x;
+  const GemmArgs& p = problem_of(grp, t);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, nl = lane & 15;
+  const int tn = (p.N + GN - 1) / GN, m0 = (t / tn) * GM, n0 = (t % tn) * GN;
+  const int mr = min(m0 + nl, p.M - 1), nc = min(n0 + 4 * nl, p.N - 4);    // rows and columns past the end repeat the last ones
+  f32x4_t acc[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) acc[u] = zero4();
 
-  // one k segment; AK / BK: k contiguous in memory
-  auto segment = [&](auto ak_, auto bk_, const float* A, const float* B, int K, int64_t lda, int64_t ldb) BEAGLE_INLINE_LAMBDA {
+  // AK / BK: k contiguous in memory
+  auto contract = [&](auto ak_, auto bk_) BEAGLE_INLINE_LAMBDA {
     constexpr bool AK = decltype(ak_)::value, BK = decltype(bk_)::value;
-    const float* ap = AK ? A + mr * lda : A + mr;
-    const float* bp = BK ? B + nc * ldb : B + nc;
-    // 32 k of both operands: register 4 i + e is k = k0 + 8 i + 4 hf + e; past K: zeros on both sides (0 * inf is a NaN)
-    auto load = [&](int k0, float (&a)[16], float (&b)[16]) BEAGLE_INLINE_LAMBDA {
+    // chunk c of both segments' 32 k each: register 4 j + e is k = 16 j + 4 g + e of it; past K: zeros on both sides (0 * inf is a NaN)
+    const int nc1 = (p.K + 31) / 32, chunks = nc1 + (p.A2 ? (p.K2 + 31) / 32 : 0);
+    auto load = [&](int c, float (&a)[8], float (&b)[4][8]) BEAGLE_INLINE_LAMBDA {
+      const bool two = c >= nc1;
+      const float* A = (const float*)(two ? p.A2 : p.A);
+      const float* B = (const float*)(two ? p.B2 : p.B);
+      const int64_t lda = two ? p.lda2 : p.lda, ldb = two ? p.ldb2 : p.ldb;
+      const int K = two ? p.K2 : p.K, k0 = 32 * (two ? c - nc1 : c);
+      auto at = [&](int k, int i, bool in) BEAGLE_INLINE_LAMBDA {      // one k of the operands that are not k-contiguous
+        if (!AK) { const float v = A[k * lda + mr]; a[i] = in ? v : 0.f; }
+        if (!BK) {
+          const float4 v = *(const float4*)(B + k * ldb + nc);
+          b[0][i] = in ? v.x : 0.f; b[1][i] = in ? v.y : 0.f; b[2][i] = in ? v.z : 0.f; b[3][i] = in ? v.w : 0.f;
+        }
+      };
+      auto four = [&](int k, int j, bool in) BEAGLE_INLINE_LAMBDA {    // four of those that are
+        auto put = [&](float (&f)[8], const float4& v) BEAGLE_INLINE_LAMBDA {
+          f[4 * j] = in ? v.x : 0.f; f[4 * j + 1] = in ? v.y : 0.f; f[4 * j + 2] = in ? v.z : 0.f; f[4 * j + 3] = in ? v.w : 0.f;
+        };
+        if (AK) put(a, *(const float4*)(A + mr * lda + k));
+        if (BK) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) put(b[u], *(const float4*)(B + (nc + u) * ldb + k));
+        }
+      };
       if (k0 + 32 <= K) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int k = k0 + 8 * i + 4 * hf;
-          if (AK) { const float4 v = *(const float4*)(ap + k); a[4 * i] = v.x; a[4 * i + 1] = v.y; a[4 * i + 2] = v.z; a[4 * i + 3] = v.w; }
-          if (BK) { const float4 v = *(const float4*)(bp + k); b[4 * i] = v.x; b[4 * i + 1] = v.y; b[4 * i + 2] = v.z; b[4 * i + 3] = v.w; }
+        for (int j = 0; j < 2; ++j) {
+          const int k = k0 + 16 * j + 4 * g;
+          four(k, j, true);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (!AK) a[4 * i + e] = ap[(k + e) * lda];
-            if (!BK) b[4 * i + e] = bp[(k + e) * ldb];
-          }
+          for (int e = 0; e < 4; ++e) at(k + e, 4 * j + e, true);
         }
       } else {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int k = k0 + 8 * (i >> 2) + 4 * hf + (i & 3), kc = min(k, K - 1);
-          const float v = AK ? ap[kc] : ap[kc * lda], w = BK ? bp[kc] : bp[kc * ldb];
-          a[i] = k < K ? v : 0.f;
-          b[i] = k < K ? w : 0.f;
+        for (int j = 0; j < 2; ++j) {
+          const int k = k0 + 16 * j + 4 * g;
+          if (AK || BK) four(min(k, K - 4), j, k < K);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) at(min(k + e, K - 1), 4 * j + e, k + e < K);
         }
       }
     };
-    auto compute = [&](const float (&a)[16], const float (&b)[16]) BEAGLE_INLINE_LAMBDA {
+    auto compute = [&](const float (&a)[8], const float (&b)[4][8]) BEAGLE_INLINE_LAMBDA {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc = mfma(a[i], b[i], acc);
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[u] = mfma16(a[i], b[u][i], acc[u]);
     };
-    // two chunks in flight; a contraction of up to 256 (64 with one wave) is loaded whole before the first product
-    float a0[16], b0[16], a1[16], b1[16];
-    int k = KG == 4 ? 32 * wave : 0;
-    constexpr int STEP = 32 * KG;
-    if (k < K) load(k, a0, b0);
-    if (k + STEP < K) load(k + STEP, a1, b1);
-    for (; k < K; k += 2 * STEP) {
+    // (AHEAD: a contraction of up to 512 is loaded whole before the first product)
+    float a0[8], b0[4][8], a1[8], b1[4][8];
+    int c = wave;
+    if constexpr (!AHEAD) {
+      for (; c < chunks; c += GW) { load(c, a0, b0); compute(a0, b0); }
+      return;
+    }
+    if (c < chunks) load(c, a0, b0);
+    if (c + GW < chunks) load(c + GW, a1, b1);
+    for (; c < chunks; c += 2 * GW) {
       compute(a0, b0);
-      if (k + 2 * STEP < K) load(k + 2 * STEP, a0, b0);
-      if (k + STEP < K) {
+      if (c + 2 * GW < chunks) load(c + 2 * GW, a0, b0);
+      if (c + GW < chunks) {
         compute(a1, b1);
-        if (k + 3 * STEP < K) load(k + 3 * STEP, a1, b1);
+        if (c + 3 * GW < chunks) load(c + 3 * GW, a1, b1);
       }
     }
   };
-  auto both = [&](auto ak_, auto bk_) BEAGLE_INLINE_LAMBDA {
-    segment(ak_, bk_, (const float*)g.A, (const float*)g.B, g.K, g.lda, g.ldb);
-    if (g.A2) segment(ak_, bk_, (const float*)g.A2, (const float*)g.B2, g.K2, g.lda2, g.ldb2);
-  };
-  if (g.a_kmajor && g.b_kmajor) both(int_c<1>{}, int_c<1>{});
-  else if (g.a_kmajor) both(int_c<1>{}, int_c<0>{});
-  else both(int_c<0>{}, int_c<0>{});
+  if (p.a_kmajor && p.b_kmajor) contract(int_c<1>{}, int_c<1>{});
+  else if (p.a_kmajor) contract(int_c<1>{}, int_c<0>{});
+  else contract(int_c<0>{}, int_c<0>{});
 
-  float* C = (float*)g.C;
-  const float* R = (const float*)g.R;
-  if (KG == 4) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) red[wave][acc_row(e, hf)][ql] = acc[e];
-    __syncthreads();
-    const int r = tid >> 3, c = (tid & 7) * 4, m = m0 + r;
-    if (m < g.M) {
+  for (int e = 0; e < 4; ++e)
+    *(float4*)&red[wave][4 * g + e][4 * nl] = make_float4(acc[0][e], acc[1][e], acc[2][e], acc[3][e]);
+  __syncthreads();
+  const int r = tid >> 5, c = 2 * (tid & 31), m = m0 + r, n = n0 + c;
+  if (m >= p.M || n >= p.N) return;
+  float2 v = *(const float2*)&red[0][r][c];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int n = n0 + c + u;
-        if (n >= g.N) break;
-        float v = ((red[0][r][c + u] + red[KG == 4 ? 1 : 0][r][c + u]) + red[KG == 4 ? 2 : 0][r][c + u]) + red[KG == 4 ? 3 : 0][r][c + u];
-        if (R) v += R[m * g.ldr + n];
-        C[m * g.ldc + n] = v;
-      }
-    }
-  } else {
-    const int n = n0 + ql;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int m = m0 + acc_row(e, hf);
-      if (m < g.M && n < g.N) C[m * g.ldc + n] = acc[e] + (R ? R[m * g.ldr + n] : 0.f);
-    }
+  for (int w = 1; w < GW; ++w) {
+    const float2 x = *(const float2*)&red[w][r][c];
+    v.x += x.x; v.y += x.y;
   }
+  if (p.R) {
+    const float2 x = *(const float2*)((const float*)p.R + m * p.ldr + n);
+    v.x += x.x; v.y += x.y;
+  }
+  *(float2*)((float*)p.C + m * p.ldc + n) = v;
 }
 
 }  // namespace
 
-// 32 x 32 tiles while they are fewer than fit the chip twice over at four workgroups per CU; 64 x 64 beyond
+// Requests a chunk ahead up to two workgroups per CU, workgroups in pairs beyond.  Steps, us, ahead / in pairs: 128 rows at
+// 4 x 128 channels 57.8 / 60.5 (59.0 by this rule: its last launch has 896 tiles), 200 at 4 x 128 77.4 / 77.0 (75.5), 600 at 8 x 64
+// 122 / 115, 1040 at 4 x 128 238 / 219, 3000 at 8 x 64 756 / 724.  (Tiles of 32 rows: 62.8, 76.5, 120, 218, 712; of 64 x 64 without a
+// split of the contraction, as large problems were worked before: the last two 231 and 824.)
 void launch_gemm_f32(const GemmGroup& g, hipStream_t s, const char* name) {
-  int64_t t32 = 0, t64 = 0;
-  for (int i = 0; i < g.count; ++i) {
-    t32 += (int64_t)((g.p[i].M + 31) / 32) * ((g.p[i].N + 31) / 32);
-    t64 += (int64_t)((g.p[i].M + 63) / 64) * ((g.p[i].N + 63) / 64);
+  TiledGroup t;
+  int64_t tiles = 0;
+  for (int i = 0; i < 6; ++i) {
+    t.first[i] = i < g.count ? (int32_t)tiles : INT32_MAX;
+    if (i < g.count) tiles += (int64_t)((g.p[i].M + GM - 1) / GM) * ((g.p[i].N + GN - 1) / GN);
   }
-  if (t32 == 0) return;
+  if (tiles == 0) return;
+  memcpy(t.p, g.p, sizeof(t.p));
   ProfScope ps(name, s);
-  if (t32 < 2048) hipLaunchKernelGGL(gemm_f32_kernel<4>, dim3((unsigned)t32), dim3(256), 0, s, g);
-  else hipLaunchKernelGGL(gemm_f32_kernel<1>, dim3((unsigned)t64), dim3(256), 0, s, g);
+  if (tiles <= 512) hipLaunchKernelGGL(gemm_f32_kernel<true>, dim3((unsigned)tiles), dim3(64 * GW), 0, s, t);
+  else hipLaunchKernelGGL(gemm_f32_kernel<false>, dim3((unsigned)tiles), dim3(64 * GW), 0, s, t);
 }
 
 // the instantiation of a head width: 32-channel blocks, and whether they are full
