@@ -106,7 +106,21 @@ __global__ __launch_bounds__(256, 2) void skinny_gemm_kernel(const bf16_t* __res
   const int n0 = blockIdx.x * SG_N, ks = blockIdx.y, k0 = ks * SG_K;
   const int mblocks = (M + 31) / 32;
 
-  // Loads whose values this wave needs first go first (a wave's loads return in order).
+  // The whole tile is requested at once: 16 loads of 16 bytes per lane in flight.  A wave's loads return in order, so what the first
+  // quarter's products need goes first -- but its weights ahead of x, whose requests (16 bytes of each of up to 64 rows) take some 200
+  // cycles each to issue, while nothing else is under way.  (x first, weights first, us: 1 query over 4096 rows 34.5, 34.3; 16 over 1024
+  // 30.4, 29.4; 32 over 4096 45.0, 44.3; 64 over 4096 57.5, 56.7; a block's step of 8 over 1500 104.0, 102.6.)
+  const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void*)W, 0, (int)((int64_t)K * N * 2), 0x00020000);
+  auto request = [&](bf16_t* wq, int c) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int q = tid + 256 * i, k = q >> 3, ch = (q & 7) ^ (((k >> 1) & 1) << 2);
+      const int off = (int)(((int64_t)(k0 + c * SG_KQ + k) * N + n0 + 8 * ch) * 2);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lds_void_ptr)(wq + (i * 4 + wave) * 512), 16, off, 0, 0, 0);
+    }
+  };
+  request(wt0, 0);
+  __builtin_amdgcn_sched_barrier(0);
   // plain: x fragments (B operand): lane holds x[m][k0 + 128 c + 32 wave + 16 s2 + 8 hf .. +7] as xf[mb][2 c + s2]
   bf16x8_t xf[2][8];
   // COMBINE: item = (query m, head hh of the 4, float4 column c4); all R ranges of a thread's (up to two) items
@@ -158,17 +172,7 @@ __global__ __launch_bounds__(256, 2) void skinny_gemm_kernel(const bf16_t* __res
   }
   __builtin_amdgcn_sched_barrier(0);
 
-  // the whole tile is requested at once: 16 loads of 16 bytes per lane in flight
-  const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void*)W, 0, (int)((int64_t)K * N * 2), 0x00020000);
-  auto request = [&](bf16_t* wq, int c) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int q = tid + 256 * i, k = q >> 3, ch = (q & 7) ^ (((k >> 1) & 1) << 2);
-      const int off = (int)(((int64_t)(k0 + c * SG_KQ + k) * N + n0 + 8 * ch) * 2);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(wrs, (lds_void_ptr)(wq + (i * 4 + wave) * 512), 16, off, 0, 0, 0);
-    }
-  };
-  request(wt0, 0); request(wt1, 1); request(wt2, 2); request(wt3, 3);
+  request(wt1, 1); request(wt2, 2); request(wt3, 3);
   __builtin_amdgcn_sched_barrier(0);
 
   float lsev[COMBINE ? NIT : 1];             // stored at the end: a store in flight would blur the count of landed requests
