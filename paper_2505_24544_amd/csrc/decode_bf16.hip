@@ -401,6 +401,7 @@ constexpr int ST_N = 16;                 // output columns per workgroup
 constexpr int ST_FLIGHT = 4;             // weight macro-steps (4 KB) in flight per wave, over all matrices
 constexpr int ST_ROUND = 4;              // macro-steps per unrolled round of the loop
 constexpr int ST_MAXM = 16;              // rows per launch
+constexpr int ST_WHOLE_WAVES = 8;        // strip_gemm_whole_kernel
 }  // namespace dec
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
@@ -668,6 +669,111 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
   }
   if (MODE == 1 && blockIdx.x == 0 && (lane & 7) == 0 && (lane >> 3) < nst)
     cb.lse[(int64_t)(wave + WAVES * (lane >> 3)) * cb.lse_stride] = lse_out;
+}
+
+// The same for one matrix whose macro-steps a wave can request all at once, with their activations: STEPS of them in straight-line
+// code, without the ring and the chunks.  What bounds it is the weights' stream and the trip ahead of it, so what counts is how soon a
+// wave's requests are out: the general kernel asks for and parks a second chunk of activations, empty or not, works a depth of five in
+// two rounds of four, and carries the code of all its modes.  Steps on packed weights, us, before and now: 6 queries over 619 rows,
+// 8 of 32 heads' keys, 23.6, 21.6; 4 over 2500 29.5, 27.7; at 5120 channels 3 over 1000 45.8, 35.3, 16 over 700 51.8, 40.6; at 8192
+// 2 over 700 65.7, 62.4; a block's step of 4 over 700 78.7, 75.4.
+template <int ROWS, int STEPS, bool TABLE>
+__global__ __launch_bounds__(512, 1) void strip_gemm_whole_kernel(const bf16_t* __restrict__ a, const bf16_t* __restrict__ Wt,
+                                                                void* __restrict__ yout, const bf16_t* __restrict__ res, int M, int N,
+                                                                int K, int out_f32, float norm_eps, RopeRows rope) {
+  using namespace dec;
+  asm volatile("" :: "s"(a), "s"(Wt), "s"(yout), "s"(res), "s"(M), "s"(N), "s"(K), "s"(out_f32), "s"(norm_eps));
+  if (TABLE && (int)blockIdx.x == N / ST_N) {               // (one more workgroup when there is a table to write)
+    rope_table(rope, M, threadIdx.x, 512);
+    return;
+  }
+  constexpr int WAVES = ST_WHOLE_WAVES, LPS = ROWS / 4, NLD = STEPS * LPS;
+  __shared__ __attribute__((aligned(1024))) unsigned char abuf[WAVES * STEPS * ROWS * 256];       // 16 rows, 5 steps: all 160 KB
+  // a wave's sums, and its share of the rows' sums of squares (RMSNorm), replace its activations
+  auto red = [&](int w, int m, int n) -> float& { return ((float*)(abuf + w * (STEPS * ROWS * 256)))[m * 16 + n]; };
+  auto ssw = [&](int w, int m) -> float& { return ((float*)(abuf + w * (STEPS * ROWS * 256)))[ROWS * 16 + m]; };
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nl = lane & 15, kg = lane >> 4;
+  const int n0 = blockIdx.x * ST_N, nst = ((K >> 7) - wave + WAVES - 1) / WAVES;      // wave w takes macro-steps w, w + 8, ...
+  unsigned char* aw = abuf + wave * (STEPS * ROWS * 256);
+  // activations: load q covers rows 4 g + kg of step i, (i, g) = divmod(q, LPS): lane (kg, nl) reads chunk nl ^ row of its row and
+  // parks it at chunk nl; rows and steps past the end arrive as zeros
+  const __amdgpu_buffer_rsrc_t ars = __builtin_amdgcn_make_buffer_rsrc((void*)a, 0, (int)((int64_t)M * K * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void*)Wt, 0, (int)((int64_t)N * K * 2), 0x00020000);
+  xload_t av[NLD];
+#pragma unroll
+  for (int q = 0; q < NLD; ++q) {
+    const int i = q / LPS, row = 4 * (q % LPS) + kg;
+    av[q] = __builtin_amdgcn_raw_buffer_load_b128(
+        ars, (i < nst && row < M) ? (row * K + (wave + WAVES * i) * 128 + 8 * (nl ^ row)) * 2 : (int)0x80000000, 0, 0);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const int wbase = blockIdx.x * 4096 + lane * 16, wstep = (N / ST_N) * 4096;
+  union frag_t { xload_t u; bf16x8_t v; };
+  frag_t bw[STEPS][4];
+#pragma unroll
+  for (int u = 0; u < STEPS; ++u)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      bw[u][j].u = __builtin_amdgcn_raw_buffer_load_b128(wrs, u < nst ? wbase + (wave + WAVES * u) * wstep + j * 1024 : (int)0x80000000, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < NLD; ++q) *(xload_t*)(aw + ((q / LPS) * ROWS + 4 * (q % LPS)) * 256 + lane * 16) = av[q];
+  const bool rownorm = norm_eps >= 0.f;
+  float ssl[LPS];                       // this lane's share of its rows' sums of squares
+#pragma unroll
+  for (int g = 0; g < LPS; ++g) ssl[g] = 0.f;
+  if (rownorm) {
+#pragma unroll
+    for (int q = 0; q < NLD; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float lo = __uint_as_float(av[q][e] << 16), hi = __uint_as_float(av[q][e] & 0xffff0000u);
+        ssl[q % LPS] += lo * lo + hi * hi;
+      }
+#pragma unroll
+    for (int g = 0; g < LPS; ++g) {     // a row's 16 chunk lanes (same kg) add up, then the waves do below
+      float t = ssl[g];
+      t += __shfl_xor(t, 1); t += __shfl_xor(t, 2); t += __shfl_xor(t, 4); t += __shfl_xor(t, 8);
+      ssl[g] = t;
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int mr = nl & (ROWS - 1);
+#pragma unroll
+  for (int u = 0; u < STEPS; ++u) {
+    frag_t af[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) af[j].u = *(const xload_t*)(aw + (u * ROWS + mr) * 256 + (((4 * j + kg) ^ mr) & 15) * 16);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[j].v, bw[u][j].v, acc, 0, 0, 0);
+  }
+  // the waves' k shares, added in wave order; output row 4 kg + e, column nl
+  if (kg < LPS) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red(wave, 4 * kg + e, nl) = acc[e];
+  }
+  if (rownorm && nl == 0) {
+#pragma unroll
+    for (int g = 0; g < LPS; ++g) ssw(wave, 4 * g + kg) = ssl[g];
+  }
+  __syncthreads();
+  if (tid < M * 16) {
+    const int m = tid >> 4, n = tid & 15;
+    float v = red(0, m, n);
+#pragma unroll
+    for (int wv = 1; wv < WAVES; ++wv) v += red(wv, m, n);
+    if (rownorm) {
+      float ss = ssw(0, m);
+#pragma unroll
+      for (int wv = 1; wv < WAVES; ++wv) ss += ssw(wv, m);
+      v *= 1.f / sqrtf(ss / (float)K + norm_eps);
+    }
+    const int64_t o = (int64_t)m * N + n0 + n;
+    if (res) v += __uint_as_float((uint32_t)res[o] << 16);
+    if (out_f32) ((float*)yout)[o] = v;                       // the queries: the attention kernel wants them unrounded
+    else ((bf16_t*)yout)[o] = (bf16_t)(cvt_pk(v, 0.f) & 0xffffu);
+  }
 }
 
 // The one-time re-layout of a weight matrix W [K][N] (row-major) for strip_gemm_kernel: one thread per 16 bytes of
@@ -1448,6 +1554,20 @@ void launch_strip_gemm(const bf16_t* a, const bf16_t* wt, const bf16_t* wt2, voi
   // one matrix: eight waves, one workgroup per CU (N / 16 is about the number of CUs for the attention's projections);
   // the feed-forward pair has several strips per CU: four waves and two workgroups per CU, so that one's start and
   // final reduction hide behind the other's stream; the K/V pair of the cache append (y2 given) is as wide as one matrix
+  auto whole = [&](auto rows_, auto steps_) {
+    constexpr int R = decltype(rows_)::value, S = decltype(steps_)::value;
+    if (rope.tab) hipLaunchKernelGGL((strip_gemm_whole_kernel<R, S, true>), grid, dim3(512), 0, s, a, wt, y, res, M, N, K, f, norm_eps, rope);
+    else hipLaunchKernelGGL((strip_gemm_whole_kernel<R, S, false>), grid, dim3(512), 0, s, a, wt, y, res, M, N, K, f, norm_eps, rope);
+  };
+  const int steps = (K / 128 + ST_WHOLE_WAVES - 1) / ST_WHOLE_WAVES;       // macro-steps of a wave
+  if (!merge && !wt2 && steps <= (M <= 8 ? 8 : 5)) {
+    if (M > 8 && steps <= 4) whole(int_c<16>{}, int_c<4>{});
+    else if (M > 8) whole(int_c<16>{}, int_c<5>{});
+    else if (steps <= 4) whole(int_c<8>{}, int_c<4>{});
+    else if (steps == 5) whole(int_c<8>{}, int_c<5>{});
+    else whole(int_c<8>{}, int_c<8>{});
+    return;
+  }
 #define STRIP_ARGS a, wt, wt2, y, y2, res, M, N, K, cb, f, norm_eps, rope
   if (merge) hipLaunchKernelGGL((strip_gemm_kernel<1, false, 8>), grid, dim3(512), 0, s, STRIP_ARGS);
   else if (wt2 && y2 && M <= 8) hipLaunchKernelGGL((strip_gemm_kernel<3, false, 8>), grid, dim3(512), 0, s, STRIP_ARGS);
