@@ -102,6 +102,16 @@ __device__ __forceinline__ float half_pair_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// the same over a lane and its partner lane ^ 16
+__device__ __forceinline__ float quarter_pair_max(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float quarter_pair_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 __device__ __forceinline__ uint32_t cvt_pk(float lo, float hi) {
   f32x2_t f = {lo, hi};
   bf16x2_t b = __builtin_convertvector(f, bf16x2_t);

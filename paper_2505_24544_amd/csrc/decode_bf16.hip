@@ -827,16 +827,20 @@ typedef lds_u32x2_t u32x2_t;
 // (H >> hs_log2, R); row i of its 32 rows is query i % 2^row_log2 of head i >> row_log2 ("query" below), and rows whose query is
 // past M read zeros and are not stored.  A kernel of its own: with the rows' arithmetic in it, the one for heads alone took 0.3 -
 // 0.5 us longer (32 queries over 2000 rows 12.7 -> 13.1).
-// NQB = 1 (up to 32 queries): the four waves split each 128-key step by rows, 32 keys each.  A wave requests, reads
-// and refills only its own 32 rows of the two stages, so the step loop has no barrier; a stage half (the wave's K
-// rows, then its V rows) is refilled for the step after next as soon as its fragments sit in registers, i.e. BEFORE
-// the step's arithmetic: with both stages landed and nothing requested, HBM would idle for as long as a step
-// computes (measured: 3 us of the kernel's 16).
-// NQB = 2 (33 .. 64 queries): the same split of a step by rows; every wave works its 32 keys against both blocks of
-// 32 queries, so K and V fragments are read from LDS once for the two blocks, no wave reads another's rows and the
-// loop is as free of barriers as with one block.  (Waves 0, 1 on the first block and waves 2, 3 on the second, each
-// with 64 keys of a step, was the earlier shape: stages shared between waves, hence a barrier per step with the
-// refill issued only behind it -- 4 400 cycles of arithmetic and 2 700 of request issue per step, one after the other.)
+// The four waves split each 128-key step by rows, 32 keys each; a wave works them against every block of queries, so K and V fragments are
+// read from LDS once for all of them.  It requests, reads and refills only its own 32 rows of the two stages, so the step
+// loop has no barrier; a stage half (the wave's K rows, then its V rows) is refilled for the step after next as soon as its
+// fragments sit in registers, i.e. BEFORE the step's arithmetic: with both stages landed and nothing requested, HBM would idle for
+// as long as a step computes (measured: 3 us of the kernel's 16).
+// NQB: blocks of 32 queries (1 or 2), or 0 for one of 16.  What lies between the last byte and the kernel's end -- a step, the merge --
+// is exposed, all workgroups being in the same place, and with up to 16 rows half of a 32-column product is for nothing: there the
+// scores are blocks of 16 keys by 16 queries (24 instructions of 16 cycles per step for 24 of 32), a lane has 8 of them and 32 of O
+// instead of 16 and 64, a wave leaves its partial in its own rows of a stage (no barrier in front) and every thread of the merge works the
+// waves' weights out itself (no phase for them).  By stamps, 1 query over 4096 rows: a step 2 000 -> 1 500 cycles, from the loop's end to the
+// kernel's 2 900 -> 2 000, and what a step needs beside q is worked out while the first one travels (1 600 cycles).  Steps, us,
+// blocks of 32 / 16: 1 query over 4096 rows 34.1 / 33.2, 16 over
+// 1024 29.6 / 28.6; on packed weights 6 over 619 rows in 8 groups 21.6 / 20.5, 10 over 2000 29.8 / 28.7; the tree's block 90.9 / 89.4.
+// With more rows blocks of 16 are no gain (17 .. 32 rows: 2 % slower; 64: 1 % faster, 40: 4 % slower).
 // QS: k-slices of q that are requested at once: one on packed weights, where q comes as a single slice (asked for as eight,
 // seven of them past the buffer's end, they took the summing wave another 28 requests), else eight; more in further trips.
 template <int NQB, int QS, bool GROUPED>
@@ -846,16 +850,20 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
   // two stages of a tile kind are 32 KB apart (within the offset field of an LDS read)
   __shared__ __attribute__((aligned(1024))) bf16_t kvt[4 * TILE];
   auto tile_of = [&](int si, int t) { return kvt + (2 * t + si) * TILE; };
-  // q as bf16 planes of 32 queries: plane b = hi part of block b, plane NQB + b = its lo part.  With two blocks that
-  // makes 160 KB with the stages: the merge's small arrays live in the planes, which are dead after the prologue.
-  __shared__ __attribute__((aligned(1024))) bf16_t qbuf[2 * NQB * 32 * HD];
-  typedef float ml_t[NQB][2][32];
-  typedef float sc_t[NQB][32];
+  // q as bf16 planes: its hi part, then its lo part.  With two blocks of 32 that makes 160 KB with the stages: the merge's small arrays
+  // live in the planes, which are dead after the prologue.  (A block of 16 has its own: a wave may be there while another reads q.)
+  constexpr bool W16 = NQB == 0;
+  constexpr int QROWS = W16 ? 16 : 32 * NQB, PLANE = QROWS * HD;
+  __shared__ __attribute__((aligned(1024))) bf16_t qbuf[2 * PLANE];
+  __shared__ float2 s_ml16[W16 ? 4 : 1][16];                            // [wave]: running max, sum of its queries
+  constexpr int NQ = W16 ? 1 : NQB;                                     // q is summed 32 rows at a time
+  typedef float ml_t[NQ][2][32];
+  typedef float sc_t[NQ][32];
   ml_t* const s_ml = (ml_t*)qbuf;                                       // [wave]: running max, sum of its queries
-  sc_t* const s_sc = (sc_t*)((float*)qbuf + 4 * NQB * 2 * 32);          // [wave]: merge weight of a wave's partial
-  ml_t& s_mm = *(ml_t*)((float*)qbuf + 4 * NQB * 3 * 32);               // merged max, sum per block
-  static_assert((4 * NQB * 3 * 32 + NQB * 2 * 32) * sizeof(float) <= sizeof(qbuf), "merge arrays must fit in the q planes");
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hf = lane >> 5, ql = lane & 31;
+  sc_t* const s_sc = (sc_t*)((float*)qbuf + 4 * NQ * 2 * 32);           // [wave]: merge weight of a wave's partial
+  ml_t& s_mm = *(ml_t*)((float*)qbuf + 4 * NQ * 3 * 32);                // merged max, sum per block
+  static_assert((4 * NQ * 3 * 32 + NQ * 2 * 32) * sizeof(float) <= sizeof(qbuf), "merge arrays must fit in the q planes");
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), hf = lane >> 5, ql = lane & 31, lg = lane >> 4, nl = lane & 15;
   const int h = GROUPED ? blockIdx.x << a.hs_log2 : blockIdx.x, r = blockIdx.y;      // (first) head
   const int mtot = GROUPED ? 1 << (a.hs_log2 + a.row_log2) : a.M;                    // the workgroup's rows
   auto row_query = [&](int row) { return GROUPED ? row & ((1 << a.row_log2) - 1) : row; };
@@ -900,7 +908,6 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
   };
   auto fetch_own = [&](int si, int step) { fetch_own_half(si, step, 0); fetch_own_half(si, step, 1); };
   typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-  typedef float f32x4_t __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) float* lds_float_ptr;
   typedef __attribute__((address_space(3))) bf16_t* lds_bf16_ptr;
   const float4 zero4 = {0.f, 0.f, 0.f, 0.f};
@@ -980,7 +987,7 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
     q_rest(qb, mrows, qwaves, acc);
     if (a.rope_tab) {
       q_angles_t cs;
-      if constexpr (NQB == 1) { q_angles(qb, qwaves, cs); q_rotate(cs, acc); }
+      if constexpr (NQ == 1) { q_angles(qb, qwaves, cs); q_rotate(cs, acc); }
       else                                                   // (no registers for all of them beside both blocks' slices)
         static_for<0, 4>([&](auto i_) { constexpr int i = decltype(i_)::value; q_angle(qb, qwaves, i, cs[i]); q_rotate_one(cs[i], acc[i]); });
     }
@@ -1010,7 +1017,7 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
       q_split(acc[i], hi, lo);
       const u32x2_t vh = {hi.x, hi.y}, vl = {lo.x, lo.y};
       asm volatile("ds_write_b64 %0, %1" : : "v"((lds_bf16_ptr)(qbuf + qb * 32 * HD + q_slot(m, c4))), "v"(vh) : "memory");
-      asm volatile("ds_write_b64 %0, %1" : : "v"((lds_bf16_ptr)(qbuf + (NQB + qb) * 32 * HD + q_slot(m, c4))), "v"(vl) : "memory");
+      asm volatile("ds_write_b64 %0, %1" : : "v"((lds_bf16_ptr)(qbuf + PLANE + qb * 32 * HD + q_slot(m, c4))), "v"(vl) : "memory");
     }
   };
   // B-operand fragments of a plane (explicit ds_read, see above): channels 16 s + 8 hf .. + 7 of query ql
@@ -1035,8 +1042,44 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
 
   // this lane's fragments of q (one block; with two they stay in their LDS planes and are read again in every step)
   bf16x8_t qh[1][8], qlo[1][8];
+  // W16: channels 32 s + 8 lg .. + 7 of query nl, hi and lo part
+  qfrag_t qh16[4], ql16[4];
+  auto read_frags16 = [&]() {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const lds_bf16_ptr p = (lds_bf16_ptr)(qbuf + nl * HD + (((4 * s + lg) ^ nl) << 3));
+      asm volatile("ds_read_b128 %0, %1" : "=v"(qh16[s].u) : "v"(p));
+      asm volatile("ds_read_b128 %0, %1" : "=v"(ql16[s].u) : "v"(p + PLANE));
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(qh16[s].u), "+v"(ql16[s].u));
+  };
+  // W16: what the steps need beside q.  Scores are K q^T in 16 x 16 blocks: a wave's 32 keys are two of them, and score e of block kb in
+  // this lane belongs to key 16 kb + 4 rv + e, rv = lg with its two bits exchanged.  Any order serves as long as V's rows (the k of
+  // the second product) come in the same one, and with this one neither fragment read has a bank conflict: lanes 0 .. 31 of a
+  // transpose read take rows 0 .. 3 and 8 .. 11, whose chunks lie in different banks (those of rows 4 .. 7 lie with rows 0 .. 3).
+  const int rv = ((lg & 1) << 1) | (lg >> 1);
+  uint32_t ka16[4], va16[8];                                 // LDS byte addresses; stages and 16-row blocks add compile-time offsets
+  f32x4_t o16[8];
+  float m16 = -INFINITY, l16 = 0.f;                          // l16: this lane's share
+  auto prepare16 = [&]() {
+    const uint32_t base = (uint32_t)(uintptr_t)(lds_bf16_ptr)kvt;
+    const int krow = 4 * (((nl >> 2 & 1) << 1) | (nl >> 3)) + (nl & 3), vrow = 4 * rv + (nl >> 2);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      ka16[s] = base + 2 * ((wave * 32 + krow) * HD + (((4 * s + lg) ^ swz(krow)) << 3));
+      asm volatile("" : "+v"(ka16[s]));
+    }
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) {
+      va16[cb] = base + 2 * (2 * TILE + (wave * 32 + vrow) * HD + (((2 * cb + ((nl & 3) >> 1)) ^ swz(vrow)) << 3) + 4 * (nl & 1));
+      o16[cb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      asm volatile("" : "+v"(va16[cb]), "+v"(o16[cb]));
+    }
+  };
   bool shared_first_steps = false;                           // steps 0 and 1 requested across waves (barrier before step 1)
-  if (NQB == 1 && mtot <= 8) {
+  if (W16 && mtot <= 8) {
     // Up to 8 queries: wave 0 alone sums (one round trip for its 32 loads) while waves 1 .. 3 request the first
     // two K/V steps at once, wave 0's share included: the 64 requests of a step go round waves 1, 2, 3 (22, 21 and
     // 21 of them).  q is there long before the first step has landed.
@@ -1059,14 +1102,12 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
         uint2 hi, lo;
         q_split(acc[i], hi, lo);
         *(uint2*)(qbuf + q_slot(m, c4)) = hi;
-        *(uint2*)(qbuf + 32 * HD + q_slot(m, c4)) = lo;
+        *(uint2*)(qbuf + PLANE + q_slot(m, c4)) = lo;
       }
     } else {
-      // rows 8 .. 31 hold no query: zeros in both planes (16 bytes per thread and step)
-      for (int idx = tid - 64; idx < 2 * 24 * 16; idx += 192) {
-        const int pl = idx / (24 * 16), rest = idx % (24 * 16);
-        *(uint4*)(qbuf + pl * 32 * HD + (8 + rest / 16) * HD + (rest % 16) * 8) = make_uint4(0, 0, 0, 0);
-      }
+      // rows 8 .. 15 hold no query: zeros in both planes (16 bytes per thread and step)
+      for (int idx = tid - 64; idx < 2 * 8 * 16; idx += 192)
+        *(uint4*)(qbuf + (idx >> 7) * PLANE + (8 + ((idx >> 4) & 7)) * HD + (idx & 15) * 8) = make_uint4(0, 0, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
     if (wave > 0) {
@@ -1074,40 +1115,34 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
       if (nsteps > 1) fetch3(1, 1);
     }
     __builtin_amdgcn_sched_barrier(0);
+    prepare16();
+    __builtin_amdgcn_sched_barrier(0);
     if (nsteps > 0 && wave > 0) {
       // all but the wave's requests of the second step have landed
       if (nsteps == 1) wait_vmem(); else if (wave == 1) wait_vmem_n<22>(); else wait_vmem_n<21>();
     }
     lds_barrier();                                             // first K/V step landed; q sum visible
-    read_frags(0, qh[0]);
-    read_frags(1, qlo[0]);
-  } else if (NQB == 1) {
+    read_frags16();
+  } else if (NQB <= 1) {
     // 9 .. 32 queries: two or four waves sum.  Every wave requests its own rows of step 0, then its q slices, then
     // its rows of step 1 -- the K/V stream starts with the kernel, and q (loads return in order) is complete when
     // step 0 has landed, which the arithmetic has to wait for anyway.
-    const int qwaves = mtot <= 16 ? 2 : 4;
+    constexpr int qwaves = W16 ? 2 : 4;
     u32x4_t t[4][QS];
     float4 acc[4] = {zero4, zero4, zero4, zero4};
     fetch_own(0, 0);
     q_issue(0, mtot, qwaves, 0, t);
     fetch_own(1, 1);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (W16) { prepare16(); __builtin_amdgcn_sched_barrier(0); }
     wait_vmem_n<16>();                                         // all but step 1's requests
     q_add(t, acc);
     if (wave < qwaves) {
       q_finish(0, mtot, qwaves, acc);
       q_store(0, qwaves, acc);
-    } else {
-      // rows 16 .. 31 hold no query (two summing waves cover 16): zeros in both planes, from the other two waves
-      for (int idx = tid - 64 * qwaves; idx < 2 * 16 * 16; idx += 256 - 64 * qwaves) {
-        const int pl = idx >> 8, rest = idx & 255;
-        const u32x4_t z = {0u, 0u, 0u, 0u};
-        asm volatile("ds_write_b128 %0, %1" : : "v"((lds_bf16_ptr)(qbuf + pl * 32 * HD + (16 + (rest >> 4)) * HD + (rest & 15) * 8)), "v"(z) : "memory");
-      }
     }
     lds_barrier();                                             // q visible
-    read_frags(0, qh[0]);
-    read_frags(1, qlo[0]);
+    if constexpr (W16) read_frags16(); else { read_frags(0, qh[0]); read_frags(1, qlo[0]); }
   } else {
     // 33 .. 64 queries, all four waves sum both blocks: own rows of step 0, block 0's slices, own rows of step 1,
     // block 1's slices -- the last of these only issue as the oldest requests retire (a wave holds at most 63), which
@@ -1128,16 +1163,16 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
     for (int i = 0; i < 4; ++i) acc[i] = zero4;
     q_add(t1, acc);
     q_finish(1, mtot - 32, 4, acc);
-    q_store(NQB - 1, 4, acc);
+    q_store(NQ - 1, 4, acc);
     lds_barrier();                                             // both blocks visible
   }
   const float c2 = a.scale * LOG2E;
   const FragOffs fo = make_frag_offs(lane);
 
-  f32x16_t o[NQB][4];
-  float mrun[NQB], lrun[NQB];
+  f32x16_t o[NQ][4];
+  float mrun[NQ], lrun[NQ];
 #pragma unroll
-  for (int b = 0; b < NQB; ++b) {
+  for (int b = 0; b < NQ; ++b) {
     mrun[b] = -INFINITY; lrun[b] = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -1162,7 +1197,119 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
 
   // One 128-key step on stage SI: this wave's 32 rows of the step tiles against its query blocks; `refill` requests
   // the same rows of step + 2 into the stage as soon as their fragments have been read.
-  auto step_compute = [&](auto stage_c, int step, bool refill) {
+  auto step16 = [&](auto stage_c, int step, bool refill) {
+    constexpr int SI = decltype(stage_c)::value;
+    constexpr int STAGE_B = TILE * 2, KB_B = 16 * HD * 2;      // byte distances
+    const int jw = j_begin + step * KSTEP + 32 * wave;         // the wave's first key
+    if (jw < j_end) {
+      // Explicit ds_read instructions: for LDS reads it can see, the compiler waits until no HBM -> LDS request is in flight at all, and
+      // the refills would never overlap the arithmetic.
+      union { xload_t u; bf16x8_t v; } kf[2][4];
+      union { struct { u32x2_t x, y; } s; bf16x8_t v; } vf[8];
+      static_for<0, 2>([&](auto kb_) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) lds_read_b128<SI * STAGE_B + decltype(kb_)::value * KB_B>(kf[decltype(kb_)::value][s].u, ka16[s]);
+      });
+#pragma unroll
+      for (int cb = 0; cb < 8; ++cb) {
+        lds_read_tr16_b64<SI * STAGE_B>(vf[cb].s.x, va16[cb]);
+        lds_read_tr16_b64<SI * STAGE_B + KB_B>(vf[cb].s.y, va16[cb]);
+      }
+      // LDS reads return in order and the counter holds at most 15: at most 15 of 24 still out means the first 9
+      // are there, the 8 K fragments among them
+      asm volatile("s_waitcnt lgkmcnt(15)" ::: "memory");
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(kf[kb][s].u));
+      // four independent accumulation chains (hi and lo part of q, two key blocks) hide the dependent-MFMA latency
+      f32x4_t st[2][2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) st[c][kb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+          st[0][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][s].v, qh16[s].v, st[0][kb], 0, 0, 0);
+          st[1][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][s].v, ql16[s].v, st[1][kb], 0, 0, 0);
+        }
+      // The wave's K rows are in registers: refill them.  Behind the MFMAs in program order: while every CU
+      // streams, a request waits in the issue stage for a slot in the memory pipeline (about 170 cycles each),
+      // and the matrix pipe works through the scores meanwhile.
+      __builtin_amdgcn_sched_barrier(0);
+      if (refill) fetch_own_half(SI, step + 2, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      union { uint32_t u[4]; bf16x8_t v; } pf;
+      float sb[8];                                             // element 4 kb + e: key jw + 16 kb + 4 rv + e
+#pragma unroll
+      for (int i = 0; i < 8; ++i) sb[i] = st[0][i >> 2][i & 3] + st[1][i >> 2][i & 3];
+      if (jw + 32 > j_end) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (jw + 16 * (i >> 2) + 4 * rv + (i & 3) >= j_end) sb[i] = -INFINITY;
+      }
+      if (a.tree != nullptr && jw + 32 > a.n_true) {
+        // drafted rows: bit i of `vis` says whether this lane's query sees key jw + i (true rows: yes)
+        const int off = jw - a.n_true;                       // tree bit of key jw; negative inside the true rows
+        const int w0 = off >> 5, sh = off & 31;              // floor division: -1 for the straddling block
+        const int m = row_query(nl);
+        const uint32_t* row = a.tree + (int64_t)m * a.tree_words;
+        const bool real = nl < mtot && (!GROUPED || m < a.M);
+        const uint32_t lo = w0 < 0 ? 0xffffffffu : (real && w0 < a.tree_words ? row[w0] : 0u);
+        const uint32_t hi = real && w0 + 1 < a.tree_words ? row[w0 + 1] : 0u;
+        const uint32_t vis = (uint32_t)((((uint64_t)hi << 32) | lo) >> sh);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (!((vis >> (16 * (i >> 2) + 4 * rv + (i & 3))) & 1u)) sb[i] = -INFINITY;
+      }
+      float mx = sb[0];
+#pragma unroll
+      for (int i = 1; i < 8; ++i) mx = fmaxf(mx, sb[i]);
+      mx = half_pair_max(quarter_pair_max(mx));
+      // the running reference moves only when the block maximum exceeds it by more than 2^8 in the
+      // exponent (p then ranges up to 2^8: harmless for float sums and bf16 probabilities), so that most
+      // steps skip the rescaling of O
+      const bool grow = (mx - m16) * c2 > 8.f;           // also true at the first step (reference -inf)
+      if (__builtin_amdgcn_ballot_w64(grow) != 0) {          // wave-uniform
+        const float m_new = grow ? mx : m16;             // finite: the block holds at least one real key
+        const float alpha = grow ? __builtin_amdgcn_exp2f((m16 - m_new) * c2) : 1.f;
+        l16 *= alpha;
+        m16 = m_new;
+        if (!o_zero) {                                       // (the first block a wave works on always grows: O is still 0)
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o16[i][e] *= alpha;
+        }
+      }
+      const float mc = (m16 == -INFINITY ? 0.f : m16) * c2;   // nothing visible so far: p = exp2(-inf) = 0
+      float rs = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; i += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(sb[i] * c2 - mc);
+        const float p1 = __builtin_amdgcn_exp2f(sb[i + 1] * c2 - mc);
+        rs += p0 + p1;
+        pf.u[i >> 1] = cvt_pk(p0, p1);
+      }
+      l16 += rs;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the V fragments
+#pragma unroll
+      for (int cb = 0; cb < 8; ++cb) asm volatile("" : "+v"(vf[cb].s.x), "+v"(vf[cb].s.y));
+#pragma unroll
+      for (int cb = 0; cb < 8; ++cb) o16[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[cb].v, pf.v, o16[cb], 0, 0, 0);
+      o_zero = false;
+      __builtin_amdgcn_sched_barrier(0);
+      if (refill) fetch_own_half(SI, step + 2, 1);             // ... and the wave's V rows, behind the P V MFMAs
+      __builtin_amdgcn_sched_barrier(0);
+    } else if (refill) {
+      fetch_own(SI, step + 2);                                 // keeps every wave's request count the same
+    }
+  };
+
+  // the same for blocks of 32 queries
+  auto step32 = [&](auto stage_c, int step, bool refill) {
     constexpr int SI = decltype(stage_c)::value;
     const int kb = wave;                                       // 32-row block of the step tiles
     const int jw = j_begin + step * KSTEP + 32 * kb;           // its first key
@@ -1183,14 +1330,14 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
       };
 #pragma unroll
       for (int s = 0; s < 8; ++s) lds_read_b128<SI * STAGE_B>(kf[s].u, ka[s]);
-      f32x16_t st[NQB];
+      f32x16_t st[NQ];
 #pragma unroll
-      for (int b = 0; b < NQB; ++b)
+      for (int b = 0; b < NQ; ++b)
 #pragma unroll
         for (int e = 0; e < 16; ++e) st[b][e] = 0.f;
       // LDS reads return in order and the counter holds at most 15: at most 15 of 24 still out means the first 9
       // are there, the 8 K fragments among them
-      if constexpr (NQB == 1) {
+      if constexpr (NQ == 1) {
         issue_v();
         asm volatile("s_waitcnt lgkmcnt(15)" ::: "memory");
 #pragma unroll
@@ -1209,8 +1356,8 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
       } else {
         // One chain per block, hi parts first.  q's fragments come from their LDS planes in every step (128 more registers of
         // fragments did not survive register allocation while the scores took accumulation registers too): the lo fragments land during the hi parts' MFMAs, the V fragments during the lo parts'.
-        qfrag_t qf[NQB][8], ql_[NQB][8];
-        static_for<0, NQB>([&](auto b_) {
+        qfrag_t qf[NQ][8], ql_[NQ][8];
+        static_for<0, NQ>([&](auto b_) {
           constexpr int b = decltype(b_)::value;
 #pragma unroll
           for (int s = 0; s < 8; ++s) lds_read_b128<b * PLANE_B>(qf[b][s].u, qa[s]);
@@ -1219,24 +1366,24 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
 #pragma unroll
         for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(kf[s].u));
 #pragma unroll
-        for (int b = 0; b < NQB; ++b) tie_frags(qf[b]);
-        static_for<0, NQB>([&](auto b_) {
+        for (int b = 0; b < NQ; ++b) tie_frags(qf[b]);
+        static_for<0, NQ>([&](auto b_) {
           constexpr int b = decltype(b_)::value;
 #pragma unroll
-          for (int s = 0; s < 8; ++s) lds_read_b128<(NQB + b) * PLANE_B>(ql_[b][s].u, qa[s]);
+          for (int s = 0; s < 8; ++s) lds_read_b128<(NQ + b) * PLANE_B>(ql_[b][s].u, qa[s]);
         });
 #pragma unroll
         for (int s = 0; s < 8; ++s)
 #pragma unroll
-          for (int b = 0; b < NQB; ++b) st[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s].v, qf[b][s].v, st[b], 0, 0, 0);
+          for (int b = 0; b < NQ; ++b) st[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s].v, qf[b][s].v, st[b], 0, 0, 0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int b = 0; b < NQB; ++b) tie_frags(ql_[b]);
+        for (int b = 0; b < NQ; ++b) tie_frags(ql_[b]);
         issue_v();
 #pragma unroll
         for (int s = 0; s < 8; ++s)
 #pragma unroll
-          for (int b = 0; b < NQB; ++b) st[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s].v, ql_[b][s].v, st[b], 0, 0, 0);
+          for (int b = 0; b < NQ; ++b) st[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s].v, ql_[b][s].v, st[b], 0, 0, 0);
       }
       // The wave's K rows are in registers: refill them.  Behind the MFMAs in program order: while every CU
       // streams, a request waits in the issue stage for a slot in the memory pipeline (about 170 cycles each),
@@ -1244,9 +1391,9 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
       __builtin_amdgcn_sched_barrier(0);
       if (refill) fetch_own_half(SI, step + 2, 0);
       __builtin_amdgcn_sched_barrier(0);
-      uint32_t pk[NQB][8];
+      uint32_t pk[NQ][8];
 #pragma unroll
-      for (int b = 0; b < NQB; ++b) {
+      for (int b = 0; b < NQ; ++b) {
         f32x16_t& sb = st[b];
         if (jw + 32 > j_end) {
 #pragma unroll
@@ -1307,7 +1454,7 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int b = 0; b < NQB; ++b) {
+        for (int b = 0; b < NQ; ++b) {
           union { uint32_t u[4]; bf16x8_t v; } pf;
 #pragma unroll
           for (int i = 0; i < 4; ++i) pf.u[i] = pk[b][4 * t + i];
@@ -1322,6 +1469,10 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
     } else if (refill) {
       fetch_own(SI, step + 2);                                 // keeps every wave's request count the same
     }
+  };
+
+  auto step_compute = [&](auto stage_c, int step, bool refill) {
+    if constexpr (W16) step16(stage_c, step, refill); else step32(stage_c, step, refill);
   };
 
   // Two stages.  Before step s the wave's rows of s must have landed: the only younger requests are those of
@@ -1340,13 +1491,61 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
     }
   }
 
+  if constexpr (W16) {
+    // ---- merge the waves' partials (fixed order) and write this key range's partial.  A wave leaves its [16 queries][128
+    // channels] floats in its own 32 rows of a tile, where no other wave reads or writes any more; a float4 of query q sits 4 q floats further
+    // round its row, so that neither the per-query writes nor the per-channel reads conflict.
+    static_assert(16 * HD * sizeof(float) == 32 * HD * sizeof(bf16_t), "a block's partial fills a wave's rows of a tile");
+    wait_vmem();                                                 // (requests past the last step, of rows past the range)
+    auto part_of = [&](int w) { return (float*)(kvt + w * 32 * HD); };
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb)
+      *(float4*)(part_of(wave) + nl * HD + ((16 * cb + 4 * lg + 4 * nl) & (HD - 1))) = make_float4(o16[cb][0], o16[cb][1], o16[cb][2], o16[cb][3]);
+    l16 = half_pair_sum(quarter_pair_sum(l16));
+    if (lg == 0) s_ml16[wave][nl] = make_float2(m16, l16);
+    __syncthreads();
+    const int64_t pbase = ((int64_t)h * a.R + r) * a.Mpad;
+    const int hstep = a.R * a.Mpad;                              // from one head's partials to the next one's
+    // 32 threads to a query; two queries per thread, whose LDS reads are all on their way before the first is used
+    if (tid < mtot * 32) {                                       // padding rows are never read
+      float2 ml[2][4];
+      float4 v[2][4];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int i = tid + 256 * u, c4 = i & 31, qq = i >> 5;
+#pragma unroll
+        for (int wv = 0; wv < 4; ++wv) {
+          ml[u][wv] = s_ml16[wv][qq];
+          v[u][wv] = *(const float4*)(part_of(wv) + qq * HD + ((4 * c4 + 4 * qq) & (HD - 1)));
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int i = tid + 256 * u, c4 = i & 31, qq = i >> 5, m = row_query(qq);
+        if (i >= mtot * 32 || (GROUPED && m >= a.M)) continue;
+        const float mm = fmaxf(fmaxf(ml[u][0].x, ml[u][1].x), fmaxf(ml[u][2].x, ml[u][3].x));
+        float lt = 0.f;
+        float4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int wv = 0; wv < 4; ++wv) {
+          const float sc = ml[u][wv].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ml[u][wv].x - mm) * c2);
+          lt += ml[u][wv].y * sc;
+          acc.x += v[u][wv].x * sc; acc.y += v[u][wv].y * sc; acc.z += v[u][wv].z * sc; acc.w += v[u][wv].w * sc;
+        }
+        const int64_t out = pbase + row_head(qq) * hstep + m;
+        *(float4*)(a.opart + out * HD + 4 * c4) = acc;
+        if (c4 == 0) { a.mlpart[out * 2] = mm; a.mlpart[out * 2 + 1] = lt; }
+      }
+    }
+    return;
+  }
   // ---- merge the waves' partials of each query block (fixed order) and write this key range's partial.
   // Buffer of block b (64 KB of the stages): [4 waves][32 queries][128 channels] floats; a float4 of query q sits 4 q floats
   // further round its row, so that neither the per-query writes nor the per-channel reads conflict.
   __syncthreads();
-  static_assert(NQB * 4 * 32 * HD * sizeof(float) <= sizeof(kvt), "the merge buffers must fit in the stages");
+  static_assert(NQ * 4 * 32 * HD * sizeof(float) <= sizeof(kvt), "the merge buffers must fit in the stages");
 #pragma unroll
-  for (int b = 0; b < NQB; ++b) {
+  for (int b = 0; b < NQ; ++b) {
     float* ob = (float*)kvt + b * 4 * 32 * HD;
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb)
@@ -1359,7 +1558,7 @@ __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
     if (hf == 0) { s_ml[wave][b][0][ql] = mrun[b]; s_ml[wave][b][1][ql] = lrun[b]; }
   }
   __syncthreads();
-  if (tid < 32 * NQB) {                                       // per query: the merged (max, sum) and each wave's weight
+  if (tid < 32 * NQ) {                                       // per query: the merged (max, sum) and each wave's weight
     const int qb = tid >> 5, q = tid & 31;
     float mm = -INFINITY;
 #pragma unroll
@@ -1630,11 +1829,16 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
       ProfScope ps("draft_attn", s);
       const dim3 grid(a.H >> w.hs_log2, w.R), wg(256);
       const bool grouped = w.hs_log2 > 0;                    // (up to 32 rows)
-      if (Mp > 32) hipLaunchKernelGGL((decode_attn_kernel<2, 8, false>), grid, wg, 0, s, t);
-      else if (t.KSq == 1 && grouped) hipLaunchKernelGGL((decode_attn_kernel<1, 1, true>), grid, wg, 0, s, t);
-      else if (t.KSq == 1) hipLaunchKernelGGL((decode_attn_kernel<1, 1, false>), grid, wg, 0, s, t);
-      else if (grouped) hipLaunchKernelGGL((decode_attn_kernel<1, 8, true>), grid, wg, 0, s, t);
-      else hipLaunchKernelGGL((decode_attn_kernel<1, 8, false>), grid, wg, 0, s, t);
+      const int rows = grouped ? 1 << (w.hs_log2 + w.row_log2) : Mp;
+      auto go = [&](auto qs_) {                              // (packed weights serve up to 16 queries)
+        constexpr int QS = decltype(qs_)::value;
+        if (rows > 32) hipLaunchKernelGGL((decode_attn_kernel<2, 8, false>), grid, wg, 0, s, t);
+        else if (rows > 16 && grouped) hipLaunchKernelGGL((decode_attn_kernel<1, QS, true>), grid, wg, 0, s, t);
+        else if (rows > 16) hipLaunchKernelGGL((decode_attn_kernel<1, 8, false>), grid, wg, 0, s, t);
+        else if (grouped) hipLaunchKernelGGL((decode_attn_kernel<0, QS, true>), grid, wg, 0, s, t);
+        else hipLaunchKernelGGL((decode_attn_kernel<0, QS, false>), grid, wg, 0, s, t);
+      };
+      if (t.KSq == 1) go(int_c<1>{}); else go(int_c<8>{});
     }
     if (a.wo_pk) {
       // out-projection on the transposed weights: no k split, so no partial sums and no launch to add them
