@@ -647,6 +647,11 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
 
   // ---- rows out, through the wave's own slot of the last phase (nobody else touches it any more): whole row segments.
   // Chunk c (16 bytes) of patch row r sits at c ^ (r % chunks), which spreads the column-wise writes over the banks.
+  // (the bounds in registers: otherwise every one of the stores fetches them again from the arguments and waits)
+  int gm = g.M, gn = g.N;
+  int64_t ldc = g.ldc;
+  void* cptr = g.C;
+  asm volatile("" : "+s"(gm), "+s"(gn), "+s"(ldc), "+s"(cptr));
   static_for<0, OWN>([&](auto i_) BEAGLE_INLINE_LAMBDA {
     constexpr int i = decltype(i_)::value;
     const int mb = m0 + wm + 32 * (i + kg * OWN), nb = n0 + wn;
@@ -662,7 +667,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
       for (int it = 0; it < 16; ++it) {
         const int r = 2 * it + hf, p = ql, m = mb + r, n = nb + 4 * (p ^ r);
         const float4 v = *(const float4*)(patch + r * 128 + 4 * p);
-        if (m < g.M && n < g.N) *(float4*)((float*)g.C + (int64_t)m * g.ldc + n) = v;
+        if (m < gm && n < gn) *(float4*)((float*)cptr + (int64_t)m * ldc + n) = v;
       }
     } else {
       bf16_t* patch = (bf16_t*)(slot + i * 4096);   // 32 rows x 128: 16 chunks of eight per row
@@ -672,7 +677,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
         for (int it = 0; it < 8; ++it) {
           const int r = 4 * it + rr, m = mb + r, n = nb + 8 * (p ^ (r & 15));
           uint4 v = {0, 0, 0, 0};
-          if (m < g.M && n < g.N) v = *(const uint4*)((const bf16_t*)g.R + (int64_t)m * g.ldr + n);
+          if (m < gm && n < gn) v = *(const uint4*)((const bf16_t*)g.R + (int64_t)m * g.ldr + n);
           *(uint4*)(patch + r * 128 + 8 * p) = v;
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -694,7 +699,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
       for (int it = 0; it < 8; ++it) {
         const int r = 4 * it + rr, m = mb + r, n = nb + 8 * (p ^ (r & 15));
         const uint4 v = *(const uint4*)(patch + r * 128 + 8 * p);
-        if (m < g.M && n < g.N) *(uint4*)((bf16_t*)g.C + (int64_t)m * g.ldc + n) = v;
+        if (m < gm && n < gn) *(uint4*)((bf16_t*)cptr + (int64_t)m * ldc + n) = v;
       }
     }
   });
