@@ -414,6 +414,7 @@ void kv_append_run(const Dims& d, const void* x_new, const void* wk, const void*
     g.count = 2;
     g.p[0] = gemm_nn(x_new, wk, kdst, d.S, d.GD, d.D);
     g.p[1] = gemm_nn(x_new, wv, vdst, d.S, d.GD, d.D);
+    g.p[0].c_kept = g.p[1].c_kept = 1;
     run_gemm(d, g, s, "kv_append");
   }
   if (d.rope) {   // the new K rows at their sequence positions (given, or the row indices)
