@@ -20,9 +20,10 @@ __device__ __forceinline__ f32x4_t zero4() { return f32x4_t{0.f, 0.f, 0.f, 0.f};
 // without leaving their registers.  NC: 32-channel blocks of the head width.
 //
 // What bounds these kernels is one wave's serial chain, behind one trip to memory: the problems are small (128 rows of 4 heads are
-// 32 workgroups).  Blocks of 16 x 16 and eight waves make the chain a quarter of what blocks of 32 x 32 and four waves had (8 and 32
-// instructions of 32 cycles per 16 channels, forward and dK/dV, for 16 and 64 of 64), and reading four channels of a row at once
-// (below) takes 28 requests instead of 104.
+// 32 workgroups).  Blocks of 16 x 16 and eight waves make the chain a quarter of what blocks of 32 x 32 and four waves had (at 64
+// channels 32 and 64 instructions of 32 cycles, forward and dK/dV, for 64 and 128 of 64), and reading four channels of a row at once
+// (below) takes 28 requests instead of 104.  Steps, us, before and now: 128 rows at 4 x 64 channels 46.6, 39.4, at 4 x 128 75.5, 62.4;
+// 2 x 300 at 4 x 64 in 2 groups 95.7, 62.7; 24 at 4 x 32 30.3, 28.9 (the GEMMs the same on both sides).
 // ---------------------------------------------------------------------------
 constexpr int AW = 8;                                   // waves of a workgroup
 constexpr int AT = 16;                                  // queries (keys) of a workgroup, keys (queries) of a wave's block
@@ -78,7 +79,7 @@ __device__ __forceinline__ float quad_max(float v) { v = fmaxf(v, __shfl_xor(v, 
 
 // Infinities and NaN behind the mask.  The second products multiply the rows that a query (key) must not see by a zero weight,
 // which leaves nothing behind unless such a row is not finite.  Over the tiles that hold hidden pairs the waves therefore sum
-// v * 0 over the fragments (a step of 128 rows takes 48 us with and without); where that is a NaN at the end, the wave starts over
+// v * 0 over the fragments (a step of 128 rows took 48 us with and without, in blocks of 32 x 32); where that is a NaN at the end, the wave starts over
 // on plain code that reads only what each query (key) sees: the functions *_plain below, for which a lane keeps the row and the
 // channels of its accumulators.
 template <int N>
