@@ -12,13 +12,14 @@
 //   * Small tiles (16 x 64, 16 x 16 scores) whose eight waves split the
 //     contraction, so that a 128 x 256 output occupies 32 workgroups and a
 //     contraction of 256 is one trip to memory and 32 instructions of 32 cycles per
-//     wave; the eight sums meet in LDS.
+//     wave; the eight sums meet in LDS.  (Wide models' tiles: 32 x 64.)
 //   * Everything independent shares a launch: problems of different storage
 //     orders in one GEMM group, dQ with dK / dV in one attention launch.
 // One training step at 128 rows, hidden 256, 4 heads of 64: 367 us on scalar
 // kernels (nine launches), 46.5 on 32 x 32 x 2 instructions and four waves, 37.6 now.
 #include <string.h>
 #include "attn_f32.h"
+#include "f32_plan.h"
 
 namespace beagle {
 namespace {
@@ -43,40 +44,53 @@ __device__ __forceinline__ const GemmArgs& problem_of(const TiledGroup& grp, int
 }
 
 // ---------------------------------------------------------------------------
-// GEMM: a tile of 16 x 64 per workgroup, whose eight waves take chunks of 32 k in turn; the eight sums meet in LDS.
+// GEMM: a tile of 16 MR x 64 per workgroup, whose eight waves take chunks of 32 k in turn; the eight sums meet in LDS.
 // Bound by one trip to memory and the chain behind it.  Lane (n, g) of a 16 x 16 x 4 instruction supplies row (column) n at k = g, and
 // what it stands for is free: k = 16 j + 4 g + e of a chunk, so that a k-contiguous operand comes 16 bytes at a time, and column
 // 4 n + u of the tile in instruction u, so that a row-contiguous B does too (10 requests per 32 k, and 32 instructions of 32 cycles;
 // 32 x 32 tiles on 32 x 32 x 2 instructions took 20 requests, 16 of them of 4 bytes, and with four waves twice the chain).
 // Every N and leading dimension is a multiple of 4, and so is K where an operand is k-contiguous (the descriptor's checks on widths).
 // AHEAD: two chunks of a wave in flight, which leaves registers for one workgroup per CU; without, two share a CU.
+// MR = 2: B's fragments serve two blocks of rows (12 requests for 64 instructions): wide problems, which tiles of 16 rows make a
+// stream of B out of L2, take two thirds of the time.  Launches at hidden 4096, us, MR = 1 / 2: 2048 rows through Wo 993 / 727, the
+// input and weight gradients behind them 3250 / 2480 (134 registers: one workgroup per CU; tiles of 64 rows whose waves share the
+// contraction four ways 705 and 2330, but where a launch is a few rounds of tiles they are the slower ones: 128 rows through Wo 56 / 95).
 // ---------------------------------------------------------------------------
-constexpr int GW = 8, GM = 16, GN = 64;
-template <bool AHEAD>
-__global__ __launch_bounds__(64 * GW, AHEAD ? 2 : 4) void gemm_f32_kernel(TiledGroup grp) {
+constexpr int GW = 8, GN = GEMM_F32_COLS;
+template <int MR, bool AHEAD>
+__global__ __launch_bounds__(64 * GW, AHEAD || MR > 1 ? 2 : 4) void gemm_f32_kernel(TiledGroup grp) {
+  constexpr int GM = 16 * MR;
   __shared__ __attribute__((aligned(16))) float red[GW][GM][GN + 4];
   int t = blockIdx.x;
   const GemmArgs& p = problem_of(grp, t);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, nl = lane & 15;
   const int tn = (p.N + GN - 1) / GN, m0 = (t / tn) * GM, n0 = (t % tn) * GN;
-  const int mr = min(m0 + nl, p.M - 1), nc = min(n0 + 4 * nl, p.N - 4);    // rows and columns past the end repeat the last ones
-  f32x4_t acc[4];
+  const int nc = min(n0 + 4 * nl, p.N - 4);                                // rows and columns past the end repeat the last ones
+  int mr[MR];
+  f32x4_t acc[MR][4];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) acc[u] = zero4();
+  for (int i = 0; i < MR; ++i) {
+    mr[i] = min(m0 + 16 * i + nl, p.M - 1);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[i][u] = zero4();
+  }
 
   // AK / BK: k contiguous in memory
   auto contract = [&](auto ak_, auto bk_) BEAGLE_INLINE_LAMBDA {
     constexpr bool AK = decltype(ak_)::value, BK = decltype(bk_)::value;
     // chunk c of both segments' 32 k each: register 4 j + e is k = 16 j + 4 g + e of it; past K: zeros on both sides (0 * inf is a NaN)
     const int nc1 = (p.K + 31) / 32, chunks = nc1 + (p.A2 ? (p.K2 + 31) / 32 : 0);
-    auto load = [&](int c, float (&a)[8], float (&b)[4][8]) BEAGLE_INLINE_LAMBDA {
+    auto load = [&](int c, float (&a)[MR][8], float (&b)[4][8]) BEAGLE_INLINE_LAMBDA {
       const bool two = c >= nc1;
       const float* A = (const float*)(two ? p.A2 : p.A);
       const float* B = (const float*)(two ? p.B2 : p.B);
       const int64_t lda = two ? p.lda2 : p.lda, ldb = two ? p.ldb2 : p.ldb;
       const int K = two ? p.K2 : p.K, k0 = 32 * (two ? c - nc1 : c);
       auto at = [&](int k, int i, bool in) BEAGLE_INLINE_LAMBDA {      // one k of the operands that are not k-contiguous
-        if (!AK) { const float v = A[k * lda + mr]; a[i] = in ? v : 0.f; }
+        if (!AK) {
+#pragma unroll
+          for (int r = 0; r < MR; ++r) { const float v = A[k * lda + mr[r]]; a[r][i] = in ? v : 0.f; }
+        }
         if (!BK) {
           const float4 v = *(const float4*)(B + k * ldb + nc);
           b[0][i] = in ? v.x : 0.f; b[1][i] = in ? v.y : 0.f; b[2][i] = in ? v.z : 0.f; b[3][i] = in ? v.w : 0.f;
@@ -86,7 +100,10 @@ __global__ __launch_bounds__(64 * GW, AHEAD ? 2 : 4) void gemm_f32_kernel(TiledG
         auto put = [&](float (&f)[8], const float4& v) BEAGLE_INLINE_LAMBDA {
           f[4 * j] = in ? v.x : 0.f; f[4 * j + 1] = in ? v.y : 0.f; f[4 * j + 2] = in ? v.z : 0.f; f[4 * j + 3] = in ? v.w : 0.f;
         };
-        if (AK) put(a, *(const float4*)(A + mr * lda + k));
+        if (AK) {
+#pragma unroll
+          for (int r = 0; r < MR; ++r) put(a[r], *(const float4*)(A + mr[r] * lda + k));
+        }
         if (BK) {
 #pragma unroll
           for (int u = 0; u < 4; ++u) put(b[u], *(const float4*)(B + (nc + u) * ldb + k));
@@ -110,14 +127,16 @@ __global__ __launch_bounds__(64 * GW, AHEAD ? 2 : 4) void gemm_f32_kernel(TiledG
         }
       }
     };
-    auto compute = [&](const float (&a)[8], const float (&b)[4][8]) BEAGLE_INLINE_LAMBDA {
+    auto compute = [&](const float (&a)[MR][8], const float (&b)[4][8]) BEAGLE_INLINE_LAMBDA {
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) acc[u] = mfma16(a[i], b[u][i], acc[u]);
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int r = 0; r < MR; ++r) acc[r][u] = mfma16(a[r][i], b[u][i], acc[r][u]);
     };
     // (AHEAD: a contraction of up to 512 is loaded whole before the first product)
-    float a0[8], b0[4][8], a1[8], b1[4][8];
+    float a0[MR][8], b0[4][8], a1[MR][8], b1[4][8];
     int c = wave;
     if constexpr (!AHEAD) {
       for (; c < chunks; c += GW) { load(c, a0, b0); compute(a0, b0); }
@@ -139,42 +158,47 @@ __global__ __launch_bounds__(64 * GW, AHEAD ? 2 : 4) void gemm_f32_kernel(TiledG
   else contract(int_c<0>{}, int_c<0>{});
 
 #pragma unroll
-  for (int e = 0; e < 4; ++e)
-    *(float4*)&red[wave][4 * g + e][4 * nl] = make_float4(acc[0][e], acc[1][e], acc[2][e], acc[3][e]);
-  __syncthreads();
-  const int r = tid >> 5, c = 2 * (tid & 31), m = m0 + r, n = n0 + c;
-  if (m >= p.M || n >= p.N) return;
-  float2 v = *(const float2*)&red[0][r][c];
+  for (int i = 0; i < MR; ++i)
 #pragma unroll
-  for (int w = 1; w < GW; ++w) {
-    const float2 x = *(const float2*)&red[w][r][c];
-    v.x += x.x; v.y += x.y;
+    for (int e = 0; e < 4; ++e)
+      *(float4*)&red[wave][16 * i + 4 * g + e][4 * nl] = make_float4(acc[i][0][e], acc[i][1][e], acc[i][2][e], acc[i][3][e]);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < MR; ++i) {
+    const int r = 16 * i + (tid >> 5), c = 2 * (tid & 31), m = m0 + r, n = n0 + c;
+    if (m >= p.M || n >= p.N) return;
+    float2 v = *(const float2*)&red[0][r][c];
+#pragma unroll
+    for (int w = 1; w < GW; ++w) {
+      const float2 x = *(const float2*)&red[w][r][c];
+      v.x += x.x; v.y += x.y;
+    }
+    if (p.R) {
+      const float2 x = *(const float2*)((const float*)p.R + m * p.ldr + n);
+      v.x += x.x; v.y += x.y;
+    }
+    *(float2*)((float*)p.C + m * p.ldc + n) = v;
   }
-  if (p.R) {
-    const float2 x = *(const float2*)((const float*)p.R + m * p.ldr + n);
-    v.x += x.x; v.y += x.y;
-  }
-  *(float2*)((float*)p.C + m * p.ldc + n) = v;
 }
 
 }  // namespace
 
-// Requests a chunk ahead up to two workgroups per CU, workgroups in pairs beyond.  Steps, us, ahead / in pairs: 128 rows at
-// 4 x 128 channels 57.8 / 60.5 (59.0 by this rule: its last launch has 896 tiles), 200 at 4 x 128 77.4 / 77.0 (75.5), 600 at 8 x 64
-// 122 / 115, 1040 at 4 x 128 238 / 219, 3000 at 8 x 64 756 / 724.  (Tiles of 32 rows: 62.8, 76.5, 120, 218, 712; of 64 x 64 without a
-// split of the contraction, as large problems were worked before: the last two 231 and 824.)
 void launch_gemm_f32(const GemmGroup& g, hipStream_t s, const char* name) {
+  F32Problem sh[6];
+  for (int i = 0; i < g.count; ++i) sh[i] = {g.p[i].M, g.p[i].N, (g.p[i].K + 31) / 32 + (g.p[i].A2 ? (g.p[i].K2 + 31) / 32 : 0)};
+  const int rows = gemm_f32_rows(sh, g.count);
   TiledGroup t;
   int64_t tiles = 0;
   for (int i = 0; i < 6; ++i) {
     t.first[i] = i < g.count ? (int32_t)tiles : INT32_MAX;
-    if (i < g.count) tiles += (int64_t)((g.p[i].M + GM - 1) / GM) * ((g.p[i].N + GN - 1) / GN);
+    if (i < g.count) tiles += gemm_f32_tiles(sh[i], rows);
   }
   if (tiles == 0) return;
   memcpy(t.p, g.p, sizeof(t.p));
   ProfScope ps(name, s);
-  if (tiles <= 512) hipLaunchKernelGGL(gemm_f32_kernel<true>, dim3((unsigned)tiles), dim3(64 * GW), 0, s, t);
-  else hipLaunchKernelGGL(gemm_f32_kernel<false>, dim3((unsigned)tiles), dim3(64 * GW), 0, s, t);
+  if (rows == 32) hipLaunchKernelGGL((gemm_f32_kernel<2, false>), dim3((unsigned)tiles), dim3(64 * GW), 0, s, t);
+  else if (gemm_f32_ahead(tiles)) hipLaunchKernelGGL((gemm_f32_kernel<1, true>), dim3((unsigned)tiles), dim3(64 * GW), 0, s, t);
+  else hipLaunchKernelGGL((gemm_f32_kernel<1, false>), dim3((unsigned)tiles), dim3(64 * GW), 0, s, t);
 }
 
 // the instantiation of a head width: 32-channel blocks, and whether they are full
