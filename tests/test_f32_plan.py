@@ -62,7 +62,15 @@ def test_projections_of_a_draft_step_keep_the_narrow_tiles(plan, queries):
 
 def test_the_steps_of_the_gpu_tests_reach_every_kernel(plan):
     got = {s[:6]: plan(*step(*s[:6])) for s in tiles.STEPS}
+    assert all(l["ahead"] for l in got[(529, 600, 260, 4, 2, 44)])
+    assert all(l["rows"] == 16 and l["tiles"] > 512 and not l["ahead"] for l in got[(700, 333, 772, 12, 2, 60)])
     assert all(l["rows"] == 32 for s in ((777, 600, 1540, 16, 4, 100), (512, 1024, 1024, 16, 16, 64)) for l in got[s])
+
+
+def test_the_long_step_beside_them(plan):
+    """The last row of test_gpu_f32_kernels.py."""
+    got = plan(*step(1200, 1200, 2048, 2, 1, 64))
+    assert [(l["rows"], l["ahead"]) for l in got] == [(32, False), (16, False), (16, True), (32, False)]
 
 
 def test_the_wide_block_adds_its_residuals_on_tiles_of_32_rows(plan):

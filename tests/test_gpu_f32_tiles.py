@@ -14,7 +14,8 @@ STEPS = [
     (17, 129, 64, 2, 2, 64, 2, 1),             # one key past a round
     (128, 128, 256, 4, 4, 64, 4, 0),           # the reference problem
     (145, 272, 548, 4, 2, 68, 4, 3),           # three rounds of the contraction, the last of four; four channels in the third block
-    (529, 600, 260, 4, 2, 44, 8, 5),           # more than 512 tiles in a launch, the last ones ending inside, in rows and columns
+    (529, 600, 260, 4, 2, 44, 8, 5),           # up to 479 tiles in a launch, the last ones ending inside, in rows and columns
+    (700, 333, 772, 12, 2, 60, 8, 3),          # every launch past 512 tiles of 16 rows: rows, columns and chunks end inside, both segments
     (777, 600, 1540, 16, 4, 100, 4, 1),        # every launch on tiles of 32 rows: 9 and 24 rows in the last, 4 and 16 columns, chunks of 4 - 28
     (512, 1024, 1024, 16, 16, 64, 16, 0),      # the same, whole everywhere
 ]
