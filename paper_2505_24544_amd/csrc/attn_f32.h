@@ -1,6 +1,7 @@
 // The float attention kernels, and the float matrix instruction that the float GEMM (f32_kernels.hip) shares with them.
 #pragma once
 #include "common.h"
+#include "f32_plan.h"
 
 namespace beagle {
 namespace {
@@ -154,13 +155,13 @@ __device__ __forceinline__ void fwd_plain(const AttnArgs& a, const float* q, con
 }
 
 template <int NC, bool FULL>
-__global__ __launch_bounds__(64 * AW, 1) void attn_fwd_f32_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * AW, 1) void attn_fwd_f32_kernel(AttnArgs a, int last) {
   constexpr int LD = 32 * NC + 4;
   __shared__ __attribute__((aligned(16))) float ob[AW][AT * LD];
   __shared__ float ms[AW][AT], ls[AW][AT];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, nl = lane & 15;
   const int h = blockIdx.y, b = blockIdx.z, kvh = h / (a.H / a.G), d = a.d;
-  const int q0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * AT;          // the queries that see the most keys first
+  const int q0 = (last - (int)blockIdx.x) * AT;                        // the queries that see the most keys first
   const SeqView sv = seq_view(a, b);
   if (q0 >= sv.S) return;                               // packed batch: a shorter entry
   const int q = q0 + nl, qc = min(q, sv.S - 1);
@@ -281,10 +282,10 @@ __device__ __forceinline__ void dkv_plain(const AttnArgs& a, const SeqView& sv, 
 }
 
 // Both halves of the backward in one launch (they are independent: each forms delta = rowsum(dO * O) for itself).
-//   blocks [0, n_dq)  : dQ of 16 queries of one head, over the keys they see; also stores delta
-//   the rest          : dK, dV of 16 keys of one key/value head, over the (head, query block) pairs that see them
+//   blocks [0, part.n_first) : dQ of 16 queries of one head, over the keys they see; also stores delta
+//   the rest                 : dK, dV of 16 keys of one key/value head, over the (head, query block) pairs that see them
 template <int NC, bool FULL>
-__global__ __launch_bounds__(64 * AW, 1) void attn_bwd_f32_kernel(AttnArgs a, int n_dq) {
+__global__ __launch_bounds__(64 * AW, 1) void attn_bwd_f32_kernel(AttnArgs a, GridPart part) {
   constexpr int LD = 32 * NC + 4;
   __shared__ __attribute__((aligned(16))) float ob[AW][AT * LD];
   __shared__ __attribute__((aligned(16))) float st[AW][2][AT];
@@ -305,10 +306,9 @@ __global__ __launch_bounds__(64 * AW, 1) void attn_bwd_f32_kernel(AttnArgs a, in
       *(float4*)(out + r * stride + c) = make_float4(t.x * scale, t.y * scale, t.z * scale, t.w * scale);
     }
   };
-  if ((int)blockIdx.x < n_dq) {
-    const int nq = (a.S + AT - 1) / AT;
-    const int row = blockIdx.x / nq, q0 = (nq - 1 - (int)blockIdx.x % nq) * AT;
-    const int h = row % a.H, b = row / a.H, kvh = h / rep;
+  if (blockIdx.x < part.n_first) {
+    const uint32_t nq = (a.S + AT - 1) / AT, at = part.blk0 + blockIdx.x, row = part.row0 + at / nq;
+    const int q0 = (int)(nq - 1 - at % nq) * AT, h = row % (uint32_t)a.H, b = row / (uint32_t)a.H, kvh = h / rep;
     const SeqView sv = seq_view(a, b);
     if (q0 >= sv.S) return;
     const int q = q0 + nl, qc = min(q, sv.S - 1);
@@ -366,8 +366,8 @@ __global__ __launch_bounds__(64 * AW, 1) void attn_bwd_f32_kernel(AttnArgs a, in
     park<NC>(ob[wave], dq, nl, g);
     rows_out((float*)a.dq + ((sv.q0 + q0) * a.H + h) * d, qs, min(AT, sv.S - q0), a.scale);
   } else {
-    const int nk = (a.L + AT - 1) / AT, n = (int)blockIdx.x - n_dq;
-    const int row = n / nk, j0 = (n % nk) * AT, kvh = row % a.G, b = row / a.G;
+    const uint32_t nk = (a.L + AT - 1) / AT, at = part.blk1 + (blockIdx.x - part.n_first), row = part.row1 + at / nk;
+    const int j0 = (int)(at % nk) * AT, kvh = row % (uint32_t)a.G, b = row / (uint32_t)a.G;
     const SeqView sv = seq_view(a, b);
     if (j0 >= sv.L) return;
     const int j = j0 + nl;

@@ -27,12 +27,12 @@ namespace {
 // A group and where each of its problems' tiles begin.  A workgroup finds its problem in one trip to the kernel's arguments and has all
 // that the problem says in a second one (walking from problem to problem took a trip each).
 struct TiledGroup {
-  int32_t first[6];                                                    // past the last problem: beyond every tile
+  int32_t first[6];                                                    // from the launch's first tile on; past the last problem: beyond every tile
   GemmArgs p[6];
 };
 __device__ __forceinline__ const GemmArgs& problem_of(const TiledGroup& grp, int& t) {
-  asm volatile("" :: "s"(grp.first[1]), "s"(grp.first[2]), "s"(grp.first[3]), "s"(grp.first[4]), "s"(grp.first[5]));
-  int pi = 0, f = 0;
+  asm volatile("" :: "s"(grp.first[0]), "s"(grp.first[1]), "s"(grp.first[2]), "s"(grp.first[3]), "s"(grp.first[4]), "s"(grp.first[5]));
+  int pi = 0, f = grp.first[0];
 #pragma unroll
   for (int i = 1; i < 6; ++i)
     if (t >= grp.first[i]) { pi = i; f = grp.first[i]; }
@@ -187,18 +187,19 @@ void launch_gemm_f32(const GemmGroup& g, hipStream_t s, const char* name) {
   F32Problem sh[6];
   for (int i = 0; i < g.count; ++i) sh[i] = {g.p[i].M, g.p[i].N, (g.p[i].K + 31) / 32 + (g.p[i].A2 ? (g.p[i].K2 + 31) / 32 : 0)};
   const int rows = gemm_f32_rows(sh, g.count);
-  TiledGroup t;
-  int64_t tiles = 0;
-  for (int i = 0; i < 6; ++i) {
-    t.first[i] = i < g.count ? (int32_t)tiles : INT32_MAX;
-    if (i < g.count) tiles += gemm_f32_tiles(sh[i], rows);
-  }
+  int64_t first[6], tiles = 0;
+  for (int i = 0; i < g.count; ++i) { first[i] = tiles; tiles += gemm_f32_tiles(sh[i], rows); }
   if (tiles == 0) return;
+  TiledGroup t;
   memcpy(t.p, g.p, sizeof(t.p));
   ProfScope ps(name, s);
-  if (rows == 32) hipLaunchKernelGGL((gemm_f32_kernel<2, false>), dim3((unsigned)tiles), dim3(64 * GW), 0, s, t);
-  else if (gemm_f32_ahead(tiles)) hipLaunchKernelGGL((gemm_f32_kernel<1, true>), dim3((unsigned)tiles), dim3(64 * GW), 0, s, t);
-  else hipLaunchKernelGGL((gemm_f32_kernel<1, false>), dim3((unsigned)tiles), dim3(64 * GW), 0, s, t);
+  for_launches(tiles, 64 * GW, [&](int64_t at, int64_t n) {            // (2^31 tiles and more would not fit the memory)
+    for (int i = 0; i < 6; ++i) t.first[i] = i < g.count ? (int32_t)(first[i] - at) : INT32_MAX;
+    const dim3 grid((unsigned)n), wg(64 * GW);
+    if (rows == 32) hipLaunchKernelGGL((gemm_f32_kernel<2, false>), grid, wg, 0, s, t);
+    else if (gemm_f32_ahead(tiles)) hipLaunchKernelGGL((gemm_f32_kernel<1, true>), grid, wg, 0, s, t);
+    else hipLaunchKernelGGL((gemm_f32_kernel<1, false>), grid, wg, 0, s, t);
+  });
 }
 
 // the instantiation of a head width: 32-channel blocks, and whether they are full
@@ -210,16 +211,23 @@ static void launch_widths(const AttnArgs& a, F&& go) {
 
 void launch_attn_fwd_f32(const AttnArgs& a, hipStream_t s) {
   ProfScope ps("attn_fwd_f32", s);
+  const int nq = (a.S + AT - 1) / AT;
   launch_widths(a, [&](auto nc_, auto full_) {
-    hipLaunchKernelGGL((attn_fwd_f32_kernel<decltype(nc_)::value, decltype(full_)::value>), dim3((a.S + AT - 1) / AT, a.H, a.B), dim3(64 * AW), 0, s, a);
+    for_launches(nq, 64 * AW, [&](int64_t at, int64_t n) {
+      hipLaunchKernelGGL((attn_fwd_f32_kernel<decltype(nc_)::value, decltype(full_)::value>), dim3((unsigned)n, a.H, a.B), dim3(64 * AW), 0, s, a,
+                         nq - 1 - (int)at);
+    });
   });
 }
 
 void launch_attn_bwd_f32(const AttnArgs& a, hipStream_t s) {
   ProfScope ps("attn_bwd_f32", s);
-  const int n_dq = ((a.S + AT - 1) / AT) * a.H * a.B, n_dkv = ((a.L + AT - 1) / AT) * a.G * a.B;
+  const int64_t nq = (a.S + AT - 1) / AT, nk = (a.L + AT - 1) / AT, rows_q = (int64_t)a.H * a.B, rows_kv = (int64_t)a.G * a.B;
   launch_widths(a, [&](auto nc_, auto full_) {
-    hipLaunchKernelGGL((attn_bwd_f32_kernel<decltype(nc_)::value, decltype(full_)::value>), dim3(n_dq + n_dkv), dim3(64 * AW), 0, s, a, n_dq);
+    for_launches(rows_q * nq + rows_kv * nk, 64 * AW, [&](int64_t at, int64_t n) {
+      hipLaunchKernelGGL((attn_bwd_f32_kernel<decltype(nc_)::value, decltype(full_)::value>), dim3((unsigned)n), dim3(64 * AW), 0, s, a,
+                         grid_part(at, n, rows_q, nq, nk));
+    });
   });
 }
 

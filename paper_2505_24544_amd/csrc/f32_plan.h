@@ -1,4 +1,4 @@
-// Which tiles a launch of the float GEMM takes.  No HIP in here: the tests compile it for the host.
+// Which tiles a launch of the float GEMM takes, and how many launches a long grid is.  No HIP in here: the tests compile it for the host.
 #pragma once
 #include <stdint.h>
 
@@ -34,5 +34,21 @@ inline int gemm_f32_rows(const F32Problem* p, int count) {
 // Tiles of 16 rows request a chunk ahead up to two workgroups per CU; beyond, workgroups go in pairs.  Steps, us, ahead / in pairs: 128
 // rows at 4 x 128 channels 57.8 / 60.5 (59.0 by this rule: its last launch has 896 tiles), 200 at 4 x 128 77.4 / 77.0 (75.5).
 inline bool gemm_f32_ahead(int64_t tiles) { return tiles <= 512; }
+
+// A launch holds fewer than 2^32 threads in a dimension; what the entry points accept can be more (a million rows of 3 x 4096 columns
+// are 12 million tiles of 512 threads): launch(first block, blocks) for each part.
+template <class F>
+inline void for_launches(int64_t blocks, int threads, F&& launch) {
+  const int64_t most = (int64_t)UINT32_MAX / threads;
+  for (int64_t at = 0; at < blocks; at += most) launch(at, blocks - at < most ? blocks - at : most);
+}
+
+// Where part [at, at + blocks) of a grid stands that is `rows` runs of n0 blocks, then runs of n1: how many of its blocks are of the first
+// kind, and the run and the place in it at which each kind goes on.
+struct GridPart { uint32_t n_first, row0, blk0, row1, blk1; };
+inline GridPart grid_part(int64_t at, int64_t blocks, int64_t rows, int64_t n0, int64_t n1) {
+  const int64_t first = rows * n0, left = at < first ? first - at : 0, past = at > first ? at - first : 0;
+  return {(uint32_t)(left < blocks ? left : blocks), (uint32_t)(at / n0), (uint32_t)(at % n0), (uint32_t)(past / n1), (uint32_t)(past % n1)};
+}
 
 }  // namespace beagle

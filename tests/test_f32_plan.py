@@ -21,10 +21,13 @@ def plan(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("plan") / "f32_plan_driver")
     subprocess.run([cxx, "-std=c++17", os.path.join(HERE, "f32_plan_driver.cpp"), "-o", exe], check=True)
 
+    def lines(text):
+        return subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=60).stdout.splitlines()
+
     def run(*launches):
-        text = "".join("%d %s\n" % (len(l), " ".join("%d %d %d" % p for p in l)) for l in launches)
-        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=60).stdout.splitlines()
+        out = lines("".join("%d %s\n" % (len(l), " ".join("%d %d %d" % p for p in l)) for l in launches))
         return [dict(rows=int(r), tiles=int(t), ahead=a == "1") for r, t, a in (l.split() for l in out)]
+    run.grid = lambda *g: [int(v) for v in lines("0 %d %d %d\n" % g)[0].split()]
     return run
 
 
@@ -76,3 +79,18 @@ def test_the_long_step_beside_them(plan):
 def test_the_wide_block_adds_its_residuals_on_tiles_of_32_rows(plan):
     S, D, q, f = block.S, block.D, block.H * 64, block.FFN
     assert [l["rows"] for l in plan([(S, D, _chunks(q))], [(S, D, _chunks(f))])] == [32, 32]
+
+
+@pytest.mark.parametrize("rows,n0,n1", [
+    (4, 8, 8), (1, 1, 1),
+    (32, 1 << 18, 3), (32, (1 << 18) + 7, 1 << 18),               # 2^22 rows of 32 heads: more than one launch of queries
+    (1, 1, 1 << 25), (3, (1 << 23) - 1, 5),                       # many keys; a part that ends a block past a launch
+    (65535 * 64, 1024, 1),                                        # packed entries, one of them long: more blocks than 32 bits count
+])
+def test_long_grids_go_in_launches_that_hip_takes(plan, rows, n0, n1):
+    """HIP refuses a launch of 2^32 threads and more in a dimension; workgroups have 512."""
+    got, at = plan.grid(rows, n0, n1), 0
+    for first, blocks, right in zip(got[::3], got[1::3], got[2::3]):
+        assert first == at and 0 < blocks * 512 < 1 << 32 and right == 1
+        at += blocks
+    assert at == rows * (n0 + 2 * n1)
