@@ -841,8 +841,9 @@ typedef lds_u32x2_t u32x2_t;
 // blocks of 32 / 16: 1 query over 4096 rows 34.1 / 33.2, 16 over
 // 1024 29.6 / 28.6; on packed weights 6 over 619 rows in 8 groups 21.6 / 20.5, 10 over 2000 29.8 / 28.7; the tree's block 90.9 / 89.4.
 // With more rows blocks of 16 are no gain (17 .. 32 rows: 2 % slower; 64: 1 % faster, 40: 4 % slower).
-// QS: k-slices of q that are requested at once: one on packed weights, where q comes as a single slice (asked for as eight,
-// seven of them past the buffer's end, they took the summing wave another 28 requests), else eight; more in further trips.
+// QS: k-slices of q that are requested at once: one where q is a single slice, on packed weights and at hidden up to 512 (asked for as
+// eight, seven of them past the buffer's end, they took a summing wave another 28 requests: 32 queries over 4000 rows at hidden 512
+// 28.7 -> 28.1 us, 24 over 1000 21.6 -> 20.9), else eight; more in further trips.
 template <int NQB, int QS, bool GROUPED>
 __global__ __launch_bounds__(256, 1) void decode_attn_kernel(DecAttnArgs a) {
   using namespace dec;
@@ -1830,11 +1831,11 @@ void launch_decode_bf16(const DecodeArgs& a, hipStream_t s) {
       const dim3 grid(a.H >> w.hs_log2, w.R), wg(256);
       const bool grouped = w.hs_log2 > 0;                    // (up to 32 rows)
       const int rows = grouped ? 1 << (w.hs_log2 + w.row_log2) : Mp;
-      auto go = [&](auto qs_) {                              // (packed weights serve up to 16 queries)
+      auto go = [&](auto qs_) {
         constexpr int QS = decltype(qs_)::value;
         if (rows > 32) hipLaunchKernelGGL((decode_attn_kernel<2, 8, false>), grid, wg, 0, s, t);
         else if (rows > 16 && grouped) hipLaunchKernelGGL((decode_attn_kernel<1, QS, true>), grid, wg, 0, s, t);
-        else if (rows > 16) hipLaunchKernelGGL((decode_attn_kernel<1, 8, false>), grid, wg, 0, s, t);
+        else if (rows > 16) hipLaunchKernelGGL((decode_attn_kernel<1, QS, false>), grid, wg, 0, s, t);
         else if (grouped) hipLaunchKernelGGL((decode_attn_kernel<0, QS, true>), grid, wg, 0, s, t);
         else hipLaunchKernelGGL((decode_attn_kernel<0, QS, false>), grid, wg, 0, s, t);
       };
