@@ -369,7 +369,8 @@ __global__ __launch_bounds__(256) void sum_gate_kernel(const float* __restrict__
 
 // ---------------------------------------------------------------------------
 // (D')  y[m][n] = sum_k a[m][k] * W[k][n]  (+ res[m][n]) for up to 16 rows, on a weight matrix that was packed for
-// this kernel once per model load (pack_strips_kernel below).  A workgroup owns a strip of 16 output columns over the
+// this kernel once per model load (pack_strips_kernel below).  One matrix whose macro-steps a wave holds at once has a kernel of its
+// own, strip_gemm_whole_kernel below.  A workgroup owns a strip of 16 output columns over the
 // whole of K, so there are N / 16 workgroups (one per CU at N = 4096) without any k split: no partial sums in memory
 // and no launch to add them up.  Its waves take the 128-k macro-steps of the strip in turn.
 //
@@ -390,7 +391,7 @@ __global__ __launch_bounds__(256) void sum_gate_kernel(const float* __restrict__
 // are not stored.
 //
 // MODE 1 (one query): a is not read; it is the attention output merged here from the split-KV partials of (B), as
-// in skinny_gemm_kernel<true>, each wave for the heads that are its macro-steps (at most ST_CH: K <= 4096);
+// in skinny_gemm_kernel<true>, each wave for the heads that are its macro-steps (at most ST_RING: up to 32 heads);
 // workgroup 0 writes the LSE.
 // MODE 2 (feed-forward layer, Eq. 1): two weight matrices share the activations, and the strip's result is
 // silu(a W) * (a W2): the gate needs no launch of its own.
@@ -406,8 +407,7 @@ constexpr int ST_WHOLE_WAVES = 8;        // strip_gemm_whole_kernel
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
 // TABLE (MODE 0): the launch also writes the rotary angles.  Launches without it, as those of modes 1 and 2, neither fetch the
-// rotary arguments nor carry the code: with both in every launch a strip launch took 0.1 - 0.25 us longer (packed steps, us: 6
-// queries over 3000 rows 31.8 -> 31.1, 12 over 2000 30.4 -> 29.8, 16 over 700 at 5120 channels 52.7 -> 52.0).
+// rotary arguments nor carry the code: with both in every launch a strip launch took 0.1 - 0.25 us longer.
 template <int MODE, bool ROWS16, int WAVES, bool TABLE = false>
 __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const bf16_t* __restrict__ a, const bf16_t* __restrict__ Wt,
                                                             const bf16_t* __restrict__ Wt2, void* __restrict__ yout,
@@ -519,7 +519,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
   }
   __builtin_amdgcn_sched_barrier(0);
 
-  // ---- the first ST_RING macro-steps of weights (one matrix at K = 4096: all of them)
+  // ---- the first ST_RING macro-steps of weights (MODE 1: all of them)
   const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void*)(second ? Wt2 : Wt), 0, (int)((int64_t)N * K * 2), 0x00020000);
   const __amdgpu_buffer_rsrc_t wrs2 = MODE == 3 ? wrs : __builtin_amdgcn_make_buffer_rsrc((void*)(MODE == 2 ? Wt2 : Wt), 0, (int)((int64_t)N * K * 2), 0x00020000);
   constexpr int W2OFF = MODE == 3 ? 4 * 4096 : 0;           // from the first strip's block to the second's
@@ -591,10 +591,10 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
 #pragma unroll
       for (int j = 0; j < 4; ++j) acc[w] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[j].v, bw[w][u][j].v, acc[w], 0, 0, 0);
   };
-  if (ST_RING == ST_ROUND && nst <= ST_RING) {      // the ring holds every macro-step: nothing to request any more
+  if constexpr (MODE == 1) {                        // the ring holds every macro-step: nothing to request any more
 #pragma unroll
     for (int u = 0; u < ST_RING; ++u) step(u, (u / ST_CH) & 1 ? aw1 : aw0, u % ST_CH);
-  } else if constexpr (MODE != 1) {
+  } else {
     int i0 = 0;
     do {
 #pragma unroll
