@@ -406,6 +406,42 @@ constexpr int ST_WHOLE_WAVES = 8;        // strip_gemm_whole_kernel
 }  // namespace dec
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
+// What the strip kernels share.  Activations: load q of a run of macro-steps covers rows 4 g + kg of step i, (i, g) = divmod(q, LPS = ROWS /
+// 4): lane (kg, nl) = (lane / 16, lane % 16) reads chunk nl ^ row of its row and parks it at chunk nl, i.e. at lane * 16 of the 1 KB
+// piece.  Rows and steps past the end arrive as zeros.
+__device__ __forceinline__ xload_t strip_request(__amdgpu_buffer_rsrc_t ars, bool there, int row, int step, int K, int nl) {
+  return __builtin_amdgcn_raw_buffer_load_b128(ars, there ? (row * K + step * 128 + 8 * (nl ^ row)) * 2 : (int)0x80000000, 0, 0);
+}
+template <int ROWS, int NLD>
+__device__ __forceinline__ void strip_park(const xload_t (&av)[NLD], unsigned char* buf, int lane) {
+  constexpr int LPS = ROWS / 4;
+#pragma unroll
+  for (int q = 0; q < NLD; ++q) *(xload_t*)(buf + ((q / LPS) * ROWS + 4 * (q % LPS)) * 256 + lane * 16) = av[q];
+}
+// RMSNorm of the activation rows (norm_eps >= 0; Eq. 1's block normalises each sublayer's input): the gain is folded into the packed
+// weights and the row factor 1 / sqrt(mean(a^2) + eps) is applied to the finished sums, so all that is needed is the rows' sums of
+// squares, gathered while the rows pass through registers on their way to LDS: load q holds 8 values of row 4 (q % LPS) + kg.
+template <int LPS, int NLD>
+__device__ __forceinline__ void strip_squares(const xload_t (&av)[NLD], float (&ssl)[LPS]) {
+#pragma unroll
+  for (int q = 0; q < NLD; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float lo = __uint_as_float(av[q][e] << 16), hi = __uint_as_float(av[q][e] & 0xffff0000u);
+      ssl[q % LPS] += lo * lo + hi * hi;
+    }
+}
+__device__ __forceinline__ float strip_chunk_sum(float t) {     // a row's 16 chunk lanes (same kg) add up; the waves do behind the barrier
+  t += __shfl_xor(t, 1); t += __shfl_xor(t, 2); t += __shfl_xor(t, 4);
+  return t + __shfl_xor(t, 8);
+}
+union strip_frag_t { xload_t u; bf16x8_t v; };
+__device__ __forceinline__ void strip_store(void* yout, const bf16_t* res, int64_t o, float v, int out_f32) {
+  if (res) v += __uint_as_float((uint32_t)res[o] << 16);
+  if (out_f32) ((float*)yout)[o] = v;                           // the queries: the attention kernel wants them unrounded
+  else ((bf16_t*)yout)[o] = (bf16_t)(cvt_pk(v, 0.f) & 0xffffu);
+}
+
 // TABLE (MODE 0): the launch also writes the rotary angles.  Launches without it, as those of modes 1 and 2, neither fetch the
 // rotary arguments nor carry the code: with both in every launch a strip launch took 0.1 - 0.25 us longer.
 template <int MODE, bool ROWS16, int WAVES, bool TABLE = false>
@@ -468,33 +504,18 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
   };
   if constexpr (MODE == 3) __builtin_amdgcn_sched_barrier(0);
   if (nst > 0) {                        // (a wave without a macro-step, K < 1024, only adds zeros below)
-  // ---- activations.  Load q of chunk c covers rows 4 g + kg of step c ST_CH + i, (i, g) = divmod(q, LPS):
-  // lane (kg, nl) reads chunk nl ^ row of its row and parks it at chunk nl, i.e. at lane * 16 of the 1 KB piece.
+  // ---- activations, a chunk of ST_CH macro-steps at a time
   const __amdgpu_buffer_rsrc_t ars = __builtin_amdgcn_make_buffer_rsrc((void*)a, 0, MODE == 1 ? 0 : (int)((int64_t)M * K * 2), 0x00020000);
   auto stage_issue = [&](xload_t (&av)[NLD], int c) {
 #pragma unroll
     for (int q = 0; q < NLD; ++q) {
       const int i = c * ST_CH + q / LPS, row = 4 * (q % LPS) + kg;
-      av[q] = __builtin_amdgcn_raw_buffer_load_b128(
-          ars, (i < nst && row < M) ? (row * K + (wave + WAVES * i) * 128 + 8 * (nl ^ row)) * 2 : (int)0x80000000, 0, 0);
+      av[q] = strip_request(ars, i < nst && row < M, row, wave + WAVES * i, K, nl);
     }
   };
-  // RMSNorm of the activation rows (norm_eps >= 0; Eq. 1's block normalises each sublayer's input): the gain is folded
-  // into the packed weights and the row factor 1 / sqrt(mean(a^2) + eps) is applied to the finished sums, so all that is
-  // needed here is the rows' sums of squares, gathered while the rows pass through registers on their way to LDS.
-  // Load q of a chunk holds 8 values of row 4 (q % LPS) + kg; rows and steps past the end arrive as zeros.
   auto stage_park = [&](const xload_t (&av)[NLD], unsigned char* buf) {
-#pragma unroll
-    for (int q = 0; q < NLD; ++q) *(xload_t*)(buf + ((q / LPS) * ROWS + 4 * (q % LPS)) * 256 + lane * 16) = av[q];
-    if (rownorm) {
-#pragma unroll
-      for (int q = 0; q < NLD; ++q)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float lo = __uint_as_float(av[q][e] << 16), hi = __uint_as_float(av[q][e] & 0xffff0000u);
-          ssl[q % LPS] += lo * lo + hi * hi;
-        }
-    }
+    strip_park<ROWS>(av, buf, lane);
+    if (rownorm) strip_squares<LPS>(av, ssl);
   };
   xload_t av0[MODE == 1 ? 1 : NLD], av1[MODE == 1 ? 1 : NLD];
   float2 mlv = {-INFINITY, 0.f};
@@ -525,8 +546,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
   constexpr int W2OFF = MODE == 3 ? 4 * 4096 : 0;           // from the first strip's block to the second's
   const int wbase = strip * 4096 + lane * 16;               // this strip's block of macro-step 0, this lane's 16 bytes
   const int wstep = (N / ST_N) * 4096;                      // from one macro-step's blocks to the next's
-  union frag_t { xload_t u; bf16x8_t v; };
-  frag_t bw[NW][ST_RING][4];
+  strip_frag_t bw[NW][ST_RING][4];
   auto load_b = [&](int u, int i) {
 #pragma unroll
     for (int w = 0; w < NW; ++w)
@@ -583,7 +603,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
   // arrive as zeros, so every path holds the same number of requests in flight.
   const int mr = nl & (ROWS - 1);
   auto step = [&](int u, const unsigned char* buf, int slot) {
-    frag_t af[4];
+    strip_frag_t af[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) af[j].u = *(const xload_t*)(buf + (slot * ROWS + mr) * 256 + (((4 * j + kg) ^ mr) & 15) * 16);
 #pragma unroll
@@ -619,11 +639,9 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
 #pragma unroll
     for (int e = 0; e < 4; ++e) red[w][wave][4 * kg + e][nl] = acc[w][e];
   if (MODE != 1 && rownorm) {
-    // a row's 16 chunk lanes (same kg) add up, then the waves do below
 #pragma unroll
     for (int g = 0; g < LPS; ++g) {
-      float t = ssl[g];
-      t += __shfl_xor(t, 1); t += __shfl_xor(t, 2); t += __shfl_xor(t, 4); t += __shfl_xor(t, 8);
+      const float t = strip_chunk_sum(ssl[g]);
       if (nl == 0) ssw[wave][4 * g + kg] = t;
     }
     if (ROWS == 8 && lane < 8) ssw[wave][8 + lane] = 0.f;
@@ -663,9 +681,7 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
         return;
       }
     }
-    if (res) v += __uint_as_float((uint32_t)res[o] << 16);
-    if (out_f32) ((float*)yout)[o] = v;                       // the queries: the attention kernel wants them unrounded
-    else ((bf16_t*)yout)[o] = (bf16_t)(cvt_pk(v, 0.f) & 0xffffu);
+    strip_store(yout, res, o, v, out_f32);
   }
   if (MODE == 1 && blockIdx.x == 0 && (lane & 7) == 0 && (lane >> 3) < nst)
     cb.lse[(int64_t)(wave + WAVES * (lane >> 3)) * cb.lse_stride] = lse_out;
@@ -695,54 +711,39 @@ __global__ __launch_bounds__(512, 1) void strip_gemm_whole_kernel(const bf16_t* 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nl = lane & 15, kg = lane >> 4;
   const int n0 = blockIdx.x * ST_N, nst = ((K >> 7) - wave + WAVES - 1) / WAVES;      // wave w takes macro-steps w, w + 8, ...
   unsigned char* aw = abuf + wave * (STEPS * ROWS * 256);
-  // activations: load q covers rows 4 g + kg of step i, (i, g) = divmod(q, LPS): lane (kg, nl) reads chunk nl ^ row of its row and
-  // parks it at chunk nl; rows and steps past the end arrive as zeros
   const __amdgpu_buffer_rsrc_t ars = __builtin_amdgcn_make_buffer_rsrc((void*)a, 0, (int)((int64_t)M * K * 2), 0x00020000);
   const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void*)Wt, 0, (int)((int64_t)N * K * 2), 0x00020000);
   xload_t av[NLD];
 #pragma unroll
   for (int q = 0; q < NLD; ++q) {
     const int i = q / LPS, row = 4 * (q % LPS) + kg;
-    av[q] = __builtin_amdgcn_raw_buffer_load_b128(
-        ars, (i < nst && row < M) ? (row * K + (wave + WAVES * i) * 128 + 8 * (nl ^ row)) * 2 : (int)0x80000000, 0, 0);
+    av[q] = strip_request(ars, i < nst && row < M, row, wave + WAVES * i, K, nl);
   }
   __builtin_amdgcn_sched_barrier(0);
   const int wbase = blockIdx.x * 4096 + lane * 16, wstep = (N / ST_N) * 4096;
-  union frag_t { xload_t u; bf16x8_t v; };
-  frag_t bw[STEPS][4];
+  strip_frag_t bw[STEPS][4];
 #pragma unroll
   for (int u = 0; u < STEPS; ++u)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       bw[u][j].u = __builtin_amdgcn_raw_buffer_load_b128(wrs, u < nst ? wbase + (wave + WAVES * u) * wstep + j * 1024 : (int)0x80000000, 0, 0);
   __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int q = 0; q < NLD; ++q) *(xload_t*)(aw + ((q / LPS) * ROWS + 4 * (q % LPS)) * 256 + lane * 16) = av[q];
+  strip_park<ROWS>(av, aw, lane);
   const bool rownorm = norm_eps >= 0.f;
   float ssl[LPS];                       // this lane's share of its rows' sums of squares
 #pragma unroll
   for (int g = 0; g < LPS; ++g) ssl[g] = 0.f;
   if (rownorm) {
+    strip_squares<LPS>(av, ssl);
 #pragma unroll
-    for (int q = 0; q < NLD; ++q)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float lo = __uint_as_float(av[q][e] << 16), hi = __uint_as_float(av[q][e] & 0xffff0000u);
-        ssl[q % LPS] += lo * lo + hi * hi;
-      }
-#pragma unroll
-    for (int g = 0; g < LPS; ++g) {     // a row's 16 chunk lanes (same kg) add up, then the waves do below
-      float t = ssl[g];
-      t += __shfl_xor(t, 1); t += __shfl_xor(t, 2); t += __shfl_xor(t, 4); t += __shfl_xor(t, 8);
-      ssl[g] = t;
-    }
+    for (int g = 0; g < LPS; ++g) ssl[g] = strip_chunk_sum(ssl[g]);
   }
   __builtin_amdgcn_sched_barrier(0);
   f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int mr = nl & (ROWS - 1);
 #pragma unroll
   for (int u = 0; u < STEPS; ++u) {
-    frag_t af[4];
+    strip_frag_t af[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) af[j].u = *(const xload_t*)(aw + (u * ROWS + mr) * 256 + (((4 * j + kg) ^ mr) & 15) * 16);
 #pragma unroll
@@ -769,10 +770,7 @@ __global__ __launch_bounds__(512, 1) void strip_gemm_whole_kernel(const bf16_t* 
       for (int wv = 1; wv < WAVES; ++wv) ss += ssw(wv, m);
       v *= 1.f / sqrtf(ss / (float)K + norm_eps);
     }
-    const int64_t o = (int64_t)m * N + n0 + n;
-    if (res) v += __uint_as_float((uint32_t)res[o] << 16);
-    if (out_f32) ((float*)yout)[o] = v;                       // the queries: the attention kernel wants them unrounded
-    else ((bf16_t*)yout)[o] = (bf16_t)(cvt_pk(v, 0.f) & 0xffffu);
+    strip_store(yout, res, (int64_t)m * N + n0 + n, v, out_f32);
   }
 }
 
