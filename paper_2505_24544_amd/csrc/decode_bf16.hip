@@ -623,7 +623,10 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void strip_gemm_kernel(const
         unsigned char* buf = (c & 1) ? aw1 : aw0;
         if (u % ST_CH == 0) stage_issue(av0, c + 2);
         step(u % ST_RING, buf, u % ST_CH);
+        // (kept there: with the refills among the MFMAs a block's step of 10 queries took 89.5 us, not 89.1, of 4 74.1, not 73.6)
+        if constexpr (MODE == 0) __builtin_amdgcn_sched_barrier(0);
         load_b(u % ST_RING, i0 + u + ST_RING);
+        if constexpr (MODE == 0) __builtin_amdgcn_sched_barrier(0);
         if (u % ST_CH == ST_CH - 1) stage_park(av0, buf);
       }
       i0 += ST_ROUND;
