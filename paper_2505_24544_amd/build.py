@@ -22,8 +22,9 @@ FLAGS = [
 ]
 # Matrix instructions write either register file.  By default all of a kernel's write accumulation registers as soon as it needs any
 # of those, and every score, probability or sum that vector instructions go on to use is copied over first.  By file, us without / with:
-# dK/dV see attn_bwd_bf16.hip; draft step of 64 queries over 4096 rows 57.3 / 56.4, of one 34.6 / 34.4.  The other files' kernels come
-# out the same either way.
+# dK/dV see attn_bwd_bf16.hip; draft step of 64 queries over 4096 rows 57.6 / 56.8, of 16 over 1024 28.8 / 28.5, on packed weights of 12 over
+# 3000 in 8 groups 28.5 / 27.8 (the kernels of up to 16 rows take 80 accumulation registers without, none with).  The other
+# files' kernels come out the same either way.
 VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 VGPR_FORM_SOURCES = ("attn_bwd_bf16.hip", "decode_bf16.hip")
 

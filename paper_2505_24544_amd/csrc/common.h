@@ -73,7 +73,7 @@ struct GemmArgs {
   int64_t lda2, ldb2;
   const void* R;         // optional residual added in the epilogue: C = A B (+ A2 B2) + R; storage type of A,
   int64_t ldr;           // row stride ldr; not with c_is_f32
-  int32_t c_kept;        // bf16: C is a cache that the call itself reads little of: the small tiles' rows go past L2
+  int32_t c_kept;        // bf16: C is rows of a cache: the small tiles' rows go past L2
 };
 // Independent GEMMs in one launch (they share one grid): up to 4 of the same storage orders in bf16, up to 6 of any in float.
 struct GemmGroup {

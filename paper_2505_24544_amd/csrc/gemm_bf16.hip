@@ -656,8 +656,9 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_ksplit_kernel(GemmGroup grp)
   int gm = g.M, gn = g.N;
   int64_t ldc = g.ldc;
   out_ptr cptr = (out_ptr)g.C;
-  // Rows of a cache go past L2: the 64 KB of each of 256 tiles all leave at once (1013 states into the cache 69.4 -> 67.2 us, 700 55.8 ->
-  // 53.2).  Outputs that the next launch reads do not: it cost steps of 400 and 777 rows 0.5 %.
+  // Rows of a cache go past L2: the 64 KB of each of 256 tiles all leave at once.  Appends, us, no rows / V / K / both past L2: 1013 states
+  // 71.7 / 70.2 / 70.7 / 69.6, 700 57.7 / 55.6 / 57.2 / 55.1, with K read back by its rotary embedding in the next launch; without one 1013
+  // 66.9 / 65.5 / 65.2 / 64.6.  A training step's outputs do not: it cost 400 and 777 rows 0.5 %.
   const int kept = XK && !WK && !F32OUT ? g.c_kept : 0;
   asm volatile("" : "+s"(gm), "+s"(gn), "+s"(ldc), "+s"(cptr));
   static_for<0, OWN>([&](auto i_) BEAGLE_INLINE_LAMBDA {
