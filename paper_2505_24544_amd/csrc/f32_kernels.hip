@@ -9,7 +9,7 @@
 //     the matrix instruction's layout, 16 bytes at a time: the two operands only
 //     have to agree on what k a lane group stands for, and which of a tile's columns
 //     is an instruction's n-th is free.
-//   * Small tiles (16 x 64, 16 x 16 scores) whose eight waves split the
+//   * Small tiles (16 x 64 and half of that, 16 x 16 scores) whose eight waves split the
 //     contraction, so that a 128 x 256 output occupies 32 workgroups and a
 //     contraction of 256 is one trip to memory and 32 instructions of 32 cycles per
 //     wave; the eight sums meet in LDS.  (Wide models' tiles: 32 x 64.)
@@ -44,35 +44,40 @@ __device__ __forceinline__ const GemmArgs& problem_of(const TiledGroup& grp, int
 }
 
 // ---------------------------------------------------------------------------
-// GEMM: a tile of 16 MR x 64 per workgroup, whose eight waves take chunks of 32 k in turn; the eight sums meet in LDS.
+// GEMM: a tile of 16 MR x 16 NU per workgroup, whose eight waves take chunks of 32 k in turn; the eight sums meet in LDS.
 // Bound by one trip to memory and the chain behind it.  Lane (n, g) of a 16 x 16 x 4 instruction supplies row (column) n at k = g, and
 // what it stands for is free: k = 16 j + 4 g + e of a chunk, so that a k-contiguous operand comes 16 bytes at a time, and column
 // 4 n + u of the tile in instruction u, so that a row-contiguous B does too (10 requests per 32 k, and 32 instructions of 32 cycles;
 // 32 x 32 tiles on 32 x 32 x 2 instructions took 20 requests, 16 of them of 4 bytes, and with four waves twice the chain).
 // Every N and leading dimension is a multiple of 4, and so is K where an operand is k-contiguous (the descriptor's checks on widths).
-// AHEAD: two chunks of a wave in flight, which leaves registers for one workgroup per CU; without, two share a CU.
+// AHEAD: two chunks of a wave in flight, which leaves registers for one workgroup per CU; without, several share one.
 // MR = 2: B's fragments serve two blocks of rows (12 requests for 64 instructions): wide problems, which tiles of 16 rows make a
 // stream of B out of L2, take two thirds of the time.  Launches at hidden 4096, us, MR = 1 / 2: 2048 rows through Wo 993 / 727, the
-// input and weight gradients behind them 3250 / 2480 (134 registers: one workgroup per CU; tiles of 64 rows whose waves share the
-// contraction four ways 705 and 2330, but where a launch is a few rounds of tiles they are the slower ones: 128 rows through Wo 56 / 95).
+// input and weight gradients behind them 3250 / 2320.  NU = 2: tiles of 32 columns, twice as many workgroups for a few rows.
+// (Measured and not taken: 64 x 64 whose waves share the contraction four ways, 5 - 7 % faster than 32 x 64 at 1000 rows of 5120, 70 % slower
+// at 128 of 4096; 32 x 64 a chunk ahead, 3 - 10 % slower.  f32_plan.h says which tiles a launch takes.)
 // ---------------------------------------------------------------------------
-constexpr int GW = 8, GN = GEMM_F32_COLS;
-template <int MR, bool AHEAD>
-__global__ __launch_bounds__(64 * GW, AHEAD || MR > 1 ? 2 : 4) void gemm_f32_kernel(TiledGroup grp) {
-  constexpr int GM = 16 * MR;
-  __shared__ __attribute__((aligned(16))) float red[GW][GM][GN + 4];
+constexpr int GW = 8;
+template <int MR, int NU, bool AHEAD, bool ALONE>
+__global__ __launch_bounds__(64 * GW, ALONE || MR > 1 ? 2 : 4) void gemm_f32_kernel(TiledGroup grp) {
+  constexpr int GM = 16 * MR, GN = 16 * NU;
+  typedef float bvec_t __attribute__((ext_vector_type(NU)));
+  typedef float ovec_t __attribute__((ext_vector_type(NU / 2)));
+  // (more than half of the CU's LDS: nothing else fits, and the compiler spends the registers)
+  constexpr int SUMS = ALONE ? 81920 / (GM * (GN + 4) * 4) + 1 : GW;
+  __shared__ __attribute__((aligned(16))) float red[SUMS][GM][GN + 4];
   int t = blockIdx.x;
   const GemmArgs& p = problem_of(grp, t);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, nl = lane & 15;
   const int tn = (p.N + GN - 1) / GN, m0 = (t / tn) * GM, n0 = (t % tn) * GN;
-  const int nc = min(n0 + 4 * nl, p.N - 4);                                // rows and columns past the end repeat the last ones
+  const int nc = min(n0 + NU * nl, p.N - NU);                              // rows and columns past the end repeat the last ones
   int mr[MR];
-  f32x4_t acc[MR][4];
+  f32x4_t acc[MR][NU];
 #pragma unroll
   for (int i = 0; i < MR; ++i) {
     mr[i] = min(m0 + 16 * i + nl, p.M - 1);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc[i][u] = zero4();
+    for (int u = 0; u < NU; ++u) acc[i][u] = zero4();
   }
 
   // AK / BK: k contiguous in memory
@@ -80,7 +85,7 @@ __global__ __launch_bounds__(64 * GW, AHEAD || MR > 1 ? 2 : 4) void gemm_f32_ker
     constexpr bool AK = decltype(ak_)::value, BK = decltype(bk_)::value;
     // chunk c of both segments' 32 k each: register 4 j + e is k = 16 j + 4 g + e of it; past K: zeros on both sides (0 * inf is a NaN)
     const int nc1 = (p.K + 31) / 32, chunks = nc1 + (p.A2 ? (p.K2 + 31) / 32 : 0);
-    auto load = [&](int c, float (&a)[MR][8], float (&b)[4][8]) BEAGLE_INLINE_LAMBDA {
+    auto load = [&](int c, float (&a)[MR][8], float (&b)[NU][8]) BEAGLE_INLINE_LAMBDA {
       const bool two = c >= nc1;
       const float* A = (const float*)(two ? p.A2 : p.A);
       const float* B = (const float*)(two ? p.B2 : p.B);
@@ -92,8 +97,9 @@ __global__ __launch_bounds__(64 * GW, AHEAD || MR > 1 ? 2 : 4) void gemm_f32_ker
           for (int r = 0; r < MR; ++r) { const float v = A[k * lda + mr[r]]; a[r][i] = in ? v : 0.f; }
         }
         if (!BK) {
-          const float4 v = *(const float4*)(B + k * ldb + nc);
-          b[0][i] = in ? v.x : 0.f; b[1][i] = in ? v.y : 0.f; b[2][i] = in ? v.z : 0.f; b[3][i] = in ? v.w : 0.f;
+          const bvec_t v = *(const bvec_t*)(B + k * ldb + nc);
+#pragma unroll
+          for (int u = 0; u < NU; ++u) b[u][i] = in ? v[u] : 0.f;
         }
       };
       auto four = [&](int k, int j, bool in) BEAGLE_INLINE_LAMBDA {    // four of those that are
@@ -106,7 +112,7 @@ __global__ __launch_bounds__(64 * GW, AHEAD || MR > 1 ? 2 : 4) void gemm_f32_ker
         }
         if (BK) {
 #pragma unroll
-          for (int u = 0; u < 4; ++u) put(b[u], *(const float4*)(B + (nc + u) * ldb + k));
+          for (int u = 0; u < NU; ++u) put(b[u], *(const float4*)(B + (nc + u) * ldb + k));
         }
       };
       if (k0 + 32 <= K) {
@@ -127,19 +133,26 @@ __global__ __launch_bounds__(64 * GW, AHEAD || MR > 1 ? 2 : 4) void gemm_f32_ker
         }
       }
     };
-    auto compute = [&](const float (&a)[MR][8], const float (&b)[4][8]) BEAGLE_INLINE_LAMBDA {
+    auto compute = [&](const float (&a)[MR][8], const float (&b)[NU][8]) BEAGLE_INLINE_LAMBDA {
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < NU; ++u)
 #pragma unroll
           for (int r = 0; r < MR; ++r) acc[r][u] = mfma16(a[r][i], b[u][i], acc[r][u]);
     };
     // (AHEAD: a contraction of up to 512 is loaded whole before the first product)
-    float a0[MR][8], b0[4][8], a1[MR][8], b1[4][8];
+    float a0[MR][8], b0[NU][8], a1[MR][8], b1[NU][8];
     int c = wave;
     if constexpr (!AHEAD) {
-      for (; c < chunks; c += GW) { load(c, a0, b0); compute(a0, b0); }
+      for (; c < chunks; c += GW) {
+        load(c, a0, b0);
+        if constexpr (ALONE) {                                         // (piece by piece, as they land, wide launches took 3 - 8 % longer)
+          __builtin_amdgcn_s_waitcnt(0x0F70);                          // vmcnt(0)
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        compute(a0, b0);
+      }
       return;
     }
     if (c < chunks) load(c, a0, b0);
@@ -160,24 +173,22 @@ __global__ __launch_bounds__(64 * GW, AHEAD || MR > 1 ? 2 : 4) void gemm_f32_ker
 #pragma unroll
   for (int i = 0; i < MR; ++i)
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      *(float4*)&red[wave][16 * i + 4 * g + e][4 * nl] = make_float4(acc[i][0][e], acc[i][1][e], acc[i][2][e], acc[i][3][e]);
+    for (int e = 0; e < 4; ++e) {
+      bvec_t v;
+#pragma unroll
+      for (int u = 0; u < NU; ++u) v[u] = acc[i][u][e];
+      *(bvec_t*)&red[wave][16 * i + 4 * g + e][NU * nl] = v;
+    }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < MR; ++i) {
-    const int r = 16 * i + (tid >> 5), c = 2 * (tid & 31), m = m0 + r, n = n0 + c;
+  for (int i = 0; i < MR; ++i) {                     // 32 threads to a row
+    const int r = 16 * i + (tid >> 5), c = NU / 2 * (tid & 31), m = m0 + r, n = n0 + c;
     if (m >= p.M || n >= p.N) return;
-    float2 v = *(const float2*)&red[0][r][c];
+    ovec_t v = *(const ovec_t*)&red[0][r][c];
 #pragma unroll
-    for (int w = 1; w < GW; ++w) {
-      const float2 x = *(const float2*)&red[w][r][c];
-      v.x += x.x; v.y += x.y;
-    }
-    if (p.R) {
-      const float2 x = *(const float2*)((const float*)p.R + m * p.ldr + n);
-      v.x += x.x; v.y += x.y;
-    }
-    *(float2*)((float*)p.C + m * p.ldc + n) = v;
+    for (int w = 1; w < GW; ++w) v += *(const ovec_t*)&red[w][r][c];
+    if (p.R) v += *(const ovec_t*)((const float*)p.R + m * p.ldr + n);
+    *(ovec_t*)((float*)p.C + m * p.ldc + n) = v;
   }
 }
 
@@ -186,19 +197,21 @@ __global__ __launch_bounds__(64 * GW, AHEAD || MR > 1 ? 2 : 4) void gemm_f32_ker
 void launch_gemm_f32(const GemmGroup& g, hipStream_t s, const char* name) {
   F32Problem sh[6];
   for (int i = 0; i < g.count; ++i) sh[i] = {g.p[i].M, g.p[i].N, (g.p[i].K + 31) / 32 + (g.p[i].A2 ? (g.p[i].K2 + 31) / 32 : 0)};
-  const int rows = gemm_f32_rows(sh, g.count);
+  const F32Plan plan = gemm_f32_plan(sh, g.count);
+  if (plan.tiles == 0) return;
   int64_t first[6], tiles = 0;
-  for (int i = 0; i < g.count; ++i) { first[i] = tiles; tiles += gemm_f32_tiles(sh[i], rows); }
-  if (tiles == 0) return;
+  for (int i = 0; i < g.count; ++i) { first[i] = tiles; tiles += gemm_f32_tiles(sh[i], plan.rows, plan.cols); }
   TiledGroup t;
   memcpy(t.p, g.p, sizeof(t.p));
   ProfScope ps(name, s);
   for_launches(tiles, 64 * GW, [&](int64_t at, int64_t n) {            // (2^31 tiles and more would not fit the memory)
     for (int i = 0; i < 6; ++i) t.first[i] = i < g.count ? (int32_t)(first[i] - at) : INT32_MAX;
     const dim3 grid((unsigned)n), wg(64 * GW);
-    if (rows == 32) hipLaunchKernelGGL((gemm_f32_kernel<2, false>), grid, wg, 0, s, t);
-    else if (gemm_f32_ahead(tiles)) hipLaunchKernelGGL((gemm_f32_kernel<1, true>), grid, wg, 0, s, t);
-    else hipLaunchKernelGGL((gemm_f32_kernel<1, false>), grid, wg, 0, s, t);
+    if (plan.rows == 32 && plan.alone) hipLaunchKernelGGL((gemm_f32_kernel<2, 4, false, true>), grid, wg, 0, s, t);
+    else if (plan.rows == 32) hipLaunchKernelGGL((gemm_f32_kernel<2, 4, false, false>), grid, wg, 0, s, t);
+    else if (plan.cols == 32) hipLaunchKernelGGL((gemm_f32_kernel<1, 2, false, false>), grid, wg, 0, s, t);
+    else if (plan.ahead) hipLaunchKernelGGL((gemm_f32_kernel<1, 4, true, true>), grid, wg, 0, s, t);
+    else hipLaunchKernelGGL((gemm_f32_kernel<1, 4, false, false>), grid, wg, 0, s, t);
   });
 }
 

@@ -1,5 +1,5 @@
 // Host build of csrc/f32_plan.h.  Input, one per line:
-//   a launch of the float GEMM: count, then M N chunks of each problem    -> rows of a tile, tiles, whether a chunk is requested ahead
+//   a launch of the float GEMM: count, then M N chunks of each problem    -> its plan: rows and columns of a tile, tiles, ahead, alone
 //   0 rows n0 n1: a backward's grid, rows runs of n0 blocks, then 2 rows of n1 -> its launches, first block and blocks of each, and
 //     whether every launch's first and last block of either kind come out as the block they are
 #include <cstdio>
@@ -34,9 +34,7 @@ int main() {
       p[i] = {m, c, k};
     }
     if (n == 0) { grid(m, c, k); continue; }
-    const int rows = beagle::gemm_f32_rows(p, n);
-    long long tiles = 0;
-    for (int i = 0; i < n; ++i) tiles += beagle::gemm_f32_tiles(p[i], rows);
-    printf("%d %lld %d\n", rows, tiles, rows == 16 && beagle::gemm_f32_ahead(tiles) ? 1 : 0);
+    const beagle::F32Plan q = beagle::gemm_f32_plan(p, n);
+    printf("%d %d %lld %d %d\n", q.rows, q.cols, (long long)q.tiles, q.ahead ? 1 : 0, q.alone ? 1 : 0);
   }
 }

@@ -1,6 +1,6 @@
-"""Which tiles the launches of the float GEMM take (csrc/f32_plan.h, compiled for the host): the wide problems' tiles of 32 rows where
-tiles of 16 were up to 8 % slower than what was there before them, those of 16 where they are the faster ones.  And that the GPU tests of
-the float kernels reach the launches they are there for."""
+"""Which tiles the launches of the float GEMM take (csrc/f32_plan.h, compiled for the host): 32 rows for the wide problems and 32 columns for
+a few rows, where tiles of 16 x 64 were up to 8 and 10 % slower than what was there before them.  And that the GPU tests of the float
+kernels reach the launches they are there for."""
 import os
 import shutil
 import subprocess
@@ -26,7 +26,7 @@ def plan(tmp_path_factory):
 
     def run(*launches):
         out = lines("".join("%d %s\n" % (len(l), " ".join("%d %d %d" % p for p in l)) for l in launches))
-        return [dict(rows=int(r), tiles=int(t), ahead=a == "1") for r, t, a in (l.split() for l in out)]
+        return [dict(tile=(int(r), int(c)), tiles=int(t), ahead=a == "1", alone=o == "1") for r, c, t, a, o in (l.split() for l in out)]
     run.grid = lambda *g: [int(v) for v in lines("0 %d %d %d\n" % g)[0].split()]
     return run
 
@@ -44,41 +44,49 @@ def step(S, L, D, H, G, hd):
             [(L, D, _chunks(k, k)), (S, D, _chunks(q)), (D, q, _chunks(S)), (D, k, _chunks(L)), (D, k, _chunks(L))])
 
 
-@pytest.mark.parametrize("shape,rows", [
-    ((128, 128, 256, 4, 4, 64), (16, 16, 16, 16)),                # the reference problem
-    ((200, 200, 512, 4, 4, 128), (16, 16, 16, 16)),
-    ((16, 16, 4096, 32, 32, 128), (16, 16, 16, 16)),              # one chunk of rows: nothing to share B with
-    ((128, 128, 4096, 32, 32, 128), (32, 32, 32, 32)),            # the steps that had become slower
-    ((512, 512, 2048, 16, 16, 128), (32, 32, 32, 32)),
-    ((1024, 1024, 4096, 32, 32, 128), (32, 32, 32, 32)),
-    ((1000, 1000, 5120, 40, 40, 128), (32, 32, 32, 32)),
-    ((2048, 2048, 4096, 32, 8, 128), (32, 32, 32, 32)),
+def kinds(launches):
+    """n: 16 x 32; a, p: 16 x 64, a chunk ahead or workgroups in pairs; w, v: 32 x 64, alone on a CU or in pairs"""
+    return "".join("n" if l["tile"] == (16, 32) else ("a" if l["ahead"] else "p") if l["tile"] == (16, 64) else
+                   {(32, 64): "w" if l["alone"] else "v"}[l["tile"]] for l in launches)
+
+
+@pytest.mark.parametrize("shape,want", [
+    ((128, 128, 256, 4, 4, 64), "nnna"),                          # the reference problem
+    ((200, 200, 512, 4, 4, 128), "anap"),
+    ((16, 16, 4096, 32, 32, 128), "anvv"),                        # one chunk of rows
+    ((128, 128, 4096, 32, 32, 128), "wwvv"),                      # the steps that had become slower
+    ((512, 512, 2048, 16, 16, 128), "wwww"),
+    ((1024, 1024, 4096, 32, 32, 128), "wwww"),
+    ((1000, 1000, 5120, 40, 40, 128), "wwww"),
+    ((2048, 2048, 4096, 32, 8, 128), "wwww"),
 ])
-def test_tiles_of_a_step(plan, shape, rows):
-    assert tuple(l["rows"] for l in plan(*step(*shape))) == rows
+def test_tiles_of_a_step(plan, shape, want):
+    assert kinds(plan(*step(*shape))) == want
 
 
-@pytest.mark.parametrize("queries", [1, 16, 40])
-def test_projections_of_a_draft_step_keep_the_narrow_tiles(plan, queries):
-    assert [(l["rows"], l["ahead"]) for l in plan([(queries, 4096, 128)], [(queries, 5120, 160)])] == [(16, True)] * 2
+@pytest.mark.parametrize("rows,D,want", [(1, 4096, "n"), (16, 5120, "n"), (16, 8192, "n"), (32, 4096, "n"), (40, 4096, "a"), (16, 8256, "a")])
+def test_projections_of_a_few_rows(plan, rows, D, want):
+    assert kinds(plan([(rows, D, _chunks(D))])) == want
 
 
 def test_the_steps_of_the_gpu_tests_reach_every_kernel(plan):
-    got = {s[:6]: plan(*step(*s[:6])) for s in tiles.STEPS}
-    assert all(l["ahead"] for l in got[(529, 600, 260, 4, 2, 44)])
-    assert all(l["rows"] == 16 and l["tiles"] > 512 and not l["ahead"] for l in got[(700, 333, 772, 12, 2, 60)])
-    assert all(l["rows"] == 32 for s in ((777, 600, 1540, 16, 4, 100), (512, 1024, 1024, 16, 16, 64)) for l in got[s])
-
-
-def test_the_long_step_beside_them(plan):
-    """The last row of test_gpu_f32_kernels.py."""
-    got = plan(*step(1200, 1200, 2048, 2, 1, 64))
-    assert [(l["rows"], l["ahead"]) for l in got] == [(32, False), (16, False), (16, True), (32, False)]
+    got = {s[:6]: kinds(plan(*step(*s[:6]))) for s in tiles.STEPS}
+    assert got[(17, 129, 64, 2, 2, 64)] == "nnnn" and got[(45, 97, 1028, 20, 5, 52)] == "nnpp"
+    assert got[(529, 600, 260, 4, 2, 44)] == "aaaa"
+    assert got[(600, 300, 900, 12, 2, 60)] == "pppp"
+    assert got[(777, 600, 1540, 16, 4, 100)] == got[(512, 1024, 1024, 16, 16, 64)] == "wwww"
+    assert got[(130, 140, 1540, 16, 4, 100)] == "wapv"
+    assert kinds(plan(*step(1200, 1200, 2048, 2, 1, 64))) == "wvav"        # the last row of test_gpu_f32_kernels.py
 
 
 def test_the_wide_block_adds_its_residuals_on_tiles_of_32_rows(plan):
     S, D, q, f = block.S, block.D, block.H * 64, block.FFN
-    assert [l["rows"] for l in plan([(S, D, _chunks(q))], [(S, D, _chunks(f))])] == [32, 32]
+    assert kinds(plan([(S, D, _chunks(q))], [(S, D, _chunks(f))])) == "ww"
+
+
+def test_the_long_append_is_more_than_one_launch(plan):
+    n = (1 << 27) + 160
+    assert plan([(n, 4, 1), (n, 4, 1)])[0]["tiles"] * 512 >= 1 << 32
 
 
 @pytest.mark.parametrize("rows,n0,n1", [

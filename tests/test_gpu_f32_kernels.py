@@ -1,5 +1,5 @@
 """The float path where its kernels can go wrong: contractions and head widths that end inside a 32-wide chunk, rows and
-columns that end inside a tile, one and many chunks per wave, both GEMM tile sizes.  Against float64 PyTorch on the card;
+columns that end inside a tile, one and many chunks per wave, all GEMM tile sizes.  Against float64 PyTorch on the card;
 1e-5 of the largest value, the float path's bound (sums of up to 2048 terms: sqrt(n) 6e-8, through five of them)."""
 import pytest
 import torch
@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
     (200, 200, 256, 4, 2, 100, 4, 2),          # four blocks, the last of four channels
     (150, 97, 128, 2, 1, 128, 3, 0),           # more queries than keys
     (97, 290, 96, 2, 2, 64, 8, 7),             # more keys than queries, three key blocks per wave
-    (1200, 1200, 2048, 2, 1, 64, 4, 0),        # 32 x 64 GEMM tiles, but for the output (16 x 64, past 512) and dO, dWo (16 x 64)
+    (1200, 1200, 2048, 2, 1, 64, 4, 0),        # 32 x 64 GEMM tiles, but for dO, dWo (16 x 64)
 ])
 def test_step_against_float64(S, L, D, H, G, hd, k, eps):
     gen = torch.Generator(device="cuda").manual_seed(S + D)

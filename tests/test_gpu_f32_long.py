@@ -27,7 +27,7 @@ def _close(name, got, ref, tol=1e-5):
 
 
 def test_append_of_a_row_block_past_one_launch():
-    n = (1 << 26) + 40                                   # 2 x 4194307 tiles
+    n = (1 << 27) + 160                                  # 2 x 4194309 tiles of 32 rows
     r = _rand(1)
     x, wk, wv = r(n, 4), r(4, 4), r(4, 4)
     d = bx.make_desc(batch=1, seq_q=n, seq_kv=n, hidden=4, n_q_heads=1, n_kv_heads=1, head_dim=4, io_dtype=bx.BEAGLE_F32)
