@@ -10,13 +10,13 @@
 //     have to agree on what k a lane group stands for, and which of a tile's columns
 //     is an instruction's n-th is free.
 //   * Small tiles (16 x 64 and half of that, 16 x 16 scores) whose eight waves split the
-//     contraction, so that a 128 x 256 output occupies 32 workgroups and a
-//     contraction of 256 is one trip to memory and 32 instructions of 32 cycles per
+//     contraction, so that a 128 x 256 output occupies 64 workgroups and a
+//     contraction of 256 is one trip to memory and 16 instructions of 32 cycles per
 //     wave; the eight sums meet in LDS.  (Wide models' tiles: 32 x 64.)
 //   * Everything independent shares a launch: problems of different storage
 //     orders in one GEMM group, dQ with dK / dV in one attention launch.
 // One training step at 128 rows, hidden 256, 4 heads of 64: 367 us on scalar
-// kernels (nine launches), 46.5 on 32 x 32 x 2 instructions and four waves, 37.6 now.
+// kernels (nine launches), 46.5 on 32 x 32 x 2 instructions and four waves, 34.7 now.
 #include <string.h>
 #include "attn_f32.h"
 #include "f32_plan.h"
